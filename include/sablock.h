@@ -82,8 +82,8 @@ typedef struct {
                                  of 128; 0 = whole rounds of one workgroup per compute unit */
     int32_t window_chunk;     /* keys per workgroup of sablock_window_attention and of the one-read row statistics,
                                  >= 32, rounded down to a multiple of 32; 0 = whole rounds of workgroups */
-    int32_t topb_slices;      /* workgroups per row of the two Top-B passes of sablock_search_select, 1 .. 64
-                                 (1 = the per-row kernel alone); 0 = by problems per compute unit */
+    int32_t topb_slices;      /* workgroups per row of the Top-B pass over the rows of sablock_search_select, 1 .. 64
+                                 (1 = the per-row kernel alone); 0 = by row length and problems per compute unit */
     int32_t stats_per_key;    /* which kernel forms the row statistics where two exist (head_dim 128; 129 .. 256
                                  window-query rows per KV head, and G = 4 with W = 32): 1 = the kernel with a lane per
                                  key on blocks of 128 rows (two blocks: K read twice by that pass), 2 = the kernel with a

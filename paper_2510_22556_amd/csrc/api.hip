@@ -288,6 +288,7 @@ static sablock_status make_candlist(const char *who, const int32_t *cand, int32_
         if (c && cand[c] <= cand[c - 1]) return fail(SABLOCK_ERR_INVALID_ARG, "%s: cand must be strictly ascending", who);
         if (cand[c] > 64) return fail(SABLOCK_ERR_UNSUPPORTED, "%s: block size %d > 64", who, cand[c]);
         cl->g[c] = cand[c];
+        cl->inv[c] = ((1 << CAND_INV_BITS) + cand[c] - 1) / cand[c];
     }
     return SABLOCK_OK;
 }

@@ -39,9 +39,11 @@ struct SeqPtr {                    // host CSR pointers of the segment offsets, 
     int32_t ptr[MAX_SEQ + 1];
 };
 
+// candidate block sizes; x / g = (x * inv) >> CAND_INV_BITS for 0 <= x < 4 160 (inv = ceil(2^19 / g), g <= 64)
+constexpr int CAND_INV_BITS = 19;
 struct CandList {
     int32_t n;
-    int32_t g[MAX_CAND];
+    int32_t g[MAX_CAND], inv[MAX_CAND];
 };
 
 __host__ __device__ inline int32_t seq_of_problem(const Dims &d, int32_t p) { return p / (d.n_layers * d.Hkv); }

@@ -1,16 +1,14 @@
 // Budget-driven block-size search and selection (Alg. 2; Eqs. topk,
 // implicit_budget, rk, gk_star, final_selection).
 //
-// topb_kernel     one workgroup per problem: radix select of the min(B,T)-th best
-//                 score (12 bits over the row, then 10 + 10 on an LDS candidate
-//                 list), ties resolved by ascending index.
+// topb_kernel     one workgroup per problem: the min(B,T)-th best score of the row, ties
+//                 resolved by ascending index.
 //                 Result: (ordered key v, index cut c); token t is in T_topB iff
 //                 key(t) > v or (key(t) == v and t <= c).  Its last phase counts
 //                 the Top-B tokens of every segment: the implicit budgets b_k.
-// heavy_list_kernel one workgroup per problem: segments with b_k >= 2 are appended to
-//                 ONE list for the whole call (only they need a search; b_k == 1
-//                 means g_k* = 1, b_k == 0 means g_k* = 0).
-// search_kernel   wavefronts stride over that list: Score_base of a segment, then
+// heavy_list_kernel one workgroup per problem: segments with b_k >= 2 are recorded (only
+//                 they need a search; b_k == 1 means g_k* = 1, b_k == 0 means g_k* = 0).
+// search_kernel   wavefronts stride over a problem's records: Score_base of a segment, then
 //                 the candidates largest first.
 // seg_prefix_kernel one workgroup per problem: prefix sum of b_k (output offsets); the
 //                 segments that retain anything are appended to one of two lists for
@@ -18,9 +16,9 @@
 // select_light_kernel sixteen lanes per token-level segment: its Top-B tokens in order.
 // select_kernel   wavefronts stride over the other list: T_k(g_k*) written in
 //                 ascending order at the segment's offset.
-// A list entry carries everything its consumer needs (problem, segment bounds, budget,
-// block size, output offset), so a consumer starts with one 32-byte load; the lists
-// are filled through one atomic counter per call, their order does not matter.
+// A record carries everything its consumer needs (segment bounds, budget, block size,
+// output offset), so a consumer starts with one 32-byte load; the order of the records
+// does not matter.
 //
 // All quantities that decide an integer (block sums Phi, Score_k(g), Score_base,
 // tau * Score_base) are fp64 and summed in ascending token order, one addition at
@@ -44,19 +42,41 @@ struct __attribute__((aligned(32))) SegRec {
     int32_t out;         // search that also selects: offset of the segment's tokens in the problem's idx_out row
 };
 
-// LDS slices of a search/select wavefront: tokens whose scores are staged, blocks whose Phi / class are kept.
-// Two sizes: the small one keeps many wavefronts resident for the bulk of the segments; segments longer than
-// CAPT go to a second list that is served by the same kernels with the large slices.
-constexpr int CAPT = 512, CAPB = 256;
-constexpr int CAPT_LONG = 4096, CAPB_LONG = 2048;
+// LDS of a select wavefront: tokens whose scores are staged (CAPT), blocks whose Phi / class are kept (CAPB).
+// Two sizes: the small one keeps many wavefronts resident for the bulk of the segments; longer segments go to a
+// second list that is served by the same kernel with the large one.
+constexpr int CAPB = 256, CAPT = 2 * CAPB;
+constexpr int CAPB_LONG = 2048, CAPT_LONG = 2 * CAPB_LONG;
+// Tokens of a segment whose prefix sums fit the LDS of a search wavefront (5 KiB: 32 wavefronts per CU), and of one that
+// the per-problem workgroups search.
+constexpr int PRE_TOKENS = 639, PRE_LONG = 4095;
 constexpr int MAX_G = 64;           // largest candidate block size
 
 // Wavefront reductions without LDS round trips: four DPP steps inside each row of 16 lanes (lane ^ 1, lane ^ 2,
-// mirror inside 8, mirror inside 16: together they pair every lane with every other lane of its row), then the
-// four row results are read as scalars.  The results are wave-uniform.
+// mirror inside 8, mirror inside 16: together they pair every lane with every other lane of its row), then lane 15 of
+// rows 0 and 2 joins the row behind it and lane 31 the upper half, so lane 63 holds the result, which is read as a
+// scalar: it is wave-uniform.
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140, DPP_BCAST15 = 0x142, DPP_BCAST31 = 0x143;
 template <int CTRL>
-__device__ inline int dpp_i(int v) { return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xf, 0xf, false); }
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+__device__ inline int dpp_i(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true); }     // every lane has a source
+template <int CTRL, int ROWS>
+__device__ inline int dpp_rows_i(int old, int v) { return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false); }
+template <int CTRL>
+__device__ inline double dpp_d(double v) { return __hiloint2double(dpp_i<CTRL>(__double2hiint(v)), dpp_i<CTRL>(__double2loint(v))); }
+template <int CTRL, int ROWS>
+__device__ inline double dpp_rows_d(double old, double v)
+{
+    return __hiloint2double(dpp_rows_i<CTRL, ROWS>(__double2hiint(old), __double2hiint(v)),
+                            dpp_rows_i<CTRL, ROWS>(__double2loint(old), __double2loint(v)));
+}
+__device__ inline double readlane_d(double v, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane), __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+__device__ inline double shfl_d(double v, int lane)
+{
+    return __hiloint2double(__shfl(__double2hiint(v), lane), __shfl(__double2loint(v), lane));
+}
 
 __device__ inline int wave_sum_i(int v)
 {
@@ -64,18 +84,72 @@ __device__ inline int wave_sum_i(int v)
     v += dpp_i<DPP_XOR2>(v);
     v += dpp_i<DPP_HALF_MIRROR>(v);
     v += dpp_i<DPP_MIRROR>(v);
-    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
-           __builtin_amdgcn_readlane(v, 48);
+    v += dpp_rows_i<DPP_BCAST15, 0xa>(0, v);
+    v += dpp_rows_i<DPP_BCAST31, 0xc>(0, v);
+    return __builtin_amdgcn_readlane(v, 63);
 }
-__device__ inline int wave_max_i(int v)
+template <typename V>
+__device__ inline V wave_max_32(V v)                           // int or uint32_t
 {
-    v = max(v, dpp_i<DPP_XOR1>(v));
-    v = max(v, dpp_i<DPP_XOR2>(v));
-    v = max(v, dpp_i<DPP_HALF_MIRROR>(v));
-    v = max(v, dpp_i<DPP_MIRROR>(v));
-    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+    v = max(v, (V)dpp_i<DPP_XOR1>((int)v));
+    v = max(v, (V)dpp_i<DPP_XOR2>((int)v));
+    v = max(v, (V)dpp_i<DPP_HALF_MIRROR>((int)v));
+    v = max(v, (V)dpp_i<DPP_MIRROR>((int)v));
+    v = max(v, (V)dpp_rows_i<DPP_BCAST15, 0xa>((int)v, (int)v));
+    v = max(v, (V)dpp_rows_i<DPP_BCAST31, 0xc>((int)v, (int)v));
+    return (V)__builtin_amdgcn_readlane((int)v, 63);
 }
+__device__ inline int wave_max_i(int v) { return wave_max_32<int>(v); }
+__device__ inline uint32_t wave_max_u(uint32_t v) { return wave_max_32<uint32_t>(v); }
+__device__ inline double wave_max_d(double v)
+{
+    v = fmax(v, dpp_d<DPP_XOR1>(v));
+    v = fmax(v, dpp_d<DPP_XOR2>(v));
+    v = fmax(v, dpp_d<DPP_HALF_MIRROR>(v));
+    v = fmax(v, dpp_d<DPP_MIRROR>(v));
+    v = fmax(v, dpp_rows_d<DPP_BCAST15, 0xa>(v, v));
+    v = fmax(v, dpp_rows_d<DPP_BCAST31, 0xc>(v, v));
+    return readlane_d(v, 63);
+}
+// only for sums that do not round (the order differs from an ascending one)
+__device__ inline double wave_sum_d(double v)
+{
+    v += dpp_d<DPP_XOR1>(v);
+    v += dpp_d<DPP_XOR2>(v);
+    v += dpp_d<DPP_HALF_MIRROR>(v);
+    v += dpp_d<DPP_MIRROR>(v);
+    v += dpp_rows_d<DPP_BCAST15, 0xa>(0.0, v);
+    v += dpp_rows_d<DPP_BCAST31, 0xc>(0.0, v);
+    return readlane_d(v, 63);
+}
+// Inclusive prefix sums over the wavefront: shifts by 1, 2, 4 and 8 lanes inside a row of 16 (a lane without a source
+// adds zero), then the two steps across rows
+__device__ inline uint32_t wave_scan_u(uint32_t v)
+{
+    v += (uint32_t)dpp_rows_i<0x111, 0xf>(0, (int)v);
+    v += (uint32_t)dpp_rows_i<0x112, 0xf>(0, (int)v);
+    v += (uint32_t)dpp_rows_i<0x114, 0xf>(0, (int)v);
+    v += (uint32_t)dpp_rows_i<0x118, 0xf>(0, (int)v);
+    v += (uint32_t)dpp_rows_i<DPP_BCAST15, 0xa>(0, (int)v);
+    v += (uint32_t)dpp_rows_i<DPP_BCAST31, 0xc>(0, (int)v);
+    return v;
+}
+__device__ inline double wave_scan_d(double v)                 // exact sums only, as wave_sum_d
+{
+    v += dpp_rows_d<0x111, 0xf>(0.0, v);
+    v += dpp_rows_d<0x112, 0xf>(0.0, v);
+    v += dpp_rows_d<0x114, 0xf>(0.0, v);
+    v += dpp_rows_d<0x118, 0xf>(0.0, v);
+    v += dpp_rows_d<DPP_BCAST15, 0xa>(0.0, v);
+    v += dpp_rows_d<DPP_BCAST31, 0xc>(0.0, v);
+    return v;
+}
+// lanes below this one whose bit is set
+__device__ inline int lanes_below(unsigned long long m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
 // best (value descending, index ascending) of the lanes' (value, index) pairs
 __device__ inline bool pair_better(double op, int om, double bp, int bm) { return op > bp || (op == bp && om < bm); }
 template <int CTRL>
@@ -117,16 +191,25 @@ __device__ inline double add_in_order(double acc, unsigned long long mask, float
 
 // ------------------------------------------------------------------ Top-B
 constexpr int TB_THREADS = 1024;
-constexpr int TB_OFFS = 4096;              // segment offsets and per-segment counts kept in LDS while the implicit budgets are counted:
-constexpr int TB_OFFS_MAX = 16384;         // the launch picks 4 096, 8 192 or 16 384 entries (dynamic LDS: two int32 arrays of that size)
-constexpr int TB_HITS = 4096;              // Top-B tokens collected in LDS before they are assigned to segments
-constexpr int TB_HITS_MAX = 16384;         // ... when the launch gives the list dynamic LDS (8 192 or 16 384 entries)
-constexpr int TB_CAND = 4096;              // tokens of the threshold's 12-bit bin that the LDS candidate list holds
+constexpr int TB_WAVES = TB_THREADS / 64;
+constexpr int TB_REG = 16;                         // values of a row that a thread holds at a time
+constexpr int TB_ROUND = TB_THREADS * TB_REG;      // ... and the workgroup: 16 384
+constexpr int TB_BINS = 4096;
+constexpr int TB_RANKED = 1024;                    // entries of one bin that are ranked one against another
+constexpr int TB_BUDGET_MAX = 16384;               // budgets of the one-call form
+constexpr int TB_OFFS = 4096;                      // segment offsets and counters of a sequence kept in LDS:
+constexpr int TB_OFFS_MAX = 16384;                 // the launch picks 4 096, 8 192 or 16 384 entries
 
 __device__ inline bool in_topb(float v, int t, uint32_t thr_key, int thr_cut)
 {
     const uint32_t key = ordered_key(v);
     return key > thr_key || (key == thr_key && t <= thr_cut);
+}
+
+// the float that a key stands for (of the two zeros, +0)
+__device__ inline float float_of_key(uint32_t key)
+{
+    return __uint_as_float((key & 0x80000000u) ? key ^ 0x80000000u : ~key);
 }
 
 // segment of token t: the k with seg_off[k] <= t < seg_off[k+1], 0 <= k < K
@@ -140,415 +223,232 @@ __device__ inline int segment_of(const int32_t *off, int K, int t)
     return lo;
 }
 
-// f(t, s_tilde[t]) for every token of a row, in no particular order: 16-byte loads, four in flight per thread
-// (the passes over a row are latency-bound), scalar loads for the unaligned head and the tail
+// A row of T scores as 16-byte vectors: `head` scalars in front of the first aligned one, nvec vectors, a tail of
+// at most three scalars.  The scalars are dealt out to the first threads, one each (`extra`, -1: none).
+struct RowView {
+    const float *sp;
+    const float4 *vp;
+    int head, nvec, extra;
+    __device__ inline RowView(const float *sp_, int T, int tid) : sp(sp_)
+    {
+        head = min(T, (int)(((16u - (uint32_t)((uintptr_t)sp & 15u)) & 15u) >> 2));
+        nvec = (T - head) >> 2;
+        vp = reinterpret_cast<const float4 *>(sp + head);
+        const int tail0 = head + 4 * nvec;
+        extra = tid < head ? tid : tid >= 4 && tid - 4 < T - tail0 ? tail0 + tid - 4 : -1;
+    }
+    __device__ inline int token(int i) const { return head + 4 * i; }
+};
+
+// f(t, s_tilde[t]) for every token of a row, in no particular order
 template <typename F>
-__device__ inline void scan_row(const float *sp, int T, int tid, F &&f)
+__device__ inline void scan_row(const RowView &r, int tid, F &&f)
 {
-    const int head = min(T, (int)(((16u - (uint32_t)((uintptr_t)sp & 15u)) & 15u) >> 2));
-    const int nvec = (T - head) >> 2;
-    const float4 *vp = reinterpret_cast<const float4 *>(sp + head);
-    for (int i0 = tid; i0 < nvec; i0 += 4 * TB_THREADS) {
+    for (int i0 = tid; i0 < r.nvec; i0 += 4 * TB_THREADS) {
         float4 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) { const int i = i0 + j * TB_THREADS; v[j] = vp[i < nvec ? i : nvec - 1]; }
+        for (int j = 0; j < 4; ++j) v[j] = r.vp[min(i0 + j * TB_THREADS, r.nvec - 1)];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int i = i0 + j * TB_THREADS;
-            if (i < nvec) {
-                const int t = head + 4 * i;
+            if (i < r.nvec) {
+                const int t = r.token(i);
                 f(t, v[j].x); f(t + 1, v[j].y); f(t + 2, v[j].z); f(t + 3, v[j].w);
             }
         }
     }
-    if (tid < head) f(tid, sp[tid]);
-    const int t_tail = head + 4 * nvec + tid;
-    if (t_tail < T) f(t_tail, sp[t_tail]);
+    if (r.extra >= 0) f(r.extra, r.sp[r.extra]);
 }
 
-// Bin of the k-th entry counted from the top bin of hist[0 .. nbins): wavefront 0 scans, everyone gets
-// (bin, entries in the bins above it).  nbins is a multiple of 64.  Ends with a barrier.
-__device__ inline void find_bin_from_top(const uint32_t *hist, int nbins, uint32_t krem, uint32_t *sh_pair,
-                                         uint32_t &bin, uint32_t &above)
-{
-    const int lane = threadIdx.x & 63;
-    if ((threadIdx.x >> 6) == 0) {
-        // position r counts bins from the top: r = nbins-1-bin; lane owns `per` consecutive positions
-        const int per = nbins / 64;
-        uint32_t mine = 0;
-        for (int j = 0; j < per; ++j) mine += hist[nbins - 1 - (lane * per + j)];
-        uint32_t incl = mine;
-        for (int off = 1; off < 64; off <<= 1) {
-            uint32_t o = __shfl_up(incl, off);
-            if (lane >= off) incl += o;
-        }
-        const uint32_t excl = incl - mine;
-        if (excl < krem && krem <= incl) {
-            uint32_t run = excl;
-            for (int j = 0; j < per; ++j) {
-                const int bn = nbins - 1 - (lane * per + j);
-                const uint32_t c = hist[bn];
-                if (run + c >= krem) { sh_pair[0] = (uint32_t)bn; sh_pair[1] = run; break; }
-                run += c;
-            }
-        }
-    }
-    __syncthreads();
-    bin = sh_pair[0];
-    above = sh_pair[1];
-}
-
-// grid (P).  With seg_budget != NULL the kernel also clears the problem's seg_budget / block_size rows, counts
-// the implicit budgets (Eq. implicit_budget) into seg_budget, and workgroup 0 clears counter[0..1].
-//
-// Selection of the k-th best score, k = min(B, T).  Usual path, two passes over the row: a histogram of the
-// keys' top 12 bits locates the bin of the k-th key; the second pass puts the tokens of higher bins straight
-// into the list of Top-B tokens and the tokens of that bin (key, index) into a candidate list in LDS, on which
-// the remaining 20 bits are resolved without touching global memory again.  If the bin holds more candidates
-// than the list (or k exceeds the token list), three histogram passes over the row (11 + 11 + 10 bits) do it.
-// Ties at the threshold are cut by ascending index with one ordered pass over the row.
-//
-// PLAN (the search that also selects; the host launches it only when 0 < B < T, B <= hit_cap and every sequence
-// has fewer than `offs_cap` segments, so the Top-B tokens and the segment counters are in LDS): the same workgroup
-// goes on to the exclusive prefix of b_k (each segment's offset in the problem's idx_out row), writes n_sel, the
-// single token of every segment with b_k == 1 (g_k* = 1) straight to its place, and appends the segments with
-// b_k >= 2 to the call's search lists with their output offset.  `counter` must then be zero on entry.
-struct PlanArgs {
-    SegRec *list, *list_long;
-    int capacity;
-    int32_t *idx_out, *n_sel_out;
-    // results of the sliced passes over the rows (null: the workgroup scans its row itself)
-    const uint32_t *pre_hist;    // [P][4096] histogram of the keys' top 12 bits
-    const int32_t *pre_cnt;      // [P][2] entries of pre_hit, pre_cand
-    const int32_t *pre_hit;      // [P][TB_HITS] tokens of the bins above the threshold's bin
-    const uint32_t *pre_cand;    // [P][TB_CAND][2] (key, token) of the threshold's bin
+struct TopbShared {
+    uint32_t kmax[TB_WAVES], kmin[TB_WAVES];
+    uint32_t w[TB_WAVES];
+    uint32_t found[3];             // bin, entries in front of it, entries in it
+    int n;                         // length of the token list
+    int n_bin, n_rec, n_long;
+    uint32_t thr;
+    int cut;
 };
 
-// ---- the two passes over the rows with several workgroups per row (few problems in a call: one workgroup per
-// row leaves most of the chip idle and is bound by the latency of its own loads).  grid (slices, P).
-__device__ inline void slice_of_row(int T, int n_slices, int sl, int &a, int &b)
+// Bin that holds the entry of rank r (1-based, counted from bin 0) of hist[0 .. TB_BINS): (bin, entries in front,
+// entries in it).  Every thread has read its bins when the first of the two barriers is passed.
+__device__ inline void find_bin(const uint32_t *hist, uint32_t r, TopbShared &sh, uint32_t &bin, uint32_t &above, uint32_t &count)
 {
-    const int per = ((T + n_slices - 1) / n_slices + 3) & ~3;
-    a = min(sl * per, T);
-    b = min(a + per, T);
-}
-
-// pass A: histogram of the top 12 key bits of a slice, added to the row's histogram (zero on entry)
-__global__ void __launch_bounds__(TB_THREADS)
-topb_hist_kernel(Dims d, const float *s_tilde, uint32_t *g_hist)
-{
-    __shared__ uint32_t hist[4096];
-    const int p = blockIdx.y, tid = threadIdx.x;
-    int a, b;
-    slice_of_row(d.T, gridDim.x, blockIdx.x, a, b);
-    for (int i = tid; i < 4096; i += TB_THREADS) hist[i] = 0;
-    __syncthreads();
-    scan_row(s_tilde + (int64_t)p * d.T + a, b - a, tid, [&](int, float v) { atomicAdd(&hist[ordered_key(v) >> 20], 1u); });
-    __syncthreads();
-    for (int i = tid; i < 4096; i += TB_THREADS) {
-        const uint32_t c = hist[i];
-        if (c) atomicAdd(&g_hist[(int64_t)p * 4096 + i], c);
-    }
-}
-
-// pass B: every workgroup finds the threshold's bin from the row's histogram, splits its slice into sure Top-B
-// tokens and candidates in LDS, reserves room in the row's two lists with one atomic each and copies them there.
-// Does nothing when the lists cannot hold the row's entries (the per-row kernel then makes its own passes).
-__global__ void __launch_bounds__(TB_THREADS)
-topb_split_kernel(Dims d, const float *s_tilde, int budget, const uint32_t *g_hist, int32_t *g_cnt, int32_t *g_hit,
-                  uint32_t *g_cand)
-{
-    __shared__ uint32_t hist[4096];              // the row's histogram, then this slice's sure tokens
-    __shared__ uint32_t lc_key[TB_CAND];
-    __shared__ int32_t lc_idx[TB_CAND];
-    __shared__ int sh_nhit, sh_ncand, sh_base[2];
-    __shared__ uint32_t sh_pair[2];
-    const int p = blockIdx.y, tid = threadIdx.x, T = d.T;
-    const int k = min(budget, T);
-    int a, b;
-    slice_of_row(T, gridDim.x, blockIdx.x, a, b);
-    for (int i = tid; i < 4096; i += TB_THREADS) hist[i] = g_hist[(int64_t)p * 4096 + i];
-    if (tid == 0) { sh_nhit = 0; sh_ncand = 0; }
-    __syncthreads();
-    uint32_t bin, above;
-    find_bin_from_top(hist, 4096, (uint32_t)k, sh_pair, bin, above);
-    const uint32_t n_bin = hist[bin];
-    __syncthreads();                             // hist is reused below
-    if (!(n_bin <= (uint32_t)TB_CAND && k <= TB_HITS)) return;
-    int32_t *lc_hit = reinterpret_cast<int32_t *>(hist);
-    scan_row(s_tilde + (int64_t)p * T + a, b - a, tid, [&](int t, float v) {
-        const uint32_t key = ordered_key(v);
-        const uint32_t kb = key >> 20;
-        if (kb > bin) lc_hit[atomicAdd(&sh_nhit, 1)] = a + t;
-        else if (kb == bin) { const int c = atomicAdd(&sh_ncand, 1); lc_key[c] = key; lc_idx[c] = a + t; }
-    });
-    __syncthreads();
-    if (tid == 0) sh_base[0] = sh_nhit > 0 ? atomicAdd(&g_cnt[2 * p], sh_nhit) : 0;
-    if (tid == 64) sh_base[1] = sh_ncand > 0 ? atomicAdd(&g_cnt[2 * p + 1], sh_ncand) : 0;
-    __syncthreads();
-    for (int i = tid; i < sh_nhit; i += TB_THREADS) g_hit[(int64_t)p * TB_HITS + sh_base[0] + i] = lc_hit[i];
-    for (int i = tid; i < sh_ncand; i += TB_THREADS) {
-        uint32_t *dst = g_cand + ((int64_t)p * TB_CAND + sh_base[1] + i) * 2;
-        dst[0] = lc_key[i];
-        dst[1] = (uint32_t)lc_idx[i];
-    }
-}
-
-template <bool PLAN>
-__global__ void __launch_bounds__(TB_THREADS)
-topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr, SegView sv, int32_t *seg_budget,
-            int32_t *block_size, int32_t *counter, PlanArgs pa, int offs_cap, int hit_cap, int hist_ways_log2)
-{
-    __shared__ uint32_t hist[TB_HITS];           // pass-A histogram (4096 bins), later the list of Top-B tokens (hit_cap == TB_HITS)
-    __shared__ uint32_t hist2[2048];             // histograms of the later passes
-    extern __shared__ int32_t sh_u[];            // [2][offs_cap]: candidates (key, index) during selection, then offsets and
-                                                 // counters; behind them [hit_cap] Top-B tokens when hit_cap > TB_HITS
-    __shared__ int sh_nhit, sh_ncand;
-    __shared__ uint32_t sh_pair[2];
-    __shared__ int sh_wcnt[TB_THREADS / 64];
-    __shared__ int sh_cut;
-    static_assert(TB_HITS == 4096 && TB_CAND <= TB_OFFS, "LDS regions are shared between phases");
-    int32_t *sh_hit = hit_cap > TB_HITS ? sh_u + 2 * offs_cap : reinterpret_cast<int32_t *>(hist);
-    uint32_t *cand_key = reinterpret_cast<uint32_t *>(sh_u);
-    int32_t *cand_idx = sh_u + offs_cap;
-    int32_t *sh_off = sh_u, *sh_cnt = sh_u + offs_cap;
-    const int p = blockIdx.x, T = d.T;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float *sp = s_tilde + (int64_t)p * T;
-    const int k = min(budget, T);
-    const int64_t row = (int64_t)p * sv.max_segments;
-    if (seg_budget) {
-        for (int i = tid; i < sv.max_segments; i += TB_THREADS) { seg_budget[row + i] = 0; block_size[row + i] = 0; }
-        if (!PLAN && counter && p == 0 && tid < 2) counter[tid] = 0;
-    }
-
-    uint32_t prefix = 0, mask = 0, krem = (uint32_t)max(k, 0), n_eq = 0;
-    int cut = T - 1;
-    bool have_hits = false;                    // sh_hit[0 .. k) holds T_topB
-    if (k <= 0) {
-        prefix = 0xFFFFFFFFu;                  // nothing is inside
-        cut = -1;
-    } else if (k < T) {
-        // ---- pass A: top 12 bits
-        const bool sliced = PLAN && pa.pre_hist;               // the passes over the row were made by sliced kernels
-        if (sliced) {
-            for (int i = tid; i < 4096; i += TB_THREADS) hist[i] = pa.pre_hist[(int64_t)p * 4096 + i];
-        } else {
-            if (hist_ways_log2 > 0) {
-                // The scores of a row crowd into a few bins, and LDS atomics of one instruction on one address run one
-                // after the other: threads are dealt out over 2 or 4 copies of the histogram (in the dynamic region,
-                // which holds nothing yet), added up afterwards.
-                uint32_t *hw = reinterpret_cast<uint32_t *>(sh_u);
-                const int sh = hist_ways_log2, way = tid & ((1 << sh) - 1);
-                for (int i = tid; i < (4096 << sh); i += TB_THREADS) hw[i] = 0;
-                __syncthreads();
-                scan_row(sp, T, tid, [&](int, float v) { atomicAdd(&hw[((ordered_key(v) >> 20) << sh) | way], 1u); });
-                __syncthreads();
-                for (int i = tid; i < 4096; i += TB_THREADS) {
-                    uint32_t c = 0;
-                    for (int w2 = 0; w2 < (1 << sh); ++w2) c += hw[(i << sh) | w2];
-                    hist[i] = c;
-                }
-            } else {
-                for (int i = tid; i < 4096; i += TB_THREADS) hist[i] = 0;
-                __syncthreads();
-                scan_row(sp, T, tid, [&](int, float v) { atomicAdd(&hist[ordered_key(v) >> 20], 1u); });
-            }
-        }
-        __syncthreads();
-        uint32_t bin, above;
-        find_bin_from_top(hist, 4096, krem, sh_pair, bin, above);
-        const uint32_t n_bin = hist[bin];
-        __syncthreads();                       // hist is reused below
-        // the candidate list is as long as the LDS arrays it sits in (the sliced passes stage theirs in TB_CAND entries)
-        const uint32_t cand_cap = sliced ? (uint32_t)TB_CAND : (uint32_t)offs_cap;
-        if (n_bin <= cand_cap && k <= hit_cap) {
-            // ---- pass B: split the row into sure Top-B tokens and candidates
-            if (sliced) {
-                const int nh = pa.pre_cnt[2 * p], nc = pa.pre_cnt[2 * p + 1];
-                for (int i = tid; i < nh; i += TB_THREADS) sh_hit[i] = pa.pre_hit[(int64_t)p * TB_HITS + i];
-                for (int i = tid; i < nc; i += TB_THREADS) {
-                    const uint32_t *src = pa.pre_cand + ((int64_t)p * TB_CAND + i) * 2;
-                    cand_key[i] = src[0];
-                    cand_idx[i] = (int32_t)src[1];
-                }
-                if (tid == 0) { sh_nhit = nh; sh_ncand = nc; }
-            } else {
-                if (tid == 0) { sh_nhit = 0; sh_ncand = 0; }
-                __syncthreads();
-                scan_row(sp, T, tid, [&](int t, float v) {
-                    const uint32_t key = ordered_key(v);
-                    const uint32_t kb = key >> 20;
-                    if (kb > bin) sh_hit[atomicAdd(&sh_nhit, 1)] = t;
-                    else if (kb == bin) { const int c = atomicAdd(&sh_ncand, 1); cand_key[c] = key; cand_idx[c] = t; }
-                });
-            }
-            __syncthreads();
-            const int ncand = sh_ncand;
-            krem -= above;
-            prefix = bin << 20;
-            mask = 0xFFF00000u;
-            // ---- the remaining 20 bits on the candidate list
-            for (int shift = 10; shift >= 0; shift -= 10) {
-                for (int i = tid; i < 1024; i += TB_THREADS) hist2[i] = 0;
-                __syncthreads();
-                for (int c = tid; c < ncand; c += TB_THREADS)
-                    if ((cand_key[c] & mask) == prefix) atomicAdd(&hist2[(cand_key[c] >> shift) & 1023u], 1u);
-                __syncthreads();
-                uint32_t b2, a2;
-                find_bin_from_top(hist2, 1024, krem, sh_pair, b2, a2);
-                krem -= a2;
-                n_eq = hist2[b2];
-                prefix |= b2 << shift;
-                mask |= 1023u << shift;
-                __syncthreads();
-            }
-            have_hits = true;
-        } else {
-            // ---- three histogram passes over the row
-            const int shifts[3] = {21, 10, 0};
-            const int bits[3] = {11, 11, 10};
-            for (int pass = 0; pass < 3; ++pass) {
-                const int nbins = 1 << bits[pass], shift = shifts[pass];
-                for (int i = tid; i < nbins; i += TB_THREADS) hist2[i] = 0;
-                __syncthreads();
-                scan_row(sp, T, tid, [&](int, float v) {
-                    const uint32_t key = ordered_key(v);
-                    if ((key & mask) == prefix) atomicAdd(&hist2[(key >> shift) & (nbins - 1)], 1u);
-                });
-                __syncthreads();
-                uint32_t b2, a2;
-                find_bin_from_top(hist2, nbins, krem, sh_pair, b2, a2);
-                krem -= a2;
-                n_eq = hist2[b2];
-                prefix |= b2 << shift;
-                mask |= (uint32_t)(nbins - 1) << shift;
-                __syncthreads();
-            }
-        }
-        // prefix is the key v of the k-th best score; krem of its n_eq ties are inside, lowest indices first
-        if (krem < n_eq) {
-            int seen = 0;
-            for (int c0 = 0; c0 < T; c0 += TB_THREADS) {
-                const int t = c0 + tid;
-                const bool tie = t < T && ordered_key(sp[t]) == prefix;
-                const unsigned long long bal = __ballot(tie);
-                if (lane == 0) sh_wcnt[wave] = __popcll(bal);
-                __syncthreads();
-                int before = 0, total = 0;
-                for (int w = 0; w < TB_THREADS / 64; ++w) { int c = sh_wcnt[w]; if (w < wave) before += c; total += c; }
-                const bool found = seen + total >= (int)krem;
-                if (found && tie && seen + before + __popcll(bal & ((1ull << lane) - 1ull)) + 1 == (int)krem) sh_cut = t;
-                __syncthreads();
-                if (found) { cut = sh_cut; break; }
-                seen += total;
-            }
-        }
-        if (have_hits) {
-            // candidates at or above the threshold complete the list of Top-B tokens
-            const int ncand = sh_ncand;
-            for (int c = tid; c < ncand; c += TB_THREADS) {
-                const uint32_t key = cand_key[c];
-                const int t = cand_idx[c];
-                if (key > prefix || (key == prefix && t <= cut)) sh_hit[atomicAdd(&sh_nhit, 1)] = t;
-            }
-            __syncthreads();                   // sh_nhit == k; the candidate region is free again
-        }
-    }   // k < T; for k >= T everything is inside: key 0 is below every score's key, cut = T - 1
-    if (tid == 0) { thr[2 * p] = (int32_t)prefix; thr[2 * p + 1] = cut; }
-    if (!seg_budget || k <= 0) return;
-
-    // ---- implicit budgets: every Top-B token adds one to its segment (rows cleared above; the barrier below
-    // orders the clearing stores of all wavefronts before the first atomic)
+    const uint4 c = reinterpret_cast<const uint4 *>(hist)[tid];
+    const uint32_t mine = c.x + c.y + c.z + c.w, incl = wave_scan_u(mine);
+    if (lane == 63) sh.w[wave] = incl;
     __syncthreads();
-    const int seq = seq_of_problem(d, p);
-    const int32_t *off = sv.seg_off + sv.seq_ptr[seq];
-    const int K = sv.seq_ptr[seq + 1] - sv.seq_ptr[seq] - 1;
-    if (k >= T) {
-        for (int j = tid; j < K; j += TB_THREADS) seg_budget[row + j] = off[j + 1] - off[j];
-        return;
-    }
-    if (!have_hits && k <= hit_cap) {
-        // collect T_topB with one more pass over the row
-        if (tid == 0) sh_nhit = 0;
-        __syncthreads();
-        scan_row(sp, T, tid, [&](int t, float v) {
-            if (in_topb(v, t, prefix, cut)) sh_hit[atomicAdd(&sh_nhit, 1)] = t;      // exactly k of them
-        });
-        __syncthreads();
-        have_hits = true;
-    }
-    if (have_hits && K + 1 <= offs_cap) {
-        // assign the listed tokens to segments in parallel: binary search on an LDS copy of the offsets, LDS counters
-        for (int j = tid; j <= K; j += TB_THREADS) { sh_off[j] = off[j]; sh_cnt[j] = 0; }
-        __syncthreads();
-        for (int i = tid; i < sh_nhit; i += TB_THREADS) atomicAdd(&sh_cnt[segment_of(sh_off, K, sh_hit[i])], 1);
-        __syncthreads();
-        for (int j = tid; j < K; j += TB_THREADS) seg_budget[row + j] = sh_cnt[j];
-        if (PLAN) {
-            // exclusive prefix of the counters in place (K + 1 entries: b_k = pos[k + 1] - pos[k]); offs_cap / 1024
-            // consecutive entries per thread, wavefront scan, then the sixteen wavefront totals
-            __syncthreads();
-            constexpr int PER_MAX = TB_OFFS_MAX / TB_THREADS;
-            const int per = offs_cap / TB_THREADS;
-            const int j0 = per * tid;
-            int c[PER_MAX], tot = 0;
+    uint32_t before = incl - mine;
 #pragma unroll
-            for (int i = 0; i < PER_MAX; ++i) { c[i] = (i < per && j0 + i < K) ? sh_cnt[j0 + i] : 0; tot += c[i]; }
-            int incl = tot;
-            for (int o = 1; o < 64; o <<= 1) { const int x = __shfl_up(incl, o); if (lane >= o) incl += x; }
-            if (lane == 63) sh_wcnt[wave] = incl;
-            __syncthreads();
-            int run = incl - tot;
-            for (int w = 0; w < wave; ++w) run += sh_wcnt[w];
+    for (int w = 0; w < TB_WAVES; ++w) before += w < wave ? sh.w[w] : 0u;
+    if (before < r && r <= before + mine) {
+        uint32_t b = 4 * tid, n = c.x;
+        if (before + n < r) { before += n; ++b; n = c.y; }
+        if (before + n < r) { before += n; ++b; n = c.z; }
+        if (before + n < r) { before += n; ++b; n = c.w; }
+        sh.found[0] = b; sh.found[1] = before; sh.found[2] = n;
+    }
+    __syncthreads();
+    bin = sh.found[0]; above = sh.found[1]; count = sh.found[2];
+}
+
+// Histogram of the workgroup's keys (N per thread, bit e of `valid`: key e counts) over TB_BINS bins of equal width
+// that span exactly the keys there are, bin 0 the largest.  The span is what keeps the LDS atomics apart: scores of a
+// row crowd into a few bins of a fixed digit of the key.  At least one key must be valid; ends with a barrier.
+template <int N>
+__device__ inline void span_histogram(const uint32_t (&key)[N], uint32_t valid, uint32_t *hist, TopbShared &sh, uint32_t &top, int &shift)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t mx = 0u, mn = 0xFFFFFFFFu;
 #pragma unroll
-            for (int i = 0; i < PER_MAX; ++i) { if (i < per && j0 + i <= K) sh_cnt[j0 + i] = run; run += c[i]; }
-            __syncthreads();
-            int32_t *out = pa.idx_out + (int64_t)p * budget;
-            if (tid == 0) pa.n_sel_out[p] = k;                 // k = B < T here, so there is nothing to pad
-            // the token of every single-token segment goes straight to its place
-            for (int i = tid; i < sh_nhit; i += TB_THREADS) {
-                const int t = sh_hit[i], sg = segment_of(sh_off, K, t);
-                if (sh_cnt[sg + 1] - sh_cnt[sg] == 1) { out[sh_cnt[sg]] = t; block_size[row + sg] = 1; }
-            }
-            // the others to the search lists (as in heavy_list_kernel), with their output offset
-            const int32_t thr_key = (int32_t)prefix;
-            for (int c0 = 0; c0 < K; c0 += TB_THREADS) {
-                const int sg = c0 + tid;
-                const int bk = sg < K ? sh_cnt[sg + 1] - sh_cnt[sg] : 0;
-                const int a = sg < K ? sh_off[sg] : 0, b = sg < K ? sh_off[sg + 1] : 0;
-                const bool hv = bk >= 2 && b - a <= CAPT, hx = bk >= 2 && b - a > CAPT;
-                const unsigned long long bal = __ballot(hv), bax = __ballot(hx);
-                __syncthreads();                               // the previous round's sh_pair reads are done
-                if (lane == 0) { sh_wcnt[wave] = __popcll(bal) | (__popcll(bax) << 16); }
-                __syncthreads();
-                int before = 0, total = 0, before_x = 0, total_x = 0;
-                for (int w = 0; w < TB_THREADS / 64; ++w) {
-                    const int n0 = sh_wcnt[w] & 0xffff, n1 = sh_wcnt[w] >> 16;
-                    if (w < wave) { before += n0; before_x += n1; }
-                    total += n0; total_x += n1;
-                }
-                if (tid == 0 && total > 0) sh_pair[0] = (uint32_t)atomicAdd(&counter[0], total);
-                if (tid == 1 && total_x > 0) sh_pair[1] = (uint32_t)atomicAdd(&counter[1], total_x);
-                __syncthreads();
-                if (hv || hx) {
-                    const unsigned long long lt = (1ull << lane) - 1ull;
-                    const int pos = hv ? (int)sh_pair[0] + before + __popcll(bal & lt) : (int)sh_pair[1] + before_x + __popcll(bax & lt);
-                    if (pos < pa.capacity) {
-                        SegRec r;
-                        r.p = p; r.k = sg; r.a = a; r.b = b; r.bk = bk; r.g = thr_key; r.pos = cut; r.out = sh_cnt[sg];
-                        (hv ? pa.list : pa.list_long)[pos] = r;
-                    }
-                }
-            }
+    for (int e = 0; e < N; ++e)
+        if ((valid >> e) & 1u) { mx = max(mx, key[e]); mn = min(mn, key[e]); }
+    mx = wave_max_u(mx);
+    mn = ~wave_max_u(~mn);
+    if (lane == 0) { sh.kmax[wave] = mx; sh.kmin[wave] = mn; }
+    reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
+    static_assert(TB_BINS == 4 * TB_THREADS, "four bins per thread");
+    __syncthreads();
+    mx = 0u; mn = 0xFFFFFFFFu;
+#pragma unroll
+    for (int w = 0; w < TB_WAVES; ++w) { mx = max(mx, sh.kmax[w]); mn = min(mn, sh.kmin[w]); }
+    const uint32_t range = mx - mn;
+    shift = range < TB_BINS ? 0 : 20 - __builtin_clz(range);
+    top = mx;
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+        if ((valid >> e) & 1u) atomicAdd(&hist[(mx - key[e]) >> shift], 1u);
+    __syncthreads();
+}
+
+// Key and index cut of the k-th best of the workgroup's (key, token) pairs, value descending, token ascending, 1 <= k
+// <= their number: the histogram gives its bin, the entries of the bin (usually a handful) are ranked one against
+// another.  false when the bin holds more than TB_RANKED of them.
+template <int N, typename TOK>
+__device__ inline bool kth_best(const uint32_t (&key)[N], uint32_t valid, TOK tok, int k, int T, uint32_t *hist, TopbShared &sh,
+                                uint32_t &thr, int &cut)
+{
+    const int tid = threadIdx.x;
+    uint32_t top, bin, above, count;
+    int shift;
+    if (tid == 0) sh.n_bin = 0;
+    span_histogram<N>(key, valid, hist, sh, top, shift);
+    find_bin(hist, (uint32_t)k, sh, bin, above, count);
+    if (count > (uint32_t)TB_RANKED) return false;
+    uint2 *ent = reinterpret_cast<uint2 *>(hist);              // the histogram has been read by everyone
+#pragma unroll
+    for (int e = 0; e < N; ++e)
+        if (((valid >> e) & 1u) && (top - key[e]) >> shift == bin) ent[atomicAdd(&sh.n_bin, 1)] = make_uint2(key[e], (uint32_t)tok(e));
+    __syncthreads();
+    if (tid < (int)count) {
+        const uint2 me = ent[tid];
+        int rank = 0, gt = 0, eq = 0;
+        for (int j = 0; j < (int)count; ++j) {
+            const uint2 o = ent[j];
+            gt += o.x > me.x;
+            eq += o.x == me.x;
+            rank += o.x > me.x || (o.x == me.x && o.y < me.y);
         }
-    } else if (have_hits) {
-        for (int i = tid; i < sh_nhit; i += TB_THREADS) atomicAdd(&seg_budget[row + segment_of(off, K, sh_hit[i])], 1);
-    } else {
-        scan_row(sp, T, tid, [&](int t, float v) {
-            if (in_topb(v, t, prefix, cut)) atomicAdd(&seg_budget[row + segment_of(off, K, t)], 1);
-        });
+        const int krem = k - (int)above;
+        if (rank == krem - 1) {
+            sh.thr = me.x;
+            sh.cut = krem - gt == eq ? T - 1 : (int)me.y;      // all ties inside: no cut
+        }
     }
+    __syncthreads();
+    thr = sh.thr;
+    cut = sh.cut;
+    return true;
+}
+
+// Appends the tokens t0[j] + 0 .. 3 of the vectors v[j] that `take` to the workgroup's list: one LDS atomic per
+// wavefront.  Tokens behind the list's end are counted but not stored.
+template <int J, typename F>
+__device__ inline void append_tokens(const float4 (&v)[J], const int (&t0)[J], F take, int32_t *list, int cap, TopbShared &sh)
+{
+    unsigned long long m[4 * J];
+    int total = 0;
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        m[4 * j] = __ballot(take(t0[j], v[j].x));
+        m[4 * j + 1] = __ballot(take(t0[j] + 1, v[j].y));
+        m[4 * j + 2] = __ballot(take(t0[j] + 2, v[j].z));
+        m[4 * j + 3] = __ballot(take(t0[j] + 3, v[j].w));
+    }
+#pragma unroll
+    for (int e = 0; e < 4 * J; ++e) total += __popcll(m[e]);
+    if (total == 0) return;
+    const int lane = threadIdx.x & 63;
+    int base = 0;
+    if (lane == 0) base = atomicAdd(&sh.n, total);
+    base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+    for (int e = 0; e < 4 * J; ++e) {
+        if (m[e] == 0) continue;
+        const int pos = base + lanes_below(m[e]);
+        if (((m[e] >> lane) & 1ull) && pos < cap) list[pos] = t0[e >> 2] + (e & 3);
+        base += __popcll(m[e]);
+    }
+}
+
+// A lower bound of the k-th best score of a row, from a sample of TB_ROUND of its values (512 pieces of 128 bytes,
+// evenly spaced): the edge of the bin that holds the sample's `rank`-th best, where `rank` lies so far behind the share
+// of the k best that falls into a sample that they are all above it (see topb_rank).  A bound that is wrong all the
+// same is noticed by the count of what lies above it.
+__device__ inline float sample_bound(const RowView &r, int rank, uint32_t *hist, TopbShared &sh)
+{
+    if (rank >= TB_ROUND) return -INFINITY;
+    const int tid = threadIdx.x, pieces = r.nvec >> 3;         // >= 512
+    float4 v[TB_REG / 4];
+#pragma unroll
+    for (int j = 0; j < TB_REG / 4; ++j) {
+        const int c = (j * TB_THREADS + tid) >> 3;
+        v[j] = r.vp[(int)(((int64_t)c * pieces) >> 9) * 8 + (tid & 7)];
+    }
+    uint32_t key[TB_REG];
+#pragma unroll
+    for (int j = 0; j < TB_REG / 4; ++j) {
+        key[4 * j] = ordered_key(v[j].x); key[4 * j + 1] = ordered_key(v[j].y);
+        key[4 * j + 2] = ordered_key(v[j].z); key[4 * j + 3] = ordered_key(v[j].w);
+    }
+    uint32_t top, bin, above, count;
+    int shift;
+    span_histogram<TB_REG>(key, 0xFFFFu, hist, sh, top, shift);
+    find_bin(hist, (uint32_t)rank, sh, bin, above, count);
+    const uint64_t down = (((uint64_t)bin + 1) << shift) - 1;  // the bin's smallest key is `down` below the largest
+    return down >= top ? -INFINITY : float_of_key(top - (uint32_t)down);
+}
+
+// tokens [a, b) of the row's vectors (multiples of the round only at a) whose score reaches `bound`, to the list
+__device__ inline void collect_above(const RowView &r, int i_begin, int i_end, float bound, int32_t *list, int cap, TopbShared &sh)
+{
+    const int tid = threadIdx.x;
+    constexpr int J = TB_REG / 4;
+    float4 nxt[J];
+    auto fetch = [&](int i0) {
+#pragma unroll
+        for (int j = 0; j < J; ++j) nxt[j] = r.vp[min(i0 + j * TB_THREADS + tid, r.nvec - 1)];
+    };
+    fetch(i_begin);
+    for (int i0 = i_begin; i0 < i_end; i0 += J * TB_THREADS) {
+        float4 v[J];
+        int t0[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int i = i0 + j * TB_THREADS + tid;
+            v[j] = nxt[j];
+            t0[j] = i < i_end ? r.token(i) : -4;
+        }
+        if (i0 + J * TB_THREADS < i_end) fetch(i0 + J * TB_THREADS);
+        append_tokens<J>(v, t0, [&](int t, float x) { return t >= 0 && x >= bound; }, list, cap, sh);
+    }
+}
+
+// one scalar token per thread (or none)
+__device__ inline void append_extra(const RowView &r, bool take, int32_t *list, int cap, TopbShared &sh)
+{
+    if (take) { const int pos = atomicAdd(&sh.n, 1); if (pos < cap) list[pos] = r.extra; }
 }
 
 // ------------------------------------------------------------------ one segment, one block size
@@ -705,139 +605,798 @@ __device__ inline void segment_fill(V val, int a, int b, int g, int bk, WaveScra
     __builtin_amdgcn_wave_barrier();
 }
 
+// ------------------------------------------------------------------ sums that cannot round
+// The scores of a segment are fp32 values, summed in fp64.  Every value and every partial sum is a multiple of the
+// last bit of the smallest nonzero one, and the sum of n of them stays below n times twice the power of two of the
+// largest, so as long as
+//     exponent range + 24 bits of mantissa + ceil(log2 n) <= 53
+// no partial sum rounds in ANY order: prefix sums by lane shuffles, differences of prefixes and sums over arbitrary
+// subsets then equal the ordered sums bit for bit.  Segments whose scores span more (23 powers of two at 64 tokens, 17
+// at 4 095) take the ordered sums (segment_fill above).
+// biggest: the largest |score| of a segment; smallest: the smallest nonzero one as its bits doubled, less one; total:
+// the sum (not finite when a score is not); n >= 2
+__device__ inline void note_size(float v, float &biggest, uint32_t &smallest)
+{
+    biggest = fmaxf(biggest, fabsf(v));
+    smallest = min(smallest, (__float_as_uint(v) << 1) - 1u);  // zero becomes the largest value
+}
+__device__ inline bool sums_are_exact(float biggest, uint32_t smallest, double total, int n)
+{
+    const int hi = max(wave_max_i(__float_as_int(biggest)) >> 23, 1), lo = max((int)((~wave_max_u(~smallest) + 1u) >> 24), 1);
+    return hi - lo <= 29 - (32 - __builtin_clz(n - 1)) && fabs(total) < INFINITY;
+}
+
+// ranks of the block walk of Alg. 2 without the short last block's own place in the order: how many blocks are taken
+// whole, and how many tokens they hold.  q: blocks ranked before the short last one (`ts` < g tokens; unused else)
+__device__ inline void whole_blocks(int nb, int g, int ts, int c, int r, int q, int &rstar, int &nwhole)
+{
+    if (ts == g) {
+        rstar = min(nb, c);
+        nwhole = rstar * g;
+        return;
+    }
+    if (q < c) {
+        if (ts <= r) { rstar = c + 1; nwhole = c * g + ts; } else { rstar = c; nwhole = c * g - g + ts; }
+    } else if (q == c) {
+        if (ts <= r) { rstar = c + 1; nwhole = c * g + ts; } else { rstar = c; nwhole = c * g; }
+    } else {
+        rstar = c; nwhole = c * g;
+    }
+    rstar = min(rstar, nb);
+}
+
+// order-preserving signed key of a float (the two zeros: callers pass no -0)
+__device__ inline int key_of(float x) { const int b = __float_as_int(x); return b ^ ((b >> 31) & 0x7fffffff); }
+constexpr int NO_KEY = (int)0x80000000;
+
+// Lane of the largest x (lowest lane among equal ones) whose key, of x rounded to fp32, is not NO_KEY: one 32-bit
+// reduction, and an fp64 one only where several x round to the same fp32 value.
+__device__ inline int best_lane(double x, int key)
+{
+    const int mk = wave_max_i(key);
+    unsigned long long m = __ballot(key == mk);
+    if (m & (m - 1)) {
+        const double mx = wave_max_d(key == mk ? x : -INFINITY);
+        m = __ballot(key == mk && x == mx);
+    }
+    return __builtin_ctzll(m);
+}
+
+// The best `rem` (value descending, index ascending) of the sz <= 64 scores that lanes 0 .. sz - 1 hold; adds their sum
+// to `score`.
+constexpr int FEW_TOKENS = 4;              // up to so many are picked one by one, more by their ranks
+__device__ inline unsigned long long best_tokens(float v, int sz, int rem, double &score)
+{
+    const int lane = threadIdx.x & 63;
+    v += 0.f;                                                  // no -0
+    if (rem <= FEW_TOKENS) {
+        unsigned long long taken = 0;
+        int key = lane < sz ? key_of(v) : NO_KEY;
+#pragma nounroll
+        for (int j = 0; j < rem; ++j) {
+            const int l = __builtin_ctzll(__ballot(key == wave_max_i(key)));
+            taken |= 1ull << l;
+            score += (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+            if (lane == l) key = NO_KEY;
+        }
+        return taken;
+    }
+    int rk = 0;
+#pragma nounroll
+    for (int j = 0; j < sz; ++j) {
+        const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
+        rk += (o > v || (o == v && j < lane)) ? 1 : 0;
+    }
+    const bool tk = lane < sz && rk < rem;
+    score += wave_sum_d(tk ? (double)v : 0.0);
+    return __ballot(tk);
+}
+
+// T_k(g) of a segment of n tokens whose sums are exact; pre[x], 0 <= x <= n, is the sum of its first x scores.  Returns
+// Score_k(g).  Up to 64 blocks: one per lane, the blocks taken whole are the bits of `blocks`.  More: block lane + 64 i
+// is taken whole when bit i of the lane's `whole` is set.  Tokens plo + j of the cut block (plo < 0: none) are taken
+// when bit j of pmask is set.  inv: see CandList.
+struct Fill {
+    unsigned long long blocks, pmask;
+    uint32_t whole;
+    int plo;
+};
+__device__ inline uint64_t ordered_key_d(double x)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(x == 0.0 ? 0.0 : x);       // the zeros rank as equal
+    return (u >> 63) ? ~u : u | (1ull << 63);
+}
+constexpr int FEW_PICKS = 16;              // of more than 64 blocks, so many are picked one by one, more by bisection of their sums
+
+__device__ inline double fill_prefix(const double *pre, int n, int g, int inv, int bk, Fill &f)
+{
+    const int lane = threadIdx.x & 63;
+    const int nb = ((n + g - 1) * inv) >> CAND_INV_BITS, ts = n - (nb - 1) * g;
+    const int c = (bk * inv) >> CAND_INV_BITS, r = bk - c * g;
+    int rstar, nwhole, q = 0;
+    double score = 0.0;
+    f.plo = -1;
+    f.pmask = 0;
+    int rem;
+    if (nb <= 64) {
+        const int x0 = min(lane * g, n), x1 = min(x0 + g, n);
+        const double phi = pre[x1] - pre[x0];
+        if (ts != g) {
+            const double pt = readlane_d(phi, nb - 1);
+            q = __popcll(__ballot(lane < nb - 1 && phi >= pt));     // an equal sum ranks first
+        }
+        whole_blocks(nb, g, ts, c, r, q, rstar, nwhole);
+        if (rstar >= nb) {
+            f.blocks = ~0ull;
+            return pre[n];
+        }
+        rem = bk - nwhole;
+        int key = lane < nb ? key_of((float)phi) : NO_KEY;
+        f.blocks = 0;
+        // pick the blocks one by one, best first (sum descending, index ascending); the last pick is the cut block
+        const int picks = rstar + (rem > 0 ? 1 : 0);
+#pragma nounroll
+        for (int sel = 0; sel < picks; ++sel) {
+            const int m = best_lane(phi, key);
+            if (sel < rstar) {
+                f.blocks |= 1ull << m;
+                score += readlane_d(phi, m);
+                if (lane == m) key = NO_KEY;
+            } else {
+                f.plo = m * g;
+            }
+        }
+    } else {
+        auto phi = [&](int m) { return pre[min(m * g + g, n)] - pre[m * g]; };
+        if (ts != g) {
+            const double pt = phi(nb - 1);
+            int cnt = 0;
+#pragma nounroll
+            for (int m = lane; m < nb - 1; m += 64) cnt += phi(m) >= pt ? 1 : 0;
+            q = wave_sum_i(cnt);
+        }
+        whole_blocks(nb, g, ts, c, r, q, rstar, nwhole);
+        f.whole = 0;
+        if (rstar >= nb) {
+            f.whole = ~0u;
+            return pre[n];
+        }
+        rem = bk - nwhole;
+        int one_by_one = rstar;
+        if (rstar > FEW_PICKS) {
+            one_by_one = 0;
+            // the largest key with at least rstar blocks at or above it, by bisection
+            uint64_t lo = 0, hi = ~0ull;                       // count(>= lo) >= rstar
+#pragma nounroll
+            while (lo < hi) {
+                const uint64_t mid = lo + ((hi - lo) >> 1) + 1;
+                int cnt = 0;
+#pragma nounroll
+                for (int m = lane; m < nb; m += 64) cnt += ordered_key_d(phi(m)) >= mid ? 1 : 0;
+                if (wave_sum_i(cnt) >= rstar) lo = mid; else hi = mid - 1;
+            }
+            int gt = 0;
+#pragma nounroll
+            for (int m = lane; m < nb; m += 64) gt += ordered_key_d(phi(m)) > lo ? 1 : 0;
+            int ties = rstar - wave_sum_i(gt);                 // ties at the threshold: lowest indices first
+            double part = 0.0;
+#pragma nounroll
+            for (int i = 0; i < (nb + 63) / 64; ++i) {
+                const int m = lane + 64 * i;
+                const double x = m < nb ? phi(m) : 0.0;
+                const uint64_t key = ordered_key_d(x);
+                const unsigned long long eq = __ballot(m < nb && key == lo);
+                const bool take = m < nb && (key > lo || (key == lo && lanes_below(eq) < ties));
+                ties -= min(ties, (int)__popcll(eq));
+                if (take) { f.whole |= 1u << i; part += x; }
+            }
+            score = wave_sum_d(part);
+        }
+        const int picks = one_by_one + (rem > 0 ? 1 : 0);
+#pragma nounroll
+        for (int sel = 0; sel < picks; ++sel) {
+            double mx = -INFINITY;
+            int bm = 0x7fffffff;
+#pragma nounroll
+            for (int m = lane, i = 0; m < nb; m += 64, ++i) {
+                const double x = phi(m);
+                if (!((f.whole >> i) & 1u) && x > mx) { mx = x; bm = m; }
+            }
+            const double all = wave_max_d(mx);
+            bm = -wave_max_i(mx == all ? -bm : -0x7fffffff);
+            if (sel < one_by_one) {
+                score += all;
+                if (lane == (bm & 63)) f.whole |= 1u << (bm >> 6);
+            } else {
+                f.plo = bm * g;
+            }
+        }
+    }
+    if (rem > 0) {
+        const int sz = min(g, n - f.plo), t = f.plo + min(lane, sz - 1);
+        f.pmask = best_tokens((float)(pre[t + 1] - pre[t]), sz, rem, score);     // the scores themselves, exactly
+    }
+    return score;
+}
+
+// What a wavefront needs to know of its problem and call
+struct SearchCtx {
+    const float *sp;           // the problem's scores
+    int32_t *block_size;       // its row
+    int32_t *out;              // its idx_out row
+    int budget;
+    float tau;
+    int cand_g, cand_inv, n_cand;          // lane c: candidate c (the wavefront's copy of CandList)
+    __device__ inline SearchCtx(const float *s_tilde, int T, int p, int32_t *bs, int max_segments, int32_t *idx, int budget_, float tau_,
+                                const CandList &cand)
+        : sp(s_tilde + (int64_t)p * T), block_size(bs + (int64_t)p * max_segments), out(idx ? idx + (int64_t)p * budget_ : nullptr),
+          budget(budget_), tau(tau_), cand_g(cand.g[threadIdx.x & (MAX_CAND - 1)]), cand_inv(cand.inv[threadIdx.x & (MAX_CAND - 1)]),
+          n_cand(cand.n)
+    {
+    }
+};
+
+// appends the tokens c0 + lane of mask m, ascending, at `pos` of the problem's idx_out row
+__device__ inline void put_tokens(const SearchCtx &x, int &pos, int c0, unsigned long long m)
+{
+    const int lane = threadIdx.x & 63, jo = pos + lanes_below(m);
+    if (((m >> lane) & 1ull) && jo < x.budget) x.out[jo] = c0 + lane;
+    pos += __popcll(m);
+}
+// T_k(1) = T_topB & S_k (b_k is the implicit budget)
+__device__ inline void put_topb(const SearchCtx &x, const SegRec &r)
+{
+    const int lane = threadIdx.x & 63;
+    int pos = r.out;
+#pragma nounroll
+    for (int c0 = r.a; c0 < r.b; c0 += 64) {
+        const int t = c0 + lane;
+        put_tokens(x, pos, c0, __ballot(t < r.b && in_topb(x.sp[min(t, r.b - 1)], t, (uint32_t)r.g, r.pos)));
+    }
+}
+
+// The search of one segment by one wavefront: Score_base, then the candidates largest first, g_k* and (EMIT) T_k(g_k*) in
+// ascending order at the record's `out`.  false, and nothing written, when its sums may round.  pre: LDS for n + 1 (at
+// least 129) prefix sums; v: first_scores of the segment.
+//
+// What bounds this is the length of the wavefront's instruction stream, so a segment's scores are turned into prefix sums
+// once, where a block's sum is one subtraction for every candidate.
+// A segment's scores as search_exact takes them, behind its end those of its last token: up to 64 tokens one per lane, up
+// to 128 two; of longer segments nothing is needed.
+__device__ inline float2 first_scores(const float *sp, const SegRec &r)
+{
+    const int lane = threadIdx.x & 63, last = r.b - 1;
+    if (r.b - r.a <= 64) return make_float2(sp[min(r.a + lane, last)], 0.f);
+    return make_float2(sp[min(r.a + 2 * lane, last)], sp[min(r.a + 2 * lane + 1, last)]);
+}
+
+template <bool EMIT>
+__device__ inline bool search_exact(const SearchCtx &x, const SegRec &r, float2 v, double *pre)
+{
+    const int lane = threadIdx.x & 63;
+    const int a = r.a, n = r.b - a, bk = r.bk, gcap = min(n, bk);                // G_k: g <= min(|S_k|, b_k, g_max)
+    const float *sp = x.sp;
+    // ---- Score_base, prefix sums (R tokens per lane and round of 64 R), sizes of the scores
+    double base, total;
+    float big = 0.f;
+    uint32_t small = ~0u;
+    const float thr = r.g ? float_of_key((uint32_t)r.g) : -INFINITY;             // key 0: everything is inside
+    auto top = [&](float v, int t) { return v > thr || (v == thr && a + t <= r.pos); };    // finite scores: as in_topb
+    if (n <= 64) {
+        const float w = lane < n ? v.x : 0.f;
+        note_size(w, big, small);
+        base = top(w, lane) && lane < n ? (double)w : 0.0;
+        const double s = wave_scan_d((double)w);
+        if (lane == 0) pre[0] = 0.0;
+        pre[lane + 1] = s;
+        total = readlane_d(s, 63);
+    } else if (n <= 128) {
+        const int t0 = 2 * lane;
+        const float w0 = t0 < n ? v.x : 0.f, w1 = t0 + 1 < n ? v.y : 0.f;
+        note_size(w0, big, small);
+        note_size(w1, big, small);
+        base = (top(w0, t0) && t0 < n ? (double)w0 : 0.0) + (top(w1, t0 + 1) && t0 + 1 < n ? (double)w1 : 0.0);
+        const double sum = (double)w0 + (double)w1, s = wave_scan_d(sum);
+        if (lane == 0) pre[0] = 0.0;
+        pre[t0 + 1] = s - (double)w1;
+        pre[t0 + 2] = s;
+        total = readlane_d(s, 63);
+    } else {
+        base = total = 0.0;
+#pragma nounroll
+        for (int c0 = 0; c0 <= n; c0 += 512) {                 // pre[n] included
+            const int t0 = c0 + 8 * lane;
+            float w[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) w[j] = sp[min(a + t0 + j, r.b - 1)];
+            double sum = 0.0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (t0 + j >= n) w[j] = 0.f;
+                note_size(w[j], big, small);
+                sum += (double)w[j];
+                base += t0 + j < n && top(w[j], t0 + j) ? (double)w[j] : 0.0;
+            }
+            const double s = total + wave_scan_d(sum);
+            double y = s - sum;
+            if (t0 <= n) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) { pre[t0 + j] = y; y += (double)w[j]; }
+            }
+            total = readlane_d(s, 63);
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (!sums_are_exact(big, small, total, n)) return false;
+
+    // R_k(g) >= tau  <=>  Score_k(g) >= tau * Score_base; g_k* is the first accepted, largest first (Eq. gk_star)
+    const double need = (double)x.tau * wave_sum_d(base);
+    int gstar = 0, inv = 0;
+    Fill f;
+#pragma nounroll
+    for (int c = x.n_cand - 1; c >= 0; --c) {
+        const int g = __builtin_amdgcn_readlane(x.cand_g, c);
+        if (g > gcap) continue;
+        if (g == 1) { gstar = 1; break; }                      // token level: the unconditional last resort
+        inv = __builtin_amdgcn_readlane(x.cand_inv, c);
+        if (fill_prefix(pre, n, g, inv, bk, f) >= need) { gstar = g; break; }
+    }
+    if (lane == 0) x.block_size[r.k] = gstar;
+    if (EMIT && gstar == 1) put_topb(x, r);
+    if (EMIT && gstar > 1) {
+        int pos = r.out;
+        const bool few = n <= 64 * gstar;
+#pragma nounroll
+        for (int c0 = 0; c0 < n; c0 += 64) {
+            const int t = c0 + lane, m = (t * inv) >> CAND_INV_BITS, j = t - f.plo;
+            bool tk;
+            if (few) tk = (f.blocks >> m) & 1ull;
+            else tk = ((uint32_t)__shfl((int)f.whole, m & 63) >> (m >> 6)) & 1u;
+            put_tokens(x, pos, a + c0, __ballot(t < n && (tk || (f.plo >= 0 && j >= 0 && j < 64 && ((f.pmask >> j) & 1ull)))));
+        }
+    }
+    __builtin_amdgcn_wave_barrier();                           // `pre` is reused by the next segment
+    return true;
+}
+
+// Records of segments whose prefix sums exceed the LDS slice of a search wavefront (PRE_TOKENS), searched by the
+// per-problem workgroup that made them: recs[0 .. n) , LDS for PRE_LONG + 1 prefix sums.  Segments up to a quarter of
+// that go to four wavefronts at a time.  A record is kept (compacted to the front) for the search kernel when its
+// segment is longer still or its sums may round; returns how many were.  All threads take part.
+template <bool EMIT>
+__device__ inline int search_long(const SearchCtx &x, SegRec *recs, int n, double *pre, int *kept)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x == 0) *kept = 0;
+    __syncthreads();
+    for (int i0 = 0; i0 < n; i0 += 4) {
+        const SegRec r = recs[min(i0 + min(wave, 3), n - 1)];
+        const int len = r.b - r.a;
+        const bool mine = wave < 4 && i0 + wave < n, quarter = len <= PRE_LONG / 4;
+        __syncthreads();                                       // read before any is overwritten
+#pragma nounroll
+        for (int turn = 0; turn < 5; ++turn) {                 // 0: a quarter each, 1 .. 4: the whole area, one after the other
+            if (mine && (turn == 0 ? quarter : !quarter && wave == turn - 1)) {
+                const bool done = len <= PRE_LONG &&
+                    search_exact<EMIT>(x, r, first_scores(x.sp, r), pre + (turn == 0 ? wave * ((PRE_LONG + 1) / 4) : 0));
+                if (!done && lane == 0) recs[atomicAdd(kept, 1)] = r;
+            }
+            __syncthreads();
+        }
+    }
+    return *kept;
+}
+
+// What the search that also selects needs of the Top-B kernel (see topb_kernel<true, ..>)
+struct PlanArgs {
+    SegRec *list;                // [P][capacity] records
+    int32_t *counts;             // [P]
+    int capacity;
+    int32_t *idx_out, *n_sel_out;
+    // tokens at or above the row's bound, collected by several workgroups per row (null: the workgroup scans its row)
+    const int32_t *pre_list;     // [P][n_slices][pre_cap]
+    const int32_t *pre_cnt;      // [P][n_slices], more than pre_cap when some were dropped
+    int n_slices, pre_cap;
+};
+
+// ---- several workgroups per row (few problems in a call, long rows: one workgroup per row would be bound by the
+// latency of its own loads).  grid (slices, P): every workgroup forms the row's bound from the same sample and
+// collects its slice's tokens above it.
+__global__ void __launch_bounds__(TB_THREADS)
+topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, int32_t *pre_list, int32_t *pre_cnt)
+{
+    extern __shared__ uint32_t sh_dyn[];         // histogram, then the list
+    __shared__ TopbShared sh;
+    uint32_t *hist = sh_dyn;
+    int32_t *list = reinterpret_cast<int32_t *>(sh_dyn + TB_BINS);
+    const int p = blockIdx.y, sl = blockIdx.x, tid = threadIdx.x;
+    const RowView r(s_tilde + (int64_t)p * d.T, d.T, tid);
+    if (tid == 0) sh.n = 0;
+    const float bound = r.nvec > TB_ROUND / 4 ? sample_bound(r, sample_rank, hist, sh) : -INFINITY;
+    __syncthreads();
+    const int per = (r.nvec + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int i0 = min(sl * per, r.nvec), i1 = min(i0 + per, r.nvec);
+    if (i0 < i1) collect_above(r, i0, i1, bound, list, pre_cap, sh);
+    if (sl == 0) append_extra(r, r.extra >= 0 && r.sp[max(r.extra, 0)] >= bound, list, pre_cap, sh);
+    __syncthreads();
+    const int64_t o = (int64_t)p * gridDim.x + sl;
+    for (int i = tid; i < min(sh.n, pre_cap); i += TB_THREADS) pre_list[o * pre_cap + i] = list[i];
+    if (tid == 0) pre_cnt[o] = sh.n;
+}
+
+// grid (P).  Selection of the k-th best score, k = min(B, T), as (ordered key v, index cut c), and, with seg_budget
+// != NULL, the implicit budgets (Eq. implicit_budget).
+//
+// What bounds it: LDS atomics, if every score is counted (a histogram of 12 key bits puts a fifth of a row into one bin),
+// and two reads of the row; so only a sample is counted, in bins fitted to it, and the row is read once.  256 rows of
+// 131 040: 77 -> 46 us (134 MB, 2.9 TB/s with the sample); 1 024 rows of 65 472: 402 -> 111 us; 8 rows of 8 160, where
+// the chain of barriers is all there is: 18.6 -> 15.4 us.
+//
+// A row of up to TB_ROUND tokens is held in registers and its k-th best found there (kth_best).  Of a longer row a
+// sample gives a lower bound first, ONE pass over the row lists the tokens that reach it (somewhat more than k), and the
+// k-th best is found among those.  E * 1024 tokens fit the list; when they do not (many equal scores, a sample that
+// misled), three histogram passes over the row (11 + 11 + 10 bits) and one to cut the ties by ascending index decide.
+//
+// PLAN (the search that also selects; the host launches it only when 0 < B < T, B fits the list and every sequence has
+// fewer than `offs_cap` segments): the same workgroup goes on to the exclusive prefix of b_k (each segment's offset in
+// the problem's idx_out row), writes n_sel, the token of every segment with b_k == 1 (g_k* = 1) straight to its place,
+// and records the segments with b_k >= 2 for the search, with their output offset.
+template <bool PLAN, int E>
+__global__ void __launch_bounds__(TB_THREADS, E <= 8 ? 8 : 4)
+topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView sv, int32_t *seg_budget,
+            int32_t *block_size, PlanArgs pa, CandList cand, float tau, int offs_cap, int sample_rank)
+{
+    constexpr int CAP = E * TB_THREADS;          // tokens the list holds
+    extern __shared__ uint32_t sh_dyn[];         // histogram [TB_BINS] and list [CAP]; later offsets and counters [2][offs_cap]
+    __shared__ TopbShared sh;
+    uint32_t *hist = sh_dyn;
+    int32_t *list = reinterpret_cast<int32_t *>(sh_dyn + TB_BINS);
+    int32_t *sh_off = reinterpret_cast<int32_t *>(sh_dyn), *sh_cnt = sh_off + offs_cap;
+    const int p = blockIdx.x, T = d.T;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const RowView r(s_tilde + (int64_t)p * T, T, tid);
+    const int k = min(budget, T);
+    const int64_t row = (int64_t)p * sv.max_segments;
+
+    uint32_t thr = 0u;                           // k >= T: everything is inside, key 0 is below every score's key
+    int cut = T - 1;
+    int hit[E];                                  // this thread's share of T_topB (-1: none)
+    bool have_hits = false;
+    if (tid == 0) sh.n = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) hit[e] = -1;
+    auto hits_from_list = [&]() {
+        __syncthreads();
+        const int n = min(sh.n, CAP);
+#pragma unroll
+        for (int e = 0; e < E; ++e) hit[e] = tid + e * TB_THREADS < n ? list[tid + e * TB_THREADS] : -1;
+        have_hits = true;
+    };
+    if (k <= 0) {
+        thr = 0xFFFFFFFFu;                       // nothing is inside
+        cut = -1;
+    } else if (k < T) {
+        const bool sliced = PLAN && pa.pre_list;
+        bool found = false;
+        if (!sliced && r.nvec <= TB_ROUND / 4) {
+            // ---- the whole row in registers
+            constexpr int J = TB_REG / 4;
+            float4 v[J];
+            int t0[J];
+            uint32_t valid = 0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int i = j * TB_THREADS + tid;
+                v[j] = r.nvec > 0 ? r.vp[min(i, r.nvec - 1)] : make_float4(0.f, 0.f, 0.f, 0.f);
+                t0[j] = i < r.nvec ? r.token(i) : -4;
+                if (i < r.nvec) valid |= 15u << (4 * j);
+            }
+            const float ve = r.extra >= 0 ? r.sp[r.extra] : 0.f;
+            if (r.extra >= 0) valid |= 1u << TB_REG;
+            uint32_t key[TB_REG + 1];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                key[4 * j] = ordered_key(v[j].x); key[4 * j + 1] = ordered_key(v[j].y);
+                key[4 * j + 2] = ordered_key(v[j].z); key[4 * j + 3] = ordered_key(v[j].w);
+            }
+            key[TB_REG] = ordered_key(ve);
+            found = kth_best<TB_REG + 1>(key, valid, [&](int e) { return e == TB_REG ? r.extra : t0[e >> 2] + (e & 3); }, k, T, hist,
+                                         sh, thr, cut);
+            if (found && k <= CAP && seg_budget) {
+                append_tokens<J>(v, t0, [&](int t, float x) { return t >= 0 && in_topb(x, t, thr, cut); }, list, CAP, sh);
+                append_extra(r, r.extra >= 0 && in_topb(ve, r.extra, thr, cut), list, CAP, sh);
+                hits_from_list();                // exactly k of them
+            }
+        } else if (k <= CAP) {
+            // ---- the tokens that reach a lower bound of the k-th best
+            if (sliced) {
+                int base = 0;
+                for (int sl = 0; sl < pa.n_slices; ++sl) {
+                    const int64_t o = (int64_t)p * pa.n_slices + sl;
+                    const int n = pa.pre_cnt[o];
+                    if (n > pa.pre_cap || base + n > CAP) { base = CAP + 1; break; }
+                    for (int i = tid; i < n; i += TB_THREADS) list[base + i] = pa.pre_list[o * pa.pre_cap + i];
+                    base += n;
+                }
+                if (tid == 0) sh.n = base;
+            } else {
+                const float bound = sample_bound(r, sample_rank, hist, sh);
+                __syncthreads();                 // the list's length is zero
+                collect_above(r, 0, r.nvec, bound, list, CAP, sh);
+                append_extra(r, r.extra >= 0 && r.sp[max(r.extra, 0)] >= bound, list, CAP, sh);
+            }
+            __syncthreads();
+            const int n = sh.n;
+            if (n >= k && n <= CAP) {
+                uint32_t key[E], valid = 0;
+                float x[E];
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (tid + e * TB_THREADS < n) { hit[e] = list[tid + e * TB_THREADS]; x[e] = r.sp[hit[e]]; valid |= 1u << e; }
+#pragma unroll
+                for (int e = 0; e < E; ++e) key[e] = (valid >> e) & 1u ? ordered_key(x[e]) : 0u;
+                found = kth_best<E>(key, valid, [&](int e) { return hit[e]; }, k, T, hist, sh, thr, cut);
+                if (found) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e)
+                        if (!(((valid >> e) & 1u) && (key[e] > thr || (key[e] == thr && hit[e] <= cut)))) hit[e] = -1;
+                    have_hits = true;
+                }
+            }
+        }
+        if (!found) {
+            // ---- three histogram passes over the row
+            uint32_t prefix = 0, mask = 0, krem = (uint32_t)k, n_eq = 0;
+            const int shifts[3] = {21, 10, 0};
+            const int bits[3] = {11, 11, 10};
+            for (int pass = 0; pass < 3; ++pass) {
+                const uint32_t last = (1u << bits[pass]) - 1u;
+                const int shift = shifts[pass];
+                __syncthreads();
+                reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
+                __syncthreads();
+                scan_row(r, tid, [&](int, float x) {
+                    const uint32_t key = ordered_key(x);
+                    if ((key & mask) == prefix) atomicAdd(&hist[last - ((key >> shift) & last)], 1u);    // bin 0: the largest
+                });
+                __syncthreads();
+                uint32_t bin, above, count;
+                find_bin(hist, krem, sh, bin, above, count);
+                krem -= above;
+                n_eq = count;
+                prefix |= (last - bin) << shift;
+                mask |= last << shift;
+            }
+            // prefix is the key of the k-th best score; krem of its n_eq ties are inside, lowest indices first
+            thr = prefix;
+            cut = T - 1;
+            if (krem < n_eq) {
+                int seen = 0;
+                for (int c0 = 0; c0 < T; c0 += TB_THREADS) {
+                    const int t = c0 + tid;
+                    const bool tie = t < T && ordered_key(r.sp[t]) == prefix;
+                    const unsigned long long bal = __ballot(tie);
+                    __syncthreads();
+                    if (lane == 0) sh.w[wave] = __popcll(bal);
+                    __syncthreads();
+                    int before = 0, total = 0;
+                    for (int w = 0; w < TB_WAVES; ++w) { const int c = sh.w[w]; if (w < wave) before += c; total += c; }
+                    const bool last = seen + total >= (int)krem;
+                    if (last && tie && seen + before + lanes_below(bal) + 1 == (int)krem) sh.cut = t;
+                    __syncthreads();
+                    if (last) { cut = sh.cut; break; }
+                    seen += total;
+                }
+            }
+            if (k <= CAP && seg_budget) {
+                __syncthreads();
+                if (tid == 0) sh.n = 0;
+                __syncthreads();
+                scan_row(r, tid, [&](int t, float x) {
+                    if (in_topb(x, t, thr, cut)) list[atomicAdd(&sh.n, 1)] = t;                          // exactly k of them
+                });
+                hits_from_list();
+            }
+        }
+    }
+    if (tid == 0) { thr_out[2 * p] = (int32_t)thr; thr_out[2 * p + 1] = cut; }
+    if (!seg_budget) return;
+
+    // ---- implicit budgets: every Top-B token adds one to its segment
+    const int seq = seq_of_problem(d, p);
+    const int32_t *off = sv.seg_off + sv.seq_ptr[seq];
+    const int K = sv.seq_ptr[seq + 1] - sv.seq_ptr[seq] - 1;
+    const bool counted = have_hits && K + 1 <= offs_cap;       // in LDS; always so with PLAN
+    if (!counted) {
+        for (int j = tid; j < sv.max_segments; j += TB_THREADS) {
+            seg_budget[row + j] = k >= T && k > 0 && j < K ? off[j + 1] - off[j] : 0;
+            block_size[row + j] = 0;
+        }
+        if (k <= 0 || k >= T) return;
+        __syncthreads();                       // the clearing stores of all wavefronts before the first atomic
+        if (have_hits) {
+#pragma unroll
+            for (int e = 0; e < E; ++e)
+                if (hit[e] >= 0) atomicAdd(&seg_budget[row + segment_of(off, K, hit[e])], 1);
+        } else {
+            scan_row(r, tid, [&](int t, float x) {
+                if (in_topb(x, t, thr, cut)) atomicAdd(&seg_budget[row + segment_of(off, K, t)], 1);
+            });
+        }
+        return;
+    }
+    __syncthreads();                           // the list has been read by everyone
+    for (int j = tid; j <= K; j += TB_THREADS) { sh_off[j] = off[j]; sh_cnt[j] = 0; }
+    if (tid == 0) { sh.n_rec = 0; sh.n_long = 0; }
+    __syncthreads();
+    int seg[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (hit[e] >= 0) { seg[e] = segment_of(sh_off, K, hit[e]); atomicAdd(&sh_cnt[seg[e]], 1); }
+    __syncthreads();
+    for (int j = tid; j < sv.max_segments; j += TB_THREADS) {
+        const int c = j < K ? sh_cnt[j] : 0;
+        seg_budget[row + j] = c;
+        block_size[row + j] = PLAN && c == 1 ? 1 : 0;          // the others: written by the search
+    }
+    if (!PLAN) return;
+    // exclusive prefix of the counters in place (K + 1 entries: b_k = pos[k + 1] - pos[k]); offs_cap / 1024
+    // consecutive entries per thread, wavefront scan, then the sixteen wavefront totals
+    __syncthreads();
+    {
+        constexpr int PER_MAX = TB_OFFS_MAX / TB_THREADS;
+        const int per = offs_cap / TB_THREADS;
+        const int j0 = per * tid;
+        int c[PER_MAX], tot = 0;
+#pragma unroll
+        for (int i = 0; i < PER_MAX; ++i) { c[i] = (i < per && j0 + i < K) ? sh_cnt[j0 + i] : 0; tot += c[i]; }
+        const int incl = (int)wave_scan_u((uint32_t)tot);
+        if (lane == 63) sh.w[wave] = incl;
+        __syncthreads();
+        int run = incl - tot;
+#pragma unroll
+        for (int w = 0; w < TB_WAVES; ++w) run += w < wave ? (int)sh.w[w] : 0;
+#pragma unroll
+        for (int i = 0; i < PER_MAX; ++i) { if (i < per && j0 + i <= K) sh_cnt[j0 + i] = run; run += c[i]; }
+    }
+    __syncthreads();
+    int32_t *out = pa.idx_out + (int64_t)p * budget;
+    if (tid == 0) pa.n_sel_out[p] = k;                         // k = B < T here, so there is nothing to pad
+    // the token of every single-token segment goes straight to its place
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (hit[e] >= 0 && sh_cnt[seg[e] + 1] - sh_cnt[seg[e]] == 1) out[sh_cnt[seg[e]]] = hit[e];
+    // the others to the search's list, with their output offset; segments too long for it are searched here, once the
+    // list is otherwise complete (their records are last) and the offsets in LDS are no longer needed
+    SegRec *recs = pa.list + (int64_t)p * pa.capacity;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int sg = tid; sg < K; sg += TB_THREADS) {
+            const int bk = sh_cnt[sg + 1] - sh_cnt[sg];
+            if (bk < 2 || (sh_off[sg + 1] - sh_off[sg] > PRE_TOKENS) != (pass == 1)) continue;
+            SegRec rec;
+            rec.p = p; rec.k = sg; rec.a = sh_off[sg]; rec.b = sh_off[sg + 1]; rec.bk = bk; rec.g = (int32_t)thr; rec.pos = cut;
+            rec.out = sh_cnt[sg];
+            recs[atomicAdd(pass == 1 ? &sh.n_long : &sh.n_rec, 1)] = rec;
+        }
+        __syncthreads();
+        if (pass == 0 && tid == 0) sh.n_long = sh.n_rec;
+        __syncthreads();
+    }
+    int n_rec = sh.n_rec;
+    const int n_long = sh.n_long - n_rec;
+    if (n_long > 0)
+        n_rec += search_long<true>(SearchCtx(s_tilde, T, p, block_size, sv.max_segments, pa.idx_out, budget, tau, cand), recs + n_rec,
+                                   n_long, reinterpret_cast<double *>(sh_dyn), &sh.n);
+    if (tid == 0) pa.counts[p] = n_rec;
+}
+
 // ------------------------------------------------------------------ search
-// One workgroup per problem: g_k* = 1 where b_k == 1 (the rows are zero elsewhere), and the segments with
-// b_k >= 2 are appended to the call's search list.
+// One workgroup per problem: g_k* = 1 where b_k == 1 (the rows are zero elsewhere), and the segments with b_k >= 2 are
+// recorded for the search (by topb_kernel itself when the search also selects).
 constexpr int LIST_THREADS = 1024;         // threads of the per-problem list-building kernels: segments handled per step
 
 __global__ void __launch_bounds__(LIST_THREADS)
-heavy_list_kernel(Dims d, SegView sv, const int32_t *thr, const int32_t *seg_budget, int32_t *block_size,
-                  SegRec *list, SegRec *list_long, int32_t *counters, int capacity)
+heavy_list_kernel(Dims d, const float *s_tilde, SegView sv, CandList cand, float tau, const int32_t *thr, const int32_t *seg_budget,
+                  int32_t *block_size, SegRec *list, int32_t *counts, int capacity)
 {
-    __shared__ int sh_w[LIST_THREADS / 64], sh_x[LIST_THREADS / 64];
-    __shared__ int sh_base[2];
-    const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ double pre[PRE_LONG + 1];
+    __shared__ int n_rec, n_long;
+    const int p = blockIdx.x, tid = threadIdx.x;
     const int seq = seq_of_problem(d, p);
     const int32_t *off = sv.seg_off + sv.seq_ptr[seq];
     const int K = sv.seq_ptr[seq + 1] - sv.seq_ptr[seq] - 1;
     const int64_t row = (int64_t)p * sv.max_segments;
-    const int32_t thr_key = thr[2 * p], thr_cut = thr[2 * p + 1];
-    for (int c0 = 0; c0 < K; c0 += LIST_THREADS) {
-        const int k = c0 + tid;
-        const int bk = k < K ? seg_budget[row + k] : 0;
-        if (k < K && bk == 1) block_size[row + k] = 1;
-        const int a = k < K ? off[k] : 0, b = k < K ? off[k + 1] : 0;
-        const bool hv = bk >= 2 && b - a <= CAPT, hx = bk >= 2 && b - a > CAPT;
-        const unsigned long long bal = __ballot(hv), bax = __ballot(hx);
-        if (lane == 0) { sh_w[wave] = __popcll(bal); sh_x[wave] = __popcll(bax); }
-        __syncthreads();
-        int before = 0, total = 0, before_x = 0, total_x = 0;
-        for (int w = 0; w < LIST_THREADS / 64; ++w) {
-            if (w < wave) { before += sh_w[w]; before_x += sh_x[w]; }
-            total += sh_w[w]; total_x += sh_x[w];
+    SegRec *recs = list + (int64_t)p * capacity;
+    if (tid == 0) n_long = 0;
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {                     // 0: long segments, 1: the others
+        for (int k = tid; k < K; k += LIST_THREADS) {
+            const int bk = seg_budget[row + k];
+            const bool is_long = off[k + 1] - off[k] > PRE_TOKENS;
+            if (pass == 0 && bk == 1) block_size[row + k] = 1;
+            if (bk < 2 || is_long != (pass == 0)) continue;
+            SegRec r;
+            r.p = p; r.k = k; r.a = off[k]; r.b = off[k + 1]; r.bk = bk; r.g = thr[2 * p]; r.pos = thr[2 * p + 1]; r.out = 0;
+            recs[atomicAdd(pass == 0 ? &n_long : &n_rec, 1)] = r;
         }
-        if (tid == 0 && total > 0) sh_base[0] = atomicAdd(&counters[0], total);
-        if (tid == 1 && total_x > 0) sh_base[1] = atomicAdd(&counters[1], total_x);
         __syncthreads();
-        if (hv || hx) {
-            const unsigned long long lt = (1ull << lane) - 1ull;
-            const int pos = hv ? sh_base[0] + before + __popcll(bal & lt) : sh_base[1] + before_x + __popcll(bax & lt);
-            if (pos < capacity) {
-                SegRec r;
-                r.p = p; r.k = k; r.a = a; r.b = b; r.bk = bk; r.g = thr_key; r.pos = thr_cut; r.out = 0;
-                (hv ? list : list_long)[pos] = r;
-            }
-        }
+        if (pass == 0 && n_long > 0)
+            search_long<false>(SearchCtx(s_tilde, d.T, p, block_size, sv.max_segments, nullptr, 0, tau, cand), recs, n_long, pre, &n_rec);
+        else if (pass == 0 && tid == 0) n_rec = 0;
+        __syncthreads();
     }
+    if (tid == 0) counts[p] = n_rec;
 }
 
-// one wavefront per workgroup, striding over the call's search list
-constexpr int SEARCH_WGS = 65536;
+// One wavefront per workgroup; the wavefronts of a problem (grid.x) stride over its records.  EMIT: see search_exact; no
+// select pass over the segment is then needed.
+constexpr int SLICE_BYTES = 8 * (PRE_TOKENS + 1);
+static_assert(17 * CAPB <= SLICE_BYTES, "ordered sums: CAPT scores (fp32), block sums (fp64) and block classes");
 
-// EMIT: the wavefront also writes T_k(g_k*) in ascending order at the segment's offset in idx_out (the record's
-// `out`), so that no select pass over the segment is needed.
-template <int CT, int CB, bool EMIT>
-__global__ void __launch_bounds__(64)
-search_kernel(Dims d, const float *s_tilde, SegView sv, CandList cand, float tau,
-              const SegRec *list, const int32_t *counter, int capacity, int32_t *block_size, int budget, int32_t *idx_out)
+template <bool EMIT>
+__global__ void __launch_bounds__(64, 7)
+search_kernel(Dims d, const float *s_tilde, int32_t max_segments, CandList cand, float tau, const SegRec *list,
+              const int32_t *counts, int capacity, int32_t *block_size, int budget, int32_t *idx_out)
 {
-    __shared__ double sh_phi[CB];
-    __shared__ float sh_val[CT];
-    __shared__ uint8_t sh_cls[CB];
-    __shared__ unsigned long long sh_mask[EMIT ? CT / 64 : 1];   // the taken tokens of the candidate just tried
-    const int lane = threadIdx.x;
-    int j = blockIdx.x;                                     // < capacity: the grid is no larger than the list can get
-    SegRec r = list[j];                                     // fetched together with the list length
-    const int n_list = min(*counter, capacity);
-    for (; j < n_list; j += gridDim.x, r = list[min(j, capacity - 1)]) {
-    const int p = r.p, a = r.a, b = r.b, bk = r.bk;
-    const int64_t o = (int64_t)p * sv.max_segments + r.k;
-    const float *sp = s_tilde + (int64_t)p * d.T;
-    const uint32_t thr_key = (uint32_t)r.g;
-    const int thr_cut = r.pos;
+    __shared__ __attribute__((aligned(16))) char slice[SLICE_BYTES];
+    const int p = blockIdx.y, lane = threadIdx.x;
+    const SegRec *recs = list + (int64_t)p * capacity;
+    const SearchCtx x(s_tilde, d.T, p, block_size, max_segments, EMIT ? idx_out : nullptr, budget, tau, cand);
+    const float *sp = x.sp;
 
-    // token-level baseline Score_base = sum over T_topB & S_k, ascending; segments that fit are copied to LDS
-    // on the way so that the candidate loop never goes back to global memory
-    const bool staged = b - a <= CT;
-    double base = 0.0;
-    for (int c0 = a; c0 < b; c0 += 64) {
-        const int t = c0 + lane;
-        float v = 0.f;
-        bool in = false;
-        if (t < b) {
-            v = sp[t];
-            in = in_topb(v, t, thr_key, thr_cut);
-            if (staged) sh_val[t - a] = v;
+    int i = blockIdx.x;                                        // < capacity: the grid is no wider than the list can get
+    SegRec nxt = recs[i];                                      // fetched together with the list's length
+    const int n_rec = min(counts[p], capacity);
+    if (i >= n_rec) return;
+    float2 v_nxt = first_scores(sp, nxt);
+    for (bool more = true; more; i += gridDim.x) {
+        const SegRec r = nxt;
+        const float2 v0 = v_nxt;
+        more = i + (int)gridDim.x < n_rec;
+        if (more) {                                            // the next record and its scores, under this one's work
+            nxt = recs[i + gridDim.x];
+            v_nxt = first_scores(sp, nxt);
         }
-        base = add_in_order(base, __ballot(in), v);
-    }
-    __builtin_amdgcn_wave_barrier();
-    int gstar = 0;
-    const int gcap = min(b - a, bk);                        // G_k: g <= min(|S_k|, b_k, g_max)
-    const double need = (double)tau * base;                // R_k(g) >= tau  <=>  Score_k(g) >= tau * Score_base
-    WaveScratch ws{sh_phi, sh_cls, CB};
-    auto run = [&](auto val) {
-        for (int c = cand.n - 1; c >= 0; --c) {
-            const int g = cand.g[c];
-            if (g > gcap) continue;
-            if (g == 1) { gstar = 1; break; }               // token level: the unconditional last resort
+        const int a = r.a, b = r.b, n = b - a;
+        if (n <= PRE_TOKENS && search_exact<EMIT>(x, r, v0, reinterpret_cast<double *>(slice))) continue;
+
+        // ---- ordered sums; scores in LDS when they fit
+        float *lv = reinterpret_cast<float *>(slice);
+        const bool staged = n <= CAPT;
+        WaveScratch ws{reinterpret_cast<double *>(slice + (staged ? 8 * CAPB : 0)), reinterpret_cast<uint8_t *>(slice + 16 * CAPB), CAPB};
+        const int gcap = min(n, r.bk);
+        double sum = 0.0;
+#pragma nounroll
+        for (int c0 = a; c0 < b; c0 += 64) {
+            const int t = c0 + lane;
+            const float v = t < b ? sp[t] : 0.f;
+            if (staged && t < b) lv[t - a] = v;
+            sum = add_in_order(sum, __ballot(t < b && in_topb(v, t, (uint32_t)r.g, r.pos)), v);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const double need = (double)tau * sum;
+        int gstar = 0, pos = r.out;
+        bool writing = false;                                  // the accepted candidate once more, for its tokens
+#pragma nounroll
+        for (int c = cand.n - 1; c >= 0;) {
+            const int g = __builtin_amdgcn_readlane(x.cand_g, c);
+            if (g > gcap) { --c; continue; }
+            if (g == 1) { gstar = 1; break; }
             double score = 0.0;
-            segment_fill(val, a, b, g, bk, ws, [&](int c0, unsigned long long m, float v) {
-                score = add_in_order(score, m, v);
-                if (EMIT && staged && lane == 0) sh_mask[(c0 - a) >> 6] = m;
+            segment_fill([&](int t) { return staged ? lv[t - a] : sp[t]; }, a, b, g, r.bk, ws, [&](int c0, unsigned long long m, float v) {
+                if (EMIT && writing) put_tokens(x, pos, c0, m);
+                else score = add_in_order(score, m, v);
             });
-            if (score >= need) { gstar = g; break; }        // Eq. gk_star: first accepted, largest first
+            if (writing) break;
+            if (score >= need) {
+                gstar = g;
+                if (!EMIT) break;
+                writing = true;
+            } else --c;
         }
-    };
-    float *lv = sh_val;
-    if (staged) run([lv, a](int t) { return lv[t - a]; });
-    else run([sp](int t) { return sp[t]; });
-    if (lane == 0) block_size[o] = gstar;
-    if (EMIT) {
-        int32_t *out = idx_out + (int64_t)p * budget;
-        int pos = r.out;
-        const unsigned long long lt = (1ull << lane) - 1ull;
-        auto put = [&](int c0, unsigned long long m, float) {
-            const int jo = pos + __popcll(m & lt);
-            if (((m >> lane) & 1ull) && jo < budget) out[jo] = c0 + lane;
-            pos += __popcll(m);
-        };
-        if (gstar == 1) {                                   // T_k(1) = T_topB & S_k (b_k is the implicit budget)
-            for (int c0 = a; c0 < b; c0 += 64) {
-                const int t = c0 + lane;
-                const float v = staged ? lv[min(t, b - 1) - a] : sp[min(t, b - 1)];
-                put(c0, __ballot(t < b && in_topb(v, t, thr_key, thr_cut)), 0.f);
-            }
-        } else if (gstar > 1) {
-            if (staged) {                                   // the accepted candidate was the last one tried
-                __builtin_amdgcn_wave_barrier();
-                for (int c0 = a; c0 < b; c0 += 64) put(c0, sh_mask[(c0 - a) >> 6], 0.f);
-            } else {
-                segment_fill([sp](int t) { return sp[t]; }, a, b, gstar, bk, ws, put);
-            }
-        }
-    }
-    __builtin_amdgcn_wave_barrier();                        // the LDS slices are reused by the next segment
+        if (lane == 0) x.block_size[r.k] = gstar;
+        if (EMIT && gstar == 1) put_topb(x, r);
+        __builtin_amdgcn_wave_barrier();                       // the slice is reused by the next segment
     }
 }
 
@@ -845,14 +1404,6 @@ search_kernel(Dims d, const float *s_tilde, SegView sv, CandList cand, float tau
 __global__ void reset_counters_kernel(int32_t *counters)
 {
     if (threadIdx.x < 3) counters[threadIdx.x] = 0;
-}
-
-// counters of the call's lists, and the rows' histograms and list lengths of the sliced Top-B passes
-__global__ void __launch_bounds__(256)
-reset_sliced_kernel(int32_t *counters, uint32_t *words, int64_t n_words)
-{
-    if (blockIdx.x == 0 && threadIdx.x < 3) counters[threadIdx.x] = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n_words; i += (int64_t)gridDim.x * 256) words[i] = 0u;
 }
 
 // One workgroup per problem: exclusive prefix of b_k over its segments (where each segment's tokens go in the
@@ -1029,45 +1580,103 @@ select_kernel(Dims d, const float *s_tilde, const int32_t *thr, const SegRec *li
 
 }  // namespace
 
-// dynamic LDS of topb_kernel, and what a launch may take next to the kernel's 25 KiB of static LDS
-static size_t topb_lds(int offs_cap, int hit_cap)
+// ---- launches of the Top-B kernel
+// Rank in a sample of TB_ROUND scores of the row behind which the bound is taken: the share of the k best that falls into
+// the sample has mean k * TB_ROUND / T and, for scores in no particular order, a standard deviation below the root of
+// that; six of them and a constant for small shares leave room for scores that keep together.
+static int topb_rank(const Dims &d, int k)
 {
-    return ((size_t)2 * offs_cap + (hit_cap > TB_HITS ? hit_cap : 0)) * sizeof(int32_t);
+    const double share = (double)k * TB_ROUND / std::max(d.T, 1);
+    return (int)std::min<double>(TB_ROUND, share + 6.0 * sqrt(share) + 16.0);
 }
-constexpr size_t TOPB_LDS_MAX = 128 * 1024;
-static int topb_offs_cap(const SegView &sv)
+// Tokens the list must hold (thousands, one of 4, 8, 16, 32): the k best, and of a sampled row what lies above the bound
+static int topb_list_k(const Dims &d, int32_t budget)
 {
-    return sv.max_segments + 1 <= TB_OFFS ? TB_OFFS : sv.max_segments + 1 <= 2 * TB_OFFS ? 2 * TB_OFFS : TB_OFFS_MAX;
+    const int k = std::min(budget, d.T);
+    double n = k;
+    if (d.T > TB_ROUND) n = std::min<double>(d.T, 1.2 * topb_rank(d, k) * d.T / TB_ROUND + 256.0);
+    return n <= 4 * TB_THREADS ? 4 : n <= 8 * TB_THREADS ? 8 : n <= 16 * TB_THREADS ? 16 : 32;
 }
-static int topb_hit_cap(int32_t budget) { return budget <= TB_HITS ? TB_HITS : budget <= 2 * TB_HITS ? 2 * TB_HITS : TB_HITS_MAX; }
-// copies of the pass-A histogram (log2): as many as the launch's dynamic LDS holds anyway, and four (64 KiB) when
-// there is at most one workgroup per compute unit, so that the extra LDS costs no occupancy
-static int topb_hist_ways_log2(const Dims &d, size_t lds_needed) { return d.P <= d.cus || lds_needed >= 65536 ? 2 : 1; }
-static size_t topb_lds_with_hist(size_t lds_needed, int ways_log2) { return std::max(lds_needed, (size_t)16384 << ways_log2); }
+static int topb_offs_cap(int32_t max_segments)
+{
+    return max_segments + 1 <= TB_OFFS ? TB_OFFS : max_segments + 1 <= 2 * TB_OFFS ? 2 * TB_OFFS : TB_OFFS_MAX;
+}
+
+template <bool PLAN, int E>
+static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
+                           int32_t *block_size, const PlanArgs &pa, const CandList &cand, float tau, hipStream_t st)
+{
+    const int offs_cap = PLAN || seg_budget ? topb_offs_cap(sv.max_segments) : 0;
+    static_assert((TB_BINS + E * TB_THREADS) * 4 >= 8 * (PRE_LONG + 1), "prefix sums of long segments");
+    const size_t lds = std::max((size_t)(TB_BINS + E * TB_THREADS) * 4, (size_t)offs_cap * 8);
+    constexpr size_t lds_most = std::max((size_t)(TB_BINS + E * TB_THREADS) * 4, (size_t)TB_OFFS_MAX * 8);
+    if (lds > 64 * 1024) {
+        static thread_local PerDeviceOnce attr_once;
+        if (attr_once.needed()) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(topb_kernel<PLAN, E>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_most);
+            if (e != hipSuccess) return e;
+            attr_once.done();
+        }
+    }
+    hipLaunchKernelGGL((topb_kernel<PLAN, E>), dim3(d.P), dim3(TB_THREADS), lds, st, d, s_tilde, budget, thr, sv, seg_budget,
+                       block_size, pa, cand, tau, offs_cap, topb_rank(d, std::min(budget, d.T)));
+    return hipGetLastError();
+}
+
+template <bool PLAN>
+static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
+                           int32_t *block_size, const PlanArgs &pa, const CandList &cand, float tau, hipStream_t st)
+{
+    switch (topb_list_k(d, budget)) {
+    case 4: return run_topb<PLAN, 4>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    case 8: return run_topb<PLAN, 8>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    case 16: return run_topb<PLAN, 16>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    default: return run_topb<PLAN, 32>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    }
+}
 
 hipError_t launch_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, hipStream_t st)
 {
     if (d.P <= 0) return hipSuccess;
-    SegView none{};
-    hipLaunchKernelGGL(topb_kernel<false>, dim3(d.P), dim3(TB_THREADS), topb_lds(TB_OFFS, TB_HITS), st, d, s_tilde, budget, thr, none,
-                       (int32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, PlanArgs{}, TB_OFFS, TB_HITS, 1);
-    return hipGetLastError();
+    return run_topb<false>(d, s_tilde, budget, thr, SegView{}, nullptr, nullptr, PlanArgs{}, CandList{}, 0.f, st);
 }
 
-// upper bound of the search list: a listed segment holds at least two of the |T_topB| tokens
-static size_t max_heavy_segments(const Dims &d, int32_t max_segments, int32_t budget)
+// upper bound of a problem's records: a recorded segment holds at least two of the |T_topB| tokens
+static int max_heavy_segments(const Dims &d, int32_t max_segments, int32_t budget)
 {
     const int k = budget < d.T ? budget : d.T;
-    const int h = k / 2 < max_segments ? k / 2 : max_segments;
-    return (size_t)d.P * (size_t)(h > 0 ? h : 0);
+    return std::max(0, std::min(k / 2, (int)max_segments));
 }
-
-constexpr int LONG_WGS = 8192;             // workgroups of the kernels that serve the lists of long segments
 
 size_t search_ws_bytes(const Dims &d, int32_t max_segments, int32_t budget)
 {
-    const size_t cap = max_heavy_segments(d, max_segments, budget);
-    return align256((size_t)d.P * 2 * 4) + align256(8) + 2 * align256((cap > 0 ? cap : 1) * sizeof(SegRec));
+    const size_t cap = (size_t)d.P * max_heavy_segments(d, max_segments, budget);
+    return 2 * align256((size_t)d.P * 2 * 4) + align256((cap > 0 ? cap : 1) * sizeof(SegRec));
+}
+
+struct SearchWs {
+    int32_t *thr, *counts;
+    SegRec *list;
+    SearchWs(const Dims &d, void *ws)
+    {
+        char *w = static_cast<char *>(ws);
+        thr = reinterpret_cast<int32_t *>(w);
+        counts = reinterpret_cast<int32_t *>(w + align256((size_t)d.P * 2 * 4));
+        list = reinterpret_cast<SegRec *>(w + 2 * align256((size_t)d.P * 2 * 4));
+    }
+};
+
+template <bool EMIT>
+static void run_search(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand, float tau, const SearchWs &w, int cap,
+                       int32_t *block_size, int32_t budget, int32_t *idx_out, hipStream_t st)
+{
+    // wavefronts per problem: one per possible record while the chip has room for them, then SEARCH_ROUNDS times the
+    // wavefronts that are resident at once (32 per CU), striding over the records
+    constexpr int64_t SEARCH_ROUNDS = 4;
+    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)d.cus * 32 * SEARCH_ROUNDS / d.P));
+    hipLaunchKernelGGL(search_kernel<EMIT>, dim3(gx, d.P), dim3(64), 0, st, d, s_tilde, sv.max_segments, cand, tau, w.list,
+                       w.counts, cap, block_size, budget, idx_out);
 }
 
 hipError_t launch_search(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand,
@@ -1075,30 +1684,20 @@ hipError_t launch_search(const Dims &d, const float *s_tilde, const SegView &sv,
                          void *ws, hipStream_t st)
 {
     if (d.P <= 0 || sv.max_segments <= 0) return hipSuccess;
-    const size_t cap = max_heavy_segments(d, sv.max_segments, budget);
-    char *w = static_cast<char *>(ws);
-    int32_t *thr = topb_out ? topb_out : reinterpret_cast<int32_t *>(w);
-    w += align256((size_t)d.P * 2 * 4);
-    int32_t *counters = reinterpret_cast<int32_t *>(w);
-    w += align256(8);
-    SegRec *list = reinterpret_cast<SegRec *>(w);
-    w += align256((cap > 0 ? cap : 1) * sizeof(SegRec));
-    SegRec *list_long = reinterpret_cast<SegRec *>(w);
-    hipLaunchKernelGGL(topb_kernel<false>, dim3(d.P), dim3(TB_THREADS), topb_lds(TB_OFFS, TB_HITS), st, d, s_tilde, budget, thr, sv,
-                       seg_budget, block_size, counters, PlanArgs{}, TB_OFFS, TB_HITS, 1);
+    const int cap = max_heavy_segments(d, sv.max_segments, budget);
+    const SearchWs w(d, ws);
+    int32_t *thr = topb_out ? topb_out : w.thr;
+    hipError_t e = run_topb<false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, PlanArgs{}, CandList{}, 0.f, st);
+    if (e != hipSuccess) return e;
     if (budget > 0 && d.T > 0) {
-        hipLaunchKernelGGL(heavy_list_kernel, dim3(d.P), dim3(LIST_THREADS), 0, st, d, sv, thr, seg_budget, block_size,
-                           list, list_long, counters, (int)cap);
-        if (cap > 0) {
-            hipLaunchKernelGGL((search_kernel<CAPT, CAPB, false>), dim3((unsigned)(cap < SEARCH_WGS ? cap : SEARCH_WGS)), dim3(64),
-                               0, st, d, s_tilde, sv, cand, tau, list, counters, (int)cap, block_size, 0, (int32_t *)nullptr);
-            hipLaunchKernelGGL((search_kernel<CAPT_LONG, CAPB_LONG, false>), dim3((unsigned)(cap < LONG_WGS ? cap : LONG_WGS)),
-                               dim3(64), 0, st, d, s_tilde, sv, cand, tau, list_long, counters + 1, (int)cap, block_size, 0,
-                               (int32_t *)nullptr);
-        }
+        hipLaunchKernelGGL(heavy_list_kernel, dim3(d.P), dim3(LIST_THREADS), 0, st, d, s_tilde, sv, cand, tau, thr, seg_budget,
+                           block_size, w.list, w.counts, cap);
+        if (cap > 0) run_search<false>(d, s_tilde, sv, cand, tau, w, cap, block_size, 0, nullptr, st);
     }
     return hipGetLastError();
 }
+
+constexpr int LONG_WGS = 8192;             // workgroups of the kernel that selects from the list of long segments
 
 // upper bound of the select lists: a listed segment retains at least one token of its problem's budget
 static size_t max_active_segments(const Dims &d, int32_t max_segments, int32_t budget)
@@ -1152,30 +1751,31 @@ hipError_t launch_select(const Dims &d, const float *s_tilde, const SegView &sv,
 // ---- search and select in one sequence (same results as launch_search followed by launch_select)
 bool search_select_fused(const Dims &d, const SegView &sv, int32_t budget)
 {
-    if (!(budget > 0 && budget < d.T && budget <= TB_HITS_MAX && sv.max_segments + 1 <= TB_OFFS_MAX)) return false;
-    return topb_lds(topb_offs_cap(sv), topb_hit_cap(budget)) <= TOPB_LDS_MAX;
+    return budget > 0 && budget < d.T && budget <= TB_BUDGET_MAX && sv.max_segments + 1 <= TB_OFFS_MAX;
 }
 
-// Workgroups per row for the two Top-B passes of the one-call form: with few problems in a call (a layer at a
-// time) one workgroup per row would leave most of the chip idle.  1: the per-row kernel scans its row itself.
+// Workgroups per row that collect the tokens above the row's bound in the one-call form: with few problems in a call (a
+// layer at a time) one workgroup per long row would leave most of the chip idle.  1: the per-row kernel scans its row.
 static int topb_slices(const Dims &d, int32_t budget)
 {
-    if (budget > TB_HITS) return 1;                            // the sliced passes stage at most TB_HITS tokens per row
+    if (topb_list_k(d, budget) > 8 || d.T <= TB_ROUND) return 1;
     if (const int v = d.tune.topb_slices; v >= 1) return (int64_t)v * 4096 <= d.T ? v : 1;
-    int s = (int)std::min<int64_t>(16, (int64_t)d.cus / std::max(d.P, 1));
-    s = std::min(s, d.T / 8192);                               // a slice is worth a workgroup from 8 192 tokens on
-    return s >= 2 ? s : 1;
+    // a slice is one round of loads; a kernel of its own (5 us) for them pays when it saves the per-row kernel four rounds
+    // or more (both calls together, 8 rows: 32 768 tokens 32.7 us in one kernel, 34.3 in two; 65 536: 35.5, 33.0;
+    // 131 040: 41.2, 33.4; 1 000 000: 128, 77)
+    const int s = (d.T + TB_ROUND - 1) / TB_ROUND;
+    return s >= 4 && (int64_t)s * d.P <= d.cus ? std::min(s, 64) : 1;
 }
-static size_t sliced_words(const Dims &d) { return (size_t)d.P * (4096 + 2); }          // histograms, then list lengths
-static size_t sliced_bytes(const Dims &d)
+static size_t sliced_bytes(const Dims &d, int32_t budget)
 {
-    return align256(sliced_words(d) * 4) + align256((size_t)d.P * TB_HITS * 4) + align256((size_t)d.P * TB_CAND * 8);
+    const size_t n = (size_t)d.P * topb_slices(d, budget);
+    return align256(n * 4) + align256(n * topb_list_k(d, budget) * TB_THREADS * 4);
 }
 
 size_t search_select_ws_bytes(const Dims &d, int32_t max_segments, int32_t budget)
 {
     const size_t a = search_ws_bytes(d, max_segments, budget), b = select_ws_bytes(d, max_segments, budget);
-    return (a > b ? a : b) + (topb_slices(d, budget) > 1 ? sliced_bytes(d) : 0);
+    return (a > b ? a : b) + (topb_slices(d, budget) > 1 ? sliced_bytes(d, budget) : 0);
 }
 
 hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand,
@@ -1186,67 +1786,31 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
     if (!search_select_fused(d, sv, budget)) {
         hipError_t e = launch_search(d, s_tilde, sv, cand, budget, tau, seg_budget, block_size, topb_out, ws, st);
         if (e != hipSuccess) return e;
-        // the select lists reuse the workspace of the search lists, which are consumed by then; the Top-B state
+        // the select lists reuse the workspace of the search's records, which are consumed by then; the Top-B state
         // sits in front of both layouts
         const int32_t *thr = topb_out ? topb_out : static_cast<const int32_t *>(ws);
         return launch_select(d, s_tilde, sv, seg_budget, block_size, thr, budget, idx_out, n_sel_out, ws, st);
     }
-    const size_t cap = max_heavy_segments(d, sv.max_segments, budget);
-    char *w = static_cast<char *>(ws);
-    int32_t *thr = topb_out ? topb_out : reinterpret_cast<int32_t *>(w);
-    w += align256((size_t)d.P * 2 * 4);
-    int32_t *counters = reinterpret_cast<int32_t *>(w);
-    w += align256(8);
-    SegRec *list = reinterpret_cast<SegRec *>(w);
-    w += align256((cap > 0 ? cap : 1) * sizeof(SegRec));
-    SegRec *list_long = reinterpret_cast<SegRec *>(w);
-    PlanArgs pa{list, list_long, (int)cap, idx_out, n_sel_out, nullptr, nullptr, nullptr, nullptr};
-    const int n_slices = topb_slices(d, budget);
-    if (n_slices > 1) {
+    const int cap = max_heavy_segments(d, sv.max_segments, budget);
+    const SearchWs w(d, ws);
+    int32_t *thr = topb_out ? topb_out : w.thr;
+    PlanArgs pa{w.list, w.counts, cap, idx_out, n_sel_out, nullptr, nullptr, 0, 0};
+    if (const int n_slices = topb_slices(d, budget); n_slices > 1) {
         // behind the larger of the search and select layouts
-        const size_t base = search_select_ws_bytes(d, sv.max_segments, budget) - sliced_bytes(d);
-        char *x = static_cast<char *>(ws) + base;
-        uint32_t *g_hist = reinterpret_cast<uint32_t *>(x);
-        int32_t *g_cnt = reinterpret_cast<int32_t *>(g_hist + (size_t)d.P * 4096);
-        x += align256(sliced_words(d) * 4);
-        int32_t *g_hit = reinterpret_cast<int32_t *>(x);
-        x += align256((size_t)d.P * TB_HITS * 4);
-        uint32_t *g_cand = reinterpret_cast<uint32_t *>(x);
-        const int64_t n_words = (int64_t)sliced_words(d);
-        hipLaunchKernelGGL(reset_sliced_kernel, dim3((unsigned)std::min<int64_t>((n_words + 1023) / 1024, 1024)), dim3(256), 0, st,
-                           counters, g_hist, n_words);
-        hipLaunchKernelGGL(topb_hist_kernel, dim3(n_slices, d.P), dim3(TB_THREADS), 0, st, d, s_tilde, g_hist);
-        hipLaunchKernelGGL(topb_split_kernel, dim3(n_slices, d.P), dim3(TB_THREADS), 0, st, d, s_tilde, budget, g_hist, g_cnt,
-                           g_hit, g_cand);
-        pa.pre_hist = g_hist;
-        pa.pre_cnt = g_cnt;
-        pa.pre_hit = g_hit;
-        pa.pre_cand = g_cand;
-    } else {
-        hipLaunchKernelGGL(reset_counters_kernel, dim3(1), dim3(64), 0, st, counters);
+        char *x = static_cast<char *>(ws) + (search_select_ws_bytes(d, sv.max_segments, budget) - sliced_bytes(d, budget));
+        int32_t *pre_cnt = reinterpret_cast<int32_t *>(x);
+        int32_t *pre_list = reinterpret_cast<int32_t *>(x + align256((size_t)d.P * n_slices * 4));
+        const int pre_cap = topb_list_k(d, budget) * TB_THREADS;
+        hipLaunchKernelGGL(topb_collect_kernel, dim3(n_slices, d.P), dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, d, s_tilde,
+                           topb_rank(d, budget), pre_cap, pre_list, pre_cnt);
+        pa.pre_list = pre_list;
+        pa.pre_cnt = pre_cnt;
+        pa.n_slices = n_slices;
+        pa.pre_cap = pre_cap;
     }
-    // counters and offsets of all segments of a sequence, and the Top-B tokens of a row, in LDS
-    const int offs_cap = topb_offs_cap(sv), hit_cap = topb_hit_cap(budget);
-    const int ways_log2 = topb_hist_ways_log2(d, topb_lds(offs_cap, hit_cap));
-    const size_t lds = topb_lds_with_hist(topb_lds(offs_cap, hit_cap), ways_log2);
-    if (lds > topb_lds(TB_OFFS, TB_HITS)) {
-        static thread_local PerDeviceOnce attr_once;
-        if (attr_once.needed()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(topb_kernel<true>),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)TOPB_LDS_MAX);
-            if (e != hipSuccess) return e;
-            attr_once.done();
-        }
-    }
-    hipLaunchKernelGGL(topb_kernel<true>, dim3(d.P), dim3(TB_THREADS), lds, st, d, s_tilde, budget, thr,
-                       sv, seg_budget, block_size, counters, pa, offs_cap, hit_cap, ways_log2);
-    if (cap > 0) {
-        hipLaunchKernelGGL((search_kernel<CAPT, CAPB, true>), dim3((unsigned)(cap < SEARCH_WGS ? cap : SEARCH_WGS)), dim3(64),
-                           0, st, d, s_tilde, sv, cand, tau, list, counters, (int)cap, block_size, budget, idx_out);
-        hipLaunchKernelGGL((search_kernel<CAPT_LONG, CAPB_LONG, true>), dim3((unsigned)(cap < LONG_WGS ? cap : LONG_WGS)),
-                           dim3(64), 0, st, d, s_tilde, sv, cand, tau, list_long, counters + 1, (int)cap, block_size, budget,
-                           idx_out);
-    }
+    hipError_t e = run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    if (e != hipSuccess) return e;
+    if (cap > 0) run_search<true>(d, s_tilde, sv, cand, tau, w, cap, block_size, budget, idx_out, st);
     return hipGetLastError();
 }
 
