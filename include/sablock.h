@@ -138,7 +138,7 @@ SABLOCK_API sablock_status sablock_workspace_bytes(const sablock_shape *shape, i
  * any G with G * W <= 128 (e.g. G = 7 with W = 16, G = 3 with W = 32, G = 16 with W = 8), head_dim 256 with the same
  * windows and G * W <= 96 (e.g. G = 2 with W = 32), and head_dim 128 with
  * 129 .. 256 rows of a window of 32 or 64 queries (G = 5 .. 8 with W = 32, G = 3 or 4 with W = 64), runs on the
- * matrix pipe; every other shape and fp32 on a plain vector kernel, ~20 x slower per key. */
+ * bf16 matrix pipe; every other shape and fp32 on the fp32 matrix pipe, ~8 x slower per key. */
 SABLOCK_API sablock_status sablock_score(const sablock_shape *shape, const void *q_win, const void *k,
                              const float *row_lse /* nullable */, float eps,
                              float *s_out, float *ent_out,

@@ -1,0 +1,47 @@
+"""The scoring kernels for any shape against the fp64 oracle at the sizes where they change course: head dims around the
+register classes (64, 128, 256), windows around the padded ones (8, 16, 32, 64), row counts that do and do not fit LDS
+at once, lengths around a wavefront's and a workgroup's keys, chunk partials folded in either place."""
+
+import numpy as np
+import pytest
+
+import gpu_helpers as H
+from paper_2510_22556_amd import synth
+from test_gpu_parity import torch_cuda  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("G,W,D,L,dtype", [
+    (1, 1, 8, 33, "f32"), (3, 5, 16, 129, "f32"), (1, 8, 64, 31, "f32"), (4, 9, 72, 127, "f32"), (2, 16, 128, 128, "f32"),
+    (7, 17, 136, 161, "f32"), (1, 33, 256, 1000, "f32"), (5, 64, 128, 257, "f32"), (8, 32, 256, 300, "f32"),
+    (16, 64, 256, 200, "f32"), (200, 5, 24, 70, "f32"), (4, 32, 128, 9001, "f32"), (3, 12, 80, 515, "bf16"),
+    (9, 16, 128, 2049, "bf16"), (5, 64, 256, 130, "bf16"), (2, 3, 256, 65, "bf16"),
+])
+def test_generic_scores_at_the_edges(oracle, torch_cuda, G, W, D, L, dtype):  # noqa: F811
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Hkv, seed = 2, G * 1000 + W + D + L
+    q = synth.normal_torch(seed, 1, (1, 1, G * Hkv, W, D), "cuda", dt)
+    k = synth.normal_torch(seed, 2, (1, 1, Hkv, L, 2 * D), "cuda", dt)[..., D:]          # rows farther apart than they are long
+    shape = B.make_shape(q, k)
+    ws = torch.empty((B.sablock_workspace_bytes(shape, 0, 0),), dtype=torch.uint8, device="cuda")
+    s = torch.full((Hkv, L), float("nan"), dtype=torch.float32, device="cuda")
+    e = torch.full_like(s, float("nan"))
+    B.sablock_score(shape, q, k, s, e, ws)
+    # the rows' denominators handed over: in fp64, rounded once
+    x = (q[0, 0].view(Hkv, G * W, D).cpu().double() @ k[0, 0].cpu().double().transpose(1, 2)) / np.sqrt(D)
+    t, i = torch.arange(L)[None, :], torch.arange(G * W)[:, None] % W
+    x.masked_fill_((t > L - W + i)[None], float("-inf"))
+    lse = torch.logsumexp(x, dim=2).float().view(1, 1, Hkv * G, W).cuda()
+    s2, e2 = torch.full_like(s, float("nan")), torch.full_like(s, float("nan"))
+    B.sablock_score(shape, q, k, s2, e2, ws, row_lse=lse)
+    torch.cuda.synchronize()
+    for p in range(Hkv):
+        sr, er = oracle.score(H.widen(H.to_np(q[0, 0, p * G:(p + 1) * G].contiguous())), H.widen(H.to_np(k[0, 0, p].contiguous())), 1e-6)
+        for a, b in ((s, e), (s2, e2)):
+            # a D-term fp32 dot of unit normals is off by about sqrt(D) 2^-24 absolute, a probability by that relative
+            np.testing.assert_allclose(H.to_np(a[p]), sr, rtol=1e-5, atol=1e-9)
+            np.testing.assert_allclose(H.to_np(b[p]), er, rtol=1e-5, atol=2e-6)
