@@ -291,8 +291,8 @@ SABLOCK_API sablock_status sablock_window_attention(const sablock_shape *shape, 
  * a new segment starts after every token t < n_tokens - 1 whose id is in `delims`; consecutive delimiters give
  * one-token segments; a sequence without delimiters is one segment.  Two calls, because the offsets are CSR
  * with HOST pointers (see "Segments" above):
- *   1. sablock_segment_count writes the segment count K_s of every sequence to seg_count_out (device, n_seq
- *      int32); the caller reads it back and forms seg_ptr[s+1] = seg_ptr[s] + K_s + 1;
+ *   1. sablock_segment_count writes the segment count K_s of every sequence to seg_count_out (device memory, or
+ *      pinned host memory, which spares the caller a copy; n_seq int32); the caller reads it back and forms seg_ptr[s+1] = seg_ptr[s] + K_s + 1;
  *   2. sablock_segment_offsets writes, for every sequence, 0, the boundaries in ascending order, n_tokens to
  *      seg_off_out[seg_ptr[s] .. seg_ptr[s+1]) (device); entries beyond what seg_ptr leaves room for are dropped.
  * token_ids: device int32, sequence s at token_ids + s * token_stride (elements), n_tokens = T ids each (the

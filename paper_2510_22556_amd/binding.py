@@ -252,18 +252,24 @@ def sablock_validate_segments(seg_off, seg_ptr: Sequence[int], n_tokens: int, n_
 
 
 def segment(token_ids, delims: Sequence[int]) -> "Segments":
-    """Both segmentation calls and the host step between them (one read-back of n_seq counts)."""
+    """Both segmentation calls and the host step between them (one wait for n_seq counts)."""
     import torch
 
     assert token_ids.dim() == 2 and token_ids.dtype == torch.int32 and token_ids.stride(1) == 1
-    counts = torch.empty((token_ids.shape[0],), dtype=torch.int32, device=token_ids.device)
-    sablock_segment_count(token_ids, delims, counts)
-    c = counts.cpu().tolist()
+    lib, stream = load(), torch.cuda.current_stream(token_ids.device)
+    n, T = token_ids.shape
+    tokens, d = (token_ids.data_ptr(), token_ids.stride(0), n, T), (ctypes.c_int32 * max(len(delims), 1))(*delims)
+    # the kernel writes the counts straight to host memory: no copy between it and the wait
+    counts = torch.empty((n,), dtype=torch.int32, pin_memory=True)
+    _check(lib.sablock_segment_count(*tokens, d, len(delims), counts.data_ptr(), stream.cuda_stream or None))
+    stream.synchronize()
+    c = counts.tolist()
     ptr = [0]
-    for n in c:
-        ptr.append(ptr[-1] + n + 1)
+    for k in c:
+        ptr.append(ptr[-1] + k + 1)
     seg_off = torch.empty((ptr[-1],), dtype=torch.int32, device=token_ids.device)
-    sablock_segment_offsets(token_ids, delims, ptr, seg_off)
+    _check(lib.sablock_segment_offsets(*tokens, d, len(delims), (ctypes.c_int32 * (n + 1))(*ptr), seg_off.data_ptr(),
+                                       stream.cuda_stream or None))
     return Segments(seg_off, ptr, max(c))
 
 

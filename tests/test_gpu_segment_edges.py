@@ -1,0 +1,31 @@
+"""Segmentation at the sizes where its kernels change course (steps of 256 tokens, four in flight, sixteen wavefronts, up to
+eight slices, masks too many for LDS), rows at every alignment, delimiters at every place: whole numbers, exact."""
+
+import numpy as np
+import pytest
+
+from test_gpu_parity import torch_cuda  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T", [1, 2, 3, 255, 256, 257, 4096, 4099, 16383, 16384, 65472, 131075, 4_200_001])
+@pytest.mark.parametrize("density,delims", [(0.0, [7]), (0.02, [5, 9, -1]), (1.0, [1, 2]), (0.3, list(range(64))), (0.5, [])])
+def test_segment_offsets_at_the_edges(oracle, torch_cuda, T, density, delims):  # noqa: F811
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    density = min(density, 0.02) if T > 1_000_000 else density
+    rng = np.random.default_rng(T)
+    n_seq = 2 if T > 1_000_000 else 3
+    tok = rng.integers(1000, 2000, size=(n_seq, T + 3)).astype(np.int32)
+    if delims:
+        hit = rng.random(tok.shape) < density
+        tok[hit] = rng.choice(delims, size=int(hit.sum()))
+    dev = torch.as_tensor(tok).cuda()[:, 1:T + 1]              # rows start at any token, three beyond their end belong to others
+    seg = B.segment(dev, delims)
+    off = seg.seg_off.cpu().numpy()
+    for s in range(n_seq):
+        ref = oracle.segment(tok[s, 1:T + 1], delims) if T < 1_000_000 else np.concatenate(
+            [[0], np.flatnonzero(np.isin(tok[s, 1:T], delims)) + 1, [T]])
+        np.testing.assert_array_equal(off[seg.seg_ptr[s]:seg.seg_ptr[s + 1]], ref)
