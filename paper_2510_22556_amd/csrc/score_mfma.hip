@@ -343,7 +343,8 @@ constexpr int RING_BYTES = NBUF * BUF_BYTES;
 //
 // The loop over subtiles has two bodies.  The fast one assumes keys before the window (no causal mask) and no
 // re-anchoring: per head a maximum over the raw accumulators guards the exponentials, and a head that fails the
-// guard leaves the fast body BEFORE anything of it was added.  The careful one (first subtile, subtiles touching
+// guard leaves the fast body BEFORE anything of it was added.  A stream's
+// first subtile anchors the references (stats_anchor) and is then an ordinary one.  The careful body (subtiles touching
 // the window or the end of the sequence, and the rest of a subtile after a failed guard) masks, re-anchors and
 // runs the heads one after the other.  Keeping the careful code out of the fast body keeps the fast body free
 // of register copies at control-flow joins.
@@ -424,33 +425,57 @@ __device__ __forceinline__ void stats_add(const floatx16 &acc, float (&z)[16], f
 }
 
 constexpr int STATS_OK = -1;
-constexpr int STATS_PREV = 3;              // the guard failed for head 3 of the previous subtile
 
-// Fast body of one subtile.  Head h is multiplied into acc[h & 1] while head h-1 (head 3: of the previous
-// subtile, waiting in acc[1]) is exponentiated from the other accumulator; the first two k-steps of a head are
-// issued before the guard of the head before it, the other six after it, next to that head's exponentials.
-// Returns STATS_OK, or which head failed its guard: STATS_PREV, or 0..2 = that head of this subtile (the heads
-// before it were added, it and the ones after it were not).  Head 3 of this subtile is left waiting in acc[1].
-__device__ __forceinline__ int stats_fast(const bf16x8 (&qa)[4][8], const bf16x8 (&kb)[8], floatx16 (&acc)[2],
-                                          const floatx16 (&cr)[4], float (&z)[4][16], float c1, float lim)
+// Fast body of one subtile of NT tiles.  Tile J is multiplied into acc[J & 1] while tile J - 1 is exponentiated from
+// the other accumulator; the first two k-steps of a tile are issued before the guard of the tile before it, the
+// others after it, next to that tile's exponentials.  CARRY (an even number of tiles): the last tile is left waiting
+// in acc[1] and is exponentiated under the first tile of the next subtile; otherwise it is finished here.
+// Returns STATS_OK, or which tile failed its guard (the tiles before it were added, it and the ones after it were
+// not); with CARRY NT - 1 names the waiting tile of the previous subtile.
+template <int NT, int KS, bool CARRY>
+__device__ __forceinline__ int stats_fast(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[KS], floatx16 (&acc)[2],
+                                          const floatx16 (&cr)[NT], float (&z)[NT][16], float c1, float lim)
 {
-    acc[0] = chain<0, 2>(qa[0], kb, cr[0]);
-    if (stats_guard(acc[1], lim)) return STATS_PREV;
-    acc[0] = chain<2, 8>(qa[0], kb, acc[0]);
-    stats_add(acc[1], z[3], c1);
-    acc[1] = chain<0, 2>(qa[1], kb, cr[1]);
-    if (stats_guard(acc[0], lim)) return 0;
-    acc[1] = chain<2, 8>(qa[1], kb, acc[1]);
-    stats_add(acc[0], z[0], c1);
-    acc[0] = chain<0, 2>(qa[2], kb, cr[2]);
-    if (stats_guard(acc[1], lim)) return 1;
-    acc[0] = chain<2, 8>(qa[2], kb, acc[0]);
-    stats_add(acc[1], z[1], c1);
-    acc[1] = chain<0, 2>(qa[3], kb, cr[3]);
-    if (stats_guard(acc[0], lim)) return 2;
-    acc[1] = chain<2, 8>(qa[3], kb, acc[1]);
-    stats_add(acc[0], z[2], c1);
+    static_assert(!CARRY || NT % 2 == 0, "the waiting tile must not sit in the first tile's accumulator");
+#pragma unroll
+    for (int J = 0; J < NT; ++J) {
+        constexpr int LAST = NT - 1;
+        const int prev = J > 0 ? J - 1 : LAST;
+        const bool has_prev = J > 0 || CARRY;
+        acc[J & 1] = chain<0, 2>(qa[J], kb, cr[J]);
+        if (has_prev && stats_guard(acc[(J & 1) ^ 1], lim)) return prev;
+        acc[J & 1] = chain<2, KS>(qa[J], kb, acc[J & 1]);
+        if (has_prev) stats_add(acc[(J & 1) ^ 1], z[prev], c1);
+    }
+    if (!CARRY) {
+        if (stats_guard(acc[(NT - 1) & 1], lim)) return NT - 1;
+        stats_add(acc[(NT - 1) & 1], z[NT - 1], c1);
+    }
     return STATS_OK;
+}
+
+// Anchors the references of all tiles at the row maxima over the subtile in kb, none of whose keys is masked.  The
+// product is formed transposed (the MFMA's A and B swapped: the same registers), so a lane holds 16 keys of ONE row
+// and a maximum is 15 in-lane steps and one exchange, instead of five lane exchanges for each of a lane's 16 rows.
+// A workgroup runs this once, so what counts is its length (instructions that are fetched cold): with the first
+// subtile in the careful body the statistics of 8 problems of 8 192 keys took
+// 23.5 us, 15.0 us now.
+template <int NT, int KS>
+__device__ __forceinline__ void stats_anchor(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[KS], float *cref, int hf, int n)
+{
+#pragma unroll
+    for (int J = 0; J < NT; ++J) {
+        floatx16 t = {};
+#pragma unroll
+        for (int s = 0; s < KS; ++s) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[s], qa[J][s], t, 0, 0, 0);
+        float m = fmaxf(t[0], t[1]);
+#pragma unroll
+        for (int i = 2; i < 16; i += 2) m = fmaxf(fmaxf(m, t[i]), t[i + 1]);
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+        m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+        // row n of the tile is accumulator register 4 (n / 8) + n % 4 of lane half (n / 4) % 2
+        if (hf == 0 && m > -INFINITY) cref[32 * J + ((n >> 2) & 1) * 16 + ((n >> 3) << 2) + (n & 3)] = -m;
+    }
 }
 
 // Careful body: heads h_from..3 of the subtile in kb, one after the other, each multiplied afresh against the
@@ -497,8 +522,8 @@ score_mfma_stats(ScoreArgs a)
 #pragma unroll
         for (int i = 0; i < 16; ++i) { z[h][i] = 0.f; acc[h & 1][i] = -INFINITY; }
 
-    // `waiting`: head 3 of subtile u-1 sits in acc[1], multiplied but not yet reduced (never of subtile 0, which
-    // the careful body handles whole).  When nothing waits, acc[1] = -inf makes the fast body's first step add zeros.
+    // `waiting`: head 3 of subtile u-1 sits in acc[1], multiplied but not yet reduced.  When nothing waits,
+    // acc[1] = -inf makes the fast body's first step add zeros.
     const float lim = RESCALE_AT / a.c1;
     floatx16 cr[4];                                            // the rows' references as MFMA C operands (copy of cref)
 #pragma unroll
@@ -511,20 +536,30 @@ score_mfma_stats(ScoreArgs a)
         ks.fetch(u, kb);
         const int t0 = w.first + u * STRIDE;
         int code = 0;
-        const bool plain = u > 0 && t0 + SUB <= d.T;           // neither the anchoring subtile nor a masked one
-        if (plain) code = stats_fast(qa, kb, acc, cr, z, a.c1, lim);
+        const bool plain = t0 + SUB <= d.T;                    // no masked key
+        if (plain) {
+            if (u == 0) {
+                stats_anchor(qa, kb, cref, hf, n);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) cr[h] = load_cref(cref, h, hf);
+            }
+            code = stats_fast<4, 8, true>(qa, kb, acc, cr, z, a.c1, lim);
+        }
         if (code == STATS_OK) { waiting = true; continue; }
-        if (waiting && (!plain || code == STATS_PREV))         // the waiting head was not reduced by the fast body
+        const bool prev_failed = plain && code == 3;
+        if (waiting && (!plain || prev_failed))                // the waiting head was not reduced by the fast body
             stats_head_careful(acc[1], z[3], cref + 96, a.c1, false, t0 - STRIDE + n, hf, n, Tq, d.L);
-        stats_careful(qa, kb, cref, z, a.c1, (plain && code != STATS_PREV) ? code : 0, u == 0, t0 + n, hf, n, Tq, d.L);
+        stats_careful(qa, kb, cref, z, a.c1, prev_failed ? 0 : code, u == 0 && !plain, t0 + n, hf, n, Tq, d.L);
         waiting = false;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
 #pragma unroll
         for (int h = 0; h < 4; ++h) cr[h] = load_cref(cref, h, hf);     // the careful body may have moved references
     }
-    if (waiting)
-        stats_head_careful(acc[1], z[3], cref + 96, a.c1, false, w.first + (w.n_sub - 1) * STRIDE + n, hf, n, Tq, d.L);
+    if (waiting) {
+        if (!stats_guard(acc[1], lim)) stats_add(acc[1], z[3], a.c1);
+        else stats_head_careful(acc[1], z[3], cref + 96, a.c1, false, w.first + (w.n_sub - 1) * STRIDE + n, hf, n, Tq, d.L);
+    }
 
     // ---- per row: add the 32 lane sums (same reference) through the wavefront's ring (every load has landed),
     // then combine the four wavefronts' (reference, sum) pairs
@@ -1144,8 +1179,10 @@ score_mfma_columns_layer(ScoreArgs a)
 // queries, never written by pass 1 and given an infinite log-sum-exp in pass 2, so they add exact zeros.  For
 // W < 32 a tile holds several heads, so the head mean adds REGISTERS of one accumulator (register i of lane half
 // hf is row 8 (i / 4) + 4 hf + i % 4 of the tile); for W >= 32 it adds accumulators, as in the kernels above.
-// These kernels run the tiles of a subtile one after the other (no rotation of accumulators): with at most the
-// arithmetic of the 128-row case per key and usually far less they wait for memory anyway.
+// The statistics kernel rotates its tiles through two accumulators like the kernel above (the tiles one after the
+// other, references from LDS: 28 layers x 4 KV heads x 30 011 keys, 112 rows of a window of 16, 259 us; 154 us now, a
+// key stream of 0.86 GB).  The column kernel runs the tiles one after the other: its stores hold it to 50-55 ps per key
+// either way.
 template <int NT_, int W> struct Rows {
     static constexpr int NT = NT_;                          // tiles
     static constexpr int MP = 32 * NT;                      // rows of the tiles (padding included)
@@ -1203,24 +1240,52 @@ score_mfma_stats_g(ScoreArgs a)
         for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(qa[J][s]));
     for (int i = lane; i < MP; i += 64) cref[i] = 0.f;
 
+    // the loop of score_mfma_stats: an even number of tiles leaves the last one waiting under the next subtile
+    constexpr bool CARRY = NT % 2 == 0;
+    constexpr int LAST = NT - 1;
     float z[NT][16];
+    floatx16 cr[NT], acc[2];
 #pragma unroll
     for (int J = 0; J < NT; ++J)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) z[J][i] = 0.f;
+        for (int i = 0; i < 16; ++i) { z[J][i] = 0.f; cr[J][i] = 0.f; }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = -INFINITY;
     const float lim = RESCALE_AT / a.c1;
+    auto careful = [&](const floatx16 &x, int J, bool first, int t) {
+        stats_tile_careful(x, z[J], cref + 32 * J, a.c1, first, t, hf, n, [J, hf](int i) { return R::query(J, i, hf); }, d.T, d.L);
+    };
+    bool waiting = false;
     for (int u = 0; u < w.n_sub; ++u) {
         bf16x8 kb[KS];
         ks.fetch(u, kb);
         const int t0 = w.first + u * STRIDE;
-        const bool plain = u > 0 && t0 + SUB <= d.T;
+        const bool plain = t0 + SUB <= d.T;                     // no masked key
+        int code = 0;
+        if (plain) {
+            if (u == 0) {
+                stats_anchor(qa, kb, cref, hf, n);
 #pragma unroll
-        for (int J = 0; J < NT; ++J) {
-            const floatx16 acc = chain<0, KS>(qa[J], kb, load_cref(cref, J, hf));
-            if (plain && !stats_guard(acc, lim)) stats_add(acc, z[J], a.c1);
-            else stats_tile_careful(acc, z[J], cref + 32 * J, a.c1, u == 0, t0 + n, hf, n,
-                                    [J, hf](int i) { return R::query(J, i, hf); }, d.T, d.L);
+                for (int J = 0; J < NT; ++J) cr[J] = load_cref(cref, J, hf);
+            }
+            code = stats_fast<NT, KS, CARRY>(qa, kb, acc, cr, z, a.c1, lim);
         }
+        if (code == STATS_OK) { waiting = CARRY; continue; }
+        const bool prev_failed = CARRY && plain && code == LAST;
+        if (waiting && (!plain || prev_failed)) careful(acc[1], LAST, false, t0 - STRIDE + n);
+        const int from = prev_failed ? 0 : code;
+#pragma unroll
+        for (int J = 0; J < NT; ++J)
+            if (J >= from) careful(chain<0, KS>(qa[J], kb, load_cref(cref, J, hf)), J, u == 0 && !plain, t0 + n);
+        waiting = false;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
+#pragma unroll
+        for (int J = 0; J < NT; ++J) cr[J] = load_cref(cref, J, hf);
+    }
+    if (waiting) {
+        if (!stats_guard(acc[1], lim)) stats_add(acc[1], z[LAST], a.c1);
+        else careful(acc[1], LAST, false, w.first + (w.n_sub - 1) * STRIDE + n);
     }
 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
