@@ -35,6 +35,7 @@
 #include "sablock_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace sablock {
 namespace {
@@ -310,7 +311,7 @@ template <> struct StreamFor<6> { using type = KeyStreamDirect<6>; };
 template <> struct StreamFor<16> { using type = KeyStreamDirect<16>; };
 
 // A operands: the window queries of the four heads, query row `n`, k-slices (2s + hf) * 8 .. +8, into
-// accumulation registers.  All 32 loads are issued before the first is consumed.
+// accumulation registers (pin_queries).  All 32 loads are issued before the first is consumed.
 __device__ __forceinline__ void load_queries(bf16x8 (&qa)[4][8], const uint16_t *q, const Dims &d, int p, int h0, int n, int hf)
 {
 #pragma unroll
@@ -324,10 +325,15 @@ __device__ __forceinline__ void load_queries(bf16x8 (&qa)[4][8], const uint16_t 
             for (int s = 0; s < 8; ++s) qa[h][s] = bf16x8{};
         }
     }
+}
+
+template <int NT, int KS>
+__device__ __forceinline__ void pin_queries(bf16x8 (&qa)[NT][KS])
+{
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
+    for (int h = 0; h < NT; ++h)
 #pragma unroll
-        for (int s = 0; s < 8; ++s) asm volatile("" : "+a"(qa[h][s]));
+        for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(qa[h][s]));
 }
 
 constexpr int NBUF = 4;
@@ -506,12 +512,13 @@ score_mfma_stats(ScoreArgs a)
     const WaveWork w = wave_work_blocks(a, wave);
     const int Tq = d.T + w.qoff;                               // causal limit of this block's query 0: key t is visible to query i iff t <= Tq + i
 
+    // queries before keys: loads return in order, and behind the keys the queries would wait for four subtiles from HBM
+    bf16x8 qa[4][8];
+    load_queries(qa, a.q, d, w.p, w.hoff, w.qoff + n, hf);
+    pin_queries(qa);
     KeyStream<NBUF> ks;
     ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
     ks.prime();
-
-    bf16x8 qa[4][8];
-    load_queries(qa, a.q, d, w.p, w.hoff, w.qoff + n, hf);
     cref[lane] = 0.f;
     cref[lane + 64] = 0.f;
 
@@ -599,6 +606,31 @@ score_mfma_stats(ScoreArgs a)
 }
 
 // ------------------------------------------------------------------ pass 2
+// Folds the (reference, sum) pairs c0, c0 + step, ... < n of one row (`stride` floats apart) into (m, z).  The pairs
+// are read sixteen at a time, all loads in flight: what this costs a workgroup is their latency, not their bytes.
+__device__ __forceinline__ void fold_pairs(const float *pp, int64_t stride, int c0, int step, int n, float &m, float &z)
+{
+    constexpr int B = 16;
+    m = -INFINITY;
+    z = 0.f;
+    for (int c = c0; c < n; c += step * B) {
+        float2 e[B];
+#pragma unroll
+        for (int j = 0; j < B; ++j) e[j] = *reinterpret_cast<const float2 *>(pp + (int64_t)min(c + j * step, n - 1) * stride);
+        float mn = m;
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+            if (c + j * step >= n) e[j].y = 0.f;
+            if (e[j].y > 0.f) mn = fmaxf(mn, e[j].x);
+        }
+        if (z > 0.f) z *= __builtin_amdgcn_exp2f(m - mn);
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+            if (e[j].y > 0.f) z += e[j].y * __builtin_amdgcn_exp2f(e[j].x - mn);
+        m = mn;
+    }
+}
+
 // acc = <q,k> - (lse2 + log2 G)/c1 per (head, query), so exp2(c1 * acc) = A / G
 template <bool EDGE, bool ASSIGN>
 __device__ __forceinline__ void columns_head(const floatx16 &acc, float (&ab)[16], float c1, int t, int hf, int T, int L)
@@ -666,30 +698,24 @@ score_mfma_columns(ScoreArgs a)
     float *comb = lse2 + M_ROWS;                                             // [256][2] combine scratch
     const WaveWork w = wave_work(a, wave);
 
+    // row log-sum-exp: given by the caller, or combined here from the chunk partials of pass 1 (two threads per
+    // row, each folding every other chunk).  Its loads and the queries' come before the keys': loads return in order,
+    // and the fold would otherwise wait for the first keys from HBM, the queries for the fold.
+    bf16x8 qa[4][8];
+    load_queries(qa, a.q, d, w.p, 0, n, hf);
     KeyStream<NBUF> ks;
     ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-
-    // row log-sum-exp: given by the caller, or combined here from the chunk partials of pass 1 (two threads per
-    // row, each folding every other chunk with an online max / rescaled sum)
     {
         const int row = threadIdx.x & (M_ROWS - 1), half = threadIdx.x >> 7;
-        float m = -INFINITY, zz = 0.f;
+        float m, zz;
         if (a.lse) {
             m = a.lse[(int64_t)w.p * M_ROWS + row] * LOG2E;
             zz = half == 0 ? 1.f : 0.f;
         } else {
-            const float *pp = a.merged + ((int64_t)w.p * a.pc * M_ROWS + row) * 2;
-#pragma unroll 4
-            for (int c = half; c < a.pc; c += 2) {
-                const float2 e = *reinterpret_cast<const float2 *>(pp + (int64_t)c * M_ROWS * 2);
-                if (e.y > 0.f) {
-                    const float mn = fmaxf(m, e.x);
-                    zz = zz * __builtin_amdgcn_exp2f(m - mn) + e.y * __builtin_amdgcn_exp2f(e.x - mn);
-                    m = mn;
-                }
-            }
+            fold_pairs(a.merged + ((int64_t)w.p * a.pc * M_ROWS + row) * 2, M_ROWS * 2, half, 2, a.pc, m, zz);
         }
+        pin_queries(qa);
+        ks.prime();
         comb[threadIdx.x * 2] = m;
         comb[threadIdx.x * 2 + 1] = zz;
     }
@@ -705,10 +731,8 @@ score_mfma_columns(ScoreArgs a)
     }
     __syncthreads();
 
-    bf16x8 qa[4][8];
     floatx16 cinit[4], acc[2];
     const float inv_c1 = 1.0f / a.c1;
-    load_queries(qa, a.q, d, w.p, 0, n, hf);
 #pragma unroll
     for (int h = 0; h < 4; ++h) {
 #pragma unroll
@@ -863,15 +887,7 @@ score_mfma_columns8t(ScoreArgs a)
             m = a.lse[(int64_t)w.p * d.G * W + r] * LOG2E;
             zz = 1.f;
         } else {
-            const float *pp = a.merged + (((int64_t)(w.p * 2 + TL::p1_block(j)) * a.pc) * M_ROWS + TL::p1_group(j) * 32 + (i & 31)) * 2;
-            for (int c = 0; c < a.pc; ++c) {
-                const float2 e = *reinterpret_cast<const float2 *>(pp + (int64_t)c * M_ROWS * 2);
-                if (e.y > 0.f) {
-                    const float mn = fmaxf(m, e.x);
-                    zz = zz * __builtin_amdgcn_exp2f(m - mn) + e.y * __builtin_amdgcn_exp2f(e.x - mn);
-                    m = mn;
-                }
-            }
+            fold_pairs(a.merged + (((int64_t)(w.p * 2 + TL::p1_block(j)) * a.pc) * M_ROWS + TL::p1_group(j) * 32 + (i & 31)) * 2, M_ROWS * 2, 0, 1, a.pc, m, zz);
         }
         lse2[r] = m + __builtin_amdgcn_logf(zz) + a.log2_G;                   // + log2(G): exp2 then yields A / G
     }
@@ -896,10 +912,7 @@ score_mfma_columns8t(ScoreArgs a)
             for (int s = 0; s < 8; ++s) qa[j][s] = bf16x8{};
         }
     }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int s = 0; s < 8; ++s) asm volatile("" : "+a"(qa[j][s]));       // all 256 accumulation registers
+    pin_queries(qa);                                           // all 256 accumulation registers
 
     floatx16 acc[2];
     float ab[TL::NB][16];
@@ -1120,15 +1133,7 @@ score_mfma_columns_layer(ScoreArgs a)
                 m = a.lse[(int64_t)(p_first + kv) * M_ROWS + row] * LOG2E;
                 zz = 1.f;
             } else {
-                const float *pp = a.merged + ((int64_t)(p_first + kv) * a.pc * M_ROWS + row) * 2;
-                for (int c = 0; c < a.pc; ++c) {
-                    const float2 e = *reinterpret_cast<const float2 *>(pp + (int64_t)c * M_ROWS * 2);
-                    if (e.y > 0.f) {
-                        const float mn = fmaxf(m, e.x);
-                        zz = zz * __builtin_amdgcn_exp2f(m - mn) + e.y * __builtin_amdgcn_exp2f(e.x - mn);
-                        m = mn;
-                    }
-                }
+                fold_pairs(a.merged + ((int64_t)(p_first + kv) * a.pc * M_ROWS + row) * 2, M_ROWS * 2, 0, 1, a.pc, m, zz);
             }
             const int qy = row & 31, j = (kv & 1) * 4 + (row >> 5);
             const int hq = (qy >> 2) & 1, iq = ((qy >> 3) << 2) | (qy & 3);   // inverse of query_of
@@ -1151,10 +1156,7 @@ score_mfma_columns_layer(ScoreArgs a)
 #pragma unroll
         for (int s = 0; s < 8; ++s) qa[j][s] = *reinterpret_cast<const bf16x8 *>(row + (2 * s + c.hf) * 8);
     }
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int s = 0; s < 8; ++s) asm volatile("" : "+a"(qa[j][s]));       // all 256 accumulation registers
+    pin_queries(qa);                                           // all 256 accumulation registers
 
     floatx16 acc[2];
     float ab[16];
@@ -1181,8 +1183,9 @@ score_mfma_columns_layer(ScoreArgs a)
 // hf is row 8 (i / 4) + 4 hf + i % 4 of the tile); for W >= 32 it adds accumulators, as in the kernels above.
 // The statistics kernel rotates its tiles through two accumulators like the kernel above (the tiles one after the
 // other, references from LDS: 28 layers x 4 KV heads x 30 011 keys, 112 rows of a window of 16, 259 us; 154 us now, a
-// key stream of 0.86 GB).  The column kernel runs the tiles one after the other: its stores hold it to 50-55 ps per key
-// either way.
+// key stream of 0.86 GB).  The column kernel runs the tiles one after the other; the subtiles without a mask have a
+// loop of their own (32 layers x 8 KV heads x 32 768 keys, 32 rows of a window of 8: 393 us with the mask's compares
+// in the one loop, 358 us now, 2.2 GB).
 template <int NT_, int W> struct Rows {
     static constexpr int NT = NT_;                          // tiles
     static constexpr int MP = 32 * NT;                      // rows of the tiles (padding included)
@@ -1227,17 +1230,13 @@ score_mfma_stats_g(ScoreArgs a)
     const WaveWork w = wave_work(a, wave);
     const int M = d.G * W;                                                     // rows of the problem; [M, MP) is padding
 
-    typename StreamFor<KS>::type ks;
-    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-
     bf16x8 qa[NT][KS];
 #pragma unroll
     for (int J = 0; J < NT; ++J) load_query_row(qa[J], a, w.p, 32 * J + n, W, hf);   // row of the window-query matrix
-#pragma unroll
-    for (int J = 0; J < NT; ++J)
-#pragma unroll
-        for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(qa[J][s]));
+    pin_queries(qa);
+    typename StreamFor<KS>::type ks;
+    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
+    ks.prime();
     for (int i = lane; i < MP; i += 64) cref[i] = 0.f;
 
     // the loop of score_mfma_stats: an even number of tiles leaves the last one waiting under the next subtile
@@ -1339,10 +1338,9 @@ score_mfma_columns_g(ScoreArgs a)
     const WaveWork w = wave_work(a, wave);
     const int M = d.G * W;                                                   // rows of the problem; [M, MP) is padding
 
-    typename StreamFor<KS>::type ks;
-    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-
+    bf16x8 qa[NT][KS];
+#pragma unroll
+    for (int J = 0; J < NT; ++J) load_query_row(qa[J], a, w.p, 32 * J + n, W, hf);
     if (threadIdx.x >= M && threadIdx.x < MP) lse2[threadIdx.x] = INFINITY;
     if (threadIdx.x < M) {
         const int r = threadIdx.x;
@@ -1351,40 +1349,30 @@ score_mfma_columns_g(ScoreArgs a)
             m = a.lse[(int64_t)w.p * M + r] * LOG2E;
             zz = 1.f;
         } else {
-            const float *pp = a.merged + ((int64_t)w.p * a.pc * M + r) * 2;
-            for (int c = 0; c < a.pc; ++c) {
-                const float2 e = *reinterpret_cast<const float2 *>(pp + (int64_t)c * M * 2);
-                if (e.y > 0.f) {
-                    const float mn = fmaxf(m, e.x);
-                    zz = zz * __builtin_amdgcn_exp2f(m - mn) + e.y * __builtin_amdgcn_exp2f(e.x - mn);
-                    m = mn;
-                }
-            }
+            fold_pairs(a.merged + ((int64_t)w.p * a.pc * M + r) * 2, M * 2, 0, 1, a.pc, m, zz);
         }
         lse2[r] = m + __builtin_amdgcn_logf(zz) + a.log2_G;
     }
+    pin_queries(qa);
+    typename StreamFor<KS>::type ks;
+    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
+    ks.prime();
     __syncthreads();
 
-    bf16x8 qa[NT][KS];
     floatx16 cinit[NT];
     const float inv_c1 = 1.0f / a.c1;
 #pragma unroll
-    for (int J = 0; J < NT; ++J) {
-        load_query_row(qa[J], a, w.p, 32 * J + n, W, hf);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cinit[J][i] = -lse2[32 * J + R::tile_row(i, hf)] * inv_c1;
-    }
-#pragma unroll
     for (int J = 0; J < NT; ++J)
 #pragma unroll
-        for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(qa[J][s]));
+        for (int i = 0; i < 16; ++i) cinit[J][i] = -lse2[32 * J + R::tile_row(i, hf)] * inv_c1;
     float *out = (hf == 0 ? a.s_out : a.e_out) + (int64_t)w.p * d.L;
 
-    for (int u = 0; u < w.n_sub; ++u) {
+    // the subtiles without a masked key first, then the others: the mask's compares stay out of the long loop
+    auto subtile = [&](int u, auto edge_t) {
+        constexpr bool edge = decltype(edge_t)::value;
         bf16x8 kb[KS];
         ks.fetch(u, kb);
         const int t0 = w.first + u * STRIDE, t = t0 + n;
-        const bool edge = t0 + SUB > d.T;
         float ab[NS];
 #pragma unroll
         for (int i = 0; i < NS; ++i) ab[i] = 0.f;
@@ -1407,7 +1395,7 @@ score_mfma_columns_g(ScoreArgs a)
                     *dst = make_float4(ab[4 * j], ab[4 * j + 1], ab[4 * j + 2], ab[4 * j + 3]);
                 }
             }
-            continue;
+            return;
         }
         float s_part = 0.f;
 #pragma unroll
@@ -1422,7 +1410,11 @@ score_mfma_columns_g(ScoreArgs a)
         }
         const float ent = -LN2 * add_other_half(e_part);                                 // inner sum of Eq. Dk
         if (t < d.L) out[t] = hf == 0 ? sv : ent;
-    }
+    };
+    const int n_plain = w.first + SUB <= d.T ? min(w.n_sub, (d.T - SUB - w.first) / STRIDE + 1) : 0;
+    int u = 0;
+    for (; u < n_plain; ++u) subtile(u, std::false_type{});
+    for (; u < w.n_sub; ++u) subtile(u, std::true_type{});
 }
 
 template <int NT> constexpr int stats_g_lds() { return 4 * 4 * BUF_BYTES + 4 * 32 * NT * 2 * 4 + 4 * 32 * NT * 4; }
@@ -1549,9 +1541,12 @@ struct Plan {
     bool merge;       // fold the chunk partials in a kernel of its own between the passes
 };
 
-constexpr int MERGE_FROM = 8;       // chunks per problem from which the separate fold pays
+// Chunks per problem from which the separate fold pays.  Up to 32 a column workgroup folds them itself in one or two
+// reads of sixteen pairs per thread (8 problems of 8 192 keys, 32 chunks: the fold kernel took 4.1 us, the column pass is no slower without it); a workgroup of the
+// all-head column kernel folds the rows of eight KV heads and hands over earlier.
+constexpr int MERGE_FROM = 33, MERGE_FROM_LAYER = 8;
 
-Plan make_plan(const Dims &d)
+Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)
 {
     // One launch per pass covers every problem.  A workgroup owns chunk_len consecutive keys of one problem, and
     // one workgroup fills a CU (registers and the load ring).  Each round of workgroups costs a prologue and an
@@ -1570,7 +1565,7 @@ Plan make_plan(const Dims &d)
     }
     pl.chunk_len = len;
     pl.n_chunks = (d.L + len - 1) / len;
-    pl.merge = pl.n_chunks >= MERGE_FROM;
+    pl.merge = pl.n_chunks >= merge_from;
     return pl;
 }
 
@@ -1795,7 +1790,7 @@ static bool layer_kernel_shape(const Dims &d) { return d.G == 4 && d.W == 32 && 
 
 size_t score_all_heads_ws_bytes(const Dims &d)
 {
-    const Plan pl = make_plan(d);
+    const Plan pl = make_plan(d, MERGE_FROM_LAYER);
     const size_t abar = layer_kernel_shape(d) ? 0 : align256((size_t)d.P * d.L * d.W * 4);
     return partial_bytes(d, pl) + merged_bytes(d) + abar;
 }
@@ -1803,7 +1798,7 @@ size_t score_all_heads_ws_bytes(const Dims &d)
 hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, const float *row_lse, float eps,
                                   float *s_out, float *ent_out, void *ws, hipStream_t st)
 {
-    const Plan pl = make_plan(d);
+    const Plan pl = make_plan(d, MERGE_FROM_LAYER);
     ScoreArgs a;
     a.d = d;
     a.q = static_cast<const uint16_t *>(q);
