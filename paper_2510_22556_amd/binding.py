@@ -258,7 +258,8 @@ def segment(token_ids, delims: Sequence[int]) -> "Segments":
     assert token_ids.dim() == 2 and token_ids.dtype == torch.int32 and token_ids.stride(1) == 1
     lib, stream = load(), torch.cuda.current_stream(token_ids.device)
     n, T = token_ids.shape
-    tokens, d = (token_ids.data_ptr(), token_ids.stride(0), n, T), (ctypes.c_int32 * max(len(delims), 1))(*delims)
+    tokens = (token_ids.data_ptr(), token_ids.stride(0), n, T)
+    d = (ctypes.c_int32 * max(len(delims), 1))(*[int(x) for x in delims])
     # the kernel writes the counts straight to host memory: no copy between it and the wait
     counts = torch.empty((n,), dtype=torch.int32, pin_memory=True)
     _check(lib.sablock_segment_count(*tokens, d, len(delims), counts.data_ptr(), stream.cuda_stream or None))

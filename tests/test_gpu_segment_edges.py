@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T", [1, 2, 3, 255, 256, 257, 4096, 4099, 16383, 16384, 65472, 131075, 4_200_001])
-@pytest.mark.parametrize("density,delims", [(0.0, [7]), (0.02, [5, 9, -1]), (1.0, [1, 2]), (0.3, list(range(64))), (0.5, [])])
+@pytest.mark.parametrize("density,delims", [(0.0, [7]), (0.02, [5, 9, -1]), (1.0, [1, 2]), (0.3, list(range(64))), (0.5, []), (0.02, [5.0, 9.0])])
 def test_segment_offsets_at_the_edges(oracle, torch_cuda, T, density, delims):  # noqa: F811
     torch = torch_cuda
     from paper_2510_22556_amd import binding as B
