@@ -31,7 +31,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak, published
-FP32_VALU_PEAK_TFLOPS = 157.3   # MI355X fp32 vector peak, published (the generic kernels' arithmetic)
+FP32_PEAK_TFLOPS = 157.3   # MI355X fp32 peak, vector and matrix, published (the generic kernels' arithmetic)
 
 # HBM traffic of the scoring kernels per step (bytes) from two rocprofv3 --pmc runs, FETCH_SIZE then WRITE_SIZE,
 # each scaled by what the counter reads for a plain copy of known size; the summary that holds the counter rows
@@ -217,7 +217,7 @@ def mode_entry(w, alg, dt, score_ms, passes):
     """Figures of one mode of one configuration: the step, the scoring call, both rooflines."""
     total = sum(alg.values())
     mfma_path = w.dtype == "bf16" and w.head_dim == 128
-    peak = MFMA_BF16_PEAK_TFLOPS if mfma_path else FP32_VALU_PEAK_TFLOPS
+    peak = MFMA_BF16_PEAK_TFLOPS if mfma_path else FP32_PEAK_TFLOPS
     tflops = score_flops(w, passes) / (score_ms * 1e-3) / 1e12
     hbm_frac = alg["score"] / (score_ms * 1e-3) / 1e9 / HBM_PEAK_GBS
     # which roof is nearer: flops per algorithmic byte of the scoring step against the ridge of the two peaks
@@ -231,7 +231,7 @@ def mode_entry(w, alg, dt, score_ms, passes):
         "score_frac_hbm_peak": hbm_frac,
         "score_TFLOPs": tflops,
         "score_frac_compute_peak": tflops / peak,
-        "compute_peak": "bf16 MFMA 2500 TFLOP/s" if mfma_path else "fp32 vector 157.3 TFLOP/s",
+        "compute_peak": "bf16 MFMA 2500 TFLOP/s" if mfma_path else "fp32 157.3 TFLOP/s",
         "bound": ("mfma" if mfma_path else "alu") if intensity > ridge else "hbm",
         "flop_per_algorithmic_byte": intensity,
     }
