@@ -1542,8 +1542,8 @@ struct Plan {
 };
 
 // Chunks per problem from which the separate fold pays.  Up to 32 a column workgroup folds them itself in one or two
-// reads of sixteen pairs per thread (8 problems of 8 192 keys, 32 chunks: the fold kernel took 4.1 us, the column pass is no slower without it); a workgroup of the
-// all-head column kernel folds the rows of eight KV heads and hands over earlier.
+// reads of sixteen pairs per thread (8 problems of 8 192 keys, 32 chunks: the fold kernel took 4.1 us, the column pass is
+// no slower without it); a workgroup of the all-head column kernel folds the rows of eight KV heads and hands over earlier.
 constexpr int MERGE_FROM = 33, MERGE_FROM_LAYER = 8;
 
 Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)

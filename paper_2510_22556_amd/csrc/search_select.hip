@@ -855,12 +855,6 @@ __device__ inline void put_topb(const SearchCtx &x, const SegRec &r)
     }
 }
 
-// The search of one segment by one wavefront: Score_base, then the candidates largest first, g_k* and (EMIT) T_k(g_k*) in
-// ascending order at the record's `out`.  false, and nothing written, when its sums may round.  pre: LDS for n + 1 (at
-// least 129) prefix sums; v: first_scores of the segment.
-//
-// What bounds this is the length of the wavefront's instruction stream, so a segment's scores are turned into prefix sums
-// once, where a block's sum is one subtraction for every candidate.
 // A segment's scores as search_exact takes them, behind its end those of its last token: up to 64 tokens one per lane, up
 // to 128 two; of longer segments nothing is needed.
 __device__ inline float2 first_scores(const float *sp, const SegRec &r)
@@ -870,6 +864,12 @@ __device__ inline float2 first_scores(const float *sp, const SegRec &r)
     return make_float2(sp[min(r.a + 2 * lane, last)], sp[min(r.a + 2 * lane + 1, last)]);
 }
 
+// The search of one segment by one wavefront: Score_base, then the candidates largest first, g_k* and (EMIT) T_k(g_k*) in
+// ascending order at the record's `out`.  false, and nothing written, when its sums may round.  pre: LDS for n + 1 (at
+// least 129) prefix sums; v: first_scores of the segment.
+//
+// What bounds this is the length of the wavefront's instruction stream, so a segment's scores are turned into prefix sums
+// once, where a block's sum is one subtraction for every candidate.
 template <bool EMIT>
 __device__ inline bool search_exact(const SearchCtx &x, const SegRec &r, float2 v, double *pre)
 {
