@@ -153,7 +153,7 @@ decode_kernel(DecodeArgs a)
     __shared__ float sh[NWV * G * STRIDE];
     const Dims &d = a.d;
     const int p = blockIdx.y, split = blockIdx.x;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int grp = threadIdx.x / LPR, sub = threadIdx.x % LPR;
     const int r0 = split * a.rows_per_split, r1 = min(r0 + a.rows_per_split, d.L);
     const int hole_lo = a.n_sel ? a.n_sel[p] : d.L, hole_hi = a.n_sel ? a.budget : d.L;   // rows without content
@@ -182,9 +182,17 @@ decode_kernel(DecodeArgs a)
         for (int u = 0; u < UNROLL; ++u) {
             const int r = rb + grp % (64 / LPR) + u * groups;
             live[u] = r < r1 && !(r >= hole_lo && r < hole_hi);
-            const int rc = min(r, r1 - 1);                     // in bounds; the value is unused when not live
+            const int rc = min(r, r1 - 1);                     // in bounds
             kr[u] = load16(kp + (int64_t)rc * kstep);
             vr[u] = load16(vp + (int64_t)rc * vstep);
+        }
+        // a row that is not live may hold anything, NaN and infinity too, and zero times those is NaN: its V counts as
+        // zeros (its logit is replaced below).  Steps whose rows are all live skip this by a scalar test.
+        const int last_row = rb + 64 / LPR - 1 + (UNROLL - 1) * groups;
+        if (last_row >= r1 || (last_row >= hole_lo && rb < hole_hi)) {
+#pragma unroll
+            for (int u = 0; u < UNROLL; ++u)
+                if (!live[u]) vr[u] = u32x4{0, 0, 0, 0};
         }
         float x[UNROLL][GP];
         float ahead = -INFINITY;

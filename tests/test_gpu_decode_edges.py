@@ -39,3 +39,29 @@ def test_decode_group_sizes_rows_and_splits(oracle, torch_cuda, G, D, dtype, row
                                       H.widen(H.to_np(v[0, 0, p]))[keep])
         # fp32 logits of magnitude <= 250 in the log2 domain: 2^-17 relative in a probability
         np.testing.assert_allclose(H.to_np(out[0, 0, p * G:(p + 1) * G]), ref, rtol=2e-5, atol=4e-5)
+
+
+@pytest.mark.parametrize("G,D,dtype", [(1, 64, "bf16"), (4, 128, "bf16"), (7, 64, "f32"), (4, 256, "f32")])
+@pytest.mark.parametrize("rows,n_sel,budget", [(70, 9, 66), (512, 0, 500), (6000, 700, 5990), (6000, 700, 6000), (6001, 130, 3100)])
+def test_decode_skips_whatever_rows_without_an_entry_hold(torch_cuda, G, D, dtype, rows, n_sel, budget):  # noqa: F811
+    # the gap of the first problem holds NaN and infinity, of the second zeros: the same result, bit for bit.  One split
+    # and many, splits that lie wholly in the gap, that end in it (6 000 of 6 000: the last row too) and that begin in it.
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    seed = G * 1000 + D + rows
+    q = synth.normal_torch(seed, 1, (1, 1, G, D), "cuda", dt).repeat(1, 1, 2, 1)
+    k = synth.normal_torch(seed, 2, (1, 1, 1, rows, D), "cuda", dt).repeat(1, 1, 2, 1, 1)
+    v = synth.normal_torch(seed, 3, (1, 1, 1, rows, D), "cuda", dt).repeat(1, 1, 2, 1, 1)
+    for t in (k, v):
+        t[0, 0, 0, n_sel:budget] = torch.tensor([float("nan"), float("inf"), float("-inf"), 1.0], device="cuda").to(dt).repeat(D // 4)
+        t[0, 0, 1, n_sel:budget] = 0.0
+    sel = torch.full((2,), n_sel, dtype=torch.int32, device="cuda")
+    shape = B.make_cache_shape(q, k, v)
+    ws = torch.full((B.sablock_decode_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    B.sablock_decode_attention(shape, q, k, v, out, ws, n_sel=sel, budget=budget)
+    got = H.to_np(out).view(np.uint32)
+    assert np.isfinite(H.to_np(out)).all()
+    np.testing.assert_array_equal(got[0, 0, :G], got[0, 0, G:])
