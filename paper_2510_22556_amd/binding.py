@@ -261,7 +261,7 @@ def segment(token_ids, delims: Sequence[int]) -> "Segments":
     tokens = (token_ids.data_ptr(), token_ids.stride(0), n, T)
     d = (ctypes.c_int32 * max(len(delims), 1))(*[int(x) for x in delims])
     # the kernel writes the counts straight to host memory: no copy between it and the wait
-    counts = torch.empty((n,), dtype=torch.int32, pin_memory=True)
+    counts = torch.empty((n,), dtype=torch.int32, device="cpu", pin_memory=True)
     _check(lib.sablock_segment_count(*tokens, d, len(delims), counts.data_ptr(), stream.cuda_stream or None))
     stream.synchronize()
     c = counts.tolist()

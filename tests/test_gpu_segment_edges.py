@@ -29,3 +29,19 @@ def test_segment_offsets_at_the_edges(oracle, torch_cuda, T, density, delims):  
         ref = oracle.segment(tok[s, 1:T + 1], delims) if T < 1_000_000 else np.concatenate(
             [[0], np.flatnonzero(np.isin(tok[s, 1:T], delims)) + 1, [T]])
         np.testing.assert_array_equal(off[seg.seg_ptr[s]:seg.seg_ptr[s + 1]], ref)
+
+
+def test_segment_whatever_torch_s_default_device_is(torch_cuda):  # noqa: F811
+    # the counts go to pinned host memory, which a program that creates its tensors on the GPU by default has to get too
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    tok = torch.full((2, 100), 1000, dtype=torch.int32, device="cuda")
+    tok[0, 9] = tok[1, 19] = tok[1, 29] = 7
+    before = torch.get_default_device()
+    torch.set_default_device("cuda")
+    try:
+        seg = B.segment(tok, [7])
+    finally:
+        torch.set_default_device(before if before.type != "cpu" else None)
+    assert seg.seg_off.cpu().tolist() == [0, 10, 100, 0, 20, 30, 100] and list(seg.seg_ptr) == [0, 3, 7]
