@@ -8,8 +8,8 @@
 //       lane forms its share of all G products, and the sum over the row's lanes hands each lane ONE head (lane % S,
 //       S = 2, 4 or 8), so that the exponentials of a row are formed once and not once per lane; the probabilities go
 //       back to the row's lanes by DPP.  Probabilities are relative to a reference per head that the whole wavefront
-//       shares and that moves only when a logit runs more than 64 ahead of it in the log2 domain (the first rows
-//       anchor it), so the weighted sums of V are not rescaled row by row.  The lane groups of a wavefront are merged
+//       shares: it is set AHEAD (log2 domain) above the largest logit so far and moves only when a logit passes it, so
+//       the weighted sums of V are not rescaled row by row and no probability exceeds one.  The lane groups of a wavefront are merged
 //       by lane exchanges, the wavefronts through LDS.  With one split the workgroup writes the result itself, else
 //       (maximum, denominator, numerator[D]) per (problem, split, head).
 //   decode_merge_kernel  merges the splits and divides.
@@ -27,7 +27,7 @@ namespace {
 
 constexpr int unroll_of(int G) { return G <= 4 ? 4 : 2; }               // rows in flight per lane group
 constexpr int WIDE = 512;                  // threads of the workgroups that take a problem's rows alone
-constexpr float RESCALE_AT = 64.f;
+constexpr float AHEAD = 8.f;               // 2^-8 of the numbers' range at its small end, nothing at its large one
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -207,20 +207,21 @@ decode_kernel(DecodeArgs a)
                 ahead = fmaxf(ahead, x[u][j] - ref[j]);        // +inf before the first live row, NaN (no maximum) while none is
             }
         }
-        if (__ballot(ahead > RESCALE_AT) != 0ull) {
-            // every head's reference to its largest logit among the wavefront's rows, or where it was
+        if (__ballot(ahead > 0.f) != 0ull) {
+            // every head's reference to AHEAD above its largest logit among the wavefront's rows, or where it was
             float f[HP];
 #pragma unroll
             for (int j = 0; j < HP; ++j) {
-                float m = ref[j];
+                float m = x[0][j];
 #pragma unroll
-                for (int u = 0; u < UNROLL; ++u) m = fmaxf(m, x[u][j]);
+                for (int u = 1; u < UNROLL; ++u) m = fmaxf(m, x[u][j]);
                 if constexpr (S <= 1) m = fmaxf(m, xor_lane<1>(m));
                 if constexpr (S <= 2) m = fmaxf(m, xor_lane<2>(m));
                 if constexpr (S <= 4) m = fmaxf(m, xor_lane<4>(m));
                 m = fmaxf(m, xor_lane<8>(m));
                 m = fmaxf(m, xor_lane<16>(m));
                 m = fmaxf(m, xor_lane<32>(m));
+                m = m > ref[j] ? m + AHEAD : ref[j];
                 f[j] = ref[j] > -INFINITY ? __builtin_amdgcn_exp2f(ref[j] - m) : 0.f;
                 ref[j] = m;
                 l[j] *= f[j];

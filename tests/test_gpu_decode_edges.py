@@ -65,3 +65,35 @@ def test_decode_skips_whatever_rows_without_an_entry_hold(torch_cuda, G, D, dtyp
     got = H.to_np(out).view(np.uint32)
     assert np.isfinite(H.to_np(out)).all()
     np.testing.assert_array_equal(got[0, 0, :G], got[0, 0, G:])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("G", [1, 4, 7])
+@pytest.mark.parametrize("rows", [200, 3000])
+@pytest.mark.parametrize("late,scale", [(5.0, 2.0 ** 108), (41.0, 2.0 ** 108), (200.0, 2.0 ** 108), (41.0, 2.0 ** -100)])
+def test_decode_values_near_the_ends_of_the_range(torch_cuda, dtype, G, rows, late, scale):  # noqa: F811
+    # logits 0 in the first half of the rows, `late` in the second: whatever the sums are relative to when the later ones
+    # arrive, values of 2^108 (2^-100) give a result of that size.  No share exceeds one, so that sums over 3 000 rows stay
+    # below 2^122; a share of 2^59 (41 nats) would take them beyond the range.
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    dt, D = (torch.float32 if dtype == "f32" else torch.bfloat16), 64
+    q = torch.zeros((1, 1, G, D), device="cuda")
+    q[..., 0] = D ** 0.5
+    k = torch.zeros((1, 1, 1, rows, D), device="cuda")
+    k[0, 0, 0, rows // 2:, 0] = late
+    v = synth.normal_torch(rows + G, 3, (1, 1, 1, rows, D), "cuda", torch.float32) * scale
+    q, k, v = q.to(dt), k.to(dt), v.to(dt)
+    shape = B.make_cache_shape(q, k, v)
+    ws = torch.full((B.sablock_decode_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda")
+    B.sablock_decode_attention(shape, q, k, v, out, ws)
+    x = k[0, 0, 0, :, 0].double()
+    w = torch.softmax(x, dim=0)
+    ref = (w @ v[0, 0, 0].double()).cpu().numpy()
+    got = H.to_np(out[0, 0]).astype(np.float64)
+    # a share is off by 2^-17 relative (logits up to 2^8.2 in the log2 domain), a sum of values of both signs by that of its
+    # largest terms
+    most = float((w[:, None] * v[0, 0, 0].double().abs()).sum(dim=0).max())
+    np.testing.assert_allclose(got, np.broadcast_to(ref, got.shape), rtol=0, atol=2e-5 * most)
