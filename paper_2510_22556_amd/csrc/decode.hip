@@ -239,7 +239,7 @@ decode_kernel(DecodeArgs a)
             float pr[HP];
 #pragma unroll
             for (int j = 0; j < HP; ++j) {
-                pr[j] = x[u][j] > -INFINITY ? __builtin_amdgcn_exp2f(x[u][j] - ref[j]) : 0.f;
+                pr[j] = x[u][j] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[u][j] - ref[j]);         // NaN stays NaN
                 l[j] += pr[j];
             }
             float ve[E];
@@ -291,14 +291,12 @@ decode_kernel(DecodeArgs a)
 #pragma unroll
         for (int w = 0; w < NWV; ++w) mx = fmaxf(mx, sh[(w * G + g) * STRIDE]);
         float num = 0.f, den = 0.f;
-        if (mx > -INFINITY) {
 #pragma unroll
-            for (int w = 0; w < NWV; ++w) {
-                const float *o = sh + (w * G + g) * STRIDE;
-                const float f = __builtin_amdgcn_exp2f(o[0] - mx);
-                den += o[1] * f;
-                num += o[2 + c] * f;
-            }
+        for (int w = 0; w < NWV; ++w) {
+            const float *o = sh + (w * G + g) * STRIDE;
+            const float f = mx > -INFINITY ? __builtin_amdgcn_exp2f(o[0] - mx) : 1.f;          // no row: zeros
+            den += o[1] * f;
+            num += o[2 + c] * f;
         }
         if (last) a.out[qbase + (int64_t)g * D + c] = den > 0.f ? num / den : 0.f;
         else {
@@ -327,7 +325,7 @@ decode_merge_kernel(DecodeArgs a)
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < MERGE_T / 64; ++w) mx = fmaxf(mx, red[w]);
-    const float f = z > 0.f ? __builtin_amdgcn_exp2f(m - mx) : 0.f;
+    const float f = z == 0.f ? 0.f : __builtin_amdgcn_exp2f(m - mx);         // no row: nothing; NaN stays NaN
     w_sh[tid] = f;
     float den = z * f;
 #pragma unroll
@@ -341,10 +339,7 @@ decode_merge_kernel(DecodeArgs a)
     float num = 0.f;
 #pragma unroll 8
     for (int s = part; s < a.n_splits; s += parts)
-    {
-        const float x = pp[s * step + 2 + c], f1 = w_sh[s];
-        num += f1 > 0.f ? x * f1 : 0.f;                        // a split without rows has written no finite sums
-    }
+        num += pp[s * step + 2 + c] * w_sh[s];                 // a split without rows has written zeros
     sum[tid] = num;
     __syncthreads();
     if (part > 0) return;

@@ -97,3 +97,25 @@ def test_decode_values_near_the_ends_of_the_range(torch_cuda, dtype, G, rows, la
     # largest terms
     most = float((w[:, None] * v[0, 0, 0].double().abs()).sum(dim=0).max())
     np.testing.assert_allclose(got, np.broadcast_to(ref, got.shape), rtol=0, atol=2e-5 * most)
+
+
+@pytest.mark.parametrize("G,D,dtype", [(1, 64, "bf16"), (4, 128, "bf16"), (7, 64, "f32")])
+@pytest.mark.parametrize("rows,at", [(70, 0), (70, 69), (512, 300), (6000, 0), (6000, 4321)])
+def test_decode_a_logit_that_is_not_a_number_is_not_dropped(torch_cuda, G, D, dtype, rows, at):  # noqa: F811
+    # the head's denominator is not a number, which gives zeros, as for a problem without rows: not the attention over
+    # the other rows.  The other problem is untouched.
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = synth.normal_torch(rows, 1, (1, 1, 2 * G, D), "cuda", dt)
+    k = synth.normal_torch(rows, 2, (1, 1, 2, rows, D), "cuda", dt)
+    v = synth.normal_torch(rows, 3, (1, 1, 2, rows, D), "cuda", dt)
+    shape = B.make_cache_shape(q, k, v)
+    ws = torch.full((B.sablock_decode_workspace_bytes(shape),), 0xFF, dtype=torch.uint8, device="cuda")
+    clean, out = (torch.full(q.shape, float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    B.sablock_decode_attention(shape, q, k, v, clean, ws)
+    k[0, 0, 0, at, 3] = float("nan")
+    B.sablock_decode_attention(shape, q, k, v, out, ws)
+    assert not H.to_np(out[0, 0, :G]).any()
+    np.testing.assert_array_equal(H.to_np(out[0, 0, G:]), H.to_np(clean[0, 0, G:]))
