@@ -1005,7 +1005,7 @@ struct PlanArgs {
 __global__ void __launch_bounds__(TB_THREADS)
 topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, int32_t *pre_list, int32_t *pre_cnt)
 {
-    extern __shared__ uint32_t sh_dyn[];         // histogram, then the list
+    extern __shared__ __attribute__((aligned(16))) uint32_t sh_dyn[];   // histogram, then the list
     __shared__ TopbShared sh;
     uint32_t *hist = sh_dyn;
     int32_t *list = reinterpret_cast<int32_t *>(sh_dyn + TB_BINS);
@@ -1047,7 +1047,7 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
             int32_t *block_size, PlanArgs pa, CandList cand, float tau, int offs_cap, int sample_rank)
 {
     constexpr int CAP = E * TB_THREADS;          // tokens the list holds
-    extern __shared__ uint32_t sh_dyn[];         // histogram [TB_BINS] and list [CAP]; later offsets and counters [2][offs_cap]
+    extern __shared__ __attribute__((aligned(16))) uint32_t sh_dyn[];   // histogram [TB_BINS] and list [CAP]; later offsets and counters [2][offs_cap]
     __shared__ TopbShared sh;
     uint32_t *hist = sh_dyn;
     int32_t *list = reinterpret_cast<int32_t *>(sh_dyn + TB_BINS);

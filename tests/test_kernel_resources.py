@@ -1,0 +1,27 @@
+"""What the compiler reports of the kernels, read from the assembly that it writes for them: no GPU is needed."""
+
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2510_22556_amd import build
+
+
+@pytest.fixture(scope="module")
+def search_select_kernels(tmp_path_factory):
+    asm = str(tmp_path_factory.mktemp("asm") / "search_select.s")
+    subprocess.run([build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, "search_select.hip"), "-o", asm],
+                   check=True, stderr=subprocess.DEVNULL)
+    with open(asm) as f:
+        text = f.read()
+    blocks = re.findall(r"\.amdhsa_kernel (\S+)\n(.*?)\.end_amdhsa_kernel", text, re.S)
+    return {name: {k: int(v) for k, v in re.findall(r"\.amdhsa_(\w+) (\d+)\n", body)} for name, body in blocks}
+
+
+def test_dynamic_lds_of_the_topb_kernels_begins_on_16_bytes(search_select_kernels):
+    # it lies behind the static part and is read and written 16 bytes at a time
+    topb = {n: k for n, k in search_select_kernels.items() if "topb_" in n}
+    assert len(topb) == 9
+    assert all(k["group_segment_fixed_size"] % 16 == 0 for k in topb.values()), topb
