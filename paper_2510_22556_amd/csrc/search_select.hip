@@ -47,9 +47,9 @@ struct __attribute__((aligned(32))) SegRec {
 // second list that is served by the same kernel with the large one.
 constexpr int CAPB = 256, CAPT = 2 * CAPB;
 constexpr int CAPB_LONG = 2048, CAPT_LONG = 2 * CAPB_LONG;
-// Tokens of a segment whose prefix sums fit the LDS of a search wavefront (5 KiB: 32 wavefronts per CU), and of one that
-// the per-problem workgroups search.
-constexpr int PRE_TOKENS = 639, PRE_LONG = 4095;
+// Tokens of a segment whose prefix sums fit the LDS of a search wavefront (5 KiB); longer ones are searched from memory
+// (search_streamed).
+constexpr int PRE_TOKENS = 639;
 constexpr int MAX_G = 64;           // largest candidate block size
 
 // Wavefront reductions without LDS round trips: four DPP steps inside each row of 16 lanes (lane ^ 1, lane ^ 2,
@@ -101,6 +101,11 @@ __device__ inline V wave_max_32(V v)                           // int or uint32_
 }
 __device__ inline int wave_max_i(int v) { return wave_max_32<int>(v); }
 __device__ inline uint32_t wave_max_u(uint32_t v) { return wave_max_32<uint32_t>(v); }
+__device__ inline uint64_t wave_max_u64(uint64_t v)
+{
+    const uint32_t hi = wave_max_u((uint32_t)(v >> 32)), lo = wave_max_u((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0u);
+    return ((uint64_t)hi << 32) | lo;
+}
 __device__ inline double wave_max_d(double v)
 {
     v = fmax(v, dpp_d<DPP_XOR1>(v));
@@ -265,7 +270,7 @@ struct TopbShared {
     uint32_t w[TB_WAVES];
     uint32_t found[3];             // bin, entries in front of it, entries in it
     int n;                         // length of the token list
-    int n_bin, n_rec, n_long;
+    int n_bin, n_rec;
     uint32_t thr;
     int cut;
 };
@@ -470,160 +475,15 @@ __device__ inline double block_sum(V val, int a, int b, int g, int m)
 }
 
 // number of blocks ranked before block m
-template <typename V>
-__device__ inline int block_rank(V val, int a, int b, int g, int nb, int m, double phi_m,
-                                 const double *phi_lds, bool fast)
+__device__ inline int block_rank(int nb, int m, double phi_m, const double *phi_lds)
 {
     int r = 0;
 #pragma unroll 4
     for (int o = 0; o < nb; ++o) {
-        double po = fast ? phi_lds[o] : block_sum(val, a, b, g, o);
+        const double po = phi_lds[o];
         r += (po > phi_m || (po == phi_m && o < m)) ? 1 : 0;
     }
     return r;
-}
-
-// T_k(g) for segment [a,b) with implicit budget bk (Alg. 2's inner loop).  Calls
-// emit(c0, taken_mask, value) for each 64-token chunk in ascending order; lane l
-// of the chunk starting at token c0 holds the value of token c0 + l.
-// Requires 1 <= g <= MAX_G, g <= min(b - a, bk); all arguments wave-uniform.
-template <typename V, typename F>
-__device__ inline void segment_fill(V val, int a, int b, int g, int bk, WaveScratch ws, F &&emit)
-{
-    const int lane = threadIdx.x & 63;
-    const int len = b - a;
-    const int nb = (len + g - 1) / g;
-    const int ts = len - (nb - 1) * g;                 // size of the last block, 1..g
-    const bool fast = nb <= ws.capb;
-    const int mt = nb - 1;
-
-    if (fast) {
-        for (int m = lane; m < nb; m += 64) ws.phi[m] = block_sum(val, a, b, g, m);
-        __builtin_amdgcn_wave_barrier();
-    }
-    // blocks taken whole: the first rstar in rank order; all blocks have g tokens except a short last one,
-    // whose rank q decides how many blocks fit
-    int rstar, nwhole;
-    if (ts == g) {
-        rstar = min(nb, bk / g);
-        nwhole = rstar * g;
-    } else {
-        const double phi_t = fast ? ws.phi[mt] : block_sum(val, a, b, g, mt);
-        int cnt = 0;
-        for (int o = lane; o < mt; o += 64) {
-            double po = fast ? ws.phi[o] : block_sum(val, a, b, g, o);
-            cnt += (po >= phi_t) ? 1 : 0;                // o < mt: an equal sum ranks first
-        }
-        const int q = wave_sum_i(cnt);
-        const int c = bk / g, r = bk - c * g;
-        if (q < c) {
-            if (ts <= r) { rstar = c + 1; nwhole = c * g + ts; } else { rstar = c; nwhole = c * g - g + ts; }
-        } else if (q == c) {
-            if (ts <= r) { rstar = c + 1; nwhole = c * g + ts; } else { rstar = c; nwhole = c * g; }
-        } else {
-            rstar = c; nwhole = c * g;
-        }
-        rstar = min(rstar, nb);
-    }
-    const int rem = bk - nwhole;                         // tokens to take from the block ranked rstar
-
-    // classify blocks; remember the cut block
-    int mp_local = -1;
-    const int picks = rstar + (rem > 0 ? 1 : 0);           // blocks to single out when rstar < nb
-    if (fast && rstar < nb && (picks <= 8 || picks * 512 <= nb * nb)) {
-        // few blocks are taken: pick them one by one, best first (sum descending, index ascending), instead of
-        // ranking every block against every other
-        for (int m = lane; m < nb; m += 64) ws.cls[m] = 0;
-        __builtin_amdgcn_wave_barrier();
-        for (int sel = 0; sel < picks; ++sel) {
-            double bp = -INFINITY;
-            int bm = 0x7fffffff;
-            for (int m = lane; m < nb; m += 64) {
-                const double pm = ws.phi[m];
-                if (ws.cls[m] == 0 && (pm > bp || (pm == bp && m < bm))) { bp = pm; bm = m; }
-            }
-            wave_argmax(bp, bm);
-            if (lane == 0) ws.cls[bm] = sel < rstar ? 1 : 2;
-            if (sel == rstar) mp_local = bm;
-            __builtin_amdgcn_wave_barrier();
-        }
-    } else if (fast) {
-        for (int m = lane; m < nb; m += 64) {
-            int rk = (rstar >= nb) ? 0 : block_rank(val, a, b, g, nb, m, ws.phi[m], ws.phi, true);
-            uint8_t c = (rk < rstar) ? 1 : ((rk == rstar && rem > 0) ? 2 : 0);
-            ws.cls[m] = c;
-            if (c == 2) mp_local = m;
-        }
-        __builtin_amdgcn_wave_barrier();
-    } else if (rem > 0 && rstar < nb) {
-        for (int m = lane; m < nb; m += 64) {
-            int rk = block_rank(val, a, b, g, nb, m, block_sum(val, a, b, g, m), nullptr, false);
-            if (rk == rstar) mp_local = m;
-        }
-    }
-    const int mp = wave_max_i(mp_local);
-
-    // inside the cut block: its best rem tokens
-    unsigned long long pmask = 0;
-    int plo = 0;
-    if (mp >= 0) {
-        plo = a + mp * g;
-        const int phi_hi = min(plo + g, b);
-        const int sz = phi_hi - plo;
-        bool tk = false;
-        if (lane < sz) {
-            const float v = val(plo + lane);
-            int rk = 0;
-            for (int j = 0; j < sz; ++j) {
-                float o = val(plo + j);
-                rk += (o > v || (o == v && j < lane)) ? 1 : 0;
-            }
-            tk = rk < rem;
-        }
-        pmask = __ballot(tk);
-    }
-
-    for (int c0 = a; c0 < b; c0 += 64) {
-        const int t = c0 + lane;
-        const bool live = t < b;
-        float v = 0.f;
-        bool take = false;
-        if (live) {
-            v = val(t);
-            const int m = (t - a) / g;
-            int c;
-            if (fast) {
-                c = ws.cls[m];
-            } else {
-                int rk = (rstar >= nb) ? 0 : block_rank(val, a, b, g, nb, m, block_sum(val, a, b, g, m), nullptr, false);
-                c = (rk < rstar) ? 1 : ((m == mp) ? 2 : 0);
-            }
-            take = (c == 1) || (c == 2 && ((pmask >> (t - plo)) & 1ull));
-        }
-        emit(c0, __ballot(take), v);
-    }
-    __builtin_amdgcn_wave_barrier();
-}
-
-// ------------------------------------------------------------------ sums that cannot round
-// The scores of a segment are fp32 values, summed in fp64.  Every value and every partial sum is a multiple of the
-// last bit of the smallest nonzero one, and the sum of n of them stays below n times twice the power of two of the
-// largest, so as long as
-//     exponent range + 24 bits of mantissa + ceil(log2 n) <= 53
-// no partial sum rounds in ANY order: prefix sums by lane shuffles, differences of prefixes and sums over arbitrary
-// subsets then equal the ordered sums bit for bit.  Segments whose scores span more (23 powers of two at 64 tokens, 17
-// at 4 095) take the ordered sums (segment_fill above).
-// biggest: the largest |score| of a segment; smallest: the smallest nonzero one as its bits doubled, less one; total:
-// the sum (not finite when a score is not); n >= 2
-__device__ inline void note_size(float v, float &biggest, uint32_t &smallest)
-{
-    biggest = fmaxf(biggest, fabsf(v));
-    smallest = min(smallest, (__float_as_uint(v) << 1) - 1u);  // zero becomes the largest value
-}
-__device__ inline bool sums_are_exact(float biggest, uint32_t smallest, double total, int n)
-{
-    const int hi = max(wave_max_i(__float_as_int(biggest)) >> 23, 1), lo = max((int)((~wave_max_u(~smallest) + 1u) >> 24), 1);
-    return hi - lo <= 29 - (32 - __builtin_clz(n - 1)) && fabs(total) < INFINITY;
 }
 
 // ranks of the block walk of Alg. 2 without the short last block's own place in the order: how many blocks are taken
@@ -648,18 +508,10 @@ __device__ inline void whole_blocks(int nb, int g, int ts, int c, int r, int q, 
 // order-preserving signed key of a float (the two zeros: callers pass no -0)
 __device__ inline int key_of(float x) { const int b = __float_as_int(x); return b ^ ((b >> 31) & 0x7fffffff); }
 constexpr int NO_KEY = (int)0x80000000;
-
-// Lane of the largest x (lowest lane among equal ones) whose key, of x rounded to fp32, is not NO_KEY: one 32-bit
-// reduction, and an fp64 one only where several x round to the same fp32 value.
-__device__ inline int best_lane(double x, int key)
+__device__ inline uint64_t ordered_key_d(double x)
 {
-    const int mk = wave_max_i(key);
-    unsigned long long m = __ballot(key == mk);
-    if (m & (m - 1)) {
-        const double mx = wave_max_d(key == mk ? x : -INFINITY);
-        m = __ballot(key == mk && x == mx);
-    }
-    return __builtin_ctzll(m);
+    const uint64_t u = (uint64_t)__double_as_longlong(x == 0.0 ? 0.0 : x);       // the zeros rank as equal
+    return (u >> 63) ? ~u : u | (1ull << 63);
 }
 
 // The best `rem` (value descending, index ascending) of the sz <= 64 scores that lanes 0 .. sz - 1 hold; adds their sum
@@ -692,6 +544,320 @@ __device__ inline unsigned long long best_tokens(float v, int sz, int rem, doubl
     return __ballot(tk);
 }
 
+// ------------------------------------------------------------------ one segment of any length, one block size
+// Where the blocks of a segment do not fit LDS, a lane forms the sum of its block in every pass over the blocks (in
+// ascending order, as block_sum), and the blocks that are taken are found as everything above a (sum, index) pair: the
+// k-th best by digits of eight bits fitted to the sums there are, the last 64 candidates ranked one against another.  Two
+// or three passes over the segment for scores in no particular order, however long it is; ranking every block against
+// every other took up to 9 s for one segment of 65 536 tokens.
+constexpr int ST_BINS = 256, ST_RANKED = 64;
+struct StreamScratch {
+    uint32_t hist[ST_BINS];
+    uint64_t key[ST_RANKED];
+    int32_t m[ST_RANKED];
+};
+static_assert(sizeof(StreamScratch) <= 8 * CAPB, "lies where the block sums of a segment that fits would");
+// block m is taken whole when the key of its sum is above `key`, or equal to it and m <= cut; mp: the block of which the
+// tokens plo + j with bit j of pmask are taken (-1: none)
+struct StreamFill {
+    uint64_t key;
+    int cut, mp, plo;
+    unsigned long long pmask;
+    __device__ inline bool whole(uint64_t k, int m) const { return k > key || (k == key && m <= cut); }
+};
+
+// Sum of block m, loads in flight; zero behind the last block
+template <typename V>
+__device__ inline double stream_sum(V val, int a, int b, int g, int m)
+{
+    const int lo = a + m * g, n = min(g, b - lo);
+    double phi = 0.0;
+#pragma nounroll
+    for (int j0 = 0; j0 < g; j0 += 8) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = val(min(lo + min(j0 + j, g - 1), b - 1));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) phi += j0 + j < n ? (double)v[j] : 0.0;
+    }
+    return phi;
+}
+
+// The blocks of T_k(g); phi(m): sum of block m of nb, any m below nb rounded up to 64.  `part` += the sum of the cut
+// block's tokens.
+template <typename P, typename V>
+__device__ inline StreamFill stream_select(P phi, V val, int a, int b, int g, int bk, StreamScratch &sc, double &part)
+{
+    const int lane = threadIdx.x & 63, nb = (b - a + g - 1) / g, mt = nb - 1, ts = b - a - mt * g;
+    StreamFill f{0, nb, -1, 0, 0};                             // everything
+    uint64_t hi = 0, lo = ~0ull;                               // the k-th best key lies in [lo, hi]
+    int q = 0;
+    {
+        const uint64_t kt = ordered_key_d(phi(mt));
+#pragma nounroll
+        for (int m0 = 0; m0 < nb; m0 += 64) {
+            const int m = m0 + lane;
+            const uint64_t k = ordered_key_d(phi(m));
+            if (m < nb) {
+                hi = max(hi, k);
+                lo = min(lo, k);
+                q += m < mt && k >= kt ? 1 : 0;                // an equal sum ranks first
+            }
+        }
+        hi = wave_max_u64(hi);
+        lo = ~wave_max_u64(~lo);
+        q = wave_sum_i(q);
+    }
+    int rstar, nwhole;
+    whole_blocks(nb, g, ts, bk / g, bk % g, q, rstar, nwhole);
+    if (rstar >= nb) return f;
+    const int rem = bk - nwhole;
+    int k_rem = rstar + (rem > 0 ? 1 : 0);                     // the cut block is the next one
+    for (;;) {
+        const uint64_t range = hi - lo;
+        const int shift = range < ST_BINS ? 0 : 56 - __builtin_clzll(range);
+        reinterpret_cast<uint4 *>(sc.hist)[lane] = make_uint4(0, 0, 0, 0);
+        static_assert(ST_BINS == 4 * 64, "four bins per lane");
+        __builtin_amdgcn_wave_barrier();
+#pragma nounroll
+        for (int m0 = 0; m0 < nb; m0 += 64) {
+            const int m = m0 + lane;
+            const uint64_t k = ordered_key_d(phi(m));
+            if (m < nb && k >= lo && k <= hi) atomicAdd(&sc.hist[(int)((hi - k) >> shift)], 1u);
+        }
+        __builtin_amdgcn_wave_barrier();
+        const uint4 c = reinterpret_cast<const uint4 *>(sc.hist)[lane];
+        __builtin_amdgcn_wave_barrier();                       // read before the next round's zeros
+        const int mine = (int)(c.x + c.y + c.z + c.w), incl = (int)wave_scan_u((uint32_t)mine);
+        int bin = 4 * lane, above = incl - mine, count = (int)c.x;
+        const int src = __builtin_ctzll(__ballot(above < k_rem && k_rem <= incl));
+        if (above + count < k_rem) { above += count; ++bin; count = (int)c.y; }
+        if (above + count < k_rem) { above += count; ++bin; count = (int)c.z; }
+        if (above + count < k_rem) { above += count; ++bin; count = (int)c.w; }
+        bin = __builtin_amdgcn_readlane(bin, src);
+        count = __builtin_amdgcn_readlane(count, src);
+        k_rem -= __builtin_amdgcn_readlane(above, src);
+        hi -= (uint64_t)bin << shift;
+        const uint64_t width = (1ull << shift) - 1;
+        if (hi - lo > width) lo = hi - width;
+        if (rem == 0 && k_rem == count) {                      // the whole bin is inside
+            f.key = lo;
+            return f;
+        }
+        if (shift == 0) {                                      // equal sums: lowest indices first
+            f.key = hi;
+#pragma nounroll
+            for (int m0 = 0; m0 < nb; m0 += 64) {
+                const int m = m0 + lane;
+                const unsigned long long eq = __ballot(m < nb && ordered_key_d(phi(m)) == hi);
+                const int c0 = __popcll(eq);
+                if (k_rem <= c0) {
+                    f.cut = m0 + __builtin_ctzll(__ballot(((eq >> lane) & 1ull) && lanes_below(eq) == k_rem - 1));
+                    break;
+                }
+                k_rem -= c0;
+            }
+            break;
+        }
+        if (count <= ST_RANKED) {
+            int at = 0;
+#pragma nounroll
+            for (int m0 = 0; m0 < nb; m0 += 64) {
+                const int m = m0 + lane;
+                const uint64_t k = ordered_key_d(phi(m));
+                const bool in = m < nb && k >= lo && k <= hi;
+                const unsigned long long bal = __ballot(in);
+                if (in) {
+                    sc.key[at + lanes_below(bal)] = k;
+                    sc.m[at + lanes_below(bal)] = m;
+                }
+                at += __popcll(bal);
+            }
+            __builtin_amdgcn_wave_barrier();
+            const uint64_t me = sc.key[min(lane, count - 1)];
+            const int m = sc.m[min(lane, count - 1)];
+            int rank = 0;
+#pragma nounroll
+            for (int j = 0; j < count; ++j) {
+                const uint64_t o = sc.key[j];
+                rank += o > me || (o == me && j < lane) ? 1 : 0;
+            }
+            const int l = __builtin_ctzll(__ballot(lane < count && rank == k_rem - 1));
+            f.key = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(me >> 32), l) << 32) | (uint32_t)__builtin_amdgcn_readlane((int)me, l);
+            f.cut = __builtin_amdgcn_readlane(m, l);
+            __builtin_amdgcn_wave_barrier();
+            break;
+        }
+    }
+    if (rem > 0) {
+        f.mp = f.cut--;
+        f.plo = a + f.mp * g;
+        const int sz = min(g, b - f.plo);
+        f.pmask = best_tokens(val(f.plo + min(lane, sz - 1)), sz, rem, part);
+    }
+    return f;
+}
+
+// emit(c0, mask of the tokens c0 + lane that are taken, value) in ascending order; 64 tokens without a taken one may be
+// left out
+template <typename P, typename V, typename F>
+__device__ inline void stream_walk(P phi, V val, int a, int b, int g, const StreamFill &f, F &&emit)
+{
+    const int lane = threadIdx.x & 63, nb = (b - a + g - 1) / g;
+#pragma nounroll
+    for (int m0 = 0; m0 < nb; m0 += 64) {
+        const int m = m0 + lane;
+        const unsigned long long any = __ballot(m < nb && (f.whole(ordered_key_d(phi(m)), m) || m == f.mp));
+        if (any == 0) continue;
+        const int first = a + m0 * g;
+        float nxt = val(min(first + lane, b - 1));             // one chunk ahead
+#pragma nounroll
+        for (int c0 = 0; c0 < 64 * g && first + c0 < b; c0 += 64) {
+            const int t = first + c0 + lane, mm = (c0 + lane) / g;
+            const float v = nxt;
+            nxt = val(min(t + 64, b - 1));
+            const bool take = t < b && ((any >> mm) & 1ull) && (m0 + mm != f.mp || ((f.pmask >> (t - f.plo)) & 1ull));
+            const unsigned long long mask = __ballot(take);
+            if (mask) emit(first + c0, mask, v);
+        }
+    }
+}
+
+// T_k(g) for segment [a,b) with implicit budget bk (Alg. 2's inner loop).  Calls
+// emit(c0, taken_mask, value) for the 64-token chunks with a taken token in ascending order; lane l
+// of the chunk starting at token c0 holds the value of token c0 + l.
+// Requires 1 <= g <= MAX_G, g <= min(b - a, bk); all arguments wave-uniform.
+template <typename V, typename F>
+__device__ inline void segment_fill(V val, int a, int b, int g, int bk, WaveScratch ws, F &&emit)
+{
+    const int lane = threadIdx.x & 63;
+    const int len = b - a;
+    const int nb = (len + g - 1) / g;
+    const int ts = len - (nb - 1) * g;                 // size of the last block, 1..g
+    const int mt = nb - 1;
+    if (nb > ws.capb) {
+        auto phi = [&](int m) { return stream_sum(val, a, b, g, m); };
+        double part = 0.0;
+        const StreamFill f = stream_select(phi, val, a, b, g, bk, *reinterpret_cast<StreamScratch *>(ws.phi), part);
+        stream_walk(phi, val, a, b, g, f, emit);
+        return;
+    }
+
+    for (int m = lane; m < nb; m += 64) ws.phi[m] = block_sum(val, a, b, g, m);
+    __builtin_amdgcn_wave_barrier();
+    // blocks taken whole: the first rstar in rank order; all blocks have g tokens except a short last one,
+    // whose rank q decides how many blocks fit
+    int rstar, nwhole, q = 0;
+    if (ts != g) {
+        const double phi_t = ws.phi[mt];
+        int cnt = 0;
+        for (int o = lane; o < mt; o += 64) cnt += (ws.phi[o] >= phi_t) ? 1 : 0;       // o < mt: an equal sum ranks first
+        q = wave_sum_i(cnt);
+    }
+    const int c = bk / g;
+    whole_blocks(nb, g, ts, c, bk - c * g, q, rstar, nwhole);
+    const int rem = bk - nwhole;                         // tokens to take from the block ranked rstar
+
+    // classify blocks; remember the cut block
+    int mp_local = -1;
+    const int picks = rstar + (rem > 0 ? 1 : 0);           // blocks to single out when rstar < nb
+    if (rstar < nb && (picks <= 8 || picks * 512 <= nb * nb)) {
+        // few blocks are taken: pick them one by one, best first (sum descending, index ascending), instead of
+        // ranking every block against every other
+        for (int m = lane; m < nb; m += 64) ws.cls[m] = 0;
+        __builtin_amdgcn_wave_barrier();
+        for (int sel = 0; sel < picks; ++sel) {
+            double bp = -INFINITY;
+            int bm = 0x7fffffff;
+            for (int m = lane; m < nb; m += 64) {
+                const double pm = ws.phi[m];
+                if (ws.cls[m] == 0 && (pm > bp || (pm == bp && m < bm))) { bp = pm; bm = m; }
+            }
+            wave_argmax(bp, bm);
+            if (lane == 0) ws.cls[bm] = sel < rstar ? 1 : 2;
+            if (sel == rstar) mp_local = bm;
+            __builtin_amdgcn_wave_barrier();
+        }
+    } else {
+        for (int m = lane; m < nb; m += 64) {
+            int rk = (rstar >= nb) ? 0 : block_rank(nb, m, ws.phi[m], ws.phi);
+            uint8_t c = (rk < rstar) ? 1 : ((rk == rstar && rem > 0) ? 2 : 0);
+            ws.cls[m] = c;
+            if (c == 2) mp_local = m;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    const int mp = wave_max_i(mp_local);
+
+    // inside the cut block: its best rem tokens
+    unsigned long long pmask = 0;
+    int plo = 0;
+    if (mp >= 0) {
+        plo = a + mp * g;
+        const int phi_hi = min(plo + g, b);
+        const int sz = phi_hi - plo;
+        bool tk = false;
+        if (lane < sz) {
+            const float v = val(plo + lane);
+            int rk = 0;
+            for (int j = 0; j < sz; ++j) {
+                float o = val(plo + j);
+                rk += (o > v || (o == v && j < lane)) ? 1 : 0;
+            }
+            tk = rk < rem;
+        }
+        pmask = __ballot(tk);
+    }
+
+    for (int c0 = a; c0 < b; c0 += 64) {
+        const int t = c0 + lane;
+        const bool live = t < b;
+        float v = 0.f;
+        bool take = false;
+        if (live) {
+            v = val(t);
+            const int c = ws.cls[(t - a) / g];
+            take = (c == 1) || (c == 2 && ((pmask >> (t - plo)) & 1ull));
+        }
+        emit(c0, __ballot(take), v);
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// ------------------------------------------------------------------ sums that cannot round
+// The scores of a segment are fp32 values, summed in fp64.  Every value and every partial sum is a multiple of the
+// last bit of the smallest nonzero one, and the sum of n of them stays below n times twice the power of two of the
+// largest, so as long as
+//     exponent range + 24 bits of mantissa + ceil(log2 n) <= 53
+// no partial sum rounds in ANY order: prefix sums by lane shuffles, differences of prefixes and sums over arbitrary
+// subsets then equal the ordered sums bit for bit.  Segments whose scores span more (23 powers of two at 64 tokens, 17
+// at 4 095) take the ordered sums (segment_fill above).
+// biggest: the largest |score| of a segment; smallest: the smallest nonzero one as its bits doubled, less one; total:
+// the sum (not finite when a score is not); n >= 2
+__device__ inline void note_size(float v, float &biggest, uint32_t &smallest)
+{
+    biggest = fmaxf(biggest, fabsf(v));
+    smallest = min(smallest, (__float_as_uint(v) << 1) - 1u);  // zero becomes the largest value
+}
+__device__ inline bool sums_are_exact(float biggest, uint32_t smallest, double total, int n)
+{
+    const int hi = max(wave_max_i(__float_as_int(biggest)) >> 23, 1), lo = max((int)((~wave_max_u(~smallest) + 1u) >> 24), 1);
+    return hi - lo <= 29 - (32 - __builtin_clz(n - 1)) && fabs(total) < INFINITY;
+}
+
+// Lane of the largest x (lowest lane among equal ones) whose key, of x rounded to fp32, is not NO_KEY: one 32-bit
+// reduction, and an fp64 one only where several x round to the same fp32 value.
+__device__ inline int best_lane(double x, int key)
+{
+    const int mk = wave_max_i(key);
+    unsigned long long m = __ballot(key == mk);
+    if (m & (m - 1)) {
+        const double mx = wave_max_d(key == mk ? x : -INFINITY);
+        m = __ballot(key == mk && x == mx);
+    }
+    return __builtin_ctzll(m);
+}
+
 // T_k(g) of a segment of n tokens whose sums are exact; pre[x], 0 <= x <= n, is the sum of its first x scores.  Returns
 // Score_k(g).  Up to 64 blocks: one per lane, the blocks taken whole are the bits of `blocks`.  More: block lane + 64 i
 // is taken whole when bit i of the lane's `whole` is set.  Tokens plo + j of the cut block (plo < 0: none) are taken
@@ -701,11 +867,6 @@ struct Fill {
     uint32_t whole;
     int plo;
 };
-__device__ inline uint64_t ordered_key_d(double x)
-{
-    const uint64_t u = (uint64_t)__double_as_longlong(x == 0.0 ? 0.0 : x);       // the zeros rank as equal
-    return (u >> 63) ? ~u : u | (1ull << 63);
-}
 constexpr int FEW_PICKS = 16;              // of more than 64 blocks, so many are picked one by one, more by bisection of their sums
 
 __device__ inline double fill_prefix(const double *pre, int n, int g, int inv, int bk, Fill &f)
@@ -834,6 +995,13 @@ struct SearchCtx {
           n_cand(cand.n)
     {
     }
+    // R_k(g) >= tau  <=>  Score_k(g) >= tau * Score_base.  tau is widened here each time: two vector registers less.
+    __device__ inline double need(double base) const
+    {
+        float t = tau;
+        asm volatile("" : "+s"(t));
+        return (double)t * base;
+    }
 };
 
 // appends the tokens c0 + lane of mask m, ascending, at `pos` of the problem's idx_out row
@@ -843,15 +1011,22 @@ __device__ inline void put_tokens(const SearchCtx &x, int &pos, int c0, unsigned
     if (((m >> lane) & 1ull) && jo < x.budget) x.out[jo] = c0 + lane;
     pos += __popcll(m);
 }
-// T_k(1) = T_topB & S_k (b_k is the implicit budget)
+// T_k(1) = T_topB & S_k (b_k is the implicit budget); J loads in flight
+template <int J>
 __device__ inline void put_topb(const SearchCtx &x, const SegRec &r)
 {
     const int lane = threadIdx.x & 63;
     int pos = r.out;
 #pragma nounroll
-    for (int c0 = r.a; c0 < r.b; c0 += 64) {
-        const int t = c0 + lane;
-        put_tokens(x, pos, c0, __ballot(t < r.b && in_topb(x.sp[min(t, r.b - 1)], t, (uint32_t)r.g, r.pos)));
+    for (int c0 = r.a; c0 < r.b; c0 += 64 * J) {
+        float v[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) v[j] = x.sp[min(c0 + 64 * j + lane, r.b - 1)];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const int t = c0 + 64 * j + lane;
+            put_tokens(x, pos, c0 + 64 * j, __ballot(t < r.b && in_topb(v[j], t, (uint32_t)r.g, r.pos)));
+        }
     }
 }
 
@@ -930,7 +1105,7 @@ __device__ inline bool search_exact(const SearchCtx &x, const SegRec &r, float2 
     if (!sums_are_exact(big, small, total, n)) return false;
 
     // R_k(g) >= tau  <=>  Score_k(g) >= tau * Score_base; g_k* is the first accepted, largest first (Eq. gk_star)
-    const double need = (double)x.tau * wave_sum_d(base);
+    const double need = x.need(wave_sum_d(base));
     int gstar = 0, inv = 0;
     Fill f;
 #pragma nounroll
@@ -942,7 +1117,7 @@ __device__ inline bool search_exact(const SearchCtx &x, const SegRec &r, float2 
         if (fill_prefix(pre, n, g, inv, bk, f) >= need) { gstar = g; break; }
     }
     if (lane == 0) x.block_size[r.k] = gstar;
-    if (EMIT && gstar == 1) put_topb(x, r);
+    if (EMIT && gstar == 1) put_topb<1>(x, r);
     if (EMIT && gstar > 1) {
         int pos = r.out;
         const bool few = n <= 64 * gstar;
@@ -959,32 +1134,92 @@ __device__ inline bool search_exact(const SearchCtx &x, const SegRec &r, float2 
     return true;
 }
 
-// Records of segments whose prefix sums exceed the LDS slice of a search wavefront (PRE_TOKENS), searched by the
-// per-problem workgroup that made them: recs[0 .. n) , LDS for PRE_LONG + 1 prefix sums.  Segments up to a quarter of
-// that go to four wavefronts at a time.  A record is kept (compacted to the front) for the search kernel when its
-// segment is longer still or its sums may round; returns how many were.  All threads take part.
+// The search of a segment of any length, from memory (it stays in the L2 cache): what search_exact does, for segments
+// whose prefix sums do not fit LDS, and where sums may round with ordered ones.  kept: LDS for n_kept block sums.  Bound by
+// the latency of one wavefront's loads.  Top-B and search, 8 rows of 32 736 tokens: segments of 800 54 us, of 4 000 168 us
+// (529 and 3 909 with prefix sums of 4 095 tokens in the LDS of the Top-B workgroup, a few segments at a time); of 131 040,
+// mean length 64, sums that may round: 55 us (1 317); one segment of 16 384 among short ones: 270 us (896 ms).
 template <bool EMIT>
-__device__ inline int search_long(const SearchCtx &x, SegRec *recs, int n, double *pre, int *kept)
+__device__ inline void search_streamed(const SearchCtx &x, const SegRec &r, StreamScratch &sc, double *kept, int n_kept)
 {
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x == 0) *kept = 0;
-    __syncthreads();
-    for (int i0 = 0; i0 < n; i0 += 4) {
-        const SegRec r = recs[min(i0 + min(wave, 3), n - 1)];
-        const int len = r.b - r.a;
-        const bool mine = wave < 4 && i0 + wave < n, quarter = len <= PRE_LONG / 4;
-        __syncthreads();                                       // read before any is overwritten
+    const int lane = threadIdx.x & 63, a = r.a, b = r.b, n = b - a, gcap = min(n, r.bk);
+    const float *sp = x.sp;
+    auto val = [&](int t) { return sp[t]; };
+    double base = 0.0, total = 0.0;
+    float big = 0.f;
+    uint32_t small = ~0u;
 #pragma nounroll
-        for (int turn = 0; turn < 5; ++turn) {                 // 0: a quarter each, 1 .. 4: the whole area, one after the other
-            if (mine && (turn == 0 ? quarter : !quarter && wave == turn - 1)) {
-                const bool done = len <= PRE_LONG &&
-                    search_exact<EMIT>(x, r, first_scores(x.sp, r), pre + (turn == 0 ? wave * ((PRE_LONG + 1) / 4) : 0));
-                if (!done && lane == 0) recs[atomicAdd(kept, 1)] = r;
-            }
-            __syncthreads();
+    for (int c0 = a; c0 < b; c0 += 512) {
+        float w[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = sp[min(c0 + 64 * j + lane, b - 1)];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int t = c0 + 64 * j + lane;
+            if (t >= b) w[j] = 0.f;
+            note_size(w[j], big, small);
+            total += (double)w[j];
+            base += t < b && in_topb(w[j], t, (uint32_t)r.g, r.pos) ? (double)w[j] : 0.0;
         }
     }
-    return *kept;
+    const bool exact = sums_are_exact(big, small, wave_sum_d(total), n);
+    if (exact) base = wave_sum_d(base);
+    else {
+        base = 0.0;
+        float nxt = sp[min(a + lane, b - 1)];
+#pragma nounroll
+        for (int c0 = a; c0 < b; c0 += 64) {
+            const int t = c0 + lane;
+            const float v = nxt;
+            nxt = sp[min(t + 64, b - 1)];
+            base = add_in_order(base, __ballot(t < b && in_topb(v, t, (uint32_t)r.g, r.pos)), v);
+        }
+    }
+    const double need = x.need(base);
+    int gstar = 0;
+#pragma nounroll
+    for (int c = x.n_cand - 1; c >= 0; --c) {
+        const int g = __builtin_amdgcn_readlane(x.cand_g, c);
+        if (g > gcap) continue;
+        if (g == 1) { gstar = 1; break; }
+        const int nb = (n + g - 1) / g;
+        const bool keep = nb <= n_kept;
+        if (keep) {
+#pragma nounroll
+            for (int m = lane; m < nb; m += 64) kept[m] = stream_sum(val, a, b, g, m);
+            __builtin_amdgcn_wave_barrier();
+        }
+        auto phi = [&](int m) { return keep ? kept[min(m, nb - 1)] : stream_sum(val, a, b, g, m); };
+        double score = 0.0;
+        const StreamFill f = stream_select(phi, val, a, b, g, r.bk, sc, score);
+        int pos = r.out;
+        bool writing = false;                                  // the accepted candidate: its tokens
+        for (;;) {
+            if (exact && !writing) {
+                double sum = 0.0;
+#pragma nounroll
+                for (int m = lane; m < nb; m += 64) {
+                    const double p = phi(m);
+                    sum += f.whole(ordered_key_d(p), m) ? p : 0.0;
+                }
+                score += wave_sum_d(sum);
+            } else {
+                if (!writing) score = 0.0;
+                stream_walk(phi, val, a, b, g, f, [&](int c0, unsigned long long m, float v) {
+                    if (EMIT && writing) put_tokens(x, pos, c0, m);
+                    else score = add_in_order(score, m, v);
+                });
+            }
+            if (writing || !(score >= need)) break;
+            gstar = g;
+            if (!EMIT) break;
+            writing = true;
+        }
+        __builtin_amdgcn_wave_barrier();                       // `kept` is filled anew by the next candidate
+        if (gstar) break;
+    }
+    if (lane == 0) x.block_size[r.k] = gstar;
+    if (EMIT && gstar == 1) put_topb<8>(x, r);
 }
 
 // What the search that also selects needs of the Top-B kernel (see topb_kernel<true, ..>)
@@ -1044,7 +1279,7 @@ topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, 
 template <bool PLAN, int E>
 __global__ void __launch_bounds__(TB_THREADS, E <= 8 ? 8 : 4)
 topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView sv, int32_t *seg_budget,
-            int32_t *block_size, PlanArgs pa, CandList cand, float tau, int offs_cap, int sample_rank)
+            int32_t *block_size, PlanArgs pa, int offs_cap, int sample_rank)
 {
     constexpr int CAP = E * TB_THREADS;          // tokens the list holds
     extern __shared__ __attribute__((aligned(16))) uint32_t sh_dyn[];   // histogram [TB_BINS] and list [CAP]; later offsets and counters [2][offs_cap]
@@ -1227,7 +1462,7 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
     }
     __syncthreads();                           // the list has been read by everyone
     for (int j = tid; j <= K; j += TB_THREADS) { sh_off[j] = off[j]; sh_cnt[j] = 0; }
-    if (tid == 0) { sh.n_rec = 0; sh.n_long = 0; }
+    if (tid == 0) sh.n_rec = 0;
     __syncthreads();
     int seg[E];
 #pragma unroll
@@ -1266,28 +1501,20 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if (hit[e] >= 0 && sh_cnt[seg[e] + 1] - sh_cnt[seg[e]] == 1) out[sh_cnt[seg[e]]] = hit[e];
-    // the others to the search's list, with their output offset; segments too long for it are searched here, once the
-    // list is otherwise complete (their records are last) and the offsets in LDS are no longer needed
+    // the others to the search's list, with their output offset; the longest ones first, as their search takes longest
     SegRec *recs = pa.list + (int64_t)p * pa.capacity;
     for (int pass = 0; pass < 2; ++pass) {
         for (int sg = tid; sg < K; sg += TB_THREADS) {
             const int bk = sh_cnt[sg + 1] - sh_cnt[sg];
-            if (bk < 2 || (sh_off[sg + 1] - sh_off[sg] > PRE_TOKENS) != (pass == 1)) continue;
+            if (bk < 2 || (sh_off[sg + 1] - sh_off[sg] > PRE_TOKENS) != (pass == 0)) continue;
             SegRec rec;
             rec.p = p; rec.k = sg; rec.a = sh_off[sg]; rec.b = sh_off[sg + 1]; rec.bk = bk; rec.g = (int32_t)thr; rec.pos = cut;
             rec.out = sh_cnt[sg];
-            recs[atomicAdd(pass == 1 ? &sh.n_long : &sh.n_rec, 1)] = rec;
+            recs[atomicAdd(&sh.n_rec, 1)] = rec;
         }
         __syncthreads();
-        if (pass == 0 && tid == 0) sh.n_long = sh.n_rec;
-        __syncthreads();
     }
-    int n_rec = sh.n_rec;
-    const int n_long = sh.n_long - n_rec;
-    if (n_long > 0)
-        n_rec += search_long<true>(SearchCtx(s_tilde, T, p, block_size, sv.max_segments, pa.idx_out, budget, tau, cand), recs + n_rec,
-                                   n_long, reinterpret_cast<double *>(sh_dyn), &sh.n);
-    if (tid == 0) pa.counts[p] = n_rec;
+    if (tid == 0) pa.counts[p] = sh.n_rec;
 }
 
 // ------------------------------------------------------------------ search
@@ -1296,45 +1523,41 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
 constexpr int LIST_THREADS = 1024;         // threads of the per-problem list-building kernels: segments handled per step
 
 __global__ void __launch_bounds__(LIST_THREADS)
-heavy_list_kernel(Dims d, const float *s_tilde, SegView sv, CandList cand, float tau, const int32_t *thr, const int32_t *seg_budget,
-                  int32_t *block_size, SegRec *list, int32_t *counts, int capacity)
+heavy_list_kernel(Dims d, SegView sv, const int32_t *thr, const int32_t *seg_budget, int32_t *block_size, SegRec *list,
+                  int32_t *counts, int capacity)
 {
-    __shared__ double pre[PRE_LONG + 1];
-    __shared__ int n_rec, n_long;
+    __shared__ int n_rec;
     const int p = blockIdx.x, tid = threadIdx.x;
     const int seq = seq_of_problem(d, p);
     const int32_t *off = sv.seg_off + sv.seq_ptr[seq];
     const int K = sv.seq_ptr[seq + 1] - sv.seq_ptr[seq] - 1;
     const int64_t row = (int64_t)p * sv.max_segments;
     SegRec *recs = list + (int64_t)p * capacity;
-    if (tid == 0) n_long = 0;
+    if (tid == 0) n_rec = 0;
     __syncthreads();
-    for (int pass = 0; pass < 2; ++pass) {                     // 0: long segments, 1: the others
+    for (int pass = 0; pass < 2; ++pass) {                     // the longest ones first, as their search takes longest
         for (int k = tid; k < K; k += LIST_THREADS) {
             const int bk = seg_budget[row + k];
-            const bool is_long = off[k + 1] - off[k] > PRE_TOKENS;
             if (pass == 0 && bk == 1) block_size[row + k] = 1;
-            if (bk < 2 || is_long != (pass == 0)) continue;
+            if (bk < 2 || (off[k + 1] - off[k] > PRE_TOKENS) != (pass == 0)) continue;
             SegRec r;
             r.p = p; r.k = k; r.a = off[k]; r.b = off[k + 1]; r.bk = bk; r.g = thr[2 * p]; r.pos = thr[2 * p + 1]; r.out = 0;
-            recs[atomicAdd(pass == 0 ? &n_long : &n_rec, 1)] = r;
+            recs[atomicAdd(&n_rec, 1)] = r;
         }
-        __syncthreads();
-        if (pass == 0 && n_long > 0)
-            search_long<false>(SearchCtx(s_tilde, d.T, p, block_size, sv.max_segments, nullptr, 0, tau, cand), recs, n_long, pre, &n_rec);
-        else if (pass == 0 && tid == 0) n_rec = 0;
         __syncthreads();
     }
     if (tid == 0) counts[p] = n_rec;
 }
 
 // One wavefront per workgroup; the wavefronts of a problem (grid.x) stride over its records.  EMIT: see search_exact; no
-// select pass over the segment is then needed.
+// select pass over the segment is then needed.  24 wavefronts per CU (80 registers) are all that fit without spills, and
+// as fast as 28 with them (256 rows of 131 040 tokens, Top-B and search: 115.7 and 122.2 us).
 constexpr int SLICE_BYTES = 8 * (PRE_TOKENS + 1);
-static_assert(17 * CAPB <= SLICE_BYTES, "ordered sums: CAPT scores (fp32), block sums (fp64) and block classes");
+static_assert(17 * CAPB + CAPT / 8 <= SLICE_BYTES, "ordered sums: CAPT scores (fp32), block sums (fp64), block classes, taken tokens");
+constexpr int STREAM_KEPT = (SLICE_BYTES - (int)sizeof(StreamScratch)) / 8;      // block sums of a segment searched from memory
 
 template <bool EMIT>
-__global__ void __launch_bounds__(64, 7)
+__global__ void __launch_bounds__(64, 6)
 search_kernel(Dims d, const float *s_tilde, int32_t max_segments, CandList cand, float tau, const SegRec *list,
               const int32_t *counts, int capacity, int32_t *block_size, int budget, int32_t *idx_out)
 {
@@ -1360,42 +1583,48 @@ search_kernel(Dims d, const float *s_tilde, int32_t max_segments, CandList cand,
         const int a = r.a, b = r.b, n = b - a;
         if (n <= PRE_TOKENS && search_exact<EMIT>(x, r, v0, reinterpret_cast<double *>(slice))) continue;
 
-        // ---- ordered sums; scores in LDS when they fit
+        if (n > CAPT) {
+            search_streamed<EMIT>(x, r, *reinterpret_cast<StreamScratch *>(slice), reinterpret_cast<double *>(slice + sizeof(StreamScratch)),
+                                  STREAM_KEPT);
+            __builtin_amdgcn_wave_barrier();                   // the slice is reused by the next segment
+            continue;
+        }
+
+        // ---- ordered sums, from LDS
         float *lv = reinterpret_cast<float *>(slice);
-        const bool staged = n <= CAPT;
-        WaveScratch ws{reinterpret_cast<double *>(slice + (staged ? 8 * CAPB : 0)), reinterpret_cast<uint8_t *>(slice + 16 * CAPB), CAPB};
+        WaveScratch ws{reinterpret_cast<double *>(slice + 8 * CAPB), reinterpret_cast<uint8_t *>(slice + 16 * CAPB), CAPB};
+        unsigned long long *taken = reinterpret_cast<unsigned long long *>(slice + 17 * CAPB);      // of the candidate just tried
         const int gcap = min(n, r.bk);
         double sum = 0.0;
 #pragma nounroll
         for (int c0 = a; c0 < b; c0 += 64) {
             const int t = c0 + lane;
             const float v = t < b ? sp[t] : 0.f;
-            if (staged && t < b) lv[t - a] = v;
+            if (t < b) lv[t - a] = v;
             sum = add_in_order(sum, __ballot(t < b && in_topb(v, t, (uint32_t)r.g, r.pos)), v);
         }
         __builtin_amdgcn_wave_barrier();
-        const double need = (double)tau * sum;
-        int gstar = 0, pos = r.out;
-        bool writing = false;                                  // the accepted candidate once more, for its tokens
+        const double need = x.need(sum);
+        int gstar = 0;
 #pragma nounroll
-        for (int c = cand.n - 1; c >= 0;) {
+        for (int c = cand.n - 1; c >= 0; --c) {
             const int g = __builtin_amdgcn_readlane(x.cand_g, c);
-            if (g > gcap) { --c; continue; }
+            if (g > gcap) continue;
             if (g == 1) { gstar = 1; break; }
             double score = 0.0;
-            segment_fill([&](int t) { return staged ? lv[t - a] : sp[t]; }, a, b, g, r.bk, ws, [&](int c0, unsigned long long m, float v) {
-                if (EMIT && writing) put_tokens(x, pos, c0, m);
-                else score = add_in_order(score, m, v);
+            segment_fill([&](int t) { return lv[t - a]; }, a, b, g, r.bk, ws, [&](int c0, unsigned long long m, float v) {
+                score = add_in_order(score, m, v);
+                if (EMIT && lane == 0) taken[(c0 - a) >> 6] = m;
             });
-            if (writing) break;
-            if (score >= need) {
-                gstar = g;
-                if (!EMIT) break;
-                writing = true;
-            } else --c;
+            if (score >= need) { gstar = g; break; }
         }
         if (lane == 0) x.block_size[r.k] = gstar;
-        if (EMIT && gstar == 1) put_topb(x, r);
+        if (EMIT && gstar == 1) put_topb<1>(x, r);
+        if (EMIT && gstar > 1) {
+            int pos = r.out;
+#pragma nounroll
+            for (int c0 = a; c0 < b; c0 += 64) put_tokens(x, pos, c0, taken[(c0 - a) >> 6]);
+        }
         __builtin_amdgcn_wave_barrier();                       // the slice is reused by the next segment
     }
 }
@@ -1566,7 +1795,7 @@ __global__ void __launch_bounds__(64)
 select_kernel(Dims d, const float *s_tilde, const int32_t *thr, const SegRec *list, const int32_t *counter,
               int capacity, int budget, int32_t *idx_out)
 {
-    __shared__ double sh_phi[CB];
+    __shared__ __attribute__((aligned(16))) double sh_phi[CB];
     __shared__ float sh_val[CT];
     __shared__ uint8_t sh_cls[CB];
     int j = blockIdx.x;                                     // < capacity: the grid is no larger than the list can get
@@ -1604,10 +1833,9 @@ static int topb_offs_cap(int32_t max_segments)
 
 template <bool PLAN, int E>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
-                           int32_t *block_size, const PlanArgs &pa, const CandList &cand, float tau, hipStream_t st)
+                           int32_t *block_size, const PlanArgs &pa, hipStream_t st)
 {
     const int offs_cap = PLAN || seg_budget ? topb_offs_cap(sv.max_segments) : 0;
-    static_assert((TB_BINS + E * TB_THREADS) * 4 >= 8 * (PRE_LONG + 1), "prefix sums of long segments");
     const size_t lds = std::max((size_t)(TB_BINS + E * TB_THREADS) * 4, (size_t)offs_cap * 8);
     constexpr size_t lds_most = std::max((size_t)(TB_BINS + E * TB_THREADS) * 4, (size_t)TB_OFFS_MAX * 8);
     if (lds > 64 * 1024) {
@@ -1620,26 +1848,26 @@ static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, 
         }
     }
     hipLaunchKernelGGL((topb_kernel<PLAN, E>), dim3(d.P), dim3(TB_THREADS), lds, st, d, s_tilde, budget, thr, sv, seg_budget,
-                       block_size, pa, cand, tau, offs_cap, topb_rank(d, std::min(budget, d.T)));
+                       block_size, pa, offs_cap, topb_rank(d, std::min(budget, d.T)));
     return hipGetLastError();
 }
 
 template <bool PLAN>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
-                           int32_t *block_size, const PlanArgs &pa, const CandList &cand, float tau, hipStream_t st)
+                           int32_t *block_size, const PlanArgs &pa, hipStream_t st)
 {
     switch (topb_list_k(d, budget)) {
-    case 4: return run_topb<PLAN, 4>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
-    case 8: return run_topb<PLAN, 8>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
-    case 16: return run_topb<PLAN, 16>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
-    default: return run_topb<PLAN, 32>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    case 4: return run_topb<PLAN, 4>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    case 8: return run_topb<PLAN, 8>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    case 16: return run_topb<PLAN, 16>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    default: return run_topb<PLAN, 32>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
     }
 }
 
 hipError_t launch_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, hipStream_t st)
 {
     if (d.P <= 0) return hipSuccess;
-    return run_topb<false>(d, s_tilde, budget, thr, SegView{}, nullptr, nullptr, PlanArgs{}, CandList{}, 0.f, st);
+    return run_topb<false>(d, s_tilde, budget, thr, SegView{}, nullptr, nullptr, PlanArgs{}, st);
 }
 
 // upper bound of a problem's records: a recorded segment holds at least two of the |T_topB| tokens
@@ -1671,10 +1899,8 @@ template <bool EMIT>
 static void run_search(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand, float tau, const SearchWs &w, int cap,
                        int32_t *block_size, int32_t budget, int32_t *idx_out, hipStream_t st)
 {
-    // wavefronts per problem: one per possible record while the chip has room for them, then SEARCH_ROUNDS times the
-    // wavefronts that are resident at once (32 per CU), striding over the records
-    constexpr int64_t SEARCH_ROUNDS = 4;
-    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)d.cus * 32 * SEARCH_ROUNDS / d.P));
+    // wavefronts per problem: one per possible record up to 128 per CU (24 are resident at once), striding over the records
+    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)d.cus * 128 / d.P));
     hipLaunchKernelGGL(search_kernel<EMIT>, dim3(gx, d.P), dim3(64), 0, st, d, s_tilde, sv.max_segments, cand, tau, w.list,
                        w.counts, cap, block_size, budget, idx_out);
 }
@@ -1687,11 +1913,11 @@ hipError_t launch_search(const Dims &d, const float *s_tilde, const SegView &sv,
     const int cap = max_heavy_segments(d, sv.max_segments, budget);
     const SearchWs w(d, ws);
     int32_t *thr = topb_out ? topb_out : w.thr;
-    hipError_t e = run_topb<false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, PlanArgs{}, CandList{}, 0.f, st);
+    hipError_t e = run_topb<false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, PlanArgs{}, st);
     if (e != hipSuccess) return e;
     if (budget > 0 && d.T > 0) {
-        hipLaunchKernelGGL(heavy_list_kernel, dim3(d.P), dim3(LIST_THREADS), 0, st, d, s_tilde, sv, cand, tau, thr, seg_budget,
-                           block_size, w.list, w.counts, cap);
+        hipLaunchKernelGGL(heavy_list_kernel, dim3(d.P), dim3(LIST_THREADS), 0, st, d, sv, thr, seg_budget, block_size, w.list,
+                           w.counts, cap);
         if (cap > 0) run_search<false>(d, s_tilde, sv, cand, tau, w, cap, block_size, 0, nullptr, st);
     }
     return hipGetLastError();
@@ -1808,7 +2034,7 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
         pa.n_slices = n_slices;
         pa.pre_cap = pre_cap;
     }
-    hipError_t e = run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cand, tau, st);
+    hipError_t e = run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
     if (e != hipSuccess) return e;
     if (cap > 0) run_search<true>(d, s_tilde, sv, cand, tau, w, cap, block_size, budget, idx_out, st);
     return hipGetLastError();

@@ -51,3 +51,84 @@ def test_search_segment_lengths_and_score_ranges(oracle, torch_cuda, n, spread):
     off = _offsets(rng, T, np.full(n_seg + 6, n))
     for budget, tau in ((T // 25 + 1, 0.85), (T // 3, 0.97), (T // 2, 0.3)):
         _assert_search_select(oracle, torch_cuda, st, off, CAND, budget, tau)
+
+
+def _scores(rng, kind, T):
+    if kind == "smooth":                                       # sums that cannot round in segments of any length here
+        return 1.0 + rng.random((2, T))
+    if kind == "wide":                                         # sums that do
+        return np.exp(5.0 * rng.standard_normal((2, T))) * 1e-6
+    if kind == "levels":                                       # equal block sums by the hundred
+        return np.round(rng.random((2, T)) ** 2 * 4) / 4
+    return np.full((2, T), 0.25)                               # all of them
+
+
+@pytest.mark.parametrize("n", [513, 640, 831, 833, 2047, 4097, 8193, 20000])
+@pytest.mark.parametrize("kind", ["smooth", "wide", "levels", "equal"])
+def test_search_and_selection_of_long_segments(oracle, torch_cuda, n, kind):  # noqa: F811
+    # segments that are searched and selected from memory: block sums that are kept in LDS or formed in every pass, few
+    # and many candidates for the last block, equal sums at the threshold; short last blocks; budgets that take a few
+    # blocks, half of them, nearly all
+    rng = np.random.default_rng(n)
+    T = 2 * n + 77
+    st = _scores(rng, kind, T)
+    off = np.array([0, n, n + 70, 2 * n + 70, T], np.int32)
+    for cand, budget, tau in (([1, 2, 3, 5, 8, 16, 31, 64], T // 50 + 2, 0.85), ([1, 2], T // 2, 0.9999), ([1, 3, 64], T - 3, 1.0),
+                              ([1, 7, 33], 130, 0.2), ([1, 2, 64], T // 3, 1.5)):
+        _assert_search_select(oracle, torch_cuda, st, off, cand, budget, tau)
+
+
+@pytest.mark.parametrize("n", [64, 300, 512, 513, 4096, 4097, 9001])
+@pytest.mark.parametrize("g", [1, 2, 3, 64])
+def test_selection_with_a_caller_s_own_budgets(oracle, torch_cuda, n, g):  # noqa: F811
+    # b_k and g_k* that no search gave: tokens ranked (g = 1) and blocks filled at lengths each side of every layout
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+    from test_gpu_parity import _stage_inputs
+
+    rng = np.random.default_rng(n + g)
+    off = np.array([0, n, n + 5, 2 * n + 5], np.int32)
+    T = int(off[-1])
+    st = np.round(rng.random((2, T)) * 500) / 512
+    bk = np.array([max(n // 3, g), 2, max(n - 1, g)], np.int32)               # a block size is at most b_k
+    gs = np.array([g, 1, g], np.int32)
+    budget = int(bk.sum())
+    q, k = _stage_inputs(torch, st)
+    shape, seg = B.make_shape(q, k), B.make_segments(off, [0, len(off)], "cuda")
+    buf = B.Buffers(shape, seg, budget, "cuda")
+    d = {x: torch.as_tensor(np.tile(y, (2, 1))).cuda() for x, y in (("b", bk), ("g", gs))}
+    B.sablock_select(shape, torch.as_tensor(st.astype(np.float32)).cuda(), seg, d["b"], d["g"], budget, buf.idx, buf.n_sel, buf.ws)
+    torch.cuda.synchronize()
+    for p in range(2):
+        idx, n_sel = oracle.select(st[p].astype(np.float32), off, bk, gs, budget)
+        assert int(buf.n_sel[p]) == n_sel == budget
+        np.testing.assert_array_equal(buf.idx[p].cpu().numpy(), idx)
+
+
+@pytest.mark.parametrize("kind", ["smooth", "wide"])
+def test_a_long_segment_does_not_hold_up_the_call(torch_cuda, kind):  # noqa: F811
+    # one segment of 16 384 tokens among short ones: 6 and 9 times the call without it where the blocks taken are found by
+    # their sums, 20 000 times where every block is ranked against every other with sums formed again for each pair
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    T, P, W, budget = 131040, 8, 32, 992
+    rng = np.random.default_rng(5)
+    q = torch.zeros((1, P, 1, W, 8), dtype=torch.float32, device="cuda")
+    shape = B.make_shape(q, torch.zeros((1, P, 1, T + W, 8), dtype=torch.float32, device="cuda"))
+    st = torch.as_tensor(np.tile(_scores(rng, kind, T), (P // 2, 1)).astype(np.float32)).cuda()
+    us = []
+    for first in (48, 16384):
+        off = np.unique(np.concatenate([[0], np.arange(first, T, 48), [T]]))
+        seg = B.make_segments(off, [0, len(off)], "cuda")
+        buf = B.Buffers(shape, seg, budget, "cuda")
+        times = []
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            B.sablock_search_select(shape, st, seg, [1, 8, 16, 32, 64], budget, 0.85, buf.seg_budget, buf.block_size, buf.idx, buf.n_sel, buf.ws)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b) * 1e3)
+        us.append(min(times))
+    assert us[1] < 100 * us[0], us
