@@ -1276,8 +1276,13 @@ topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, 
 // fewer than `offs_cap` segments): the same workgroup goes on to the exclusive prefix of b_k (each segment's offset in
 // the problem's idx_out row), writes n_sel, the token of every segment with b_k == 1 (g_k* = 1) straight to its place,
 // and records the segments with b_k >= 2 for the search, with their output offset.
-template <bool PLAN, int E>
-__global__ void __launch_bounds__(TB_THREADS, E <= 8 ? 8 : 4)
+//
+// TWO: two workgroups share a CU, which calls with more rows than CUs gain from although 64 registers spill three (Top-B
+// and search, 1 024 rows of 65 472: 505 us, 529 with one per CU; 512 rows of 8 160: 112 and 116).  With fewer rows a
+// workgroup has its CU to itself and up to 128 registers (8 rows of 8 160: 34.0 us, 35.6 with 64; 256 rows of 131 040:
+// 110 and 112).
+template <bool PLAN, int E, bool TWO>
+__global__ void __launch_bounds__(TB_THREADS, TWO ? 8 : 4)
 topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView sv, int32_t *seg_budget,
             int32_t *block_size, PlanArgs pa, int offs_cap, int sample_rank)
 {
@@ -1831,7 +1836,7 @@ static int topb_offs_cap(int32_t max_segments)
     return max_segments + 1 <= TB_OFFS ? TB_OFFS : max_segments + 1 <= 2 * TB_OFFS ? 2 * TB_OFFS : TB_OFFS_MAX;
 }
 
-template <bool PLAN, int E>
+template <bool PLAN, int E, bool TWO>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
                            int32_t *block_size, const PlanArgs &pa, hipStream_t st)
 {
@@ -1841,13 +1846,13 @@ static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, 
     if (lds > 64 * 1024) {
         static thread_local PerDeviceOnce attr_once;
         if (attr_once.needed()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(topb_kernel<PLAN, E>),
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(topb_kernel<PLAN, E, TWO>),
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_most);
             if (e != hipSuccess) return e;
             attr_once.done();
         }
     }
-    hipLaunchKernelGGL((topb_kernel<PLAN, E>), dim3(d.P), dim3(TB_THREADS), lds, st, d, s_tilde, budget, thr, sv, seg_budget,
+    hipLaunchKernelGGL((topb_kernel<PLAN, E, TWO>), dim3(d.P), dim3(TB_THREADS), lds, st, d, s_tilde, budget, thr, sv, seg_budget,
                        block_size, pa, offs_cap, topb_rank(d, std::min(budget, d.T)));
     return hipGetLastError();
 }
@@ -1856,11 +1861,12 @@ template <bool PLAN>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
                            int32_t *block_size, const PlanArgs &pa, hipStream_t st)
 {
+    const bool two = d.P > d.cus;
     switch (topb_list_k(d, budget)) {
-    case 4: return run_topb<PLAN, 4>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
-    case 8: return run_topb<PLAN, 8>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
-    case 16: return run_topb<PLAN, 16>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
-    default: return run_topb<PLAN, 32>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    case 4: return (two ? run_topb<PLAN, 4, true> : run_topb<PLAN, 4, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    case 8: return (two ? run_topb<PLAN, 8, true> : run_topb<PLAN, 8, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    case 16: return run_topb<PLAN, 16, false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    default: return run_topb<PLAN, 32, false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
     }
 }
 

@@ -132,3 +132,13 @@ def test_a_long_segment_does_not_hold_up_the_call(torch_cuda, kind):  # noqa: F8
             times.append(a.elapsed_time(b) * 1e3)
         us.append(min(times))
     assert us[1] < 100 * us[0], us
+
+
+@pytest.mark.parametrize("T", [1023, 16385, 40001])
+@pytest.mark.parametrize("budget", [100, 3000, 6000])
+def test_topb_with_more_rows_than_compute_units(oracle, torch_cuda, T, budget):  # noqa: F811
+    # two workgroups per compute unit: the kernels with fewer registers, for lists of 4 096 and 8 192 tokens
+    rng = np.random.default_rng(T)
+    st = rng.random((3, T)) ** 4
+    off = _offsets(rng, T, rng.integers(1, 80, size=T))
+    _assert_search_select(oracle, torch_cuda, st, off, CAND, min(budget, T - 1), 0.85, compute_units=2)

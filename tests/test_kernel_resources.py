@@ -23,5 +23,14 @@ def search_select_kernels(tmp_path_factory):
 def test_dynamic_lds_of_the_topb_kernels_begins_on_16_bytes(search_select_kernels):
     # it lies behind the static part and is read and written 16 bytes at a time
     topb = {n: k for n, k in search_select_kernels.items() if "topb_" in n}
-    assert len(topb) == 9
+    assert len(topb) == 13
     assert all(k["group_segment_fixed_size"] % 16 == 0 for k in topb.values()), topb
+
+
+def test_topb_and_search_kernels_do_not_spill(search_select_kernels):
+    # 64 registers are few for the Top-B kernels of which two share a CU: those may spill a few, the others none
+    scratch = {n: k["private_segment_fixed_size"] for n, k in search_select_kernels.items()}
+    two = {n for n in scratch if re.search(r"topb_kernelILb[01]ELi\d+ELb1E", n)}
+    assert len(two) == 4
+    assert all(scratch[n] <= 16 for n in two), scratch
+    assert not any(scratch[n] for n in set(scratch) - two), scratch
