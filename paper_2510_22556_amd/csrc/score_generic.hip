@@ -309,9 +309,13 @@ int row_tiles(const Dims &d)
     return wp == 64 ? 2 * d.G : (d.G * wp + 31) / 32;
 }
 
-// Workgroups that the registers let a compute unit hold: one round of them, so that none starts late
-int stats_per_cu(const Dims &d) { return d.D <= 64 ? 4 : d.D <= 128 ? 3 : 2; }
-int columns_per_cu(const Dims &d) { return d.D <= 64 ? 3 : 2; }
+// Workgroups that the registers let a compute unit hold (512 per lane and SIMD, one wavefront of each workgroup on each):
+// statistics 104 and, widened from bf16, 124 up to 64 elements, 168 and 172 up to 128, 176 above; columns up to 168, 216
+// and 216, with padded windows of 64 228, 276 and 280.  One round of them, so that none starts late: against three where
+// two fit and two where one does, columns of 8 problems of 8 200 fp32 keys, 256 rows of 128 140 -> 108 us, statistics of
+// 8 of 32 768 bf16 keys, 48 rows of 128 99 -> 67 us.
+int stats_per_cu(const Dims &d) { return d.D <= 64 ? 4 : d.D <= 128 && d.dtype == SABLOCK_F32 ? 3 : 2; }
+int columns_per_cu(const Dims &d) { return (d.D <= 64 ? 3 : 2) - (padded_window(d) == 64 ? 1 : 0); }
 
 // Pass 1: a workgroup per row tile and chunk of keys, at most 64 chunks.
 void plan_chunks(const Dims &d, int *chunk_len, int *n_chunks)
@@ -354,7 +358,10 @@ hipError_t launch(GenArgs &a, hipStream_t st)
         }
     }
     const int n_kt = (d.L + KEYS - 1) / KEYS;
-    const int64_t wgs = std::max<int64_t>(1, std::min<int64_t>((n_kt + NW - 1) / NW, (int64_t)columns_per_cu(d) * d.cus / d.P));
+    const int64_t all = (n_kt + NW - 1) / NW, room = std::max<int64_t>(1, (int64_t)columns_per_cu(d) * d.cus / d.P);
+    // queries that do not fit LDS are staged again for a second turn: a few late workgroups cost less than that (8 problems
+    // of 8 200 keys, 256 rows of 64: 65 workgroups each 52 us, 64 of them 62)
+    const int64_t wgs = all <= room + (a.stage_tiles < a.n_tiles ? room / 16 : 0) ? all : room;
     hipLaunchKernelGGL((score_generic_columns<T, KS, WP>), dim3((unsigned)wgs, d.P), dim3(NT), lds2, st, a);
     return hipGetLastError();
 }

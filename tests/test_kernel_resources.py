@@ -9,15 +9,19 @@ import pytest
 from paper_2510_22556_amd import build
 
 
-@pytest.fixture(scope="module")
-def search_select_kernels(tmp_path_factory):
-    asm = str(tmp_path_factory.mktemp("asm") / "search_select.s")
-    subprocess.run([build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, "search_select.hip"), "-o", asm],
-                   check=True, stderr=subprocess.DEVNULL)
+def _kernels(source, folder):
+    asm = str(folder / "kernels.s")
+    subprocess.run([build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, source), "-o", asm], check=True,
+                   stderr=subprocess.DEVNULL)
     with open(asm) as f:
         text = f.read()
     blocks = re.findall(r"\.amdhsa_kernel (\S+)\n(.*?)\.end_amdhsa_kernel", text, re.S)
     return {name: {k: int(v) for k, v in re.findall(r"\.amdhsa_(\w+) (\d+)\n", body)} for name, body in blocks}
+
+
+@pytest.fixture(scope="module")
+def search_select_kernels(tmp_path_factory):
+    return _kernels("search_select.hip", tmp_path_factory.mktemp("asm"))
 
 
 def test_dynamic_lds_of_the_topb_kernels_begins_on_16_bytes(search_select_kernels):
@@ -34,3 +38,22 @@ def test_topb_and_search_kernels_do_not_spill(search_select_kernels):
     assert len(two) == 4
     assert all(scratch[n] <= 16 for n in two), scratch
     assert not any(scratch[n] for n in set(scratch) - two), scratch
+
+
+def test_any_shape_scoring_plans_as_many_workgroups_as_the_registers_let_reside(tmp_path):
+    # the plan's counts per compute unit (the same rule as in the source): 512 registers per lane and SIMD, given out by the
+    # eight, and a wavefront of each workgroup on every SIMD
+    seen = 0
+    for name, k in _kernels("score_generic.hip", tmp_path).items():
+        m = re.search(r"score_generic_(stats|columns)I([ft])Li(\d+)ELi(\d+)E", name)
+        if not m:
+            continue
+        dim, window, f32 = 8 * int(m[3]), int(m[4]), m[2] == "f"
+        if m[1] == "stats":
+            planned = 4 if dim <= 64 else 3 if dim <= 128 and f32 else 2
+        else:
+            planned = (3 if dim <= 64 else 2) - (window == 64)
+        assert 512 // -(-k["next_free_vgpr"] // 8 * 8) >= planned, (name, k)
+        assert k["private_segment_fixed_size"] == 0, name
+        seen += 1
+    assert seen == 48
