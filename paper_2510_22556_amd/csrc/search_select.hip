@@ -425,7 +425,8 @@ __device__ inline float sample_bound(const RowView &r, int rank, uint32_t *hist,
     return down >= top ? -INFINITY : float_of_key(top - (uint32_t)down);
 }
 
-// tokens [a, b) of the row's vectors (multiples of the round only at a) whose score reaches `bound`, to the list
+// tokens [a, b) of the row's vectors (multiples of the round only at a) whose score reaches `bound`, to the list; one that
+// is not a number too, as its key may be above the bound's
 __device__ inline void collect_above(const RowView &r, int i_begin, int i_end, float bound, int32_t *list, int cap, TopbShared &sh)
 {
     const int tid = threadIdx.x;
@@ -446,7 +447,7 @@ __device__ inline void collect_above(const RowView &r, int i_begin, int i_end, f
             t0[j] = i < i_end ? r.token(i) : -4;
         }
         if (i0 + J * TB_THREADS < i_end) fetch(i0 + J * TB_THREADS);
-        append_tokens<J>(v, t0, [&](int t, float x) { return t >= 0 && x >= bound; }, list, cap, sh);
+        append_tokens<J>(v, t0, [&](int t, float x) { return t >= 0 && !(x < bound); }, list, cap, sh);
     }
 }
 
@@ -1252,7 +1253,7 @@ topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, 
     const int per = (r.nvec + (int)gridDim.x - 1) / (int)gridDim.x;
     const int i0 = min(sl * per, r.nvec), i1 = min(i0 + per, r.nvec);
     if (i0 < i1) collect_above(r, i0, i1, bound, list, pre_cap, sh);
-    if (sl == 0) append_extra(r, r.extra >= 0 && r.sp[max(r.extra, 0)] >= bound, list, pre_cap, sh);
+    if (sl == 0) append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, pre_cap, sh);
     __syncthreads();
     const int64_t o = (int64_t)p * gridDim.x + sl;
     for (int i = tid; i < min(sh.n, pre_cap); i += TB_THREADS) pre_list[o * pre_cap + i] = list[i];
@@ -1363,7 +1364,7 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
                 const float bound = sample_bound(r, sample_rank, hist, sh);
                 __syncthreads();                 // the list's length is zero
                 collect_above(r, 0, r.nvec, bound, list, CAP, sh);
-                append_extra(r, r.extra >= 0 && r.sp[max(r.extra, 0)] >= bound, list, CAP, sh);
+                append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, CAP, sh);
             }
             __syncthreads();
             const int n = sh.n;

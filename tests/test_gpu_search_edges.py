@@ -142,3 +142,26 @@ def test_topb_with_more_rows_than_compute_units(oracle, torch_cuda, T, budget): 
     st = rng.random((3, T)) ** 4
     off = _offsets(rng, T, rng.integers(1, 80, size=T))
     _assert_search_select(oracle, torch_cuda, st, off, CAND, min(budget, T - 1), 0.85, compute_units=2)
+
+
+@pytest.mark.parametrize("T", [5000, 20000, 40001])
+@pytest.mark.parametrize("sign", [1, -1])
+def test_scores_that_are_not_numbers_rank_alike_in_rows_of_every_length(torch_cuda, T, sign):  # noqa: F811
+    # by their bits, in front of every number or behind: the Top-B tokens, the budgets and the tokens written agree,
+    # however the k-th best is found
+    rng = np.random.default_rng(T)
+    st = rng.random((2, T)).astype(np.float32)
+    bits = st.view(np.uint32)
+    bits[:, rng.permutation(T)[:40]] = 0x7FC00000 if sign > 0 else 0xFFC00000
+    bits[:, T - 1] = bits[:, 0] = 0x7FC00001                   # the scalars around the row's vectors
+    key = np.where(bits >> 31, ~bits, bits | 0x80000000).astype(np.int64)
+    off = _offsets(rng, T, rng.integers(1, 80, size=T))
+    for budget in (3, 100, 900):
+        from test_gpu_parity import _search_select_gpu
+
+        b, g, idx, n = _search_select_gpu(torch_cuda, st, off, [1], budget, 0.85)
+        for p in range(2):
+            best = np.sort(np.lexsort((np.arange(T), -key[p]))[:budget])
+            assert n[p] == budget
+            np.testing.assert_array_equal(idx[p][:budget], best)
+            np.testing.assert_array_equal(b[p][:len(off) - 1], np.diff(np.searchsorted(best, off)))
