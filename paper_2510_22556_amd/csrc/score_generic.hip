@@ -164,7 +164,7 @@ score_generic_stats(GenArgs a)
         }
         if (m > -INFINITY) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) z += __builtin_amdgcn_exp2f(fmaf(acc[i], a.c1, -m));
+            for (int i = 0; i < 16; ++i) z += fmaxf(__builtin_amdgcn_exp2f(fmaf(acc[i], a.c1, -m)), 0.f);    // not a number: no part of the sum
         }
         if constexpr (PREFETCH) {
 #pragma unroll
@@ -290,7 +290,7 @@ score_generic_columns(GenArgs a)
                 e = fmaf(ah, __builtin_amdgcn_logf(ah + a.eps), e);
             }
             e += other_half(e);
-            if (t < d.L) out[t] = hf == 0 ? s : -LN2 * e;                                                               // inner sum of Eq. Dk
+            if (t < d.L) out[t] = hf == 0 ? s : s > 0.f ? -LN2 * e : 0.f;                                                             // inner sum of Eq. Dk
         }
         if constexpr (PREFETCH) {
 #pragma unroll

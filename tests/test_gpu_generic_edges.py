@@ -45,3 +45,38 @@ def test_generic_scores_at_the_edges(oracle, torch_cuda, G, W, D, L, dtype):  # 
             # a D-term fp32 dot of unit normals is off by about sqrt(D) 2^-24 absolute, a probability by that relative
             np.testing.assert_allclose(H.to_np(a[p]), sr, rtol=1e-5, atol=1e-9)
             np.testing.assert_allclose(H.to_np(b[p]), er, rtol=1e-5, atol=2e-6)
+
+
+@pytest.mark.parametrize("G,W,D,L,dtype", [(4, 16, 64, 3001, "f32"), (2, 64, 256, 700, "f32"), (4, 12, 80, 3001, "bf16"), (1, 1, 8, 70, "f32")])
+@pytest.mark.parametrize("step", [17, 1000])
+def test_generic_keys_that_are_not_numbers_are_no_part_of_the_others_denominators(torch_cuda, G, W, D, L, dtype, step):  # noqa: F811
+    # their own score is not a number and their entropy term zero; every other key has the score it has without them
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    q = synth.normal_torch(D + L, 1, (1, 1, G * 2, W, D), "cuda", dt)
+    k = synth.normal_torch(D + L, 2, (1, 1, 2, L, D), "cuda", dt)
+    bad = torch.zeros((L,), dtype=torch.bool, device="cuda")
+    bad[::step] = True
+    bad[min(L - 1, 64):min(L - 1, 128)] = True                 # whole tiles of them
+    k[0, 0, 0, bad, 3] = float("nan")
+    shape = B.make_shape(q, k)
+    ws = torch.empty((B.sablock_workspace_bytes(shape, 0, 0),), dtype=torch.uint8, device="cuda")
+    s = torch.empty((2, L), dtype=torch.float32, device="cuda")
+    e = torch.empty_like(s)
+    B.sablock_score(shape, q, k, s, e, ws)
+    x = (q[0, 0, :G].reshape(G * W, D).double() @ k[0, 0, 0].double().T) / D ** 0.5
+    t, i = torch.arange(L, device="cuda")[None, :], torch.arange(G * W, device="cuda")[:, None] % W
+    x.masked_fill_((t > L - W + i) | bad[None, :], float("-inf"))
+    ref = torch.softmax(x, dim=1).sum(dim=0) / G
+    ok = ~bad
+    assert torch.isnan(s[0, bad][:-W]).all() and (e[0, bad] == 0).all()
+    np.testing.assert_allclose(s[0, ok].cpu().numpy(), ref[ok].cpu().numpy(), rtol=1e-5, atol=1e-9)
+    assert torch.isfinite(e[0, ok]).all() and torch.isfinite(s[1]).all() and torch.isfinite(e[1]).all()
+    # an infinite logit leaves no score of its rows
+    k[0, 0, 0, bad, 3] = 0.0
+    k[0, 0, 0, 2, 3] = float("inf")
+    B.sablock_score(shape, q, k, s, e, ws)
+    if (q[0, 0, :G, :, 3] > 0).any():
+        assert not torch.isfinite(s[0, :L - W]).any()
