@@ -515,16 +515,16 @@ __device__ inline uint64_t ordered_key_d(double x)
     return (u >> 63) ? ~u : u | (1ull << 63);
 }
 
-// The best `rem` (value descending, index ascending) of the sz <= 64 scores that lanes 0 .. sz - 1 hold; adds their sum
-// to `score`.
+// The best `rem` (value descending, index ascending; what is not a number by its bits) of the sz <= 64 scores that lanes
+// 0 .. sz - 1 hold; adds their sum to `score`.
 constexpr int FEW_TOKENS = 4;              // up to so many are picked one by one, more by their ranks
 __device__ inline unsigned long long best_tokens(float v, int sz, int rem, double &score)
 {
     const int lane = threadIdx.x & 63;
     v += 0.f;                                                  // no -0
+    int key = lane < sz ? max(key_of(v), NO_KEY + 1) : NO_KEY;
     if (rem <= FEW_TOKENS) {
         unsigned long long taken = 0;
-        int key = lane < sz ? key_of(v) : NO_KEY;
 #pragma nounroll
         for (int j = 0; j < rem; ++j) {
             const int l = __builtin_ctzll(__ballot(key == wave_max_i(key)));
@@ -537,8 +537,8 @@ __device__ inline unsigned long long best_tokens(float v, int sz, int rem, doubl
     int rk = 0;
 #pragma nounroll
     for (int j = 0; j < sz; ++j) {
-        const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
-        rk += (o > v || (o == v && j < lane)) ? 1 : 0;
+        const int o = __builtin_amdgcn_readlane(key, j);
+        rk += (o > key || (o == key && j < lane)) ? 1 : 0;
     }
     const bool tk = lane < sz && rk < rem;
     score += wave_sum_d(tk ? (double)v : 0.0);
@@ -744,7 +744,11 @@ __device__ inline void segment_fill(V val, int a, int b, int g, int bk, WaveScra
         return;
     }
 
-    for (int m = lane; m < nb; m += 64) ws.phi[m] = block_sum(val, a, b, g, m);
+    // a sum that is not a number ranks with the infinite ones, so that every place in the order has one block
+    for (int m = lane; m < nb; m += 64) {
+        const double phi = block_sum(val, a, b, g, m);
+        ws.phi[m] = phi == phi ? phi : INFINITY;
+    }
     __builtin_amdgcn_wave_barrier();
     // blocks taken whole: the first rstar in rank order; all blocks have g tokens except a short last one,
     // whose rank q decides how many blocks fit
@@ -795,19 +799,9 @@ __device__ inline void segment_fill(V val, int a, int b, int g, int bk, WaveScra
     int plo = 0;
     if (mp >= 0) {
         plo = a + mp * g;
-        const int phi_hi = min(plo + g, b);
-        const int sz = phi_hi - plo;
-        bool tk = false;
-        if (lane < sz) {
-            const float v = val(plo + lane);
-            int rk = 0;
-            for (int j = 0; j < sz; ++j) {
-                float o = val(plo + j);
-                rk += (o > v || (o == v && j < lane)) ? 1 : 0;
-            }
-            tk = rk < rem;
-        }
-        pmask = __ballot(tk);
+        const int sz = min(g, b - plo);
+        double sum = 0.0;
+        pmask = best_tokens(val(plo + min(lane, sz - 1)), sz, rem, sum);
     }
 
     for (int c0 = a; c0 < b; c0 += 64) {

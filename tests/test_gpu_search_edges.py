@@ -165,3 +165,39 @@ def test_scores_that_are_not_numbers_rank_alike_in_rows_of_every_length(torch_cu
             assert n[p] == budget
             np.testing.assert_array_equal(idx[p][:budget], best)
             np.testing.assert_array_equal(b[p][:len(off) - 1], np.diff(np.searchsorted(best, off)))
+
+
+@pytest.mark.parametrize("n", [64, 300, 513, 4096, 9001])
+@pytest.mark.parametrize("share", [0.02, 0.5, 1.0])
+def test_scores_that_are_not_numbers_take_a_segment_s_share_and_no_more(torch_cuda, n, share):  # noqa: F811
+    # every segment gives its b_k tokens, ascending and its own, whichever blocks and tokens those are: with given block
+    # sizes (few and many blocks taken, blocks cut) and through the search
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+    from test_gpu_parity import _search_select_gpu, _stage_inputs
+
+    rng = np.random.default_rng(n)
+    off = np.array([0, n, n + 5, 2 * n + 5], np.int32)
+    T = int(off[-1])
+    st = rng.random((2, T)).astype(np.float32)
+    st[rng.random((2, T)) < share] = np.nan
+    st[1] = -st[1]
+    tokens = torch.as_tensor(st).cuda()
+    q, k = _stage_inputs(torch, st)
+    shape, seg = B.make_shape(q, k), B.make_segments(off, [0, len(off)], "cuda")
+
+    def check(idx, b):
+        for p in range(2):
+            assert (np.diff(idx[p]) > 0).all() and idx[p][0] >= 0 and idx[p][-1] < T
+            np.testing.assert_array_equal(np.diff(np.searchsorted(idx[p], off)), b[p])
+
+    for g in (1, 2, 7, 64):
+        for bk in ([max(g, 3), 2, max(n // 2, g)], [max(n // 3, g), 3, n - 1 if g < n else n]):
+            budget = sum(bk)
+            buf = B.Buffers(shape, seg, budget, "cuda")
+            d = [torch.as_tensor(np.tile(np.array(x, np.int32), (2, 1))).cuda() for x in (bk, [g, 1, g])]
+            B.sablock_select(shape, tokens, seg, *d, budget, buf.idx, buf.n_sel, buf.ws)
+            check(buf.idx.cpu().numpy(), [bk, bk])
+    for budget in (7, T // 3, T - 2):
+        b, g, idx, _ = _search_select_gpu(torch, st, off, [1, 2, 3, 8, 64], budget, 0.85)
+        check(idx[:, :budget], b[:, :len(off) - 1])
