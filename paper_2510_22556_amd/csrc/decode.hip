@@ -90,6 +90,10 @@ __device__ inline void row_sums(float (&x)[N])
         if constexpr (LPR > 32) x[j] += xor_lane<32>(x[j]);
     }
 }
+// f(integral_constant<int, g>) for every g
+template <int... g, typename F>
+__device__ inline void for_each_head(std::integer_sequence<int, g...>, F &&f) { (f(std::integral_constant<int, g>{}), ...); }
+
 // entry g of values that lie as row_sums leaves them, in every lane
 template <int S, int g, int HP>
 __device__ inline float entry(const float (&x)[HP])
@@ -226,13 +230,11 @@ decode_kernel(DecodeArgs a)
                 ref[j] = m;
                 l[j] *= f[j];
             }
-            [&]<int... g>(std::integer_sequence<int, g...>) {
-                ([&] {
-                    const float fg = entry<S, g>(f);
+            for_each_head(std::make_integer_sequence<int, G>{}, [&](auto g) {
+                const float fg = entry<S, g.value>(f);
 #pragma unroll
-                    for (int e = 0; e < E; ++e) acc[g][e] *= fg;
-                }(), ...);
-            }(std::make_integer_sequence<int, G>{});
+                for (int e = 0; e < E; ++e) acc[g.value][e] *= fg;
+            });
         }
 #pragma unroll
         for (int u = 0; u < UNROLL; ++u) {
@@ -245,13 +247,11 @@ decode_kernel(DecodeArgs a)
             float ve[E];
 #pragma unroll
             for (int e = 0; e < E; ++e) ve[e] = Chunk<BF16>::get(vr[u], e);
-            [&]<int... g>(std::integer_sequence<int, g...>) {
-                ([&] {
-                    const float pg = entry<S, g>(pr);
+            for_each_head(std::make_integer_sequence<int, G>{}, [&](auto g) {
+                const float pg = entry<S, g.value>(pr);
 #pragma unroll
-                    for (int e = 0; e < E; ++e) acc[g][e] = fmaf(pg, ve[e], acc[g][e]);
-                }(), ...);
-            }(std::make_integer_sequence<int, G>{});
+                for (int e = 0; e < E; ++e) acc[g.value][e] = fmaf(pg, ve[e], acc[g.value][e]);
+            });
         }
     }
     // merge the lane groups of the wavefront (they share the references) ...
