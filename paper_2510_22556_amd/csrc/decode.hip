@@ -9,9 +9,9 @@
 //       S = 2, 4 or 8), so that the exponentials of a row are formed once and not once per lane; the probabilities go
 //       back to the row's lanes by DPP.  Probabilities are relative to a reference per head that the whole wavefront
 //       shares: it is set AHEAD (log2 domain) above the largest logit so far and moves only when a logit passes it, so
-//       the weighted sums of V are not rescaled row by row and no probability exceeds one.  The lane groups of a wavefront are merged
-//       by lane exchanges, the wavefronts through LDS.  With one split the workgroup writes the result itself, else
-//       (maximum, denominator, numerator[D]) per (problem, split, head).
+//       the weighted sums of V are not rescaled row by row and no probability exceeds one.  The lane
+//       groups of a wavefront are merged by lane exchanges, the wavefronts through LDS.  With one split the workgroup
+//       writes the result itself, else (reference, denominator, numerator[D]) per (problem, split, head).
 //   decode_merge_kernel  merges the splits and divides.
 //
 // What bounds it: the cache read, as long as the vector work of a row stays below the time of its bytes; a read of 4 KB

@@ -21,9 +21,10 @@
 // does not matter.
 //
 // All quantities that decide an integer (block sums Phi, Score_k(g), Score_base,
-// tau * Score_base) are fp64 and summed in ascending token order, one addition at
-// a time, so that they are identical for identical fp32 inputs regardless of how
-// the work is spread over lanes.  Rankings use (value descending, index ascending).
+// tau * Score_base) are fp64 and have the bits of the sum in ascending token order,
+// one addition at a time: where no partial sum can round (sums_are_exact) they are
+// formed in any order and as differences of prefix sums, elsewhere in that order.
+// Rankings use (value descending, index ascending).
 #include "sablock_internal.h"
 
 #include <algorithm>
@@ -826,7 +827,7 @@ __device__ inline void segment_fill(V val, int a, int b, int g, int bk, WaveScra
 //     exponent range + 24 bits of mantissa + ceil(log2 n) <= 53
 // no partial sum rounds in ANY order: prefix sums by lane shuffles, differences of prefixes and sums over arbitrary
 // subsets then equal the ordered sums bit for bit.  Segments whose scores span more (23 powers of two at 64 tokens, 17
-// at 4 095) take the ordered sums (segment_fill above).
+// at 4 095) take ordered sums.
 // biggest: the largest |score| of a segment; smallest: the smallest nonzero one as its bits doubled, less one; total:
 // the sum (not finite when a score is not); n >= 2
 __device__ inline void note_size(float v, float &biggest, uint32_t &smallest)
