@@ -44,7 +44,7 @@ struct GenArgs {
     int chunk_len, n_chunks;           // keys per workgroup of pass 1, a multiple of NW * KEYS
     float c1;              // log2(e) / sqrt(D)
     float eps;
-    float *partial;        // [P][n_chunks][32 n_tiles][2] (max, sum exp2), log2 domain
+    float *partial;        // [P][n_chunks][M][2] (max, sum exp2), log2 domain; the padding has no entries
     const float *merged;   // the same with pc chunks
     int pc;
     const float *lse;      // optional [P][G * W], natural log
@@ -179,11 +179,13 @@ score_generic_stats(GenArgs a)
     if (threadIdx.x < 32) {
         m = red[2 * n]; z = red[2 * n + 1];
         for (int w = 1; w < NW; ++w) fold(m, z, red[(w * 32 + n) * 2], red[(w * 32 + n) * 2 + 1]);
-        *reinterpret_cast<float2 *>(a.partial + (((int64_t)p * a.n_chunks + chunk) * (32 * a.n_tiles) + 32 * J + n) * 2) = make_float2(m, z);
+        const int h = (32 * J + n) / WP, i = (32 * J + n) % WP;
+        if (h < d.G && i < d.W)
+            *reinterpret_cast<float2 *>(a.partial + (((int64_t)p * a.n_chunks + chunk) * d.M + h * d.W + i) * 2) = make_float2(m, z);
     }
 }
 
-// one thread per (problem, padded row): the chunks' pairs to one
+// one thread per (problem, row): the chunks' pairs to one
 __global__ void __launch_bounds__(NT)
 score_generic_combine(const float *partial, float *merged, int n_chunks, int rows, int n)
 {
@@ -232,7 +234,7 @@ score_generic_columns(GenArgs a)
                 z = 0.f;
 #pragma unroll 8
                 for (int c = 0; c < a.pc; ++c) {
-                    const float2 e = *reinterpret_cast<const float2 *>(a.merged + (((int64_t)p * a.pc + c) * rows + R) * 2);
+                    const float2 e = *reinterpret_cast<const float2 *>(a.merged + (((int64_t)p * a.pc + c) * d.M + h * d.W + i) * 2);
                     fold(m, z, e.x, e.y);
                 }
             }
@@ -350,9 +352,9 @@ hipError_t launch(GenArgs &a, hipStream_t st)
     if (!a.lse) {
         hipLaunchKernelGGL((score_generic_stats<T, KS, WP>), dim3(a.n_chunks, a.n_tiles, d.P), dim3(NT), tile_bytes + NW * 32 * 2 * 4, st, a);
         if (!folds_in_pass2(d, a.n_chunks)) {
-            float *merged = a.partial + (size_t)d.P * a.n_chunks * rows * 2;
-            const int n = d.P * rows;
-            hipLaunchKernelGGL(score_generic_combine, dim3((n + NT - 1) / NT), dim3(NT), 0, st, a.partial, merged, a.n_chunks, rows, n);
+            float *merged = a.partial + (size_t)d.P * a.n_chunks * d.M * 2;
+            const int n = d.P * d.M;
+            hipLaunchKernelGGL(score_generic_combine, dim3((n + NT - 1) / NT), dim3(NT), 0, st, a.partial, merged, a.n_chunks, d.M, n);
             a.merged = merged;
             a.pc = 1;
         }
@@ -390,7 +392,7 @@ size_t score_generic_ws_bytes(const Dims &d)
 {
     int chunk_len, n_chunks;
     plan_chunks(d, &chunk_len, &n_chunks);
-    return align256((size_t)d.P * (n_chunks + 1) * 32 * row_tiles(d) * 2 * 4);
+    return align256((size_t)d.P * (n_chunks + (folds_in_pass2(d, n_chunks) ? 0 : 1)) * d.M * 2 * 4);
 }
 
 hipError_t launch_score_generic(const Dims &d, const void *q, const void *k, const float *row_lse, float eps,

@@ -80,3 +80,29 @@ def test_generic_keys_that_are_not_numbers_are_no_part_of_the_others_denominator
     B.sablock_score(shape, q, k, s, e, ws)
     if (q[0, 0, :G, :, 3] > 0).any():
         assert not torch.isfinite(s[0, :L - W]).any()
+
+
+@pytest.mark.parametrize("n_layers,Hkv,G,W,D,L", [(626, 64, 1, 8, 8, 150), (512, 16, 5, 1, 16, 300), (3, 2, 3, 5, 16, 4000)])
+def test_generic_statistics_take_no_scratch_for_padding(torch_cuda, n_layers, Hkv, G, W, D, L):  # noqa: F811
+    # 8 bytes per row and chunk of keys, whatever a window is padded to: calls of many problems fit the static array
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    q = synth.normal_torch(L, 1, (1, n_layers, G * Hkv, W, D), "cuda", torch.float32)
+    k = synth.normal_torch(L, 2, (1, n_layers, Hkv, L, D), "cuda", torch.float32)
+    shape = B.make_shape(q, k)
+    P = n_layers * Hkv
+    need = B.sablock_workspace_bytes(shape, 0, 0)
+    assert need <= 8 * P * G * W * (min(64, -(-L // 128)) + 1) + 256           # chunks of 128 keys or more, and their fold
+    ws = torch.empty((need,), dtype=torch.uint8, device="cuda")
+    out = [torch.full((P, L), float("nan"), device="cuda") for _ in range(4)]
+    B.sablock_score(shape, q, k, out[0], out[1], ws)
+    B.sablock_score_static(shape, q, k, out[2], out[3])
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[2]) and torch.equal(out[1], out[3])
+    p = P - 1
+    x = (q[0, -1, -G:].reshape(G * W, D).double() @ k[0, -1, -1].double().T) / D ** 0.5
+    t, i = torch.arange(L, device="cuda")[None, :], torch.arange(G * W, device="cuda")[:, None] % W
+    x.masked_fill_(t > L - W + i, float("-inf"))
+    ref = torch.softmax(x, dim=1).sum(dim=0) / G
+    np.testing.assert_allclose(out[0][p].cpu().numpy(), ref.cpu().numpy(), rtol=1e-5, atol=1e-9)
