@@ -15,6 +15,7 @@ struct Dims {
     int32_t P;                                            // problems = n_seq * n_layers * Hkv
     int32_t dtype;
     int32_t cus;                                          // compute units the launch plans assume (never 0)
+    uint32_t inv_heads, inv_seq;                          // ceil(2^32 / Hkv), ceil(2^32 / (n_layers * Hkv)); 0 for a divisor of 1
     sablock_tuning tune;                                  // the caller's launch parameters, validated (0 = plan)
     int64_t qs[4], ks[4], vs[4];
 };
@@ -46,9 +47,17 @@ struct CandList {
     int32_t g[MAX_CAND], inv[MAX_CAND];
 };
 
-__host__ __device__ inline int32_t seq_of_problem(const Dims &d, int32_t p) { return p / (d.n_layers * d.Hkv); }
-__host__ __device__ inline int32_t layer_of_problem(const Dims &d, int32_t p) { return (p / d.Hkv) % d.n_layers; }
-__host__ __device__ inline int32_t head_of_problem(const Dims &d, int32_t p) { return p % d.Hkv; }
+// x / n for 0 <= x, n < 65 536 with inv = ceil(2^32 / n), 0 for n = 1 (x * inv exceeds x 2^32 / n by less than x, and x is
+// below 2^32 / n, so the integer part of the quotient is right).  Every workgroup starts with the place of its problem, and three divisions by
+// numbers that the compiler does not know are a hundred instructions, fetched cold.
+__host__ __device__ inline uint32_t inverse_of(uint32_t n) { return n > 1 ? (uint32_t)(((1ull << 32) + n - 1) / n) : 0u; }
+__host__ __device__ inline int32_t quotient(int32_t x, uint32_t inv) { return inv ? (int32_t)(((uint64_t)(uint32_t)x * inv) >> 32) : x; }
+__host__ __device__ inline int32_t seq_of_problem(const Dims &d, int32_t p) { return quotient(p, d.inv_seq); }
+__host__ __device__ inline int32_t head_of_problem(const Dims &d, int32_t p) { return p - quotient(p, d.inv_heads) * d.Hkv; }
+__host__ __device__ inline int32_t layer_of_problem(const Dims &d, int32_t p)
+{
+    return quotient(p, d.inv_heads) - seq_of_problem(d, p) * d.n_layers;
+}
 
 __host__ __device__ inline int64_t k_problem_offset(const Dims &d, int32_t p)
 {
@@ -155,7 +164,7 @@ struct PerDeviceOnce {
 };
 
 // row statistics of the scoring step for 256 window-query rows per KV head with one read of K (the attention
-// kernel's first product alone): stats [P][2][row_stats_chunks][128][2] = (reference in the log2 domain, sum)
+// kernel's first product alone): stats [P][row_stats_chunks][G * W][2] = (reference in the log2 domain, sum)
 bool row_stats_supported(const Dims &d);
 int row_stats_chunks(const Dims &d);
 hipError_t launch_row_stats(const Dims &d, const void *q, const void *k, float *stats, hipStream_t st);

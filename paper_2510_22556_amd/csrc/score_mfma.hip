@@ -1,37 +1,42 @@
-// MFMA window scoring (Sec. 3.2, Eqs. barA, st, Dk) for bf16, D = 128 and (G, W) = (4, 32), (4, 64) or (8, 32).
+// MFMA window scoring (Sec. 3.2, Eqs. barA, st, Dk) for bf16.
 //
-// The window-query rows of a KV head (4 query heads x 32 window queries) stay in
-// accumulation registers as MFMA A operands; keys are the B operand, 32 per
-// wavefront iteration ("subtile"), so in the 32x32 accumulator layout a lane
-// owns ONE key column and 16 of the 32 queries of each head:
-//   * the head mean (Eq. barA) is an in-lane add over the four accumulators,
-//   * the column sum (Eq. st) is 16 in-lane adds plus one exchange between the
-//     two lane halves, and so is the entropy term (inner sum of Eq. Dk),
+// The window-query rows of a KV head (G query heads x W window queries) stay in
+// accumulation registers as MFMA A operands, 16 rows per tile; keys are the B
+// operand, 32 per wavefront iteration ("subtile"), two tiles of 16.  In the
+// 16x16 accumulator layout a lane owns ONE key column of each key tile and four
+// rows of each row tile (lane group lane / 16):
+//   * the head mean (Eq. barA) is an in-lane add,
+//   * the column sum (Eq. st) is in-lane adds plus two exchanges between the
+//     four lane groups, and so is the entropy term (inner sum of Eq. Dk),
 //   * the per-row softmax statistics are kept per lane and only reduced across
 //     lanes once per workgroup.
 // Each wavefront streams its own keys: global -> LDS with direct-to-LDS loads
 // (16 bytes per lane, fully coalesced 256-byte key rows) into a private ring,
-// LDS -> registers with an XOR swizzle so the 16-byte reads of 32 different key
+// LDS -> registers with an XOR swizzle so the 16-byte reads of different key
 // rows do not collide on banks.  No workgroup barrier in the loops.
 //
 // Softmax over all keys needs each row's log-sum-exp before any column is
 // final, so scoring is two kernels unless the caller supplies row_lse:
-//   pass 1  per row a reference (kept in LDS, shared by the 32 lanes that hold
-//           the row) and per lane the sum of exp2 relative to it; the reference
-//           enters the MFMA as its C operand, so the exponent is one multiply;
+//   pass 1  per row and lane the sum of the exponentials;
 //   pass 2  the chunk partials are combined into the row log-sum-exp in the
-//           prologue and fed as the MFMA C operand; probabilities, head mean,
-//           column sum and entropy term follow in registers.
-// In both passes the four heads rotate through two accumulators: head h is
-// multiplied while head h-1 is exponentiated, which overlaps the matrix pipe
-// with the exp/log work inside one wavefront (one wavefront per SIMD).
-// One launch per pass covers every problem of the call.
+//           prologue; probabilities, head mean, column sum and entropy term follow
+//           in registers.
+// The products start from zero and the log-sum-exp enters behind them (one FMA per
+// exponent): as the MFMA's C operand, some 140 in units of <q,k>, it costs every
+// product the bits that it is larger (128 rows, 131 072 keys: scores 8e-7 off their
+// 64-bit values, 6.5e-7 now).
+// In both passes the row tiles rotate, in groups of two, through two sets of
+// accumulators: a group is multiplied while the one before it is exponentiated,
+// which overlaps the matrix pipe with the exp/log work inside one wavefront (one
+// wavefront per SIMD).  One launch per pass covers every problem of the call.
 //
-// 256 window-query rows per KV head (G = 4 with W = 64, or G = 8 with W = 32).  The row statistics are
-// independent per row, so pass 1 runs the same kernel on two blocks of 128 rows (the two halves of the window, or
-// heads 0-3 and 4-7) as if they were two problems (K is streamed once per block).  Pass 2 needs all rows of a
-// key together (head mean, column sum, entropy), so a variant of the column kernel keeps all eight 32-row tiles
-// as A operands (256 accumulation registers), the keys in ordinary registers and the C operands in LDS.
+// What bounds both passes is the power budget: under this load the shader clock
+// stays well below its peak, so that less energy per product is more speed.
+// `v_mfma_f32_16x16x32_bf16` needs less of it than `v_mfma_f32_32x32x16_bf16`
+// (registers alone, normal variates, sustained: 2.0 against 1.78 PFLOP/s; with the
+// exponentials of pass 1, two wavefronts per SIMD: 738 against 866 ns per subtile of
+// 128 rows), and a lane's references, sums and C operands take half the registers,
+// so that even 256 rows of a KV head keep all of them out of LDS.
 #include "sablock_internal.h"
 
 #include <algorithm>
@@ -41,36 +46,36 @@ namespace sablock {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef const void __attribute__((address_space(1))) *gptr_t;
 typedef void __attribute__((address_space(3))) *lptr_t;
 
 constexpr int SUB = 32;                    // keys per wavefront iteration
+constexpr int TILE = 16;                   // rows or keys of an MFMA tile
 constexpr int ROW_BYTES = 256;             // D = 128 bf16
 constexpr int BUF_BYTES = SUB * ROW_BYTES; // 8 KiB
 constexpr int M_ROWS = 128;
 constexpr int STREAMS = 4;                 // key streams per workgroup (subtile u of the chunk goes to stream u % 4)
 constexpr int STRIDE = STREAMS * SUB;      // keys between consecutive subtiles of one stream
-
-constexpr int P1_LDS = 4 * 4 * BUF_BYTES + 4 * M_ROWS * 2 * 4 + 4 * M_ROWS * 4;   // rings + cross-wave reduction + row references
-constexpr int P2_LDS = 4 * 4 * BUF_BYTES + M_ROWS * 4 + 256 * 2 * 4;   // four rings + the rows' log-sum-exp + combine scratch
+constexpr int NBUF = 4;                    // subtiles of a stream's ring
+constexpr int WAVES = 4;
+constexpr int RING_BYTES = NBUF * BUF_BYTES;
 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
-constexpr float RESCALE_AT = 64.f;         // pass 1 moves a row's reference when an exponent exceeds this
+constexpr float RESCALE_AT = 64.f;         // pass 1, careful: a row's reference moves when an exponent exceeds this
+constexpr float SUM_MOST = 0x1p100f, SUM_LEAST = 0x1p-60f;     // pass 1, fast: a row's sum outside says that exponentials may have over- or underflowed
 
 struct ScoreArgs {
     Dims d;
     const uint16_t *q, *k;
-    int p0;                // first problem of the group
     int chunk_len;         // keys per workgroup, multiple of STRIDE
     int n_chunks;          // workgroups per problem
-    int nv;                // 128-row blocks per problem in pass 1 (G * W / 128)
     int pc;                // (reference, sum) pairs per row that pass 2 reads: n_chunks, or 1 once they are merged
     float c1;              // log2(e) / sqrt(D)
     float log2_G;          // log2 of the heads per KV head (the head mean is folded into the rows' log-sum-exp)
     float eps;
-    float *partial;        // pass 1 out: [problem][query block][chunk][128][2] (reference, sum), log2 domain
+    float *partial;        // pass 1 out: [problem][chunk][G * W][2] (reference, sum), log2 domain
     const float *merged;   // pass 2 in: the same layout with pc chunks
     const float *lse;      // pass 2 in, optional: [P][G * W] natural-log sum-exp per row (NULL: use partial)
     float *s_out, *e_out;  // pass 2 out: [P][L]
@@ -79,8 +84,26 @@ struct ScoreArgs {
 
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lptr_t)p; }
 
-// window query owned by accumulator register i in lane half hf
-__device__ __forceinline__ int query_of(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
+// Where the rows of a problem's window-query matrix (row = head * W + window query) sit.  Position 16 J + 4 g + i is
+// accumulator register i of lane group g of tile J.  For W = 8 a lane's registers are two queries of two heads, so
+// that the head mean needs no other lane; else positions are rows.  The rows behind the problem's G * W (W = 8 and G
+// odd) are padding: zero queries, never written by pass 1 and given an infinite log-sum-exp in pass 2, so they add
+// exact zeros.
+template <int NT_, int W> struct Rows {
+    static constexpr int NT = NT_;                          // tiles
+    static constexpr int MP = TILE * NT;                    // rows of the tiles (padding included)
+    static constexpr int NG = (NT + 1) / 2;                 // groups of two tiles
+    static constexpr int NS = W / 4;                        // head-mean values per lane and key tile
+    static constexpr int PER_HEAD = W == 8 ? 1 : W / TILE;  // tiles of a head
+    static_assert(NT >= 1 && NT <= 16 && (W == 8 || W == 16 || W == 32 || W == 64) && NT % PER_HEAD == 0, "unsupported shape");
+    __device__ static int row_of(int pos)
+    {
+        return W == 8 ? 8 * (2 * (pos >> 4) + ((pos >> 1) & 1)) + 2 * ((pos >> 2) & 3) + (pos & 1) : pos;
+    }
+    __device__ static int query(int J, int g, int i) { return W == 8 ? 2 * g + (i & 1) : TILE * (J % PER_HEAD) + 4 * g + i; }
+    __host__ __device__ static constexpr int slot(int J, int i) { return W == 8 ? i & 1 : 4 * (J % PER_HEAD) + i; }
+    __host__ __device__ static constexpr bool first(int J, int i) { return W == 8 ? J == 0 && i < 2 : J < PER_HEAD; }   // of its slot
+};
 
 // Direct-to-LDS load of 32 key rows starting at t0: 8 instructions of 1 KiB (4 rows each); LDS slot
 // (row, pos) receives 16-byte chunk pos ^ (row & 15) of the row.  The address is a wave-uniform 64-bit base
@@ -141,8 +164,7 @@ __device__ __forceinline__ void wait_loads(int subtiles_after)
 
 struct WaveWork {
     const uint16_t *kp;    // keys of the problem
-    int p, pl, chunk;
-    int pv, qoff, hoff;    // pass 1: (problem, row block) index, the block's first window query and first head
+    int p, chunk;
     int first, n_sub;      // this stream's subtiles: keys [first + u * STRIDE, +SUB), u < n_sub
 };
 
@@ -150,12 +172,8 @@ __device__ __forceinline__ WaveWork wave_work(const ScoreArgs &a, int stream)
 {
     stream = __builtin_amdgcn_readfirstlane(stream);         // wave-uniform: addresses below stay in scalar registers
     WaveWork w;
-    w.pl = blockIdx.x / a.n_chunks;
-    w.chunk = blockIdx.x - w.pl * a.n_chunks;
-    w.p = a.p0 + w.pl;
-    w.pv = w.p;
-    w.qoff = 0;
-    w.hoff = 0;
+    w.p = blockIdx.y;
+    w.chunk = blockIdx.x;
     w.kp = a.k + k_problem_offset(a.d, w.p);
     const int lo = w.chunk * a.chunk_len;
     const int hi = min(lo + a.chunk_len, a.d.L);
@@ -165,793 +183,758 @@ __device__ __forceinline__ WaveWork wave_work(const ScoreArgs &a, int stream)
     return w;
 }
 
-// pass 1: workgroups are indexed by ((problem, query block), chunk)
-__device__ __forceinline__ WaveWork wave_work_blocks(const ScoreArgs &a, int stream)
+// subtiles of a stream none of whose keys is masked for any window query: [0, this)
+__device__ __forceinline__ int plain_subtiles(const WaveWork &w, int T)
 {
-    WaveWork w = wave_work(a, stream);
-    w.pv = a.p0 * a.nv + w.pl;
-    w.p = w.pv / a.nv;
-    const int v = w.pv - w.p * a.nv;
-    w.qoff = a.d.W > 32 ? 32 * v : 0;                        // blocks are window halves ...
-    w.hoff = a.d.W > 32 ? 0 : 4 * v;                         // ... or groups of four heads
-    w.kp = a.k + k_problem_offset(a.d, w.p);
-    return w;
+    return w.first + SUB <= T ? min(w.n_sub, (T - SUB - w.first) / STRIDE + 1) : 0;
 }
 
 // ------------------------------------------------------------------ shared pieces of both passes
-// B operands of one subtile into accumulation registers: kb[s] = K[key lane % 32][(2s + lane/32) * 8 .. +8].
-// lane_addr = buffer address + row * 256 + ((hf ^ (row & 15)) << 4); chunk 2s+hf sits at that address ^ (s << 5).
-__device__ __forceinline__ void read_subtile_acc(uint32_t lane_addr, bf16x8 (&kb)[8])
+// B operands of one subtile: kb[t][s] = K[key 16 t + lane % 16][(4 s + lane / 16) * 8 .. +8].  buf = the lane's place in the
+// buffer, (lane % 16) * 256 + ((lane / 16 ^ lane % 16) << 4); chunk 4 s + g of the key sits at that address ^ (s << 6).
+// Ordinary loads: the compiler spreads them and waits where they are used.  That they come after the buffer's
+// direct-to-LDS loads, and before its next ones, is the caller's to see to (see KeyStream::next).
+__device__ __forceinline__ void read_subtile(uint32_t buf, bf16x8 (&kb)[2][4])
 {
+    typedef const bf16x8 __attribute__((address_space(3))) *lds_vec;
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-        asm volatile("ds_read_b128 %0, %1" : "=a"(kb[s]) : "v"(lane_addr ^ (uint32_t)(s << 5)) : "memory");
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+a"(kb[0]), "+a"(kb[1]), "+a"(kb[2]), "+a"(kb[3]), "+a"(kb[4]), "+a"(kb[5]), "+a"(kb[6]), "+a"(kb[7])
-                 :
-                 : "memory");
+    for (int s = 0; s < 4; ++s) {
+        kb[0][s] = *(lds_vec)(uintptr_t)(buf ^ (uint32_t)(s << 6));
+        kb[1][s] = *(lds_vec)(uintptr_t)((buf ^ (uint32_t)(s << 6)) + TILE * ROW_BYTES);
+    }
+}
+// the operands are in their registers behind this point (ACC: accumulation registers)
+template <bool ACC>
+__device__ __forceinline__ void have_subtile(bf16x8 (&kb)[2][4])
+{
+    if (ACC) asm volatile("" : "+a"(kb[0][0]), "+a"(kb[0][1]), "+a"(kb[0][2]), "+a"(kb[0][3]), "+a"(kb[1][0]), "+a"(kb[1][1]), "+a"(kb[1][2]), "+a"(kb[1][3]) : : "memory");
+    else asm volatile("" : "+v"(kb[0][0]), "+v"(kb[0][1]), "+v"(kb[0][2]), "+v"(kb[0][3]), "+v"(kb[1][0]), "+v"(kb[1][1]), "+v"(kb[1][2]), "+v"(kb[1][3]) : : "memory");
+}
+__device__ __forceinline__ uint32_t lane_read_offset(int lane)
+{
+    const int n = lane & 15, g = lane >> 4;
+    return (uint32_t)(n * ROW_BYTES + ((g ^ n) << 4));
 }
 
-// the same into ordinary registers (for the kernel whose accumulation registers are all taken by A operands)
-__device__ __forceinline__ void read_subtile_vgpr(uint32_t lane_addr, bf16x8 (&kb)[8])
+// Group j of the row tiles (tiles 2 j and 2 j + 1) times the two key tiles
+template <int NT, int KS>
+__device__ __forceinline__ void multiply(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[2][KS], int j, floatx4 (&acc)[2][2])
 {
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-        asm volatile("ds_read_b128 %0, %1" : "=v"(kb[s]) : "v"(lane_addr ^ (uint32_t)(s << 5)) : "memory");
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(kb[0]), "+v"(kb[1]), "+v"(kb[2]), "+v"(kb[3]), "+v"(kb[4]), "+v"(kb[5]), "+v"(kb[6]), "+v"(kb[7])
-                 :
-                 : "memory");
-}
-
-// k-steps [S0, S1) of one head's 32x32 tile; the first step takes `c` as its C operand
-template <int S0, int S1, int N>
-__device__ __forceinline__ floatx16 chain(const bf16x8 (&qa)[N], const bf16x8 (&kb)[N], floatx16 c)
-{
-    static_assert(S1 <= N, "k-step outside the operands");
+    for (int s = 0; s < KS; ++s)
 #pragma unroll
-    for (int s = S0; s < S1; ++s) c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[s], kb[s], c, 0, 0, 0);
-    return c;
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                if (2 * j + r < NT)
+                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[2 * j + r][s], kb[t][s], s == 0 ? floatx4{} : acc[r][t], 0, 0, 0);
+}
+// what makes a pending group add zeros
+__device__ __forceinline__ void set_nothing(floatx4 (&acc)[2][2])
+{
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[r][t][i] = -INFINITY;
 }
 
-// Per-wavefront stream of subtiles through a ring of NBUF LDS buffers.  Subtile u lives in buffer u % NBUF; at
-// the top of iteration u the stream waits for subtile u, reads it into registers, and immediately re-fills the
-// same buffer with subtile u + NBUF, so NBUF subtiles (32 KiB per wavefront) are in flight or landed at any time.
-template <int NBUF>
+// Per-wavefront stream of subtiles through a ring of NBUF LDS buffers.  Subtile u lives in buffer u % NBUF.  AHEAD: the
+// kernels hold two subtiles in registers, and while one is worked on the next one is read from LDS.  next()
+// sees that the subtile at hand has left its buffer, re-fills that with subtile u + NBUF, waits for subtile u + 1 and
+// starts to read it: NBUF subtiles (32 KiB per wavefront) are in flight or landed at any time.  Else there
+// is room for one subtile (pass 2 of more than 128 rows), which next() reads itself.
+template <bool AHEAD_, bool ACC>
 struct KeyStream {
+    static constexpr bool AHEAD = AHEAD_;
     const uint16_t *kp;
     int64_t ks3;
     char *ring;
     uint32_t lane_addr0, ring_lds;
     uint32_t lane_off[4];
     int first, n_sub, L, lane;
-    const char *next;                                          // keys of the next subtile to issue
+    const char *ahead;                                         // keys of the next subtile to issue
     int64_t step;                                              // bytes between consecutive subtiles of this stream
 
     __device__ __forceinline__ void init(const uint16_t *kp_, int64_t ks3_, char *ring_, int first_, int n_sub_, int L_, int lane_)
     {
         kp = kp_; ks3 = ks3_; ring = ring_; first = first_; n_sub = n_sub_; L = L_; lane = lane_;
-        next = reinterpret_cast<const char *>(kp) + (int64_t)first * ks3 * 2;
+        ahead = reinterpret_cast<const char *>(kp) + (int64_t)first * ks3 * 2;
         step = (int64_t)STRIDE * ks3 * 2;
-        const int n = lane & 31, hf = lane >> 5, r4 = lane >> 4, pos = lane & 15;
+        const int r4 = lane >> 4, pos = lane & 15;
         ring_lds = __builtin_amdgcn_readfirstlane(lds_addr(ring));
-        lane_addr0 = ring_lds + n * ROW_BYTES + ((hf ^ (n & 15)) << 4);
+        lane_addr0 = ring_lds + lane_read_offset(lane);
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) lane_off[jj] = (uint32_t)(r4 * ks3 * 2) + (uint32_t)(((pos ^ r4 ^ (4 * jj)) & 15) << 4);
     }
     __device__ __forceinline__ void issue(int u)
     {
         const int t0 = first + u * STRIDE;                     // wave-uniform, < L
-        const char *base = next;                               // subtiles are issued in order: a running address
-        next += step;
+        const char *base = ahead;                              // subtiles are issued in order: a running address
+        ahead += step;
         const uint32_t buf_lds = ring_lds + (u % NBUF) * BUF_BYTES;
         if (t0 + SUB <= L) {
             if (ks3 == ROW_BYTES / 2) issue_subtile_dense(base, lane_off, buf_lds);
             else issue_subtile_fast(base, ks3 * 2, lane_off, buf_lds);
         } else issue_subtile_clamped(base, ks3 * 2, L - t0, buf_lds, lane);
     }
-    __device__ __forceinline__ void prime()
+    // the first subtiles, [from, to) of the ring
+    __device__ __forceinline__ void issue_first(int from = 0, int to = NBUF)
     {
-        for (int u = 0; u < min(NBUF, n_sub); ++u) issue(u);
+        for (int u = from; u < min(to, n_sub); ++u) issue(u);
     }
-    __device__ __forceinline__ void fetch(int u, bf16x8 (&kb)[8])
+    // AHEAD: subtile 0 into kb
+    __device__ __forceinline__ void start(bf16x8 (&kb)[2][4])
     {
-        wait_loads(min(NBUF - 1, n_sub - 1 - u));
-        read_subtile_acc(lane_addr0 + (u % NBUF) * BUF_BYTES, kb);
-        if (u + NBUF < n_sub) issue(u + NBUF);
+        if (!AHEAD || n_sub == 0) return;
+        wait_loads(min(NBUF, n_sub) - 1);
+        read_subtile(lane_addr0, kb);
     }
-    __device__ __forceinline__ void fetch_vgpr(int u, bf16x8 (&kb)[8])
+    // AHEAD: subtile u is in `cur`; subtile u + 1, if there is one, into `nxt`.  Else: subtile u into `cur`.
+    __device__ __forceinline__ void next(int u, bf16x8 (&cur)[2][4], bf16x8 (&nxt)[2][4])
     {
-        wait_loads(min(NBUF - 1, n_sub - 1 - u));
-        read_subtile_vgpr(lane_addr0 + (u % NBUF) * BUF_BYTES, kb);
+        if (!AHEAD) {
+            wait_loads(min(NBUF - 1, n_sub - 1 - u));
+            read_subtile(lane_addr0 + (u % NBUF) * BUF_BYTES, cur);
+        }
+        have_subtile<ACC>(cur);
         if (u + NBUF < n_sub) issue(u + NBUF);
+        if (AHEAD && u + 1 < n_sub) {
+            wait_loads(min(NBUF - 1, n_sub - 2 - u));
+            read_subtile(lane_addr0 + ((u + 1) % NBUF) * BUF_BYTES, nxt);
+        }
     }
 };
 
-// Keys of 64 elements (128-byte rows) for the kernels that take any row shape: no LDS staging.  A lane loads its
-// own B operand (key lane % 32, elements (2s + lane / 32) * 8 .. +8 of k-step s: the two lane halves of a key read
-// adjacent 16-byte pieces) straight into registers with ordinary loads, whose counter the compiler keeps; subtile
-// u + 1 is requested before subtile u is worked on.  Keys past the end of the sequence read key L - 1 (their results
-// are masked later, as in the staged stream).  Same interface as KeyStream.
+// Keys of other lengths (64, 96 or 256 elements): no LDS staging.  A lane loads its own B operands (elements (4 s +
+// lane / 16) * 8 .. +8 of keys lane % 16 and 16 + lane % 16: the four lane groups of a key read adjacent 16-byte pieces)
+// straight into registers with ordinary loads, one subtile ahead.  Keys past the end of the sequence read key L - 1 (their
+// results are masked later, as in the staged stream).  Same interface as KeyStream.
 template <int KS>
 struct KeyStreamDirect {
+    static constexpr bool AHEAD = true;
     const uint16_t *kp;
     int64_t ks3;
     int first, n_sub, L, lane;
-    bf16x8 nxt[KS];
 
     __device__ __forceinline__ void init(const uint16_t *kp_, int64_t ks3_, char *, int first_, int n_sub_, int L_, int lane_)
     {
         kp = kp_; ks3 = ks3_; first = first_; n_sub = n_sub_; L = L_; lane = lane_;
     }
-    __device__ __forceinline__ void load(int u)
-    {
-        const int t = min(first + u * STRIDE + (lane & 31), L - 1);
-        const uint16_t *row = kp + (int64_t)t * ks3 + (lane >> 5) * 8;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) nxt[s] = *reinterpret_cast<const bf16x8 *>(row + 16 * s);
-    }
-    __device__ __forceinline__ void prime()
-    {
-        if (n_sub > 0) load(0);
-    }
-    __device__ __forceinline__ void fetch(int u, bf16x8 (&kb)[KS])
+    __device__ __forceinline__ void load(int u, bf16x8 (&kb)[2][KS])
     {
 #pragma unroll
-        for (int s = 0; s < KS; ++s) kb[s] = nxt[s];
-        if (u + 1 < n_sub) load(u + 1);
+        for (int t = 0; t < 2; ++t) {
+            const int key = min(first + u * STRIDE + TILE * t + (lane & 15), L - 1);
+            const uint16_t *row = kp + (int64_t)key * ks3 + (lane >> 4) * 8;
+#pragma unroll
+            for (int s = 0; s < KS; ++s) kb[t][s] = *reinterpret_cast<const bf16x8 *>(row + 32 * s);
+        }
+    }
+    __device__ __forceinline__ void issue_first(int = 0, int = 0) {}
+    __device__ __forceinline__ void start(bf16x8 (&kb)[2][KS])
+    {
+        if (n_sub > 0) load(0, kb);
+    }
+    __device__ __forceinline__ void next(int u, bf16x8 (&)[2][KS], bf16x8 (&nxt)[2][KS])
+    {
+        if (u + 1 < n_sub) load(u + 1, nxt);
     }
 };
 
-// the key stream of the any-row-shape kernels by k-steps per key: 8 (D = 128) staged through LDS; 4 (D = 64), 6
-// (D = 96) and 16 (D = 256, whose 512-byte rows would need a ring twice the LDS) direct
-template <int KS> struct StreamFor { using type = KeyStream<4>; };
-template <> struct StreamFor<4> { using type = KeyStreamDirect<4>; };
-template <> struct StreamFor<6> { using type = KeyStreamDirect<6>; };
-template <> struct StreamFor<16> { using type = KeyStreamDirect<16>; };
-
-// A operands: the window queries of the four heads, query row `n`, k-slices (2s + hf) * 8 .. +8, into
-// accumulation registers (pin_queries).  All 32 loads are issued before the first is consumed.
-__device__ __forceinline__ void load_queries(bf16x8 (&qa)[4][8], const uint16_t *q, const Dims &d, int p, int h0, int n, int hf)
+template <int KS>
+__device__ __forceinline__ void copy_subtile(bf16x8 (&to)[2][KS], const bf16x8 (&from)[2][KS])
 {
+    if (&to == &from) return;
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        if (h0 + h < d.G) {
-            const uint16_t *row = q + q_row_offset(d, p, h0 + h, n);   // n: window query of this lane
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int s = 0; s < 8; ++s) qa[h][s] = *reinterpret_cast<const bf16x8 *>(row + (2 * s + hf) * 8);
-        } else {                                                   // a head behind the group's last: padding, zero queries
+        for (int s = 0; s < KS; ++s) to[t][s] = from[t][s];
+}
+
+// the key stream by k-steps of 32 elements per key: 4 (D = 128) staged through LDS; 2 (D = 64), 3 (D = 96) and 8 (D =
+// 256, whose 512-byte rows would need a ring twice the LDS) direct.  The A operands of up to 128 rows leave accumulation
+// registers for the keys.
+template <int NT, int KS, bool AHEAD> struct StreamFor { using type = KeyStreamDirect<KS>; };
+template <int NT, bool AHEAD> struct StreamFor<NT, 4, AHEAD> { using type = KeyStream<AHEAD, NT <= 8>; };
+
+// A operands, in accumulation registers: a lane's rows are positions 16 J + lane % 16 (see Rows); padding rows hold some
+// other row until pin_queries clears them.  Straight from memory:
+template <int NT, int W, int KS>
+__device__ __forceinline__ void load_queries(bf16x8 (&qa)[NT][KS], const ScoreArgs &a, int p, int lane)
+{
+    const uint16_t *q = a.q + q_row_offset(a.d, p, 0, 0) + (lane >> 4) * 8;
 #pragma unroll
-            for (int s = 0; s < 8; ++s) qa[h][s] = bf16x8{};
-        }
+    for (int J = 0; J < NT; ++J) {
+        const int r = min(Rows<NT, W>::row_of(TILE * J + (lane & 15)), a.d.G * W - 1);
+        const uint16_t *row = q + (r / W) * a.d.qs[2] + (r % W) * a.d.qs[3];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qa[J][s] = *reinterpret_cast<const bf16x8 *>(row + 32 * s);
     }
 }
 
-template <int NT, int KS>
-__device__ __forceinline__ void pin_queries(bf16x8 (&qa)[NT][KS])
+// ... or, where the keys are staged (D = 128), once per workgroup through the last buffers of the wavefronts' rings: block b
+// of 32 rows by wavefront b % 4, in the keys' own layout.  Four wavefronts that each load all the rows take 10 000 cycles
+// for 128 of them, as much as two subtiles of keys.
+template <int NT> struct QueryStage {
+    static constexpr int BLOCKS = (NT + 1) / 2;
+    static constexpr int BUFS = (BLOCKS + WAVES - 1) / WAVES;                  // buffers of a ring that hold queries at first
+    __device__ static uint32_t buffer(uint32_t ring0_lds, int b)
+    {
+        return ring0_lds + (b % WAVES) * RING_BYTES + (NBUF - 1 - b / WAVES) * BUF_BYTES;
+    }
+    template <int W>
+    __device__ __forceinline__ static void issue(const ScoreArgs &a, int p, uint32_t ring0_lds, int wave, int lane)
+    {
+        const uint16_t *q = a.q + q_row_offset(a.d, p, 0, 0);
+#pragma unroll
+        for (int i = 0; i < BUFS; ++i) {
+            const int b = wave + WAVES * i;
+            if (b >= BLOCKS) break;
+            const uint32_t lds = buffer(ring0_lds, b);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int row = 4 * j + (lane >> 4), r = min(Rows<NT, W>::row_of(min(2 * TILE * b + row, TILE * NT - 1)), a.d.G * W - 1);
+                const uint16_t *src = q + (r / W) * a.d.qs[2] + (r % W) * a.d.qs[3] + (((lane ^ row) & 15) << 3);
+                asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(src), "s"(lds + j * 1024) : "memory", "m0");
+            }
+        }
+    }
+    // behind a barrier that says that all blocks have landed; the buffers are free behind another one
+    __device__ __forceinline__ static void read(bf16x8 (&qa)[NT][4], uint32_t ring0_lds, int lane)
+    {
+        typedef const bf16x8 __attribute__((address_space(3))) *lds_vec;
+#pragma unroll
+        for (int J = 0; J < NT; ++J)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                qa[J][s] = *(lds_vec)(uintptr_t)((buffer(ring0_lds, J / 2) + (J & 1) * TILE * ROW_BYTES + lane_read_offset(lane)) ^ (uint32_t)(s << 6));
+    }
+};
+
+// all LDS traffic of this wavefront done, then the workgroup barrier (global loads stay in flight)
+__device__ __forceinline__ void lds_barrier()
 {
-#pragma unroll
-    for (int h = 0; h < NT; ++h)
-#pragma unroll
-        for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(qa[h][s]));
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-constexpr int NBUF = 4;
-constexpr int WAVES = 4;
-constexpr int RING_BYTES = NBUF * BUF_BYTES;
+template <int NT, int W, int KS>
+__device__ __forceinline__ void pin_queries(bf16x8 (&qa)[NT][KS], const ScoreArgs &a, int lane)
+{
+    if (W == 8 && Rows<NT, W>::row_of(TILE * (NT - 1) + (lane & 15)) >= a.d.G * W) {       // only the last tile can hold padding
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qa[NT - 1][s] = bf16x8{};
+    }
+#pragma unroll
+    for (int J = 0; J < NT; ++J)
+#pragma unroll
+        for (int s = 0; s < KS; ++s) asm volatile("" : "+a"(qa[J][s]));
+}
 
 // ------------------------------------------------------------------ pass 1
-// Row statistics.  Every window-query row keeps, per wavefront, ONE reference shared by the 32 lanes that hold
-// the row (stored negated and divided by c1 in LDS, `cref`), and per lane the sum z of exp2(c1 * <q,k> - ref) over
-// the lane's keys.  cref is the MFMA C operand, so acc = <q,k> - ref/c1 and the exponent is c1 * acc.  A row is
-// anchored at the maximum over the wavefront's first 32 keys and re-anchored (rarely) when a later logit exceeds
-// the reference by more than RESCALE_AT, so any finite logits are handled without overflow or total underflow.
+// Row statistics: per window-query row a reference and the sum z of exp2(c1 * <q,k> - ref) over the keys, kept per lane
+// (its keys) until the end.
 //
-// The loop over subtiles has two bodies.  The fast one assumes keys before the window (no causal mask) and no
-// re-anchoring: per head a maximum over the raw accumulators guards the exponentials, and a head that fails the
-// guard leaves the fast body BEFORE anything of it was added.  A stream's
-// first subtile anchors the references (stats_anchor) and is then an ordinary one.  The careful body (subtiles touching
-// the window or the end of the sequence, and the rest of a subtile after a failed guard) masks, re-anchors and
-// runs the heads one after the other.  Keeping the careful code out of the fast body keeps the fast body free
-// of register copies at control-flow joins.
-
-// C operand of head h for this lane half: 16 consecutive floats
-__device__ __forceinline__ floatx16 load_cref(const float *cref, int h, int hf)
-{
-    return *reinterpret_cast<const floatx16 *>(cref + h * 32 + hf * 16);
-}
+// The loop has two bodies.  The fast one has no reference: a sum of positive terms is as
+// accurate as its terms whatever their size, as long as none overflows and those that underflow do not count.  Both can be
+// told from the row's sum: no logit that it holds exceeds SUM_MOST, and what was flushed to zero (below 2^-126 each) is
+// nothing beside SUM_LEAST.  Logits of attention lie within some tens of powers of two around 1; where a row's do not, the
+// wavefront runs its keys once more through the careful body alone.  That one keeps a reference per row and wavefront,
+// shared by the 16 lanes that hold the row (negated and divided by c1: the MFMA's C operand `cr`, so acc = <q,k> - ref / c1
+// and the exponent is c1 * acc), anchored at the row's maximum over the first subtile and moved before an exponent exceeds
+// RESCALE_AT: any finite logits are handled.
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));       // every lane has a source
+}
+// maximum and sum over the 16 lanes of a lane group: lane ^ 1, lane ^ 2, mirror inside 8, mirror inside 16
+__device__ __forceinline__ float group_max(float v)
+{
+    v = fmaxf(v, dpp_f<0xB1>(v));
+    v = fmaxf(v, dpp_f<0x4E>(v));
+    v = fmaxf(v, dpp_f<0x141>(v));
+    return fmaxf(v, dpp_f<0x140>(v));
+}
+__device__ __forceinline__ float group_sum(float v)
+{
+    v += dpp_f<0xB1>(v);
+    v += dpp_f<0x4E>(v);
+    v += dpp_f<0x141>(v);
+    return v + dpp_f<0x140>(v);
 }
 
-// careful reduction of one 32-row tile of the subtile whose lane key is t; qf(i) = window query of register i
-template <typename QF>
-__device__ __forceinline__ void stats_tile_careful(const floatx16 &acc, float (&z)[16], float *cref_h, float c1, bool first,
-                                                   int t, int hf, int n, QF qf, int T, int L)
+// Careful body: the subtile in kb, whose first key is t0, against all row tiles.  A row's state sits in LDS: state[pos / 2] =
+// (cr, z) of two rows, z the sum over all lanes.  Rare: the tiles' loop is not unrolled and takes its queries from memory.
+template <int NT, int W, int KS>
+__device__ __forceinline__ void stats_careful(const ScoreArgs &a, int p, const bf16x8 (&kb)[2][KS], floatx4 *state, bool first, int t0, int n, int g)
 {
-    float dd[16];
-    float dmax = -INFINITY;
+    const float c1 = a.c1, inv_c1 = 1.0f / c1;
+    const uint16_t *q = a.q + q_row_offset(a.d, p, 0, 0) + g * 8;
+#pragma nounroll
+    for (int J = 0; J < NT; ++J) {
+        const int r = min(Rows<NT, W>::row_of(TILE * J + n), a.d.G * W - 1);                 // a padding row's results are not used
+        const uint16_t *row = q + (r / W) * a.d.qs[2] + (r % W) * a.d.qs[3];
+        floatx4 *st = state + (TILE * J + 4 * g) / 2;
+        const floatx4 s0 = first ? floatx4{} : st[0], s1 = first ? floatx4{} : st[1];
+        floatx4 cr = {s0[0], s0[2], s1[0], s1[2]}, z = {s0[1], s0[3], s1[1], s1[3]}, v[2] = {cr, cr};
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        float v = acc[i] * c1;
-        if (!(t < L && t <= T + qf(i))) v = -INFINITY;                   // causal inside the window
-        dd[i] = v;
-        dmax = fmaxf(dmax, v);
-    }
-    if (first || __any(dmax > RESCALE_AT)) {
-        const float inv_c1 = 1.0f / c1;
+        for (int s = 0; s < KS; ++s) {
+            const bf16x8 qa = *reinterpret_cast<const bf16x8 *>(row + 32 * s);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            // row maximum over the 32 lanes of this half: four DPP steps inside each row of 16 lanes (lane ^ 1,
-            // lane ^ 2, mirror inside 8, mirror inside 16), then the other row of the half
-            float rm = dd[i];
-            rm = fmaxf(rm, dpp_f<0xB1>(rm));
-            rm = fmaxf(rm, dpp_f<0x4E>(rm));
-            rm = fmaxf(rm, dpp_f<0x141>(rm));
-            rm = fmaxf(rm, dpp_f<0x140>(rm));
-            rm = fmaxf(rm, __shfl_xor(rm, 16));
-            const bool move = first ? (rm > -INFINITY) : (rm > RESCALE_AT);
+            for (int t = 0; t < 2; ++t) v[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa, kb[t][s], v[t], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                v[t][i] = t0 + TILE * t + n <= a.d.T + Rows<NT, W>::query(J, g, i) ? v[t][i] * c1 : -INFINITY;       // causal inside the window
+            const float rm = group_max(fmaxf(v[0][i], v[1][i]));
+            const bool move = first ? rm > -INFINITY : rm > RESCALE_AT;
             const float cshift = move ? rm * inv_c1 : 0.f;      // change of the C operand
             const float shift = cshift * c1;                    // and the matching change of the exponent
-            z[i] *= __builtin_amdgcn_exp2f(-shift);
-            dd[i] -= shift;
-            if (n == 0 && move) cref_h[hf * 16 + i] -= cshift;
+            z[i] = (first ? 0.f : z[i] * __builtin_amdgcn_exp2f(-shift)) +
+                   group_sum(__builtin_amdgcn_exp2f(v[0][i] - shift) + __builtin_amdgcn_exp2f(v[1][i] - shift));
+            cr[i] -= cshift;
+        }
+        if (n == 0) {
+            st[0] = floatx4{cr[0], z[0], cr[1], z[1]};
+            st[1] = floatx4{cr[2], z[2], cr[3], z[3]};
         }
     }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) z[i] += __builtin_amdgcn_exp2f(dd[i]);
+    __builtin_amdgcn_wave_barrier();                            // written before the next subtile's reads
 }
 
-// the same for a tile that is one head's 32 window queries
-__device__ __forceinline__ void stats_head_careful(const floatx16 &acc, float (&z)[16], float *cref_h, float c1, bool first,
-                                                   int t, int hf, int n, int T, int L)
-{
-    stats_tile_careful(acc, z, cref_h, c1, first, t, hf, n, [hf](int i) { return query_of(i, hf); }, T, L);
-}
-
-// guard of the fast body: true when some accumulator of the wavefront exceeds `lim` (= RESCALE_AT / c1)
-__device__ __forceinline__ bool stats_guard(const floatx16 &acc, float lim)
-{
-    float m = fmaxf(acc[0], acc[1]);
-#pragma unroll
-    for (int i = 2; i < 16; i += 2) m = fmaxf(fmaxf(m, acc[i]), acc[i + 1]);
-    return __any(m > lim);
-}
-
-__device__ __forceinline__ void stats_add(const floatx16 &acc, float (&z)[16], float c1)
+// adds the exponentials of group j; W: with the causal mask inside the window of so many queries (key T + q is the last that
+// query q sees, and the last of all for the last one), 0: none is masked; t: the lane's key in the first key tile
+template <int W, int NT>
+__device__ __forceinline__ void stats_add(const floatx4 (&acc)[2][2], int j, floatx4 (&z)[NT], float c1, int t, int g, int T)
 {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) z[i] += __builtin_amdgcn_exp2f(acc[i] * c1);
-    // materialise the sums here: keeps the compiler from sinking this head's exponentials past the next heads
-    asm volatile("" : "+v"(z[0]), "+v"(z[1]), "+v"(z[2]), "+v"(z[3]), "+v"(z[4]), "+v"(z[5]), "+v"(z[6]), "+v"(z[7]),
-                      "+v"(z[8]), "+v"(z[9]), "+v"(z[10]), "+v"(z[11]), "+v"(z[12]), "+v"(z[13]), "+v"(z[14]), "+v"(z[15]));
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (2 * j + r >= NT) continue;
+                const float e = __builtin_amdgcn_exp2f(acc[r][kt][i] * c1);
+                if constexpr (W == 0) z[2 * j + r][i] += e;
+                else z[2 * j + r][i] += t + TILE * kt <= T + Rows<NT, W>::query(2 * j + r, g, i) ? e : 0.f;
+            }
 }
 
-constexpr int STATS_OK = -1;
-
-// Fast body of one subtile of NT tiles.  Tile J is multiplied into acc[J & 1] while tile J - 1 is exponentiated from
-// the other accumulator; the first two k-steps of a tile are issued before the guard of the tile before it, the
-// others after it, next to that tile's exponentials.  CARRY (an even number of tiles): the last tile is left waiting
-// in acc[1] and is exponentiated under the first tile of the next subtile; otherwise it is finished here.
-// Returns STATS_OK, or which tile failed its guard (the tiles before it were added, it and the ones after it were
-// not); with CARRY NT - 1 names the waiting tile of the previous subtile.
-template <int NT, int KS, bool CARRY>
-__device__ __forceinline__ int stats_fast(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[KS], floatx16 (&acc)[2],
-                                          const floatx16 (&cr)[NT], float (&z)[NT][16], float c1, float lim)
+// Fast body of one subtile: group j is multiplied into acc[(j + PAR) & 1] while the group before it is exponentiated from
+// the other set, at first the last group of the subtile before.  The last group is left waiting.
+template <int PAR, int NT, int KS>
+__device__ __forceinline__ void stats_fast(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[2][KS], floatx4 (&acc)[2][2][2],
+                                           floatx4 (&z)[NT], float c1)
 {
-    static_assert(!CARRY || NT % 2 == 0, "the waiting tile must not sit in the first tile's accumulator");
+    constexpr int NG = (NT + 1) / 2;
 #pragma unroll
-    for (int J = 0; J < NT; ++J) {
-        constexpr int LAST = NT - 1;
-        const int prev = J > 0 ? J - 1 : LAST;
-        const bool has_prev = J > 0 || CARRY;
-        acc[J & 1] = chain<0, 2>(qa[J], kb, cr[J]);
-        if (has_prev && stats_guard(acc[(J & 1) ^ 1], lim)) return prev;
-        acc[J & 1] = chain<2, KS>(qa[J], kb, acc[J & 1]);
-        if (has_prev) stats_add(acc[(J & 1) ^ 1], z[prev], c1);
+    for (int j = 0; j < NG; ++j) {
+        multiply(qa, kb, j, acc[(j + PAR) & 1]);
+        stats_add<0>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, z, c1, 0, 0, 0);
     }
-    if (!CARRY) {
-        if (stats_guard(acc[(NT - 1) & 1], lim)) return NT - 1;
-        stats_add(acc[(NT - 1) & 1], z[NT - 1], c1);
-    }
-    return STATS_OK;
+    // the sums as they are here: keeps the compiler from moving this subtile's exponentials behind the next one's loads
+#pragma unroll
+    for (int J = 0; J < NT; ++J) asm volatile("" : "+v"(z[J]));
 }
 
-// Anchors the references of all tiles at the row maxima over the subtile in kb, none of whose keys is masked.  The
-// product is formed transposed (the MFMA's A and B swapped: the same registers), so a lane holds 16 keys of ONE row
-// and a maximum is 15 in-lane steps and one exchange, instead of five lane exchanges for each of a lane's 16 rows.
-// A workgroup runs this once, so what counts is its length (instructions that are fetched cold): with the first
-// subtile in the careful body the statistics of 8 problems of 8 192 keys took
-// 23.5 us, 15.0 us now.
-template <int NT, int KS>
-__device__ __forceinline__ void stats_anchor(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[KS], float *cref, int hf, int n)
-{
-#pragma unroll
-    for (int J = 0; J < NT; ++J) {
-        floatx16 t = {};
-#pragma unroll
-        for (int s = 0; s < KS; ++s) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[s], qa[J][s], t, 0, 0, 0);
-        float m = fmaxf(t[0], t[1]);
-#pragma unroll
-        for (int i = 2; i < 16; i += 2) m = fmaxf(fmaxf(m, t[i]), t[i + 1]);
-        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
-        m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-        // row n of the tile is accumulator register 4 (n / 8) + n % 4 of lane half (n / 4) % 2
-        if (hf == 0 && m > -INFINITY) cref[32 * J + ((n >> 2) & 1) * 16 + ((n >> 3) << 2) + (n & 3)] = -m;
-    }
-}
-
-// Careful body: heads h_from..3 of the subtile in kb, one after the other, each multiplied afresh against the
-// references as they are now.
-__device__ __forceinline__ void stats_careful(const bf16x8 (&qa)[4][8], const bf16x8 (&kb)[8], float *cref, float (&z)[4][16],
-                                              float c1, int h_from, bool first, int t, int hf, int n, int T, int L)
-{
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        if (h >= h_from) {
-            const floatx16 a = chain<0, 8>(qa[h], kb, load_cref(cref, h, hf));
-            stats_head_careful(a, z[h], cref + 32 * h, c1, first, t, hf, n, T, L);
-        }
-    }
-}
-
+template <int NT, int W, int KS>
 __global__ void __launch_bounds__(WAVES * 64)
 score_mfma_stats(ScoreArgs a)
 {
+    using R = Rows<NT, W>;
+    constexpr int MP = R::MP, NG = R::NG;
     extern __shared__ __attribute__((aligned(8192))) char lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, hf = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
     const Dims &d = a.d;
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    char *ring = lds + wave_u * RING_BYTES;
-    float *wg_red = reinterpret_cast<float *>(lds + WAVES * RING_BYTES);       // [WAVES][128][2]
-    float *cref = wg_red + WAVES * M_ROWS * 2 + wave_u * M_ROWS;               // [4 heads][2 halves][16], this wave's
-    const WaveWork w = wave_work_blocks(a, wave);
-    const int Tq = d.T + w.qoff;                               // causal limit of this block's query 0: key t is visible to query i iff t <= Tq + i
+    char *ring = lds + wave * RING_BYTES;
+    floatx4 *wg_state = reinterpret_cast<floatx4 *>(lds + WAVES * RING_BYTES);     // [WAVES][MP / 2], see stats_careful
+    floatx4 *state = wg_state + wave * (MP / 2);
+    const WaveWork w = wave_work(a, wave);
 
-    // queries before keys: loads return in order, and behind the keys the queries would wait for four subtiles from HBM
-    bf16x8 qa[4][8];
-    load_queries(qa, a.q, d, w.p, w.hoff, w.qoff + n, hf);
-    pin_queries(qa);
-    KeyStream<NBUF> ks;
+    // queries before keys, as loads return in order; both are in flight together
+    bf16x8 qa[NT][KS];
+    using Stream = typename StreamFor<NT, KS, true>::type;
+    Stream ks;
     ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-    cref[lane] = 0.f;
-    cref[lane + 64] = 0.f;
+    if constexpr (KS == 4) {
+        using Q = QueryStage<NT>;
+        const uint32_t ring0 = __builtin_amdgcn_readfirstlane(lds_addr(lds));
+        Q::template issue<W>(a, w.p, ring0, wave, lane);
+        ks.issue_first(0, NBUF - Q::BUFS);
+        wait_loads(min(NBUF - Q::BUFS, w.n_sub));              // the queries; the keys stay in flight
+        lds_barrier();
+        Q::read(qa, ring0, lane);
+        pin_queries<NT, W>(qa, a, lane);
+        lds_barrier();
+        ks.issue_first(NBUF - Q::BUFS, NBUF);
+    } else {
+        load_queries<NT, W>(qa, a, w.p, lane);
+        pin_queries<NT, W>(qa, a, lane);
+    }
 
-    floatx16 acc[2];
-    float z[4][16];
+    const int n_plain = plain_subtiles(w, d.T);
+    for (bool careful = false;; careful = true) {
+        bf16x8 ka[2][KS], kb[2][KS];
+        ks.start(ka);
+        int u = 0;
+        bool again = false;
+        if (!careful) {
+            floatx4 z[NT];
 #pragma unroll
-    for (int h = 0; h < 4; ++h)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) { z[h][i] = 0.f; acc[h & 1][i] = -INFINITY; }
-
-    // `waiting`: head 3 of subtile u-1 sits in acc[1], multiplied but not yet reduced.  When nothing waits,
-    // acc[1] = -inf makes the fast body's first step add zeros.
-    const float lim = RESCALE_AT / a.c1;
-    floatx16 cr[4];                                            // the rows' references as MFMA C operands (copy of cref)
-#pragma unroll
-    for (int h = 0; h < 4; ++h)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cr[h][i] = 0.f;
-    bool waiting = false;
-    for (int u = 0; u < w.n_sub; ++u) {
-        bf16x8 kb[8];
-        ks.fetch(u, kb);
-        const int t0 = w.first + u * STRIDE;
-        int code = 0;
-        const bool plain = t0 + SUB <= d.T;                    // no masked key
-        if (plain) {
-            if (u == 0) {
-                stats_anchor(qa, kb, cref, hf, n);
-#pragma unroll
-                for (int h = 0; h < 4; ++h) cr[h] = load_cref(cref, h, hf);
+            for (int J = 0; J < NT; ++J) z[J] = floatx4{};
+            // two subtiles a step: the operands, and with an odd number of groups the accumulators, change places
+            floatx4 acc[2][2][2];
+            set_nothing(acc[0]);
+            set_nothing(acc[1]);
+            for (; u + 1 < n_plain; u += 2) {
+                ks.next(u, ka, kb);
+                stats_fast<0>(qa, ka, acc, z, a.c1);
+                ks.next(u + 1, kb, ka);
+                stats_fast<NG & 1>(qa, kb, acc, z, a.c1);
             }
-            code = stats_fast<4, 8, true>(qa, kb, acc, cr, z, a.c1, lim);
+            if (u < n_plain) {
+                ks.next(u++, ka, kb);
+                stats_fast<0>(qa, ka, acc, z, a.c1);
+                stats_add<0>(acc[(NG & 1) ^ 1], NG - 1, z, a.c1, 0, 0, 0);
+                copy_subtile(ka, kb);
+            } else {
+                stats_add<0>(acc[1], NG - 1, z, a.c1, 0, 0, 0);
+            }
+            // the subtiles with masked keys
+            for (; u < w.n_sub; ++u) {
+                ks.next(u, ka, kb);
+#pragma unroll
+                for (int j = 0; j < NG; ++j) {
+                    multiply(qa, ka, j, acc[j & 1]);
+                    stats_add<W>(acc[j & 1], j, z, a.c1, w.first + u * STRIDE + n, g, d.T);
+                }
+                copy_subtile(ka, kb);
+            }
+            // per row: the lane group's 16 sums together
+            float least = INFINITY, most = 0.f;
+#pragma unroll
+            for (int J = 0; J < NT; ++J) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    z[J][i] = group_sum(z[J][i]);
+                    least = fminf(least, z[J][i]);
+                    most = fmaxf(most, z[J][i]);
+                }
+                if (n == 0) {
+                    floatx4 *st = state + (TILE * J + 4 * g) / 2;
+                    st[0] = floatx4{0.f, z[J][0], 0.f, z[J][1]};
+                    st[1] = floatx4{0.f, z[J][2], 0.f, z[J][3]};
+                }
+            }
+            again = most > SUM_MOST || (w.first <= d.T && least < SUM_LEAST);
+            if (w.first > d.T)                                 // inside the window: of the rows that see the stream's first key
+                for (int pos = lane; pos < MP; pos += 64)
+                    again |= w.first <= d.T + R::row_of(pos) % W && reinterpret_cast<const float *>(state)[2 * pos + 1] < SUM_LEAST;
+        } else {
+            for (; u < w.n_sub; ++u) {
+                ks.next(u, ka, kb);
+                stats_careful<NT, W>(a, w.p, ka, state, u == 0, w.first + u * STRIDE, n, g);
+                copy_subtile(ka, kb);
+            }
         }
-        if (code == STATS_OK) { waiting = true; continue; }
-        const bool prev_failed = plain && code == 3;
-        if (waiting && (!plain || prev_failed))                // the waiting head was not reduced by the fast body
-            stats_head_careful(acc[1], z[3], cref + 96, a.c1, false, t0 - STRIDE + n, hf, n, Tq, d.L);
-        stats_careful(qa, kb, cref, z, a.c1, prev_failed ? 0 : code, u == 0 && !plain, t0 + n, hf, n, Tq, d.L);
-        waiting = false;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
-#pragma unroll
-        for (int h = 0; h < 4; ++h) cr[h] = load_cref(cref, h, hf);     // the careful body may have moved references
-    }
-    if (waiting) {
-        if (!stats_guard(acc[1], lim)) stats_add(acc[1], z[3], a.c1);
-        else stats_head_careful(acc[1], z[3], cref + 96, a.c1, false, w.first + (w.n_sub - 1) * STRIDE + n, hf, n, Tq, d.L);
+        if (careful || !__any(again)) break;
+        ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
+        ks.issue_first();
     }
 
-    // ---- per row: add the 32 lane sums (same reference) through the wavefront's ring (every load has landed),
-    // then combine the four wavefronts' (reference, sum) pairs
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    float *scr_z = reinterpret_cast<float *>(ring);            // [128 rows][32 lanes]
-#pragma unroll
-    for (int h = 0; h < 4; ++h)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) scr_z[(h * 32 + query_of(i, hf)) * 32 + n] = z[h][i];
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int rr = 0; rr < 2; ++rr) {
-        const int row = lane + 64 * rr;                         // row = h * 32 + query
-        float zz = 0.f;
-        for (int j = 0; j < 32; ++j) zz += scr_z[row * 32 + ((j + lane) & 31)];
-        const int q = row & 31, hfq = (q >> 2) & 1, iq = ((q >> 3) << 2) | (q & 3);
-        wg_red[(wave * M_ROWS + row) * 2] = -cref[(row >> 5) * 32 + hfq * 16 + iq] * a.c1;   // reference, log2 domain
-        wg_red[(wave * M_ROWS + row) * 2 + 1] = zz;
-    }
+    // ---- the four wavefronts' (reference, sum) pairs together
     __syncthreads();
-    if (threadIdx.x < M_ROWS) {
-        const int row = threadIdx.x;
-        float m = -INFINITY;
+    const int row = R::row_of(threadIdx.x), M = d.G * W;
+    if (threadIdx.x < MP && row < M) {
+        float ref[WAVES], sum[WAVES], m = -INFINITY, zz = 0.f;
+#pragma unroll
         for (int wv = 0; wv < WAVES; ++wv) {
-            const float *e = wg_red + (wv * M_ROWS + row) * 2;
-            if (e[1] > 0.f) m = fmaxf(m, e[0]);
+            const float *e = reinterpret_cast<const float *>(wg_state + wv * (MP / 2)) + threadIdx.x * 2;
+            ref[wv] = -e[0] * a.c1;                            // log2 domain
+            sum[wv] = e[1];
+            if (sum[wv] > 0.f) m = fmaxf(m, ref[wv]);
         }
-        float zz = 0.f;
-        for (int wv = 0; wv < WAVES; ++wv) {
-            const float *e = wg_red + (wv * M_ROWS + row) * 2;
-            if (e[1] > 0.f) zz += e[1] * __builtin_amdgcn_exp2f(e[0] - m);
-        }
-        float *o = a.partial + (((int64_t)w.pv * a.n_chunks + w.chunk) * M_ROWS + row) * 2;
+#pragma unroll
+        for (int wv = 0; wv < WAVES; ++wv)
+            if (sum[wv] > 0.f) zz += sum[wv] * __builtin_amdgcn_exp2f(ref[wv] - m);
+        float *o = a.partial + (((int64_t)w.p * a.n_chunks + w.chunk) * M + row) * 2;
         o[0] = m;
         o[1] = zz;
     }
 }
+template <int NT> constexpr int stats_lds() { return WAVES * RING_BYTES + WAVES * TILE * NT * 2 * 4; }   // rings + the rows' state
 
 // ------------------------------------------------------------------ pass 2
 // Folds the (reference, sum) pairs c0, c0 + step, ... < n of one row (`stride` floats apart) into (m, z).  The pairs
 // are read sixteen at a time, all loads in flight: what this costs a workgroup is their latency, not their bytes.
+constexpr int FOLD_BATCH = 16;
+__device__ __forceinline__ void fold_load(float2 (&e)[FOLD_BATCH], const float *pp, int64_t stride, int c, int step, int n)
+{
+#pragma unroll
+    for (int j = 0; j < FOLD_BATCH; ++j) e[j] = *reinterpret_cast<const float2 *>(pp + (int64_t)min(c + j * step, n - 1) * stride);
+}
+__device__ __forceinline__ void fold_add(float2 (&e)[FOLD_BATCH], int c, int step, int n, float &m, float &z)
+{
+    float mn = m;
+#pragma unroll
+    for (int j = 0; j < FOLD_BATCH; ++j) {
+        if (c + j * step >= n) e[j].y = 0.f;
+        if (e[j].y > 0.f) mn = fmaxf(mn, e[j].x);
+    }
+    if (z > 0.f) z *= __builtin_amdgcn_exp2f(m - mn);
+#pragma unroll
+    for (int j = 0; j < FOLD_BATCH; ++j)
+        if (e[j].y > 0.f) z += e[j].y * __builtin_amdgcn_exp2f(e[j].x - mn);
+    m = mn;
+}
 __device__ __forceinline__ void fold_pairs(const float *pp, int64_t stride, int c0, int step, int n, float &m, float &z)
 {
-    constexpr int B = 16;
     m = -INFINITY;
     z = 0.f;
-    for (int c = c0; c < n; c += step * B) {
-        float2 e[B];
-#pragma unroll
-        for (int j = 0; j < B; ++j) e[j] = *reinterpret_cast<const float2 *>(pp + (int64_t)min(c + j * step, n - 1) * stride);
-        float mn = m;
-#pragma unroll
-        for (int j = 0; j < B; ++j) {
-            if (c + j * step >= n) e[j].y = 0.f;
-            if (e[j].y > 0.f) mn = fmaxf(mn, e[j].x);
+    for (int c = c0; c < n; c += step * FOLD_BATCH) {
+        float2 e[FOLD_BATCH];
+        fold_load(e, pp, stride, c, step, n);
+        fold_add(e, c, step, n, m, z);
+    }
+}
+
+// A row's log-sum-exp in the log2 domain plus log2 of the heads that the mean is over, into lse2[position]; +inf for
+// padding.  Given by the caller, or folded from the chunk partials of pass 1 by several threads per row.  256 threads;
+// meanwhile() runs when the first loads are on their way; ends without a barrier behind the last stores.
+template <int NT, int W, typename F>
+__device__ __forceinline__ void fold_rows(const ScoreArgs &a, int p, float log2_heads, float *lse2, float2 *comb, F &&meanwhile)
+{
+    constexpr int PER = NT <= 1 ? 16 : NT <= 2 ? 32 : NT <= 4 ? 64 : NT <= 8 ? 128 : 256, PARTS = 256 / PER;
+    const int M = a.d.G * W, pos = threadIdx.x % PER, part = threadIdx.x / PER;
+    const int r = Rows<NT, W>::row_of(pos);
+    const bool real = pos < Rows<NT, W>::MP && r < M;
+    float m = -INFINITY, z = 0.f;
+    if (a.lse) {
+        if (real && part == 0) { m = a.lse[(int64_t)p * M + r]; z = 1.f; }
+        meanwhile();
+        m *= LOG2E;
+    } else {
+        const float *pp = a.merged + ((int64_t)p * a.pc * M + min(r, M - 1)) * 2;
+        float2 e[FOLD_BATCH];
+        if (real && part < a.pc) fold_load(e, pp, M * 2, part, PARTS, a.pc);
+        meanwhile();
+        if (real && part < a.pc) fold_add(e, part, PARTS, a.pc, m, z);
+        for (int c = part + PARTS * FOLD_BATCH; real && c < a.pc; c += PARTS * FOLD_BATCH) {
+            fold_load(e, pp, M * 2, c, PARTS, a.pc);
+            fold_add(e, c, PARTS, a.pc, m, z);
         }
-        if (z > 0.f) z *= __builtin_amdgcn_exp2f(m - mn);
-#pragma unroll
-        for (int j = 0; j < B; ++j)
-            if (e[j].y > 0.f) z += e[j].y * __builtin_amdgcn_exp2f(e[j].x - mn);
-        m = mn;
     }
-}
-
-// acc = <q,k> - (lse2 + log2 G)/c1 per (head, query), so exp2(c1 * acc) = A / G
-template <bool EDGE, bool ASSIGN>
-__device__ __forceinline__ void columns_head(const floatx16 &acc, float (&ab)[16], float c1, int t, int hf, int T, int L)
-{
+    if (PARTS > 1) {
+        comb[threadIdx.x] = make_float2(m, z);
+        __syncthreads();
+        if (part != 0) return;
+        float2 e[PARTS];
+        m = -INFINITY;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        float v = __builtin_amdgcn_exp2f(acc[i] * c1);
-        if (EDGE && !(t < L && t <= T + query_of(i, hf))) v = 0.f;      // causal inside the window
-        ab[i] = ASSIGN ? v : ab[i] + v;                                   // Eq. barA, accumulated over the heads
+        for (int j = 0; j < PARTS; ++j) { e[j] = comb[j * PER + pos]; m = fmaxf(m, e[j].x); }
+        z = 0.f;
+#pragma unroll
+        for (int j = 0; j < PARTS; ++j)
+            if (e[j].y > 0.f) z += e[j].y * __builtin_amdgcn_exp2f(e[j].x - m);
     }
+    if (pos < Rows<NT, W>::MP) lse2[pos] = real ? m + __builtin_amdgcn_logf(z) + log2_heads : INFINITY;
 }
 
-// x of this lane plus x of the lane 32 away: one swap of the upper half of a register with the lower half of
-// its copy, so both results hold (lower-half value, upper-half value) in every lane
-__device__ __forceinline__ float add_other_half(float x)
+// Adds group j's probabilities (acc = <q,k>, so exp2(c1 * acc - lse2) = A / heads) to the head means; nl(J): minus the lse2
+// of tile J's rows; t: the lane's key in the first key tile
+template <int NT, int W, bool EDGE, typename NL>
+__device__ __forceinline__ void columns_add(const floatx4 (&acc)[2][2], int j, NL nl, float (&ab)[2][W / 4], float c1, int t, int g, int T, int L)
 {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// column sum (Eq. st, lane half 0) or entropy term (inner sum of Eq. Dk, lane half 1) from the lane's 16 Abar values
-__device__ __forceinline__ float columns_finish(const float (&ab)[16], float eps, int hf)
-{
-    float s_part = 0.f;
+    using R = Rows<NT, W>;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) s_part += ab[i];
-    const float s = add_other_half(s_part);
-    const float inv_s = s > 0.f ? __builtin_amdgcn_rcpf(s) : 0.f;
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int J = 2 * j + r, key = t + TILE * kt;
+                if (J >= NT) continue;
+                float v = __builtin_amdgcn_exp2f(fmaf(acc[r][kt][i], c1, nl(J)[i]));
+                if (EDGE && !(key < L && key <= T + R::query(J, g, i))) v = 0.f;          // causal inside the window
+                float &to = ab[kt][R::slot(J, i)];
+                to = R::first(J, i) ? v : to + v;                                         // Eq. barA
+            }
+}
+
+// Sums of two values over the four lane groups: lanes of the even groups get the first value's, the others the second's.
+// permlane16_swap exchanges the odd groups of its first operand with the even groups of its second, permlane32_swap the
+// upper half of the first with the lower half of the second.
+__device__ __forceinline__ float sum_groups(float x0, float x1)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x0), __float_as_uint(x1), false, false);
+    const float y = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+
+// Column sums (Eq. st, lanes 0 .. 31: one of the subtile's 32 keys each) and entropy terms (inner sum of Eq. Dk, lanes 32
+// .. 63) from the lane's head means
+template <int NS>
+__device__ __forceinline__ float columns_finish(const float (&ab)[2][NS], float eps, int lane)
+{
+    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < NS; ++i) { s0 += ab[0][i]; s1 += ab[1][i]; }
+    const float s = sum_groups(s0, s1);
+    const float inv = s > 0.f ? __builtin_amdgcn_rcpf(s) : 0.f;
+    const auto b = __builtin_amdgcn_permlane16_swap(__float_as_uint(inv), __float_as_uint(inv), false, false);
+    const float inv0 = __uint_as_float(b[0]), inv1 = __uint_as_float(b[1]);                // of the two keys of this lane
     // sum_i Ahat_i log2(Ahat_i + eps) with Ahat_i = Abar_i / s: the division of the weights is applied once, to the sum
-    float e_part = 0.f;
+    float e0 = 0.f, e1 = 0.f;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) e_part = fmaf(ab[i], __builtin_amdgcn_logf(fmaf(ab[i], inv_s, eps)), e_part);
-    const float ent = -LN2 * inv_s * add_other_half(e_part);
-    return hf == 0 ? s : ent;
+    for (int i = 0; i < NS; ++i) {
+        e0 = fmaf(ab[0][i], __builtin_amdgcn_logf(fmaf(ab[0][i], inv0, eps)), e0);
+        e1 = fmaf(ab[1][i], __builtin_amdgcn_logf(fmaf(ab[1][i], inv1, eps)), e1);
+    }
+    const float ent = -LN2 * inv * sum_groups(e0, e1);
+    return lane < 32 ? s : ent;
 }
 
-// One subtile: head h is multiplied into acc[h & 1] while head h-1 is exponentiated from the other accumulator;
-// returns the output value of the PREVIOUS subtile.
-template <bool EDGE>
-__device__ __forceinline__ float columns_body(const bf16x8 (&qa)[4][8], const bf16x8 (&kb)[8], const floatx16 (&cinit)[4],
-                                              floatx16 (&acc)[2], float (&ab)[16], float c1, float eps, int t_prev, int t_cur,
-                                              int hf, int T, int L)
-{
-    acc[0] = chain<0, 8>(qa[0], kb, cinit[0]);
-    columns_head<EDGE, false>(acc[1], ab, c1, t_prev, hf, T, L);       // last head of the previous subtile
-    const float prev = columns_finish(ab, eps, hf);
-    acc[1] = chain<0, 8>(qa[1], kb, cinit[1]);
-    columns_head<EDGE, true>(acc[0], ab, c1, t_cur, hf, T, L);
-    acc[0] = chain<0, 8>(qa[2], kb, cinit[2]);
-    columns_head<EDGE, false>(acc[1], ab, c1, t_cur, hf, T, L);
-    acc[1] = chain<0, 8>(qa[3], kb, cinit[3]);
-    columns_head<EDGE, false>(acc[0], ab, c1, t_cur, hf, T, L);
-    return prev;
-}
-
+// Column sums and entropy terms.  STORE: instead of them, write the head-group mean Abar[query][key] itself (for the mean
+// over ALL heads of a layer, which is formed across KV heads afterwards), layout [problem][W / 4][L][4]: consecutive
+// window queries of a key per store.
+//
+// Results are stored one iteration late, at the top of the next iteration, so that the multiply/exponentiate section of
+// an iteration is a single straight-line region.  The subtiles before the window (no mask) and the ones that touch the
+// window or the end of the sequence run in two consecutive loops, which keeps the masked body out of the hot loop.
+template <int NT, int W, bool STORE, int KS>
 __global__ void __launch_bounds__(WAVES * 64)
 score_mfma_columns(ScoreArgs a)
 {
+    using R = Rows<NT, W>;
+    constexpr int NG = R::NG, NS = R::NS;
     extern __shared__ __attribute__((aligned(8192))) char lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, hf = lane >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int n = lane & 15, g = lane >> 4;
     const Dims &d = a.d;
-    char *ring = lds + __builtin_amdgcn_readfirstlane(wave) * RING_BYTES;
-    float *lse2 = reinterpret_cast<float *>(lds + WAVES * RING_BYTES);       // [128] log2-domain lse + log2 G
-    float *comb = lse2 + M_ROWS;                                             // [256][2] combine scratch
+    char *ring = lds + wave * RING_BYTES;
+    float2 *comb = reinterpret_cast<float2 *>(lds + WAVES * RING_BYTES);     // [256] combine scratch
+    float *lse2 = reinterpret_cast<float *>(comb + 256);                     // [MP] see fold_rows
     const WaveWork w = wave_work(a, wave);
 
-    // row log-sum-exp: given by the caller, or combined here from the chunk partials of pass 1 (two threads per
-    // row, each folding every other chunk).  Its loads and the queries' come before the keys': loads return in order,
-    // and the fold would otherwise wait for the first keys from HBM, the queries for the fold.
-    bf16x8 qa[4][8];
-    load_queries(qa, a.q, d, w.p, 0, n, hf);
-    KeyStream<NBUF> ks;
+    // queries and the first of the fold's loads before the keys, as loads return in order; all are in flight together
+    bf16x8 qa[NT][KS];
+    using Stream = typename StreamFor<NT, KS, NT <= 8>::type;
+    Stream ks;
     ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    {
-        const int row = threadIdx.x & (M_ROWS - 1), half = threadIdx.x >> 7;
-        float m, zz;
-        if (a.lse) {
-            m = a.lse[(int64_t)w.p * M_ROWS + row] * LOG2E;
-            zz = half == 0 ? 1.f : 0.f;
-        } else {
-            fold_pairs(a.merged + ((int64_t)w.p * a.pc * M_ROWS + row) * 2, M_ROWS * 2, half, 2, a.pc, m, zz);
-        }
-        pin_queries(qa);
-        ks.prime();
-        comb[threadIdx.x * 2] = m;
-        comb[threadIdx.x * 2 + 1] = zz;
+    if constexpr (KS == 4) {
+        using Q = QueryStage<NT>;
+        const uint32_t ring0 = __builtin_amdgcn_readfirstlane(lds_addr(lds));
+        Q::template issue<W>(a, w.p, ring0, wave, lane);
+        fold_rows<NT, W>(a, w.p, a.log2_G, lse2, comb, [&]() __attribute__((always_inline)) { ks.issue_first(0, NBUF - Q::BUFS); });
+        wait_loads(min(NBUF - Q::BUFS, w.n_sub));
+        lds_barrier();
+        Q::read(qa, ring0, lane);
+        pin_queries<NT, W>(qa, a, lane);
+        lds_barrier();
+        ks.issue_first(NBUF - Q::BUFS, NBUF);
+    } else {
+        load_queries<NT, W>(qa, a, w.p, lane);
+        fold_rows<NT, W>(a, w.p, a.log2_G, lse2, comb, []() {});
+        pin_queries<NT, W>(qa, a, lane);
+        __syncthreads();
     }
-    __syncthreads();
-    if (threadIdx.x < M_ROWS) {
-        const float m0 = comb[threadIdx.x * 2], z0 = comb[threadIdx.x * 2 + 1];
-        const float m1 = comb[(threadIdx.x + M_ROWS) * 2], z1 = comb[(threadIdx.x + M_ROWS) * 2 + 1];
-        const float mn = fmaxf(m0, m1);
-        float zz = 0.f;
-        if (z0 > 0.f) zz += z0 * __builtin_amdgcn_exp2f(m0 - mn);
-        if (z1 > 0.f) zz += z1 * __builtin_amdgcn_exp2f(m1 - mn);
-        lse2[threadIdx.x] = mn + __builtin_amdgcn_logf(zz) + 2.0f;        // + log2(G): exp2 then yields A / G
-    }
-    __syncthreads();
+    bf16x8 ka[2][KS], ahead[2][KS];
+    auto &kb = Stream::AHEAD ? ahead : ka;
+    ks.start(ka);
 
-    floatx16 cinit[4], acc[2];
-    const float inv_c1 = 1.0f / a.c1;
+    floatx4 neg[NT], acc[2][2][2];
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
+    for (int J = 0; J < NT; ++J) neg[J] = -*reinterpret_cast<const floatx4 *>(lse2 + TILE * J + 4 * g);
+    auto nl = [&](int J) __attribute__((always_inline)) { return neg[J]; };
+    set_nothing(acc[0]);                                       // the "previous subtile" of iteration 0 is a no-op
+    set_nothing(acc[1]);
+    float ab[2][NS];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            cinit[h][i] = -lse2[h * 32 + query_of(i, hf)] * inv_c1;
-            acc[h & 1][i] = -INFINITY;                         // makes the "previous subtile" of iteration 0 a no-op
-        }
-    }
-    float ab[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) ab[i] = 0.f;
-    float *out = (hf == 0 ? a.s_out : a.e_out) + (int64_t)w.p * d.L;
+    for (int i = 0; i < NS; ++i) ab[0][i] = ab[1][i] = 0.f;
+    float *out = (lane < 32 ? a.s_out : a.e_out) + (int64_t)w.p * d.L;
 
-    // Results are stored one iteration late, at the top of the next iteration, so that the multiply/exponentiate
-    // section of an iteration is a single straight-line region.  The subtiles before the window (no mask) and
-    // the ones that touch the window or the end of the sequence run in two consecutive loops, which keeps the
-    // masked body and its control-flow joins out of the hot loop.
-    float pending = 0.f;
-    int pending_t = -1;
-    const int n_plain = w.first + SUB <= d.T ? min(w.n_sub, (d.T - SUB - w.first) / STRIDE + 1) : 0;
+    float pending = 0.f;                                       // result of subtile pending_u
+    int pending_u = -1;
+    auto finish = [&](int u, bool edge) __attribute__((always_inline)) {                      // the head means of subtile u are complete
+        if (!STORE) {
+            pending = columns_finish<NS>(ab, a.eps, lane);
+            pending_u = u;
+            return;
+        }
+        if (u < 0) return;
+#pragma unroll
+        for (int kt = 0; kt < 2; ++kt) {
+            const int t = w.first + u * STRIDE + TILE * kt + n;
+            if (edge && t >= d.L) continue;
+            float *row = a.abar + (int64_t)w.p * (W / 4) * d.L * 4;
+            if (W == 8) *reinterpret_cast<float2 *>(row + ((int64_t)(g >> 1) * d.L + t) * 4 + 2 * (g & 1)) = make_float2(ab[kt][0], ab[kt][1]);
+            else
+#pragma unroll
+                for (int J = 0; J < R::PER_HEAD; ++J)
+                    *reinterpret_cast<float4 *>(row + ((int64_t)(4 * J + g) * d.L + t) * 4) =
+                        make_float4(ab[kt][4 * J], ab[kt][4 * J + 1], ab[kt][4 * J + 2], ab[kt][4 * J + 3]);
+        }
+    };
+    auto put = [&](bool edge) __attribute__((always_inline)) {
+        const int t = w.first + pending_u * STRIDE + (lane & 31);
+        if (!STORE && pending_u >= 0 && (!edge || t < d.L)) out[t] = pending;
+    };
     int u = 0;
-    for (; u < n_plain; ++u) {
-        if (pending_t >= 0) out[pending_t] = pending;
-        bf16x8 kb[8];
-        ks.fetch(u, kb);
-        const int t_cur = w.first + u * STRIDE + n;
-        pending = columns_body<false>(qa, kb, cinit, acc, ab, a.c1, a.eps, t_cur - STRIDE, t_cur, hf, d.T, d.L);
-        pending_t = u > 0 ? t_cur - STRIDE : -1;
-    }
-    for (; u < w.n_sub; ++u) {
-        if (pending_t >= 0 && pending_t < d.L) out[pending_t] = pending;
-        bf16x8 kb[8];
-        ks.fetch(u, kb);
-        const int t_cur = w.first + u * STRIDE + n;
-        pending = columns_body<true>(qa, kb, cinit, acc, ab, a.c1, a.eps, t_cur - STRIDE, t_cur, hf, d.T, d.L);
-        pending_t = u > 0 ? t_cur - STRIDE : -1;
-    }
-    if (pending_t >= 0 && pending_t < d.L) out[pending_t] = pending;
-    if (w.n_sub > 0) {
-        const int t_last = w.first + (w.n_sub - 1) * STRIDE + n;
-        columns_head<true, false>(acc[1], ab, a.c1, t_last, hf, d.T, d.L);
-        const float v = columns_finish(ab, a.eps, hf);
-        if (t_last < d.L) out[t_last] = v;
-    }
-}
-
-// ------------------------------------------------------------------ pass 2, 256 rows
-// Eight 32-row tiles.  W = 64: tile j holds head j / 2, window queries 32 (j % 2) .. +32; W = 32: tile j holds
-// head j.  Groups of fewer heads than the tiles hold (G = 5 .. 7 with W = 32, G = 3 with W = 64) leave the last
-// tiles as padding: zero queries and an infinite log-sum-exp, so they add exact zeros.  Same pipeline as above with
-// the tiles rotating through two accumulators; ab[b] collects the head mean of the window queries 32 b .. 32 b + 31.
-template <int W> struct Tiles8 {
-    static constexpr int NB = W / 32;                                        // 32-query blocks of the window
-    __host__ __device__ static constexpr int head(int j) { return W == 64 ? j / 2 : j; }
-    __host__ __device__ static constexpr int qoff(int j) { return W == 64 ? 32 * (j % 2) : 0; }
-    __host__ __device__ static constexpr int blk(int j) { return W == 64 ? j % 2 : 0; }
-    __host__ __device__ static constexpr bool first(int j) { return W == 64 ? j < 2 : j == 0; }   // first tile of its block
-    // where pass 1 stored the statistics of tile j: (row block, 32-row group inside it)
-    __host__ __device__ static constexpr int p1_block(int j) { return W == 64 ? j % 2 : j / 4; }
-    __host__ __device__ static constexpr int p1_group(int j) { return W == 64 ? j / 2 : j % 4; }
-};
-constexpr int M_ROWS64 = 256;
-constexpr int P2W_LDS = 4 * 4 * BUF_BYTES + M_ROWS64 * 4 + 8 * 32 * 4;   // rings + the rows' log-sum-exp + C operands
-
-template <int NB>
-__device__ __forceinline__ float columns_finish8t(const float (&ab)[NB][16], float eps, int hf)
-{
-    float s_part = 0.f;
+    // one subtile: group j is multiplied into acc[(j + PAR) & 1] while the group before it is exponentiated
+    auto subtile = [&](bf16x8 (&cur)[2][KS], bf16x8 (&nxt)[2][KS], auto par, auto edge_t) __attribute__((always_inline)) {
+        constexpr int PAR = decltype(par)::value;
+        constexpr bool EDGE = decltype(edge_t)::value;
+        put(EDGE);
+        ks.next(u, cur, nxt);
+        const int t = w.first + u * STRIDE + n;
 #pragma unroll
-    for (int v = 0; v < NB; ++v)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) s_part += ab[v][i];
-    const float s = add_other_half(s_part);
-    const float inv_s = s > 0.f ? __builtin_amdgcn_rcpf(s) : 0.f;
-    float e_part = 0.f;
-#pragma unroll
-    for (int v = 0; v < NB; ++v)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) e_part = fmaf(ab[v][i], __builtin_amdgcn_logf(fmaf(ab[v][i], inv_s, eps)), e_part);
-    const float ent = -LN2 * inv_s * add_other_half(e_part);
-    return hf == 0 ? s : ent;
-}
-
-__device__ __forceinline__ floatx16 load_c64(const float *cmat, int j, int hf)
-{
-    return *reinterpret_cast<const floatx16 *>(cmat + j * 32 + hf * 16);
-}
-
-// One subtile; returns the output value of the PREVIOUS subtile (its last tile waits in acc[1])
-template <int W, bool EDGE, int J>
-__device__ __forceinline__ void columns_tile8t(const floatx16 &acc, float (&ab)[Tiles8<W>::NB][16], float c1, int t, int hf,
-                                               int T, int L)
-{
-    using TL = Tiles8<W>;
-    columns_head<EDGE, TL::first(J)>(acc, ab[TL::blk(J)], c1, t, hf, T + TL::qoff(J), L);
-}
-
-template <int W, bool EDGE>
-__device__ __forceinline__ float columns_body8t(const bf16x8 (&qa)[8][8], const bf16x8 (&kb)[8], const float *cmat,
-                                                floatx16 (&acc)[2], float (&ab)[Tiles8<W>::NB][16], float c1, float eps,
-                                                int t_prev, int t_cur, int hf, int T, int L)
-{
-    using TL = Tiles8<W>;
-    acc[0] = chain<0, 8>(qa[0], kb, load_c64(cmat, 0, hf));
-    columns_head<EDGE, false>(acc[1], ab[TL::blk(7)], c1, t_prev, hf, T + TL::qoff(7), L);     // tile 7 of the previous subtile
-    const float prev = columns_finish8t<TL::NB>(ab, eps, hf);
-    acc[1] = chain<0, 8>(qa[1], kb, load_c64(cmat, 1, hf));
-    columns_tile8t<W, EDGE, 0>(acc[0], ab, c1, t_cur, hf, T, L);
-    acc[0] = chain<0, 8>(qa[2], kb, load_c64(cmat, 2, hf));
-    columns_tile8t<W, EDGE, 1>(acc[1], ab, c1, t_cur, hf, T, L);
-    acc[1] = chain<0, 8>(qa[3], kb, load_c64(cmat, 3, hf));
-    columns_tile8t<W, EDGE, 2>(acc[0], ab, c1, t_cur, hf, T, L);
-    acc[0] = chain<0, 8>(qa[4], kb, load_c64(cmat, 4, hf));
-    columns_tile8t<W, EDGE, 3>(acc[1], ab, c1, t_cur, hf, T, L);
-    acc[1] = chain<0, 8>(qa[5], kb, load_c64(cmat, 5, hf));
-    columns_tile8t<W, EDGE, 4>(acc[0], ab, c1, t_cur, hf, T, L);
-    acc[0] = chain<0, 8>(qa[6], kb, load_c64(cmat, 6, hf));
-    columns_tile8t<W, EDGE, 5>(acc[1], ab, c1, t_cur, hf, T, L);
-    acc[1] = chain<0, 8>(qa[7], kb, load_c64(cmat, 7, hf));
-    columns_tile8t<W, EDGE, 6>(acc[0], ab, c1, t_cur, hf, T, L);
-    return prev;
-}
-
-template <int W>
-__global__ void __launch_bounds__(WAVES * 64)
-score_mfma_columns8t(ScoreArgs a)
-{
-    using TL = Tiles8<W>;
-    extern __shared__ __attribute__((aligned(8192))) char lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, hf = lane >> 5;
-    const Dims &d = a.d;
-    char *ring = lds + __builtin_amdgcn_readfirstlane(wave) * RING_BYTES;
-    float *lse2 = reinterpret_cast<float *>(lds + WAVES * RING_BYTES);       // [256] log2-domain lse + log2 G, row h * W + i
-    float *cmat = lse2 + M_ROWS64;                                           // [8 tiles][2 halves][16] C operands
-    const WaveWork w = wave_work(a, wave);
-
-    KeyStream<NBUF> ks;
-    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-
-    // one thread per row (h, i): its log-sum-exp, given by the caller or folded from the chunk partials of pass 1,
-    // which are stored per 128-row block (see Tiles8::p1_block / p1_group)
-    {
-        const int r = threadIdx.x, h = r / W, i = r % W;
-        const int j = W == 64 ? 2 * h + i / 32 : h;                           // the row's tile
-        float m = -INFINITY, zz = 0.f;
-        if (h >= d.G) {                                                       // padding row
-            m = INFINITY;
-            zz = 1.f;
-        } else if (a.lse) {
-            m = a.lse[(int64_t)w.p * d.G * W + r] * LOG2E;
-            zz = 1.f;
-        } else {
-            fold_pairs(a.merged + (((int64_t)(w.p * 2 + TL::p1_block(j)) * a.pc) * M_ROWS + TL::p1_group(j) * 32 + (i & 31)) * 2, M_ROWS * 2, 0, 1, a.pc, m, zz);
+        for (int j = 0; j < NG; ++j) {
+            multiply(qa, cur, j, acc[(j + PAR) & 1]);
+            if (j == 1) finish(u - 1, EDGE);                   // under this group's products
+            columns_add<NT, W, EDGE>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, nl, ab, a.c1, j > 0 ? t : t - STRIDE, g, d.T, d.L);
+            if (NG == 1) finish(u - 1, EDGE);
         }
-        lse2[r] = m + __builtin_amdgcn_logf(zz) + a.log2_G;                   // + log2(G): exp2 then yields A / G
-    }
-    __syncthreads();
-    {
-        const float inv_c1 = 1.0f / a.c1;
-        const int j = threadIdx.x >> 5, slot = threadIdx.x & 31;
-        const int i = TL::qoff(j) + query_of(slot & 15, slot >> 4);
-        cmat[threadIdx.x] = -lse2[TL::head(j) * W + i] * inv_c1;
-    }
-    __syncthreads();
-
-    bf16x8 qa[8][8];
+        // the means as they are here: keeps the compiler from moving this subtile's exponentials behind the next one's loads
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (TL::head(j) < d.G) {
-            const uint16_t *row = a.q + q_row_offset(d, w.p, TL::head(j), TL::qoff(j) + n);
-#pragma unroll
-            for (int s = 0; s < 8; ++s) qa[j][s] = *reinterpret_cast<const bf16x8 *>(row + (2 * s + hf) * 8);
-        } else {
-#pragma unroll
-            for (int s = 0; s < 8; ++s) qa[j][s] = bf16x8{};
+        for (int i = 0; i < NS; ++i) asm volatile("" : "+v"(ab[0][i]), "+v"(ab[1][i]));
+        if (!STORE) asm volatile("" : "+v"(pending));
+        ++u;
+    };
+    // two subtiles a step: the operands, and with an odd number of groups the accumulators, change places
+    auto run = [&](int end, auto edge_t) __attribute__((always_inline)) {
+        using std::integral_constant;
+        while (u + 1 < end) {
+            subtile(ka, kb, integral_constant<int, 0>{}, edge_t);
+            subtile(kb, ka, integral_constant<int, NG & 1>{}, edge_t);
         }
-    }
-    pin_queries(qa);                                           // all 256 accumulation registers
-
-    floatx16 acc[2];
-    float ab[TL::NB][16];
+        if (u < end) {
+            subtile(ka, kb, integral_constant<int, 0>{}, edge_t);
+            copy_subtile(ka, kb);
+            if (NG & 1) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        acc[0][i] = acc[1][i] = -INFINITY;
+                for (int r = 0; r < 2; ++r)
 #pragma unroll
-        for (int v = 0; v < TL::NB; ++v) ab[v][i] = 0.f;
-    }
-    float *out = (hf == 0 ? a.s_out : a.e_out) + (int64_t)w.p * d.L;
-
-    float pending = 0.f;
-    int pending_t = -1;
-    const int n_plain = w.first + SUB <= d.T ? min(w.n_sub, (d.T - SUB - w.first) / STRIDE + 1) : 0;
-    int u = 0;
-    for (; u < n_plain; ++u) {
-        if (pending_t >= 0) out[pending_t] = pending;
-        bf16x8 kb[8];
-        ks.fetch_vgpr(u, kb);
-        const int t_cur = w.first + u * STRIDE + n;
-        pending = columns_body8t<W, false>(qa, kb, cmat, acc, ab, a.c1, a.eps, t_cur - STRIDE, t_cur, hf, d.T, d.L);
-        pending_t = u > 0 ? t_cur - STRIDE : -1;
-    }
-    for (; u < w.n_sub; ++u) {
-        if (pending_t >= 0 && pending_t < d.L) out[pending_t] = pending;
-        bf16x8 kb[8];
-        ks.fetch_vgpr(u, kb);
-        const int t_cur = w.first + u * STRIDE + n;
-        pending = columns_body8t<W, true>(qa, kb, cmat, acc, ab, a.c1, a.eps, t_cur - STRIDE, t_cur, hf, d.T, d.L);
-        pending_t = u > 0 ? t_cur - STRIDE : -1;
-    }
-    if (pending_t >= 0 && pending_t < d.L) out[pending_t] = pending;
+                    for (int kt = 0; kt < 2; ++kt) acc[1][r][kt] = acc[0][r][kt];
+            }
+        }
+    };
+    run(plain_subtiles(w, d.T), std::false_type{});
+    run(w.n_sub, std::true_type{});
+    put(true);
     if (w.n_sub > 0) {
-        const int t_last = w.first + (w.n_sub - 1) * STRIDE + n;
-        columns_head<true, false>(acc[1], ab[TL::blk(7)], a.c1, t_last, hf, d.T + TL::qoff(7), d.L);
-        const float v = columns_finish8t<TL::NB>(ab, a.eps, hf);
-        if (t_last < d.L) out[t_last] = v;
+        columns_add<NT, W, true>(acc[1], NG - 1, nl, ab, a.c1, w.first + (w.n_sub - 1) * STRIDE + n, g, d.T, d.L);
+        finish(w.n_sub - 1, true);
+        put(true);
     }
 }
+template <int NT> constexpr int columns_lds() { return WAVES * RING_BYTES + 256 * 8 + TILE * NT * 4; }   // rings + combine scratch + the rows' log-sum-exp
 
 // ------------------------------------------------------------------ pass 2, all heads of a layer
 // Head mean over all 32 heads of a layer with 8 KV heads (Eq. barA taken literally) without writing the
@@ -960,10 +943,10 @@ score_mfma_columns8t(ScoreArgs a)
 // accumulation registers of A operands) and adds exp2 over its 8 heads; the four partial sums of a subtile meet
 // in LDS, where the wavefronts take turns (subtile u: wavefront u % 4) to add them and to form the column sum
 // and the entropy term.  One barrier per subtile; it waits for LDS only, never for the loads in flight.
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int LAYER_KV = 8;                   // KV heads of a layer this kernel is built for (two per wavefront)
 constexpr int XCH_BYTES = 16 * 64 * 4;        // one wavefront's partial sums of a subtile, [4][64 lanes][4]
-constexpr int PL_LDS = WAVES * RING_BYTES + 2 * 3 * XCH_BYTES + WAVES * 8 * 32 * 4;   // rings + exchange + C operands
+constexpr int LAYER_NT = 16;                  // row tiles of a wavefront: two KV heads of four heads
+constexpr int PL_LDS = WAVES * RING_BYTES + 2 * 3 * XCH_BYTES + WAVES * LAYER_NT * TILE * 4;   // rings + exchange + log-sum-exps
 
 // Two key streams of one wavefront as one sequence of half-steps: element e = 2u + s is subtile u of stream s and
 // lives in ring buffer e % NBUF, refilled with element e + NBUF right after it is read.  Subtile u covers keys
@@ -978,9 +961,9 @@ struct PairStream {
     __device__ __forceinline__ void init(const uint16_t *k0, const uint16_t *k1, int64_t ks3_, char *ring, int first_, int n_sub, int L_, int lane_)
     {
         kp0 = k0; kp1 = k1; ks3 = ks3_; first = first_; n_el = 2 * n_sub; L = L_; lane = lane_;
-        const int n = lane & 31, hf = lane >> 5, r4 = lane >> 4, pos = lane & 15;
+        const int r4 = lane >> 4, pos = lane & 15;
         ring_lds = __builtin_amdgcn_readfirstlane(lds_addr(ring));
-        lane_addr0 = ring_lds + n * ROW_BYTES + ((hf ^ (n & 15)) << 4);
+        lane_addr0 = ring_lds + lane_read_offset(lane);
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) lane_off[jj] = (uint32_t)(r4 * ks3 * 2) + (uint32_t)(((pos ^ r4 ^ (4 * jj)) & 15) << 4);
     }
@@ -994,30 +977,39 @@ struct PairStream {
             else issue_subtile_fast(base, ks3 * 2, lane_off, buf_lds);
         } else issue_subtile_clamped(base, ks3 * 2, L - t0, buf_lds, lane);
     }
-    __device__ __forceinline__ void prime() const
+    // element 0 into kb
+    __device__ __forceinline__ void start(bf16x8 (&kb)[2][4]) const
     {
 #pragma unroll
         for (int e = 0; e < NBUF; ++e)
             if (e < n_el) issue(e);
+        if (n_el == 0) return;
+        wait_loads(min(NBUF, n_el) - 1);
+        read_subtile(lane_addr0, kb);
     }
-    __device__ __forceinline__ void fetch(int e, bf16x8 (&kb)[8]) const
+    // element e is in `cur`; element e + 1, if there is one, into `nxt`
+    __device__ __forceinline__ void next(int e, bf16x8 (&cur)[2][4], bf16x8 (&nxt)[2][4]) const
     {
-        wait_loads(min(NBUF - 1, n_el - 1 - e));
-        read_subtile_vgpr(lane_addr0 + (e % NBUF) * BUF_BYTES, kb);
+        have_subtile<false>(cur);
         if (e + NBUF < n_el) issue(e + NBUF);
+        if (e + 1 < n_el) {
+            wait_loads(min(NBUF - 1, n_el - 2 - e));
+            read_subtile(lane_addr0 + ((e + 1) % NBUF) * BUF_BYTES, nxt);
+        }
     }
 };
 
 // this lane's 16 partial sums into an exchange slot / the sum of `ab` and the three slots of a buffer
-__device__ __forceinline__ void xch_write(uint32_t addr, const float (&ab)[16])
+__device__ __forceinline__ void xch_write(uint32_t addr, const float (&ab)[2][8])
 {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const floatx4 v = {ab[4 * j], ab[4 * j + 1], ab[4 * j + 2], ab[4 * j + 3]};
+        const float *x = ab[j >> 1] + 4 * (j & 1);
+        const floatx4 v = {x[0], x[1], x[2], x[3]};
         asm volatile("ds_write_b128 %0, %1" : : "v"(addr + j * 1024), "v"(v) : "memory");
     }
 }
-__device__ __forceinline__ void xch_add(uint32_t addr, float (&ab)[16])
+__device__ __forceinline__ void xch_add(uint32_t addr, float (&ab)[2][8])
 {
     floatx4 v[3][4];
 #pragma unroll
@@ -1033,73 +1025,64 @@ __device__ __forceinline__ void xch_add(uint32_t addr, float (&ab)[16])
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) ab[4 * j + c] += v[0][j][c] + v[1][j][c] + v[2][j][c];
+        for (int c = 0; c < 4; ++c) ab[j >> 1][4 * (j & 1) + c] += v[0][j][c] + v[1][j][c] + v[2][j][c];
 }
-// all LDS writes of this wavefront done, then the workgroup barrier (global loads stay in flight)
-__device__ __forceinline__ void lds_barrier()
-{
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
 struct LayerCtx {
     uint32_t xch_lds;      // exchange area
-    int wave, lane, n, hf;
+    int wave, lane, n, g;
     int lo;                // first key of the chunk
     float c1, eps;
     int T, L;
-    float *out;            // s (lane half 0) or entropy term (lane half 1) row of this (sequence, layer)
+    float *out;            // s (lanes 0 .. 31) or entropy term (lanes 32 .. 63) row of this (sequence, layer)
 };
 
 // the partial sums `ab` of subtile `up` are complete in every wavefront: hand them to wavefront up % 4 ...
-__device__ __forceinline__ void layer_give(const LayerCtx &c, int up, const float (&ab)[16])
+__device__ __forceinline__ void layer_give(const LayerCtx &c, int up, const float (&ab)[2][8])
 {
     const int fin = up & 3;
     if (c.wave != fin) xch_write(c.xch_lds + (uint32_t)(((up & 1) * 3 + ((c.wave - fin - 1) & 3)) * XCH_BYTES + c.lane * 16), ab);
 }
 // ... which, after the barrier, adds them up and stores the two results of its key
-__device__ __forceinline__ void layer_take(const LayerCtx &c, int up, float (&ab)[16])
+__device__ __forceinline__ void layer_take(const LayerCtx &c, int up, float (&ab)[2][8])
 {
     if (c.wave != (up & 3)) return;
     xch_add(c.xch_lds + (uint32_t)((up & 1) * 3 * XCH_BYTES + c.lane * 16), ab);
-    const float v = columns_finish(ab, c.eps, c.hf);
-    const int t = c.lo + up * SUB + c.n;
+    const float v = columns_finish<8>(ab, c.eps, c.lane);
+    const int t = c.lo + up * SUB + (c.lane & 31);
     if (t < c.L) c.out[t] = v;
 }
 
-// One subtile u: tiles 0-3 (KV head 2w) then 4-7 (KV head 2w+1), rotating through two accumulators; tile 7 of the
-// previous subtile is exponentiated first, which completes that subtile's partial sums (handed over mid-way).
+// One subtile u: heads 0-3 (KV head 2w) then 4-7 (KV head 2w+1), a group of two tiles each, rotating through two sets of
+// accumulators; head 7 of the previous subtile is exponentiated first, which completes that subtile's partial sums (handed
+// over mid-way).
 template <bool EDGE>
-__device__ __forceinline__ void layer_body(const LayerCtx &c, const bf16x8 (&qa)[8][8], const PairStream &ps, const float *cm,
-                                           floatx16 (&acc)[2], float (&ab)[16], int u)
+__device__ __forceinline__ void layer_body(const LayerCtx &c, const bf16x8 (&qa)[LAYER_NT][4], const PairStream &ps,
+                                           const float *cm, bf16x8 (&ka)[2][4], bf16x8 (&kb)[2][4], floatx4 (&acc)[2][2][2],
+                                           float (&ab)[2][8], int u)
 {
     const int t_cur = c.lo + u * SUB + c.n, t_prev = t_cur - SUB;
-    bf16x8 kb[8];
-    ps.fetch(2 * u, kb);
-    acc[0] = chain<0, 8>(qa[0], kb, load_c64(cm, 0, c.hf));
-    columns_head<EDGE, false>(acc[1], ab, c.c1, t_prev, c.hf, c.T, c.L);
-    float abp[16];
+    auto nl = [&](int J) { return *reinterpret_cast<const floatx4 *>(cm + J * TILE); };    // from LDS: all registers are taken
+    float abp[2][8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) abp[i] = ab[i];
-    if (u > 0) layer_give(c, u - 1, abp);
-    acc[1] = chain<0, 8>(qa[1], kb, load_c64(cm, 1, c.hf));
-    columns_head<EDGE, true>(acc[0], ab, c.c1, t_cur, c.hf, c.T, c.L);
-    acc[0] = chain<0, 8>(qa[2], kb, load_c64(cm, 2, c.hf));
-    columns_head<EDGE, false>(acc[1], ab, c.c1, t_cur, c.hf, c.T, c.L);
-    acc[1] = chain<0, 8>(qa[3], kb, load_c64(cm, 3, c.hf));
-    columns_head<EDGE, false>(acc[0], ab, c.c1, t_cur, c.hf, c.T, c.L);
-    ps.fetch(2 * u + 1, kb);
-    acc[0] = chain<0, 8>(qa[4], kb, load_c64(cm, 4, c.hf));
-    columns_head<EDGE, false>(acc[1], ab, c.c1, t_cur, c.hf, c.T, c.L);
-    if (u > 0) {                                               // u is uniform over the workgroup
-        lds_barrier();
-        layer_take(c, u - 1, abp);
+    for (int j = 0; j < 8; ++j) {
+        if (j % 4 == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(ab[0][i]), "+v"(ab[1][i]));
+            if (j == 0) ps.next(2 * u, ka, kb);
+            else ps.next(2 * u + 1, kb, ka);
+        }
+        multiply(qa, j < 4 ? ka : kb, j, acc[j & 1]);
+        columns_add<LAYER_NT, 32, EDGE>(acc[(j & 1) ^ 1], j > 0 ? j - 1 : 7, nl, ab, c.c1, j > 0 ? t_cur : t_prev, c.g, c.T, c.L);
+        if (j == 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { abp[0][i] = ab[0][i]; abp[1][i] = ab[1][i]; }
+            if (u > 0) layer_give(c, u - 1, abp);
+        }
+        if (j == 4 && u > 0) {                                 // u is uniform over the workgroup
+            lds_barrier();
+            layer_take(c, u - 1, abp);
+        }
     }
-    acc[1] = chain<0, 8>(qa[5], kb, load_c64(cm, 5, c.hf));
-    columns_head<EDGE, false>(acc[0], ab, c.c1, t_cur, c.hf, c.T, c.L);
-    acc[0] = chain<0, 8>(qa[6], kb, load_c64(cm, 6, c.hf));
-    columns_head<EDGE, false>(acc[1], ab, c.c1, t_cur, c.hf, c.T, c.L);
-    acc[1] = chain<0, 8>(qa[7], kb, load_c64(cm, 7, c.hf));
-    columns_head<EDGE, false>(acc[0], ab, c.c1, t_cur, c.hf, c.T, c.L);
 }
 
 __global__ void __launch_bounds__(WAVES * 64)
@@ -1110,8 +1093,8 @@ score_mfma_columns_layer(ScoreArgs a)
     const Dims &d = a.d;
     char *ring = lds + wave * RING_BYTES;
     char *xch = lds + WAVES * RING_BYTES;                                     // [2 buffers][3 slots][4][64 lanes][4]
-    float *cmat = reinterpret_cast<float *>(xch + 2 * 3 * XCH_BYTES);         // [wave][8 tiles][2 halves][16] C operands
-    const int sl = blockIdx.x / a.n_chunks, chunk = blockIdx.x - sl * a.n_chunks;
+    float *cmat = reinterpret_cast<float *>(xch + 2 * 3 * XCH_BYTES);         // [wave][16 tiles][16 rows] minus the log-sum-exps
+    const int sl = blockIdx.y, chunk = blockIdx.x;
     const int p_first = sl * LAYER_KV;                                        // the layer's first problem
     const int lo = chunk * a.chunk_len, hi = min(lo + a.chunk_len, d.L);
     const int n_sub = hi > lo ? (hi - lo + SUB - 1) / SUB : 0;                // the same for the four wavefronts
@@ -1119,12 +1102,13 @@ score_mfma_columns_layer(ScoreArgs a)
     PairStream ps;
     ps.init(a.k + k_problem_offset(d, p_first + 2 * wave), a.k + k_problem_offset(d, p_first + 2 * wave + 1), d.ks[3], ring, lo,
             n_sub, d.L, lane);
-    ps.prime();
+    bf16x8 ka[2][4], kb[2][4];
+    ps.start(ka);
 
-    // C operands: minus (row log-sum-exp + log2 of the number of heads) / c1, so that exp2(c1 * acc) = A / H.
+    // minus (row log-sum-exp + log2 of the number of heads), so that exp2(c1 * acc + this) = A / H.
     // Row R = kv * 128 + h * 32 + query; four rows per thread.
     {
-        const float inv_c1 = 1.0f / a.c1, log2_heads = __builtin_amdgcn_logf((float)(d.G * LAYER_KV));
+        const float log2_heads = __builtin_amdgcn_logf((float)(d.G * LAYER_KV));
 #pragma unroll
         for (int k4 = 0; k4 < 4; ++k4) {
             const int R = threadIdx.x + 256 * k4, kv = R >> 7, row = R & (M_ROWS - 1);
@@ -1135,290 +1119,45 @@ score_mfma_columns_layer(ScoreArgs a)
             } else {
                 fold_pairs(a.merged + ((int64_t)(p_first + kv) * a.pc * M_ROWS + row) * 2, M_ROWS * 2, 0, 1, a.pc, m, zz);
             }
-            const int qy = row & 31, j = (kv & 1) * 4 + (row >> 5);
-            const int hq = (qy >> 2) & 1, iq = ((qy >> 3) << 2) | (qy & 3);   // inverse of query_of
-            cmat[((kv >> 1) * 8 + j) * 32 + hq * 16 + iq] = -(m + __builtin_amdgcn_logf(zz) + log2_heads) * inv_c1;
+            cmat[R] = -(m + __builtin_amdgcn_logf(zz) + log2_heads);
         }
     }
     __syncthreads();
 
     LayerCtx c;
     c.xch_lds = __builtin_amdgcn_readfirstlane(lds_addr(xch));
-    c.wave = wave; c.lane = lane; c.n = lane & 31; c.hf = lane >> 5;
+    c.wave = wave; c.lane = lane; c.n = lane & 15; c.g = lane >> 4;
     c.lo = lo; c.c1 = a.c1; c.eps = a.eps; c.T = d.T; c.L = d.L;
-    c.out = (c.hf == 0 ? a.s_out : a.e_out) + (int64_t)sl * d.L;
-    const float *cm = cmat + wave * 8 * 32;
+    c.out = (lane < 32 ? a.s_out : a.e_out) + (int64_t)sl * d.L;
 
-    bf16x8 qa[8][8];
+    bf16x8 qa[LAYER_NT][4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const uint16_t *row = a.q + q_row_offset(d, p_first + 2 * wave + j / 4, j % 4, c.n);
+    for (int J = 0; J < LAYER_NT; ++J) {
+        const uint16_t *row = a.q + q_row_offset(d, p_first + 2 * wave + J / 8, (J % 8) / 2, TILE * (J % 2) + c.n) + c.g * 8;
 #pragma unroll
-        for (int s = 0; s < 8; ++s) qa[j][s] = *reinterpret_cast<const bf16x8 *>(row + (2 * s + c.hf) * 8);
+        for (int s = 0; s < 4; ++s) qa[J][s] = *reinterpret_cast<const bf16x8 *>(row + 32 * s);
     }
-    pin_queries(qa);                                           // all 256 accumulation registers
+    pin_queries<LAYER_NT, 32>(qa, a, lane);                    // all 256 accumulation registers
 
-    floatx16 acc[2];
-    float ab[16];
+    const float *cm = cmat + wave * LAYER_NT * TILE + 4 * c.g;
+    floatx4 acc[2][2][2];
+    set_nothing(acc[0]);
+    set_nothing(acc[1]);
+    float ab[2][8];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { acc[0][i] = acc[1][i] = -INFINITY; ab[i] = 0.f; }
+    for (int i = 0; i < 8; ++i) ab[0][i] = ab[1][i] = 0.f;
 
     const int n_plain = lo + SUB <= d.T ? min(n_sub, (d.T - SUB - lo) / SUB + 1) : 0;
     int u = 0;
-    for (; u < n_plain; ++u) layer_body<false>(c, qa, ps, cm, acc, ab, u);
-    for (; u < n_sub; ++u) layer_body<true>(c, qa, ps, cm, acc, ab, u);
-    if (n_sub > 0) {                                           // tile 7 of the last subtile, then its hand-over
-        columns_head<true, false>(acc[1], ab, c.c1, lo + (n_sub - 1) * SUB + c.n, c.hf, c.T, c.L);
+    for (; u < n_plain; ++u) layer_body<false>(c, qa, ps, cm, ka, kb, acc, ab, u);
+    for (; u < n_sub; ++u) layer_body<true>(c, qa, ps, cm, ka, kb, acc, ab, u);
+    if (n_sub > 0) {                                           // head 7 of the last subtile, then its hand-over
+        columns_add<LAYER_NT, 32, true>(acc[1], 7, [&](int J) { return *reinterpret_cast<const floatx4 *>(cm + J * TILE); }, ab, c.c1, lo + (n_sub - 1) * SUB + c.n, c.g, c.T, c.L);
         layer_give(c, n_sub - 1, ab);
         lds_barrier();
         layer_take(c, n_sub - 1, ab);
     }
 }
-
-// ------------------------------------------------------------------ other head / window shapes
-// Any G with G * W <= 128 rows, W = 8, 16, 32 or 64: NT = ceil(G * W / 32) tiles of 32 rows, row = head * W +
-// window query; the rows behind the problem's G * W are padding (W < 32 and G not a multiple of 32 / W): zero
-// queries, never written by pass 1 and given an infinite log-sum-exp in pass 2, so they add exact zeros.  For
-// W < 32 a tile holds several heads, so the head mean adds REGISTERS of one accumulator (register i of lane half
-// hf is row 8 (i / 4) + 4 hf + i % 4 of the tile); for W >= 32 it adds accumulators, as in the kernels above.
-// The statistics kernel rotates its tiles through two accumulators like the kernel above (the tiles one after the
-// other, references from LDS: 28 layers x 4 KV heads x 30 011 keys, 112 rows of a window of 16, 259 us; 154 us now, a
-// key stream of 0.86 GB).  The column kernel runs the tiles one after the other; the subtiles without a mask have a
-// loop of their own (32 layers x 8 KV heads x 32 768 keys, 32 rows of a window of 8: 393 us with the mask's compares
-// in the one loop, 358 us now, 2.2 GB).
-template <int NT_, int W> struct Rows {
-    static constexpr int NT = NT_;                          // tiles
-    static constexpr int MP = 32 * NT;                      // rows of the tiles (padding included)
-    static constexpr int QB = W >= 32 ? W / 32 : 1;         // 32-query blocks of the window
-    static constexpr int NS = W >= 32 ? 16 * QB : W / 2;    // head-mean values per lane
-    static_assert(NT >= 1 && NT <= 4 && (W == 8 || W == 16 || W == 32 || W == 64) && NT % QB == 0, "unsupported shape");
-    __device__ static int tile_row(int i, int hf) { return 8 * (i >> 2) + 4 * hf + (i & 3); }
-    __device__ static int query(int J, int i, int hf) { return W >= 32 ? 32 * (J % QB) + tile_row(i, hf) : tile_row(i, hf) % W; }
-    __host__ __device__ static constexpr int slot(int J, int i) { return W >= 32 ? 16 * (J % QB) + i : i % (W / 2); }
-    // window query that head-mean value `s` of lane half hf belongs to
-    __device__ static int slot_query(int s, int hf) { return W >= 32 ? 32 * (s / 16) + tile_row(s % 16, hf) : tile_row(s, hf) % W; }
-};
-
-// a lane's A operands: row `r` of the problem's window-query matrix, zeros for a padding row
-template <int KS>
-__device__ __forceinline__ void load_query_row(bf16x8 (&qa)[KS], const ScoreArgs &a, int p, int r, int W, int hf)
-{
-    if (r < a.d.G * W) {
-        const uint16_t *row = a.q + q_row_offset(a.d, p, r / W, r % W);
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qa[s] = *reinterpret_cast<const bf16x8 *>(row + (2 * s + hf) * 8);
-    } else {
-#pragma unroll
-        for (int s = 0; s < KS; ++s) qa[s] = bf16x8{};
-    }
-}
-
-template <int NT, int W, int KS>
-__global__ void __launch_bounds__(WAVES * 64)
-score_mfma_stats_g(ScoreArgs a)
-{
-    using R = Rows<NT, W>;
-    constexpr int MP = R::MP;
-    extern __shared__ __attribute__((aligned(8192))) char lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, hf = lane >> 5;
-    const Dims &d = a.d;
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    char *ring = lds + wave_u * RING_BYTES;
-    float *wg_red = reinterpret_cast<float *>(lds + WAVES * RING_BYTES);       // [WAVES][MP][2]
-    float *cref = wg_red + WAVES * MP * 2 + wave_u * MP;                         // [NT tiles][2 halves][16], this wave's
-    const WaveWork w = wave_work(a, wave);
-    const int M = d.G * W;                                                     // rows of the problem; [M, MP) is padding
-
-    bf16x8 qa[NT][KS];
-#pragma unroll
-    for (int J = 0; J < NT; ++J) load_query_row(qa[J], a, w.p, 32 * J + n, W, hf);   // row of the window-query matrix
-    pin_queries(qa);
-    typename StreamFor<KS>::type ks;
-    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-    for (int i = lane; i < MP; i += 64) cref[i] = 0.f;
-
-    // the loop of score_mfma_stats: an even number of tiles leaves the last one waiting under the next subtile
-    constexpr bool CARRY = NT % 2 == 0;
-    constexpr int LAST = NT - 1;
-    float z[NT][16];
-    floatx16 cr[NT], acc[2];
-#pragma unroll
-    for (int J = 0; J < NT; ++J)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) { z[J][i] = 0.f; cr[J][i] = 0.f; }
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = -INFINITY;
-    const float lim = RESCALE_AT / a.c1;
-    auto careful = [&](const floatx16 &x, int J, bool first, int t) {
-        stats_tile_careful(x, z[J], cref + 32 * J, a.c1, first, t, hf, n, [J, hf](int i) { return R::query(J, i, hf); }, d.T, d.L);
-    };
-    bool waiting = false;
-    for (int u = 0; u < w.n_sub; ++u) {
-        bf16x8 kb[KS];
-        ks.fetch(u, kb);
-        const int t0 = w.first + u * STRIDE;
-        const bool plain = t0 + SUB <= d.T;                     // no masked key
-        int code = 0;
-        if (plain) {
-            if (u == 0) {
-                stats_anchor(qa, kb, cref, hf, n);
-#pragma unroll
-                for (int J = 0; J < NT; ++J) cr[J] = load_cref(cref, J, hf);
-            }
-            code = stats_fast<NT, KS, CARRY>(qa, kb, acc, cr, z, a.c1, lim);
-        }
-        if (code == STATS_OK) { waiting = CARRY; continue; }
-        const bool prev_failed = CARRY && plain && code == LAST;
-        if (waiting && (!plain || prev_failed)) careful(acc[1], LAST, false, t0 - STRIDE + n);
-        const int from = prev_failed ? 0 : code;
-#pragma unroll
-        for (int J = 0; J < NT; ++J)
-            if (J >= from) careful(chain<0, KS>(qa[J], kb, load_cref(cref, J, hf)), J, u == 0 && !plain, t0 + n);
-        waiting = false;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[1][i] = -INFINITY;
-#pragma unroll
-        for (int J = 0; J < NT; ++J) cr[J] = load_cref(cref, J, hf);
-    }
-    if (waiting) {
-        if (!stats_guard(acc[1], lim)) stats_add(acc[1], z[LAST], a.c1);
-        else careful(acc[1], LAST, false, w.first + (w.n_sub - 1) * STRIDE + n);
-    }
-
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    float *scr_z = reinterpret_cast<float *>(ring);            // [MP rows][32 lanes]
-#pragma unroll
-    for (int J = 0; J < NT; ++J)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) scr_z[(J * 32 + R::tile_row(i, hf)) * 32 + n] = z[J][i];
-    __builtin_amdgcn_wave_barrier();
-    for (int row = lane; row < MP; row += 64) {                 // row = 32 * tile + row in tile
-        float zz = 0.f;
-        for (int j = 0; j < 32; ++j) zz += scr_z[row * 32 + ((j + lane) & 31)];
-        const int q = row & 31, hfq = (q >> 2) & 1, iq = ((q >> 3) << 2) | (q & 3);
-        wg_red[(wave * MP + row) * 2] = -cref[(row >> 5) * 32 + hfq * 16 + iq] * a.c1;   // reference, log2 domain
-        wg_red[(wave * MP + row) * 2 + 1] = zz;
-    }
-    __syncthreads();
-    if (threadIdx.x < M) {
-        const int row = threadIdx.x;
-        float m = -INFINITY;
-        for (int wv = 0; wv < WAVES; ++wv) {
-            const float *e = wg_red + (wv * MP + row) * 2;
-            if (e[1] > 0.f) m = fmaxf(m, e[0]);
-        }
-        float zz = 0.f;
-        for (int wv = 0; wv < WAVES; ++wv) {
-            const float *e = wg_red + (wv * MP + row) * 2;
-            if (e[1] > 0.f) zz += e[1] * __builtin_amdgcn_exp2f(e[0] - m);
-        }
-        float *o = a.partial + (((int64_t)w.p * a.n_chunks + w.chunk) * M + row) * 2;
-        o[0] = m;
-        o[1] = zz;
-    }
-}
-
-// STORE: instead of the column sum and entropy of the KV head, write the head-group mean Abar[query][key] itself
-// (for the mean over ALL heads of a layer, which is formed across KV heads afterwards), four consecutive window
-// queries of a key per 16-byte store, layout [problem][W / 4][L][4].
-template <int NT, int W, bool STORE, int KS>
-__global__ void __launch_bounds__(WAVES * 64)
-score_mfma_columns_g(ScoreArgs a)
-{
-    using R = Rows<NT, W>;
-    constexpr int MP = R::MP, NS = R::NS;
-    extern __shared__ __attribute__((aligned(8192))) char lds[];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, hf = lane >> 5;
-    const Dims &d = a.d;
-    char *ring = lds + __builtin_amdgcn_readfirstlane(wave) * RING_BYTES;
-    float *lse2 = reinterpret_cast<float *>(lds + WAVES * RING_BYTES);       // [MP] log2-domain lse + log2 G, row head * W + query; +inf for padding rows
-    const WaveWork w = wave_work(a, wave);
-    const int M = d.G * W;                                                   // rows of the problem; [M, MP) is padding
-
-    bf16x8 qa[NT][KS];
-#pragma unroll
-    for (int J = 0; J < NT; ++J) load_query_row(qa[J], a, w.p, 32 * J + n, W, hf);
-    if (threadIdx.x >= M && threadIdx.x < MP) lse2[threadIdx.x] = INFINITY;
-    if (threadIdx.x < M) {
-        const int r = threadIdx.x;
-        float m = -INFINITY, zz = 0.f;
-        if (a.lse) {
-            m = a.lse[(int64_t)w.p * M + r] * LOG2E;
-            zz = 1.f;
-        } else {
-            fold_pairs(a.merged + ((int64_t)w.p * a.pc * M + r) * 2, M * 2, 0, 1, a.pc, m, zz);
-        }
-        lse2[r] = m + __builtin_amdgcn_logf(zz) + a.log2_G;
-    }
-    pin_queries(qa);
-    typename StreamFor<KS>::type ks;
-    ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-    ks.prime();
-    __syncthreads();
-
-    floatx16 cinit[NT];
-    const float inv_c1 = 1.0f / a.c1;
-#pragma unroll
-    for (int J = 0; J < NT; ++J)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) cinit[J][i] = -lse2[32 * J + R::tile_row(i, hf)] * inv_c1;
-    float *out = (hf == 0 ? a.s_out : a.e_out) + (int64_t)w.p * d.L;
-
-    // the subtiles without a masked key first, then the others: the mask's compares stay out of the long loop
-    auto subtile = [&](int u, auto edge_t) {
-        constexpr bool edge = decltype(edge_t)::value;
-        bf16x8 kb[KS];
-        ks.fetch(u, kb);
-        const int t0 = w.first + u * STRIDE, t = t0 + n;
-        float ab[NS];
-#pragma unroll
-        for (int i = 0; i < NS; ++i) ab[i] = 0.f;
-#pragma unroll
-        for (int J = 0; J < NT; ++J) {
-            const floatx16 acc = chain<0, KS>(qa[J], kb, cinit[J]);
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                float v = __builtin_amdgcn_exp2f(acc[i] * a.c1);                        // A / G
-                if (edge && !(t < d.L && t <= d.T + R::query(J, i, hf))) v = 0.f;       // causal inside the window
-                ab[R::slot(J, i)] += v;                                                 // Eq. barA
-            }
-        }
-        if (STORE) {
-            if (t < d.L) {
-#pragma unroll
-                for (int j = 0; j < NS / 4; ++j) {
-                    const int qd = R::slot_query(4 * j, hf) >> 2;                        // slots 4j .. 4j+3: four consecutive queries
-                    float4 *dst = reinterpret_cast<float4 *>(a.abar) + ((int64_t)w.p * (W / 4) + qd) * d.L + t;
-                    *dst = make_float4(ab[4 * j], ab[4 * j + 1], ab[4 * j + 2], ab[4 * j + 3]);
-                }
-            }
-            return;
-        }
-        float s_part = 0.f;
-#pragma unroll
-        for (int i = 0; i < NS; ++i) s_part += ab[i];
-        const float sv = add_other_half(s_part);                                         // Eq. st
-        const float inv_s = sv > 0.f ? __builtin_amdgcn_rcpf(sv) : 0.f;
-        float e_part = 0.f;
-#pragma unroll
-        for (int i = 0; i < NS; ++i) {
-            const float ah = ab[i] * inv_s;
-            e_part = fmaf(ah, __builtin_amdgcn_logf(ah + a.eps), e_part);
-        }
-        const float ent = -LN2 * add_other_half(e_part);                                 // inner sum of Eq. Dk
-        if (t < d.L) out[t] = hf == 0 ? sv : ent;
-    };
-    const int n_plain = w.first + SUB <= d.T ? min(w.n_sub, (d.T - SUB - w.first) / STRIDE + 1) : 0;
-    int u = 0;
-    for (; u < n_plain; ++u) subtile(u, std::false_type{});
-    for (; u < w.n_sub; ++u) subtile(u, std::true_type{});
-}
-
-template <int NT> constexpr int stats_g_lds() { return 4 * 4 * BUF_BYTES + 4 * 32 * NT * 2 * 4 + 4 * 32 * NT * 4; }
-template <int NT> constexpr int columns_g_lds() { return 4 * 4 * BUF_BYTES + 32 * NT * 4; }
 
 // Folds the chunk partials of pass 1 into one (reference, sum) pair per row, one wavefront per row, so that
 // with many chunks per problem the workgroups of pass 2 do not each repeat the fold.
@@ -1461,25 +1200,24 @@ void launch_merge(const ScoreArgs &a, int blocks, int M, hipStream_t st)
                        a.partial, const_cast<float *>(a.merged), a.n_chunks, M, n_rows);
 }
 
-template <int NT, int W, bool STORE, int KS = 8>
-hipError_t launch_score_g(const ScoreArgs &a, dim3 grid, bool with_stats, hipStream_t st)
+template <int NT, int W, bool STORE, int KS = 4>
+hipError_t launch_shape(const ScoreArgs &a, dim3 grid, bool with_stats, hipStream_t st)
 {
     static thread_local PerDeviceOnce attr_once;
     if (attr_once.needed()) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_stats_g<NT, W, KS>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, stats_g_lds<NT>());
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_stats<NT, W, KS>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, stats_lds<NT>());
         if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_columns_g<NT, W, STORE, KS>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, columns_g_lds<NT>());
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_columns<NT, W, STORE, KS>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, columns_lds<NT>());
         if (e != hipSuccess) return e;
         attr_once.done();
     }
-    constexpr int lds1 = stats_g_lds<NT>(), lds2 = columns_g_lds<NT>();
     if (with_stats) {
-        hipLaunchKernelGGL((score_mfma_stats_g<NT, W, KS>), grid, dim3(WAVES * 64), lds1, st, a);
+        hipLaunchKernelGGL((score_mfma_stats<NT, W, KS>), grid, dim3(WAVES * 64), stats_lds<NT>(), st, a);
         launch_merge(a, a.d.P, a.d.G * W, st);
     }
-    hipLaunchKernelGGL((score_mfma_columns_g<NT, W, STORE, KS>), grid, dim3(WAVES * 64), lds2, st, a);
+    hipLaunchKernelGGL((score_mfma_columns<NT, W, STORE, KS>), grid, dim3(WAVES * 64), columns_lds<NT>(), st, a);
     return hipGetLastError();
 }
 
@@ -1518,18 +1256,18 @@ abar_reduce_kernel(const float *abar, int Hkv, int L, float eps, float *s_out, f
     e_out[(int64_t)sl * L + t] = -LN2 * e;
 }
 
-// the (G, W) pairs served by the generic-row kernels
-// (tiles, window) pairs of the any-row-shape kernels: tiles = ceil(G * W / 32) <= 4.  Four tiles of a 32-query
-// window are G = 4, which has kernels of its own at D = 128, so that pair is listed apart.
-#define SABLOCK_TILE_SHAPES(X) X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(1, 16) X(2, 16) X(3, 16) X(4, 16) X(1, 32) X(2, 32) X(3, 32)
-#define SABLOCK_TILE_SHAPES_W64(X) X(2, 64) X(4, 64)
+// (tiles, window) pairs: up to 128 rows; of a window of 32 or 64, up to 256 (the second list)
+#define SABLOCK_SHAPES_96(X) X(1, 8) X(2, 8) X(3, 8) X(4, 8) X(5, 8) X(6, 8) X(1, 16) X(2, 16) X(3, 16) X(4, 16) X(5, 16) X(6, 16) X(2, 32) X(4, 32) X(6, 32)
+#define SABLOCK_SHAPES(X) SABLOCK_SHAPES_96(X) X(7, 8) X(8, 8) X(7, 16) X(8, 16) X(8, 32)
+#define SABLOCK_SHAPES_W64(X) X(4, 64) X(8, 64)
+#define SABLOCK_SHAPES_WIDE(X) X(10, 32) X(12, 32) X(14, 32) X(16, 32) X(12, 64) X(16, 64)
 
 bool tile_shape(const Dims &d)
 {
     return (d.W == 8 || d.W == 16 || d.W == 32 || d.W == 64) && d.G >= 1 && d.G * d.W <= M_ROWS;
 }
-int tiles_of(const Dims &d) { return (d.G * d.W + 31) / 32; }
-// 129 .. 256 rows of a window of 32 or 64 queries (G = 5 .. 8 / G = 3, 4): the eight-tile column kernels
+int tiles_of(const Dims &d) { return d.W == 8 ? (d.G + 1) / 2 : d.G * d.W / TILE; }
+// 129 .. 256 rows of a window of 32 or 64 queries (G = 5 .. 8 / G = 3, 4)
 bool wide_shape(const Dims &d)
 {
     return (d.W == 32 || d.W == 64) && d.G * d.W > M_ROWS && d.G * d.W <= 2 * M_ROWS;
@@ -1569,8 +1307,7 @@ Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)
     return pl;
 }
 
-// bytes of the chunk partials, and of their merged form behind them
-// (more than 128 rows: two blocks of 128 rows, the second padded where G * W < 256)
+// bytes of the chunk partials, and of their merged form behind them (more than 128 rows: room for 256)
 int stat_rows(const Dims &d) { return d.G * d.W > M_ROWS ? 2 * M_ROWS : d.G * d.W; }
 size_t partial_bytes(const Dims &d, const Plan &pl) { return align256((size_t)d.P * pl.n_chunks * stat_rows(d) * 2 * 4); }
 size_t merged_bytes(const Dims &d) { return align256((size_t)d.P * stat_rows(d) * 2 * 4); }
@@ -1594,47 +1331,26 @@ void plan_partials(ScoreArgs &a, const Dims &d, const Plan &pl, void *ws)
 bool score_mfma_supported(const Dims &d)
 {
     if (d.dtype != SABLOCK_BF16) return false;
-    if (d.D == 64 || d.D == 96) return tile_shape(d);                       // up to 128 rows, kernels for any row shape
-    if (d.D == 256) return tile_shape(d) && tiles_of(d) <= 3;               // up to 96 rows: four tiles of 16 k-steps do not fit the registers
+    if (d.D == 64 || d.D == 96) return tile_shape(d);                       // up to 128 rows
+    if (d.D == 256) return tile_shape(d) && (d.G * d.W + 31) / 32 <= 3;     // up to 96 rows: more A operands of 8 k-steps do not fit the registers
     return d.D == 128 && (tile_shape(d) || wide_shape(d));
 }
 
-// pass 1 for 256 rows by the transposed-score kernel (csrc/window_attn.hip): K is read once instead of once per
-// block of 128 rows
-static bool stats_by_rows(const Dims &d)
-{
-    if (!row_stats_supported(d) || d.tune.stats_per_key == 1) return false;
-    return d.tune.stats_per_key == 2 || d.G * d.W > M_ROWS;
-}
+// pass 1 by the window-attention kernel's first product (csrc/window_attn.hip), on request
+static bool stats_by_rows(const Dims &d) { return row_stats_supported(d) && d.tune.stats_per_key == 2; }
 static size_t row_stats_bytes(const Dims &d) { return align256((size_t)d.P * 2 * row_stats_chunks(d) * M_ROWS * 2 * 4); }
 
 size_t score_mfma_ws_bytes(const Dims &d)
 {
     const Plan pl = make_plan(d);
     size_t part = partial_bytes(d, pl);
-    if (stats_by_rows(d)) part = std::max(part, row_stats_bytes(d));
+    if (stats_by_rows(d) || wide_shape(d)) part = std::max(part, row_stats_bytes(d));
     return part + merged_bytes(d);
 }
 
 hipError_t launch_score_mfma(const Dims &d, const void *q, const void *k, const float *row_lse, float eps,
                              float *s_out, float *ent_out, void *ws, hipStream_t st)
 {
-    static thread_local PerDeviceOnce attr_once;
-    if (attr_once.needed()) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_stats),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, P1_LDS);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_columns),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, P2_LDS);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_columns8t<64>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, P2W_LDS);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_columns8t<32>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, P2W_LDS);
-        if (e != hipSuccess) return e;
-        attr_once.done();
-    }
     const Plan pl = make_plan(d);
     ScoreArgs a;
     a.d = d;
@@ -1648,38 +1364,9 @@ hipError_t launch_score_mfma(const Dims &d, const void *q, const void *k, const 
     a.e_out = ent_out;
     a.lse = row_lse;
     a.abar = nullptr;
-    a.p0 = 0;
-    a.nv = d.G * d.W > M_ROWS ? 2 : 1;
-    dim3 grid((unsigned)((int64_t)d.P * pl.n_chunks));
-    if (tile_shape(d)) {
-        const int nt = tiles_of(d);
-        if (d.D == 256) {
-#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_score_g<NTV, WV, false, 16>(a, grid, !row_lse, st);
-            X(1, 8) X(2, 8) X(3, 8) X(1, 16) X(2, 16) X(3, 16) X(1, 32) X(2, 32) X(3, 32) X(2, 64)
-#undef X
-        }
-        if (d.D == 96) {
-#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_score_g<NTV, WV, false, 6>(a, grid, !row_lse, st);
-            SABLOCK_TILE_SHAPES(X)
-            X(4, 32)
-            SABLOCK_TILE_SHAPES_W64(X)
-#undef X
-        }
-        if (d.D == 64) {
-#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_score_g<NTV, WV, false, 4>(a, grid, !row_lse, st);
-            SABLOCK_TILE_SHAPES(X)
-            X(4, 32)
-            SABLOCK_TILE_SHAPES_W64(X)
-#undef X
-        }
-#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_score_g<NTV, WV, false>(a, grid, !row_lse, st);
-        SABLOCK_TILE_SHAPES(X)
-        SABLOCK_TILE_SHAPES_W64(X)
-#undef X
-    }
-    dim3 grid1((unsigned)((int64_t)d.P * a.nv * pl.n_chunks));
-    if (!row_lse && stats_by_rows(d)) {
-        // a lane per window query: one read of K serves all 256 rows; the chunks of this pass are its own
+    bool with_stats = !row_lse;
+    if (with_stats && stats_by_rows(d)) {
+        // a lane per window query; the chunks of this pass are its own
         const int nc1 = row_stats_chunks(d);
         hipError_t e = launch_row_stats(d, q, k, a.partial, st);
         if (e != hipSuccess) return e;
@@ -1687,20 +1374,29 @@ hipError_t launch_score_mfma(const Dims &d, const void *q, const void *k, const 
         a.pc = nc1;
         if (nc1 >= MERGE_FROM) {
             float *merged = reinterpret_cast<float *>(static_cast<char *>(ws) + row_stats_bytes(d));
-            const int n_rows = d.P * a.nv * M_ROWS;
+            const int n_rows = d.P * d.G * d.W;
             hipLaunchKernelGGL(merge_partials_kernel, dim3((unsigned)((n_rows + 3) / 4)), dim3(256), 0, st, a.partial, merged,
-                               nc1, M_ROWS, n_rows);
+                               nc1, d.G * d.W, n_rows);
             a.merged = merged;
             a.pc = 1;
         }
-    } else if (!row_lse) {
-        hipLaunchKernelGGL(score_mfma_stats, grid1, dim3(WAVES * 64), P1_LDS, st, a);
-        launch_merge(a, d.P * a.nv, M_ROWS, st);
+        with_stats = false;
     }
-    if (d.W == 64) hipLaunchKernelGGL(score_mfma_columns8t<64>, grid, dim3(WAVES * 64), P2W_LDS, st, a);
-    else if (d.G > 4) hipLaunchKernelGGL(score_mfma_columns8t<32>, grid, dim3(WAVES * 64), P2W_LDS, st, a);
-    else hipLaunchKernelGGL(score_mfma_columns, grid, dim3(WAVES * 64), P2_LDS, st, a);
-    return hipGetLastError();
+    dim3 grid(pl.n_chunks, d.P);
+    const int nt = tiles_of(d);
+#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_shape<NTV, WV, false, 8>(a, grid, with_stats, st);
+    if (d.D == 256) { SABLOCK_SHAPES_96(X) X(4, 64) }
+#undef X
+#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_shape<NTV, WV, false, 3>(a, grid, with_stats, st);
+    if (d.D == 96) { SABLOCK_SHAPES(X) SABLOCK_SHAPES_W64(X) }
+#undef X
+#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_shape<NTV, WV, false, 2>(a, grid, with_stats, st);
+    if (d.D == 64) { SABLOCK_SHAPES(X) SABLOCK_SHAPES_W64(X) }
+#undef X
+#define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_shape<NTV, WV, false>(a, grid, with_stats, st);
+    if (d.D == 128) { SABLOCK_SHAPES(X) SABLOCK_SHAPES_W64(X) SABLOCK_SHAPES_WIDE(X) }
+#undef X
+    return hipErrorInvalidValue;
 }
 
 namespace {
@@ -1720,16 +1416,19 @@ stream_probe_kernel(ScoreArgs a, uint32_t *sink)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     char *ring = lds + __builtin_amdgcn_readfirstlane(wave) * RING_BYTES;
     const WaveWork w = wave_work(a, wave);
-    KeyStream<NBUF> ks;
+    KeyStream<false, false> ks;
     ks.init(w.kp, a.d.ks[3], ring, w.first, w.n_sub, a.d.L, lane);
-    ks.prime();
+    ks.issue_first();
     uint32_t x = 0;
     for (int u = 0; u < w.n_sub; ++u) {
         if (READ_LDS) {
-            bf16x8 kb[8];
-            ks.fetch_vgpr(u, kb);
+            bf16x8 kb[2][4];
+            wait_loads(min(NBUF - 1, w.n_sub - 1 - u));
+            read_subtile(ks.lane_addr0 + (u % NBUF) * BUF_BYTES, kb);
+            have_subtile<false>(kb);
+            if (u + NBUF < w.n_sub) ks.issue(u + NBUF);
 #pragma unroll
-            for (int s = 0; s < 8; ++s) x ^= ((const uint32_t *)&kb[s])[0] ^ ((const uint32_t *)&kb[s])[3];
+            for (int s = 0; s < 8; ++s) x ^= ((const uint32_t *)&kb[s >> 2][s & 3])[0] ^ ((const uint32_t *)&kb[s >> 2][s & 3])[3];
         } else {
             wait_loads(min(NBUF - 1, w.n_sub - 1 - u));
             x ^= *reinterpret_cast<const volatile uint32_t *>(ring + (u % NBUF) * BUF_BYTES + lane * 4);
@@ -1755,7 +1454,7 @@ hipError_t launch_stream_probe(const Dims &d, const void *k, int read_lds, float
     static thread_local PerDeviceOnce attr_once;
     if (attr_once.needed()) {
 #define X(R, S) { hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(stream_probe_kernel<R, S>), \
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, P2_LDS); \
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, WAVES * RING_BYTES); \
                   if (e != hipSuccess) return e; }
         X(false, false) X(false, true) X(true, false) X(true, true)
 #undef X
@@ -1767,13 +1466,12 @@ hipError_t launch_stream_probe(const Dims &d, const void *k, int read_lds, float
     a.k = static_cast<const uint16_t *>(k);
     a.chunk_len = pl.chunk_len;
     a.n_chunks = pl.n_chunks;
-    a.p0 = 0;
     a.s_out = s_out;
     a.e_out = e_out;
-    dim3 grid((unsigned)((int64_t)d.P * pl.n_chunks));
+    dim3 grid(pl.n_chunks, d.P);
     uint32_t *sk = static_cast<uint32_t *>(sink);
     const bool stores = s_out != nullptr;
-#define X(R, S) if ((read_lds != 0) == R && stores == S) hipLaunchKernelGGL((stream_probe_kernel<R, S>), grid, dim3(WAVES * 64), P2_LDS, st, a, sk);
+#define X(R, S) if ((read_lds != 0) == R && stores == S) hipLaunchKernelGGL((stream_probe_kernel<R, S>), grid, dim3(WAVES * 64), WAVES * RING_BYTES, st, a, sk);
     X(false, false) X(false, true) X(true, false) X(true, true)
 #undef X
     return hipGetLastError();
@@ -1804,19 +1502,17 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
     a.q = static_cast<const uint16_t *>(q);
     a.k = static_cast<const uint16_t *>(k);
     plan_partials(a, d, pl, ws);
-    a.nv = 1;
     a.c1 = (float)(1.4426950408889634 / sqrt((double)d.D));
     a.log2_G = (float)log2((double)d.G);
     a.eps = eps;
     a.lse = row_lse;
-    a.p0 = 0;
     a.abar = nullptr;
-    dim3 grid((unsigned)((int64_t)d.P * pl.n_chunks));
+    dim3 grid(pl.n_chunks, d.P);
     if (layer_kernel_shape(d)) {
         static thread_local PerDeviceOnce attr_once;
         if (attr_once.needed()) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_stats),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, P1_LDS);
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_stats<8, 32, 4>),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, stats_lds<8>());
             if (e != hipSuccess) return e;
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(score_mfma_columns_layer),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, PL_LDS);
@@ -1826,7 +1522,7 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
         a.s_out = s_out;
         a.e_out = ent_out;
         if (!row_lse) {
-            hipLaunchKernelGGL(score_mfma_stats, grid, dim3(WAVES * 64), P1_LDS, st, a);
+            hipLaunchKernelGGL((score_mfma_stats<8, 32, 4>), grid, dim3(WAVES * 64), stats_lds<8>(), st, a);
             launch_merge(a, d.P, M_ROWS, st);
         }
         // pass 2 has its own decomposition: a workgroup walks a chunk of keys through all 8 KV heads of a layer,
@@ -1840,7 +1536,7 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
         ScoreArgs a2 = a;
         a2.chunk_len = len;
         a2.n_chunks = (d.L + len - 1) / len;
-        hipLaunchKernelGGL(score_mfma_columns_layer, dim3((unsigned)(n_sl * a2.n_chunks)), dim3(WAVES * 64), PL_LDS, st, a2);
+        hipLaunchKernelGGL(score_mfma_columns_layer, dim3(a2.n_chunks, (unsigned)n_sl), dim3(WAVES * 64), PL_LDS, st, a2);
         return hipGetLastError();
     }
     // other shapes: every KV head's head-group means go to memory, a second kernel averages them over the KV heads
@@ -1849,9 +1545,8 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
     a.abar = reinterpret_cast<float *>(static_cast<char *>(ws) + partial_bytes(d, pl) + merged_bytes(d));
     hipError_t e = hipErrorInvalidValue;
     const int nt = tiles_of(d);
-#define X(NTV, WV) if (nt == NTV && d.W == WV) e = launch_score_g<NTV, WV, true>(a, grid, !row_lse, st);
-    SABLOCK_TILE_SHAPES(X)
-    X(4, 32)
+#define X(NTV, WV) if (nt == NTV && d.W == WV) e = launch_shape<NTV, WV, true>(a, grid, !row_lse, st);
+    SABLOCK_SHAPES(X)
 #undef X
     if (e != hipSuccess) return e;
     dim3 rgrid((unsigned)((d.L + 255) / 256), (unsigned)(d.n_seq * d.n_layers));

@@ -57,7 +57,7 @@ struct WinArgs {
     float *lse;                // [P][G * W] natural log
     float *o_part;             // ... or partial results [P * NW][n_chunks][32][D], unnormalised (NW row blocks per problem)
     float *ml_part;            // [P * NW][n_chunks][32][2]: reference (log2 domain), sum
-    float *stats;              // statistics-only kernel: [P][2 row blocks][n_chunks][128][2] (reference in the log2 domain, sum)
+    float *stats;              // statistics-only kernel: [P][n_chunks][G * W][2] (reference in the log2 domain, sum)
 };
 
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lptr_t)p; }
@@ -349,12 +349,8 @@ window_attention_kernel(WinArgs a)
     const float l_tot = other_half(l, false);
     const float ref2 = r * a.c1;                               // log2 domain
     if (!WITH_V) {
-        // where the column pass for 256 rows looks for a row's statistics: two blocks of 128 rows per problem
-        // (W = 64: the window halves, rows head * 32 + query; G = 8: heads 0-3 and 4-7)
-        const int blk = d.W > ROWS ? qoff / ROWS : head / 4;
-        const int row = d.W > ROWS ? head * ROWS + n : (head & 3) * ROWS + n;
-        if (hf == 0) {
-            float *o2 = a.stats + ((((int64_t)p * (NW / 4) + blk) * a.n_chunks + chunk) * 128 + row) * 2;
+        if (hf == 0 && real_row) {
+            float *o2 = a.stats + (((int64_t)p * a.n_chunks + chunk) * (d.G * d.W) + ROWS * wave + n) * 2;
             o2[0] = ref2;
             o2[1] = l_tot;
         }
