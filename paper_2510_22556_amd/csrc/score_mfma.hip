@@ -21,10 +21,10 @@
 //   pass 2  the chunk partials are combined into the row log-sum-exp in the
 //           prologue; probabilities, head mean, column sum and entropy term follow
 //           in registers.
-// The products start from zero and the log-sum-exp enters behind them (one FMA per
-// exponent): as the MFMA's C operand, some 140 in units of <q,k>, it costs every
-// product the bits that it is larger (128 rows, 131 072 keys: scores 8e-7 off their
-// 64-bit values, 6.5e-7 now).
+// The log-sum-exp enters as the MFMA's C operand, less a power of two that all rows
+// share and that comes off the column sums in the end: in full, some 140 in units of
+// <q,k>, it would cost every product the bits that it is larger (128 rows, 131 072
+// keys: scores 8.2e-7 off their 64-bit values, 6.5e-7 now).
 // In both passes the row tiles rotate, in groups of two, through two sets of
 // accumulators: a group is multiplied while the one before it is exponentiated,
 // which overlaps the matrix pipe with the exp/log work inside one wavefront (one
@@ -216,9 +216,9 @@ __device__ __forceinline__ uint32_t lane_read_offset(int lane)
     return (uint32_t)(n * ROW_BYTES + ((g ^ n) << 4));
 }
 
-// Group j of the row tiles (tiles 2 j and 2 j + 1) times the two key tiles
-template <int NT, int KS>
-__device__ __forceinline__ void multiply(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[2][KS], int j, floatx4 (&acc)[2][2])
+// Group j of the row tiles (tiles 2 j and 2 j + 1) times the two key tiles; c(J): C operand of tile J
+template <int NT, int KS, typename C>
+__device__ __forceinline__ void multiply(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[2][KS], int j, C c, floatx4 (&acc)[2][2])
 {
 #pragma unroll
     for (int s = 0; s < KS; ++s)
@@ -227,8 +227,10 @@ __device__ __forceinline__ void multiply(const bf16x8 (&qa)[NT][KS], const bf16x
 #pragma unroll
             for (int t = 0; t < 2; ++t)
                 if (2 * j + r < NT)
-                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[2 * j + r][s], kb[t][s], s == 0 ? floatx4{} : acc[r][t], 0, 0, 0);
+                    acc[r][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[2 * j + r][s], kb[t][s], s == 0 ? c(2 * j + r) : acc[r][t], 0, 0, 0);
 }
+__device__ __forceinline__ floatx4 no_operand(int) { return floatx4{}; }
+
 // what makes a pending group add zeros
 __device__ __forceinline__ void set_nothing(floatx4 (&acc)[2][2])
 {
@@ -534,12 +536,14 @@ __device__ __forceinline__ void stats_fast(const bf16x8 (&qa)[NT][KS], const bf1
     constexpr int NG = (NT + 1) / 2;
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
-        multiply(qa, kb, j, acc[(j + PAR) & 1]);
+        multiply(qa, kb, j, no_operand, acc[(j + PAR) & 1]);
         stats_add<0>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, z, c1, 0, 0, 0);
     }
     // the sums as they are here: keeps the compiler from moving this subtile's exponentials behind the next one's loads
+    // (where a step is one subtile there is nothing behind it)
 #pragma unroll
-    for (int J = 0; J < NT; ++J) asm volatile("" : "+v"(z[J]));
+    for (int J = 0; J < NT; ++J)
+        if (NT <= 8) asm volatile("" : "+v"(z[J]));
 }
 
 template <int NT, int W, int KS>
@@ -559,7 +563,7 @@ score_mfma_stats(ScoreArgs a)
 
     // queries before keys, as loads return in order; both are in flight together
     bf16x8 qa[NT][KS];
-    using Stream = typename StreamFor<NT, KS, true>::type;
+    using Stream = typename StreamFor<NT, KS, NT <= 8>::type;
     Stream ks;
     ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
     if constexpr (KS == 4) {
@@ -592,13 +596,15 @@ score_mfma_stats(ScoreArgs a)
             floatx4 acc[2][2][2];
             set_nothing(acc[0]);
             set_nothing(acc[1]);
-            for (; u + 1 < n_plain; u += 2) {
+            constexpr bool ONE = !Stream::AHEAD && NG % 2 == 0;
+            for (; u + (ONE ? 0 : 1) < n_plain; u += ONE ? 1 : 2) {
                 ks.next(u, ka, kb);
                 stats_fast<0>(qa, ka, acc, z, a.c1);
+                if (ONE) continue;                             // nothing changes places
                 ks.next(u + 1, kb, ka);
                 stats_fast<NG & 1>(qa, kb, acc, z, a.c1);
             }
-            if (u < n_plain) {
+            if (!ONE && u < n_plain) {
                 ks.next(u++, ka, kb);
                 stats_fast<0>(qa, ka, acc, z, a.c1);
                 stats_add<0>(acc[(NG & 1) ^ 1], NG - 1, z, a.c1, 0, 0, 0);
@@ -611,7 +617,7 @@ score_mfma_stats(ScoreArgs a)
                 ks.next(u, ka, kb);
 #pragma unroll
                 for (int j = 0; j < NG; ++j) {
-                    multiply(qa, ka, j, acc[j & 1]);
+                    multiply(qa, ka, j, no_operand, acc[j & 1]);
                     stats_add<W>(acc[j & 1], j, z, a.c1, w.first + u * STRIDE + n, g, d.T);
                 }
                 copy_subtile(ka, kb);
@@ -746,10 +752,10 @@ __device__ __forceinline__ void fold_rows(const ScoreArgs &a, int p, float log2_
     if (pos < Rows<NT, W>::MP) lse2[pos] = real ? m + __builtin_amdgcn_logf(z) + log2_heads : INFINITY;
 }
 
-// Adds group j's probabilities (acc = <q,k>, so exp2(c1 * acc - lse2) = A / heads) to the head means; nl(J): minus the lse2
-// of tile J's rows; t: the lane's key in the first key tile
-template <int NT, int W, bool EDGE, typename NL>
-__device__ __forceinline__ void columns_add(const floatx4 (&acc)[2][2], int j, NL nl, float (&ab)[2][W / 4], float c1, int t, int g, int T, int L)
+// Adds group j's probabilities (acc = <q,k> - lse2 / c1, so exp2(c1 * acc) = A / heads) to the head means; t: the lane's key
+// in the first key tile
+template <int NT, int W, bool EDGE>
+__device__ __forceinline__ void columns_add(const floatx4 (&acc)[2][2], int j, float (&ab)[2][W / 4], float c1, int t, int g, int T, int L)
 {
     using R = Rows<NT, W>;
 #pragma unroll
@@ -760,7 +766,7 @@ __device__ __forceinline__ void columns_add(const floatx4 (&acc)[2][2], int j, N
             for (int i = 0; i < 4; ++i) {
                 const int J = 2 * j + r, key = t + TILE * kt;
                 if (J >= NT) continue;
-                float v = __builtin_amdgcn_exp2f(fmaf(acc[r][kt][i], c1, nl(J)[i]));
+                float v = __builtin_amdgcn_exp2f(acc[r][kt][i] * c1);
                 if (EDGE && !(key < L && key <= T + R::query(J, g, i))) v = 0.f;          // causal inside the window
                 float &to = ab[kt][R::slot(J, i)];
                 to = R::first(J, i) ? v : to + v;                                         // Eq. barA
@@ -779,9 +785,9 @@ __device__ __forceinline__ float sum_groups(float x0, float x1)
 }
 
 // Column sums (Eq. st, lanes 0 .. 31: one of the subtile's 32 keys each) and entropy terms (inner sum of Eq. Dk, lanes 32
-// .. 63) from the lane's head means
+// .. 63) from the lane's head means, which are to be taken `scale` times
 template <int NS>
-__device__ __forceinline__ float columns_finish(const float (&ab)[2][NS], float eps, int lane)
+__device__ __forceinline__ float columns_finish(const float (&ab)[2][NS], float scale, float eps, int lane)
 {
     float s0 = 0.f, s1 = 0.f;
 #pragma unroll
@@ -798,7 +804,7 @@ __device__ __forceinline__ float columns_finish(const float (&ab)[2][NS], float 
         e1 = fmaf(ab[1][i], __builtin_amdgcn_logf(fmaf(ab[1][i], inv1, eps)), e1);
     }
     const float ent = -LN2 * inv * sum_groups(e0, e1);
-    return lane < 32 ? s : ent;
+    return lane < 32 ? s * scale : ent;
 }
 
 // Column sums and entropy terms.  STORE: instead of them, write the head-group mean Abar[query][key] itself (for the mean
@@ -849,10 +855,15 @@ score_mfma_columns(ScoreArgs a)
     auto &kb = Stream::AHEAD ? ahead : ka;
     ks.start(ka);
 
-    floatx4 neg[NT], acc[2][2][2];
+    floatx4 cinit[NT], acc[2][2][2];
+    const float common = fminf(fmaxf(rintf(lse2[0]), -100.f), 100.f);        // the rows' log-sum-exps are alike
+    const float scale = __builtin_amdgcn_exp2f(-common), inv_c1 = 1.0f / a.c1;
 #pragma unroll
-    for (int J = 0; J < NT; ++J) neg[J] = -*reinterpret_cast<const floatx4 *>(lse2 + TILE * J + 4 * g);
-    auto nl = [&](int J) __attribute__((always_inline)) { return neg[J]; };
+    for (int J = 0; J < NT; ++J) {
+        cinit[J] = *reinterpret_cast<const floatx4 *>(lse2 + TILE * J + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cinit[J][i] = (common - cinit[J][i]) * inv_c1;
+    }
     set_nothing(acc[0]);                                       // the "previous subtile" of iteration 0 is a no-op
     set_nothing(acc[1]);
     float ab[2][NS];
@@ -864,7 +875,7 @@ score_mfma_columns(ScoreArgs a)
     int pending_u = -1;
     auto finish = [&](int u, bool edge) __attribute__((always_inline)) {                      // the head means of subtile u are complete
         if (!STORE) {
-            pending = columns_finish<NS>(ab, a.eps, lane);
+            pending = columns_finish<NS>(ab, scale, a.eps, lane);
             pending_u = u;
             return;
         }
@@ -874,12 +885,12 @@ score_mfma_columns(ScoreArgs a)
             const int t = w.first + u * STRIDE + TILE * kt + n;
             if (edge && t >= d.L) continue;
             float *row = a.abar + (int64_t)w.p * (W / 4) * d.L * 4;
-            if (W == 8) *reinterpret_cast<float2 *>(row + ((int64_t)(g >> 1) * d.L + t) * 4 + 2 * (g & 1)) = make_float2(ab[kt][0], ab[kt][1]);
+            if (W == 8) *reinterpret_cast<float2 *>(row + ((int64_t)(g >> 1) * d.L + t) * 4 + 2 * (g & 1)) = make_float2(ab[kt][0] * scale, ab[kt][1] * scale);
             else
 #pragma unroll
                 for (int J = 0; J < R::PER_HEAD; ++J)
                     *reinterpret_cast<float4 *>(row + ((int64_t)(4 * J + g) * d.L + t) * 4) =
-                        make_float4(ab[kt][4 * J], ab[kt][4 * J + 1], ab[kt][4 * J + 2], ab[kt][4 * J + 3]);
+                        make_float4(ab[kt][4 * J] * scale, ab[kt][4 * J + 1] * scale, ab[kt][4 * J + 2] * scale, ab[kt][4 * J + 3] * scale);
         }
     };
     auto put = [&](bool edge) __attribute__((always_inline)) {
@@ -896,9 +907,9 @@ score_mfma_columns(ScoreArgs a)
         const int t = w.first + u * STRIDE + n;
 #pragma unroll
         for (int j = 0; j < NG; ++j) {
-            multiply(qa, cur, j, acc[(j + PAR) & 1]);
+            multiply(qa, cur, j, [&](int J) { return cinit[J]; }, acc[(j + PAR) & 1]);
             if (j == 1) finish(u - 1, EDGE);                   // under this group's products
-            columns_add<NT, W, EDGE>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, nl, ab, a.c1, j > 0 ? t : t - STRIDE, g, d.T, d.L);
+            columns_add<NT, W, EDGE>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, ab, a.c1, j > 0 ? t : t - STRIDE, g, d.T, d.L);
             if (NG == 1) finish(u - 1, EDGE);
         }
         // the means as they are here: keeps the compiler from moving this subtile's exponentials behind the next one's loads
@@ -929,7 +940,7 @@ score_mfma_columns(ScoreArgs a)
     run(w.n_sub, std::true_type{});
     put(true);
     if (w.n_sub > 0) {
-        columns_add<NT, W, true>(acc[1], NG - 1, nl, ab, a.c1, w.first + (w.n_sub - 1) * STRIDE + n, g, d.T, d.L);
+        columns_add<NT, W, true>(acc[1], NG - 1, ab, a.c1, w.first + (w.n_sub - 1) * STRIDE + n, g, d.T, d.L);
         finish(w.n_sub - 1, true);
         put(true);
     }
@@ -946,7 +957,7 @@ template <int NT> constexpr int columns_lds() { return WAVES * RING_BYTES + 256 
 constexpr int LAYER_KV = 8;                   // KV heads of a layer this kernel is built for (two per wavefront)
 constexpr int XCH_BYTES = 16 * 64 * 4;        // one wavefront's partial sums of a subtile, [4][64 lanes][4]
 constexpr int LAYER_NT = 16;                  // row tiles of a wavefront: two KV heads of four heads
-constexpr int PL_LDS = WAVES * RING_BYTES + 2 * 3 * XCH_BYTES + WAVES * LAYER_NT * TILE * 4;   // rings + exchange + log-sum-exps
+constexpr int PL_LDS = WAVES * RING_BYTES + 2 * 3 * XCH_BYTES + WAVES * LAYER_NT * TILE * 4;   // rings + exchange + C operands
 
 // Two key streams of one wavefront as one sequence of half-steps: element e = 2u + s is subtile u of stream s and
 // lives in ring buffer e % NBUF, refilled with element e + NBUF right after it is read.  Subtile u covers keys
@@ -1031,7 +1042,7 @@ struct LayerCtx {
     uint32_t xch_lds;      // exchange area
     int wave, lane, n, g;
     int lo;                // first key of the chunk
-    float c1, eps;
+    float c1, scale, eps;
     int T, L;
     float *out;            // s (lanes 0 .. 31) or entropy term (lanes 32 .. 63) row of this (sequence, layer)
 };
@@ -1047,7 +1058,7 @@ __device__ __forceinline__ void layer_take(const LayerCtx &c, int up, float (&ab
 {
     if (c.wave != (up & 3)) return;
     xch_add(c.xch_lds + (uint32_t)((up & 1) * 3 * XCH_BYTES + c.lane * 16), ab);
-    const float v = columns_finish<8>(ab, c.eps, c.lane);
+    const float v = columns_finish<8>(ab, c.scale, c.eps, c.lane);
     const int t = c.lo + up * SUB + (c.lane & 31);
     if (t < c.L) c.out[t] = v;
 }
@@ -1061,7 +1072,6 @@ __device__ __forceinline__ void layer_body(const LayerCtx &c, const bf16x8 (&qa)
                                            float (&ab)[2][8], int u)
 {
     const int t_cur = c.lo + u * SUB + c.n, t_prev = t_cur - SUB;
-    auto nl = [&](int J) { return *reinterpret_cast<const floatx4 *>(cm + J * TILE); };    // from LDS: all registers are taken
     float abp[2][8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -1071,8 +1081,9 @@ __device__ __forceinline__ void layer_body(const LayerCtx &c, const bf16x8 (&qa)
             if (j == 0) ps.next(2 * u, ka, kb);
             else ps.next(2 * u + 1, kb, ka);
         }
-        multiply(qa, j < 4 ? ka : kb, j, acc[j & 1]);
-        columns_add<LAYER_NT, 32, EDGE>(acc[(j & 1) ^ 1], j > 0 ? j - 1 : 7, nl, ab, c.c1, j > 0 ? t_cur : t_prev, c.g, c.T, c.L);
+        // the C operands come from LDS: all registers are taken
+        multiply(qa, j < 4 ? ka : kb, j, [&](int J) { return *reinterpret_cast<const floatx4 *>(cm + J * TILE); }, acc[j & 1]);
+        columns_add<LAYER_NT, 32, EDGE>(acc[(j & 1) ^ 1], j > 0 ? j - 1 : 7, ab, c.c1, j > 0 ? t_cur : t_prev, c.g, c.T, c.L);
         if (j == 0) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) { abp[0][i] = ab[0][i]; abp[1][i] = ab[1][i]; }
@@ -1093,7 +1104,7 @@ score_mfma_columns_layer(ScoreArgs a)
     const Dims &d = a.d;
     char *ring = lds + wave * RING_BYTES;
     char *xch = lds + WAVES * RING_BYTES;                                     // [2 buffers][3 slots][4][64 lanes][4]
-    float *cmat = reinterpret_cast<float *>(xch + 2 * 3 * XCH_BYTES);         // [wave][16 tiles][16 rows] minus the log-sum-exps
+    float *cmat = reinterpret_cast<float *>(xch + 2 * 3 * XCH_BYTES);         // [wave][16 tiles][16 rows] C operands
     const int sl = blockIdx.y, chunk = blockIdx.x;
     const int p_first = sl * LAYER_KV;                                        // the layer's first problem
     const int lo = chunk * a.chunk_len, hi = min(lo + a.chunk_len, d.L);
@@ -1105,8 +1116,9 @@ score_mfma_columns_layer(ScoreArgs a)
     bf16x8 ka[2][4], kb[2][4];
     ps.start(ka);
 
-    // minus (row log-sum-exp + log2 of the number of heads), so that exp2(c1 * acc + this) = A / H.
-    // Row R = kv * 128 + h * 32 + query; four rows per thread.
+    // C operands: minus (row log-sum-exp + log2 of the number of heads - the part that all rows share) / c1.  Row R = kv * 128
+    // + h * 32 + query; four rows per thread.
+    float lse[4];
     {
         const float log2_heads = __builtin_amdgcn_logf((float)(d.G * LAYER_KV));
 #pragma unroll
@@ -1119,15 +1131,21 @@ score_mfma_columns_layer(ScoreArgs a)
             } else {
                 fold_pairs(a.merged + ((int64_t)(p_first + kv) * a.pc * M_ROWS + row) * 2, M_ROWS * 2, 0, 1, a.pc, m, zz);
             }
-            cmat[R] = -(m + __builtin_amdgcn_logf(zz) + log2_heads);
+            lse[k4] = m + __builtin_amdgcn_logf(zz) + log2_heads;
         }
+        if (threadIdx.x == 0) cmat[0] = lse[0];
     }
+    __syncthreads();
+    const float common = fminf(fmaxf(rintf(cmat[0]), -100.f), 100.f);
+    __syncthreads();
+#pragma unroll
+    for (int k4 = 0; k4 < 4; ++k4) cmat[threadIdx.x + 256 * k4] = (common - lse[k4]) * (1.0f / a.c1);
     __syncthreads();
 
     LayerCtx c;
     c.xch_lds = __builtin_amdgcn_readfirstlane(lds_addr(xch));
     c.wave = wave; c.lane = lane; c.n = lane & 15; c.g = lane >> 4;
-    c.lo = lo; c.c1 = a.c1; c.eps = a.eps; c.T = d.T; c.L = d.L;
+    c.lo = lo; c.c1 = a.c1; c.scale = __builtin_amdgcn_exp2f(-common); c.eps = a.eps; c.T = d.T; c.L = d.L;
     c.out = (lane < 32 ? a.s_out : a.e_out) + (int64_t)sl * d.L;
 
     bf16x8 qa[LAYER_NT][4];
@@ -1152,7 +1170,7 @@ score_mfma_columns_layer(ScoreArgs a)
     for (; u < n_plain; ++u) layer_body<false>(c, qa, ps, cm, ka, kb, acc, ab, u);
     for (; u < n_sub; ++u) layer_body<true>(c, qa, ps, cm, ka, kb, acc, ab, u);
     if (n_sub > 0) {                                           // head 7 of the last subtile, then its hand-over
-        columns_add<LAYER_NT, 32, true>(acc[1], 7, [&](int J) { return *reinterpret_cast<const floatx4 *>(cm + J * TILE); }, ab, c.c1, lo + (n_sub - 1) * SUB + c.n, c.g, c.T, c.L);
+        columns_add<LAYER_NT, 32, true>(acc[1], 7, ab, c.c1, lo + (n_sub - 1) * SUB + c.n, c.g, c.T, c.L);
         layer_give(c, n_sub - 1, ab);
         lds_barrier();
         layer_take(c, n_sub - 1, ab);
