@@ -53,3 +53,16 @@ def test_short_streams(oracle, torch_cuda, G, W, D, T):  # noqa: F811
     q = synth.normal_torch(T, 1, (1, 1, G * 2, W, D), "cuda", torch.bfloat16)
     k = synth.normal_torch(T, 2, (1, 1, 2, T + W, D), "cuda", torch.bfloat16)
     _check(oracle, torch, q, k, 2, G, W, D, T + W, score_chunk=128)
+
+
+@pytest.mark.parametrize("G,W,D", SHAPES + [(8, 32, 128), (4, 64, 128)])
+@pytest.mark.parametrize("logit", [-120.0, 60.0, 95.0])
+def test_rows_whose_logits_lie_far_from_zero(oracle, torch_cuda, G, W, D, logit):  # noqa: F811
+    # sums that under- or overflow without a reference, in one row of every head: those wavefronts start again with one
+    torch = torch_cuda
+    Hkv, L = 2, 1024 + 45 + W
+    q = synth.normal_torch(G * W + D, 3, (1, 1, G * Hkv, W, D), "cuda", torch.bfloat16)
+    k = synth.normal_torch(G * W + D, 4, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    k[..., 0] = 1.0
+    q[:, :, :, W // 2, 0] = logit * D ** 0.5                   # every logit of the row moves by that much
+    _check(oracle, torch, q, k, Hkv, G, W, D, L, score_chunk=512)
