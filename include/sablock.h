@@ -308,6 +308,27 @@ SABLOCK_API sablock_status sablock_segment_offsets(const int32_t *token_ids, int
                                        const int32_t *seg_ptr, int32_t *seg_off_out, void *stream);
 
 /*
+ * The same two steps by slices of a sequence, for a caller that fetches the counts in between in any case: with the
+ * slices' places known, no kernel walks more than its slice.  sablock_segment_slices gives the slices per sequence (0:
+ * more than 256 in the call, use the calls above).
+ *   1. sablock_segment_slice_count writes the boundaries of every slice to slice_count_out (device or pinned host memory;
+ *      n_seq * slices int32, a sequence's slices in order).
+ *   2. the caller forms slice_place (HOST, n_seq * slices + 1 entries): the first is where the offsets begin, each next one
+ *      lies the slice's boundaries further on, and 2 more behind the last slice of a sequence (its offsets 0 and n_tokens);
+ *      so entry s * slices is seg_ptr[s].
+ *   3. sablock_segment_slice_offsets writes the offsets to seg_off_out; entries beyond what slice_place leaves room for are
+ *      dropped.
+ * Errors as above; INVALID_ARG also for a slice_place that descends or leaves a sequence no room for its two ends.
+ */
+SABLOCK_API int32_t sablock_segment_slices(int32_t n_seq, int32_t n_tokens);
+SABLOCK_API sablock_status sablock_segment_slice_count(const int32_t *token_ids, int64_t token_stride, int32_t n_seq,
+                                           int32_t n_tokens, const int32_t *delims, int32_t n_delim,
+                                           int32_t *slice_count_out, void *stream);
+SABLOCK_API sablock_status sablock_segment_slice_offsets(const int32_t *token_ids, int64_t token_stride, int32_t n_seq,
+                                             int32_t n_tokens, const int32_t *delims, int32_t n_delim,
+                                             const int32_t *slice_place, int32_t *seg_off_out, void *stream);
+
+/*
  * Check of a CSR segment array on the device (Sec. 3.1: the segments S_1 .. S_K partition the compressible
  * region, so every sequence's offsets must read 0 = off[0] < off[1] < ... < off[K] = n_tokens).  The five calls
  * do not look at the values in seg_off (they are device data) and index s, ent and s_tilde with them, so offsets

@@ -26,7 +26,8 @@ EXPORTS = ("sablock_version", "sablock_last_error", "sablock_workspace_bytes", "
            "sablock_segment_count", "sablock_segment_offsets", "sablock_decode_workspace_bytes",
            "sablock_decode_attention", "sablock_score_all_heads_workspace_bytes", "sablock_score_all_heads",
            "sablock_compact_shared", "sablock_search_select", "sablock_window_attention_workspace_bytes",
-           "sablock_window_attention", "sablock_score_static", "sablock_stream_probe", "sablock_validate_segments")
+           "sablock_window_attention", "sablock_score_static", "sablock_stream_probe", "sablock_validate_segments",
+           "sablock_segment_slices", "sablock_segment_slice_count", "sablock_segment_slice_offsets")
 
 
 class SablockError(RuntimeError):
@@ -87,6 +88,9 @@ def load():
         lib.sablock_segment_count.argtypes = [vp, ctypes.c_int64, i32, i32, ctypes.POINTER(i32), i32, vp, vp]
         lib.sablock_segment_offsets.argtypes = [vp, ctypes.c_int64, i32, i32, ctypes.POINTER(i32), i32,
                                                 ctypes.POINTER(i32), vp, vp]
+        lib.sablock_segment_slices.argtypes = [i32, i32]
+        lib.sablock_segment_slice_count.argtypes = lib.sablock_segment_count.argtypes
+        lib.sablock_segment_slice_offsets.argtypes = lib.sablock_segment_offsets.argtypes
         lib.sablock_validate_segments.argtypes = [vp, ctypes.POINTER(i32), i32, i32, vp, vp]
         lib.sablock_decode_workspace_bytes.argtypes = [sp, ctypes.POINTER(ctypes.c_size_t)]
         lib.sablock_decode_attention.argtypes = [sp, vp, vp, vp, vp, i32, vp, vp, ctypes.c_size_t, vp]
@@ -260,18 +264,28 @@ def segment(token_ids, delims: Sequence[int]) -> "Segments":
     n, T = token_ids.shape
     tokens = (token_ids.data_ptr(), token_ids.stride(0), n, T)
     d = (ctypes.c_int32 * max(len(delims), 1))(*[int(x) for x in delims])
+    st = stream.cuda_stream or None
     # the kernel writes the counts straight to host memory: no copy between it and the wait
-    counts = torch.empty((n,), dtype=torch.int32, device="cpu", pin_memory=True)
-    _check(lib.sablock_segment_count(*tokens, d, len(delims), counts.data_ptr(), stream.cuda_stream or None))
+    per = lib.sablock_segment_slices(n, T)
+    counts = torch.empty((n, per or 1), dtype=torch.int32, device="cpu", pin_memory=True)
+    _check((lib.sablock_segment_slice_count if per else lib.sablock_segment_count)(*tokens, d, len(delims), counts.data_ptr(), st))
     stream.synchronize()
-    c = counts.tolist()
-    ptr = [0]
-    for k in c:
-        ptr.append(ptr[-1] + k + 1)
-    seg_off = torch.empty((ptr[-1],), dtype=torch.int32, device=token_ids.device)
-    _check(lib.sablock_segment_offsets(*tokens, d, len(delims), (ctypes.c_int32 * (n + 1))(*ptr), seg_off.data_ptr(),
-                                       stream.cuda_stream or None))
-    return Segments(seg_off, ptr, max(c))
+    if not per:                                                # too many slices for one call: by whole sequences
+        ptr = [0]
+        for k in counts[:, 0].tolist():
+            ptr.append(ptr[-1] + k + 1)
+        seg_off = torch.empty((ptr[-1],), dtype=torch.int32, device=token_ids.device)
+        _check(lib.sablock_segment_offsets(*tokens, d, len(delims), (ctypes.c_int32 * (n + 1))(*ptr), seg_off.data_ptr(), st))
+    else:
+        place = [0]
+        for row in counts.tolist():
+            for k in row:
+                place.append(place[-1] + k)
+            place[-1] += 2                                     # a sequence's offsets are its boundaries and both ends
+        ptr = place[::per]
+        seg_off = torch.empty((ptr[-1],), dtype=torch.int32, device=token_ids.device)
+        _check(lib.sablock_segment_slice_offsets(*tokens, d, len(delims), (ctypes.c_int32 * len(place))(*place), seg_off.data_ptr(), st))
+    return Segments(seg_off, ptr, max(b - a for a, b in zip(ptr, ptr[1:])) - 1)
 
 
 def layer_shape(shape: CShape) -> CShape:

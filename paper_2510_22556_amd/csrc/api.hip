@@ -2,6 +2,7 @@
 // Nothing here touches the device except kernel launches on the caller's stream.
 #include "sablock_internal.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdarg>
 #include <cstdio>
@@ -512,6 +513,50 @@ sablock_status sablock_segment_offsets(const int32_t *token_ids, int64_t token_s
     if (st != SABLOCK_OK) return st;
     return dev(launch_segment_offsets(token_ids, token_stride, n_seq, n_tokens, ds, sp, seg_off_out,
                                       static_cast<hipStream_t>(stream)), "sablock_segment_offsets");
+}
+
+int32_t sablock_segment_slices(int32_t n_seq, int32_t n_tokens)
+{
+    if (n_seq < 1 || n_seq > MAX_SEQ || n_tokens < 1) return 0;
+    const int n = segment_slices(n_tokens);
+    return (int64_t)n * n_seq <= MAX_SLICES ? n : 0;
+}
+
+sablock_status sablock_segment_slice_count(const int32_t *token_ids, int64_t token_stride, int32_t n_seq, int32_t n_tokens,
+                                           const int32_t *delims, int32_t n_delim, int32_t *slice_count_out, void *stream)
+{
+    if (!token_ids || !slice_count_out) return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_count: NULL argument");
+    if (n_seq < 1 || n_tokens < 1 || token_stride < n_tokens)
+        return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_count: need n_seq >= 1, n_tokens >= 1, token_stride >= n_tokens");
+    if (sablock_segment_slices(n_seq, n_tokens) == 0)
+        return fail(SABLOCK_ERR_UNSUPPORTED, "sablock_segment_slice_count: more than %d slices in a call", MAX_SLICES);
+    DelimSet ds;
+    sablock_status st = make_delims(delims, n_delim, &ds);
+    if (st != SABLOCK_OK) return st;
+    return dev(launch_segment_slice_count(token_ids, token_stride, n_seq, n_tokens, ds, slice_count_out, static_cast<hipStream_t>(stream)),
+               "sablock_segment_slice_count");
+}
+
+sablock_status sablock_segment_slice_offsets(const int32_t *token_ids, int64_t token_stride, int32_t n_seq, int32_t n_tokens,
+                                             const int32_t *delims, int32_t n_delim, const int32_t *slice_place, int32_t *seg_off_out,
+                                             void *stream)
+{
+    if (!token_ids || !slice_place || !seg_off_out) return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_offsets: NULL argument");
+    if (n_seq < 1 || n_tokens < 1 || token_stride < n_tokens)
+        return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_offsets: need n_seq >= 1, n_tokens >= 1, token_stride >= n_tokens");
+    const int per = sablock_segment_slices(n_seq, n_tokens), n = per * n_seq;
+    if (n == 0) return fail(SABLOCK_ERR_UNSUPPORTED, "sablock_segment_slice_offsets: more than %d slices in a call", MAX_SLICES);
+    SlicePlaces sp;
+    if (slice_place[0] < 0) return fail(SABLOCK_ERR_INVALID_ARG, "slice_place[0] < 0");
+    for (int i = 0; i <= MAX_SLICES; ++i) sp.at[i] = slice_place[std::min(i, n)];
+    for (int i = 0; i < n; ++i)
+        if (sp.at[i + 1] - sp.at[i] < ((i + 1) % per == 0 ? 2 : 0))
+            return fail(SABLOCK_ERR_INVALID_ARG, "slice_place descends, or leaves no room for the ends, at slice %d", i);
+    DelimSet ds;
+    sablock_status st = make_delims(delims, n_delim, &ds);
+    if (st != SABLOCK_OK) return st;
+    return dev(launch_segment_slice_offsets(token_ids, token_stride, n_seq, n_tokens, ds, sp, seg_off_out, static_cast<hipStream_t>(stream)),
+               "sablock_segment_slice_offsets");
 }
 
 sablock_status sablock_validate_segments(const int32_t *seg_off, const int32_t *seg_ptr, int32_t n_seq, int32_t n_tokens,

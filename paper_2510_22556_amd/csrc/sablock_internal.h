@@ -40,6 +40,11 @@ struct SeqPtr {                    // host CSR pointers of the segment offsets, 
     int32_t ptr[MAX_SEQ + 1];
 };
 
+constexpr int MAX_SLICES = 256;    // slices of all sequences of a sliced segmentation call
+struct SlicePlaces {               // place of each slice's offsets, by value in the kernel arguments; the end of the last one behind them
+    int32_t at[MAX_SLICES + 1];
+};
+
 // candidate block sizes; x / g = (x * inv) >> CAND_INV_BITS for 0 <= x < 4 160 (inv = ceil(2^19 / g), g <= 64)
 constexpr int CAND_INV_BITS = 19;
 struct CandList {
@@ -147,6 +152,12 @@ hipError_t launch_segment_count(const int32_t *tok, int64_t stride, int32_t n_se
                                 int32_t *seg_count, hipStream_t st);
 hipError_t launch_segment_offsets(const int32_t *tok, int64_t stride, int32_t n_seq, int32_t T, const DelimSet &ds,
                                   const SeqPtr &sp, int32_t *seg_off, hipStream_t st);
+// the same by slices of 16 384 tokens (segment_slices of them per sequence), whose counts the caller fetches in between
+int segment_slices(int32_t T);
+hipError_t launch_segment_slice_count(const int32_t *tok, int64_t stride, int32_t n_seq, int32_t T, const DelimSet &ds,
+                                      int32_t *count, hipStream_t st);
+hipError_t launch_segment_slice_offsets(const int32_t *tok, int64_t stride, int32_t n_seq, int32_t T, const DelimSet &ds,
+                                        const SlicePlaces &sp, int32_t *seg_off, hipStream_t st);
 hipError_t launch_segment_check(const int32_t *seg_off, int32_t n_seq, int32_t T, const SeqPtr &sp, int32_t *bad,
                                 hipStream_t st);
 

@@ -45,3 +45,19 @@ def test_segment_whatever_torch_s_default_device_is(torch_cuda):  # noqa: F811
     finally:
         torch.set_default_device(before if before.type != "cpu" else None)
     assert seg.seg_off.cpu().tolist() == [0, 10, 100, 0, 20, 30, 100] and list(seg.seg_ptr) == [0, 3, 7]
+
+
+@pytest.mark.parametrize("T", [1, 257, 4099, 16384, 65472])
+def test_the_calls_by_whole_sequences_give_the_same(torch_cuda, T):  # noqa: F811
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    rng = np.random.default_rng(T)
+    tok = torch.as_tensor(rng.integers(0, 40, size=(2, T)).astype(np.int32)).cuda()
+    seg = B.segment(tok, [3, 5])
+    count = torch.empty((2,), dtype=torch.int32, device="cuda")
+    B.sablock_segment_count(tok, [3, 5], count)
+    ptr = [0] + [int(x) for x in np.cumsum(count.cpu().numpy() + 1)]
+    off = torch.full((ptr[-1],), -1, dtype=torch.int32, device="cuda")
+    B.sablock_segment_offsets(tok, [3, 5], ptr, off)
+    assert ptr == list(seg.seg_ptr) and torch.equal(off, seg.seg_off)
