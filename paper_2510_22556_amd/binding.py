@@ -390,15 +390,20 @@ def compress(shape: CShape, q, k, v, seg: Segments, cand: Sequence[int], budget:
              eps=1e-6, alpha=0.9, eta=1.0, tau=0.85, row_lse=None, stream=None, fused=True) -> Buffers:
     """The whole hot path: score, refine, search_blocks + select (one call for both, or the two separate calls with
     ``fused=False``: same results), compact."""
-    sablock_score(shape, q, k, buf.s, buf.ent, buf.ws, eps, row_lse, stream)
-    sablock_refine(shape, buf.s, buf.ent, seg, buf.s_tilde, buf.ws, alpha, eta, buf.omega, stream)
+    # the calls above with their arguments marshalled once: small calls are bound by what the host does between launches
+    lib, st, sp = load(), _stream(stream), ctypes.byref(shape)
+    s, ent, s_tilde, topb, idx, n_sel = (t.data_ptr() for t in (buf.s, buf.ent, buf.s_tilde, buf.topb, buf.idx, buf.n_sel))
+    kp, bk, g = k.data_ptr(), buf.seg_budget.data_ptr(), buf.block_size.data_ptr()
+    ws = (buf.ws.data_ptr(), buf.ws.numel() * buf.ws.element_size(), st)
+    segs = (seg.seg_off.data_ptr(), seg.c_ptr(), seg.max_segments)
+    cl = ((ctypes.c_int32 * len(cand))(*[int(x) for x in cand]), len(cand))
+    _check(lib.sablock_score(sp, q.data_ptr(), kp, _ptr(row_lse), eps, s, ent, *ws))
+    _check(lib.sablock_refine(sp, s, ent, *segs, ctypes.byref(CHparams(0.0, alpha, eta, 0.0)), s_tilde, buf.omega.data_ptr(), *ws))
     if fused:
-        sablock_search_select(shape, buf.s_tilde, seg, cand, budget, tau, buf.seg_budget, buf.block_size, buf.idx,
-                              buf.n_sel, buf.ws, stream, topb_out=buf.topb)
+        _check(lib.sablock_search_select(sp, s_tilde, *segs, *cl, budget, tau, bk, g, topb, idx, n_sel, *ws))
     else:
-        sablock_search_blocks(shape, buf.s_tilde, seg, cand, budget, tau, buf.seg_budget, buf.block_size, buf.ws,
-                              stream, topb_out=buf.topb)
-        sablock_select(shape, buf.s_tilde, seg, buf.seg_budget, buf.block_size, budget, buf.idx, buf.n_sel, buf.ws,
-                       stream, topb=buf.topb)
-    sablock_compact(shape, k, v, buf.idx, buf.n_sel, budget, buf.append_window, buf.k_out, buf.v_out, stream)
+        _check(lib.sablock_search_blocks(sp, s_tilde, *segs, *cl, budget, tau, bk, g, topb, *ws))
+        _check(lib.sablock_select(sp, s_tilde, *segs, bk, g, topb, budget, idx, n_sel, *ws))
+    _check(lib.sablock_compact(sp, kp, v.data_ptr(), idx, n_sel, budget, 1 if buf.append_window else 0, buf.k_out.data_ptr(),
+                               buf.v_out.data_ptr(), st))
     return buf
