@@ -531,12 +531,12 @@ __device__ __forceinline__ void stats_add(const floatx4 (&acc)[2][2], int j, flo
 // the other set, at first the last group of the subtile before.  The last group is left waiting.
 template <int PAR, int NT, int KS>
 __device__ __forceinline__ void stats_fast(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[2][KS], floatx4 (&acc)[2][2][2],
-                                           floatx4 (&z)[NT], float c1)
+                                           const floatx4 (&cr)[NT], floatx4 (&z)[NT], float c1)
 {
     constexpr int NG = (NT + 1) / 2;
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
-        multiply(qa, kb, j, no_operand, acc[(j + PAR) & 1]);
+        multiply(qa, kb, j, [&](int J) { return KS == 4 ? floatx4{} : cr[J]; }, acc[(j + PAR) & 1]);
         stats_add<0>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, z, c1, 0, 0, 0);
     }
     // the sums as they are here: keeps the compiler from moving this subtile's exponentials behind the next one's loads
@@ -589,9 +589,39 @@ score_mfma_stats(ScoreArgs a)
         int u = 0;
         bool again = false;
         if (!careful) {
-            floatx4 z[NT];
+            // in two levels: beside one large term, small ones that are added to it one by one are lost, sixteen subtiles of
+            // them together are not (rows with a peak of 2^26 times the rest, 131 072 keys: sums 5e-5 off without)
+            floatx4 z[NT], zo[NT];
 #pragma unroll
-            for (int J = 0; J < NT; ++J) z[J] = floatx4{};
+            for (int J = 0; J < NT; ++J) z[J] = zo[J] = floatx4{};
+            auto level = [&]() __attribute__((always_inline)) {
+#pragma unroll
+                for (int J = 0; J < NT; ++J) {
+                    zo[J] += z[J];
+                    z[J] = floatx4{};
+                }
+            };
+            // Keys of other lengths than 128 elements: the row maxima over the first subtile as references all the same, so that
+            // the exponent of a peak is small and rounds to less (peaks of 2^26, heads of 64 elements: scores 5.9e-7 off with,
+            // 8.4e-7 without; of 128, where the products are off by as much, 1.0e-6 with and without)
+            floatx4 cr[NT];
+#pragma unroll
+            for (int J = 0; J < NT; ++J) cr[J] = floatx4{};
+            if (KS != 4 && n_plain > 0) {
+#pragma unroll
+                for (int j = 0; j < NG; ++j) {
+                    floatx4 first[2][2];
+                    multiply(qa, ka, j, no_operand, first);
+#pragma unroll
+                    for (int r = 0; r < 2; ++r)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            if (2 * j + r >= NT) continue;
+                            const float rm = group_max(fmaxf(first[r][0][i], first[r][1][i]));
+                            cr[2 * j + r][i] = fabsf(rm) < INFINITY ? -rm : 0.f;
+                        }
+                }
+            }
             // two subtiles a step: the operands, and with an odd number of groups the accumulators, change places
             floatx4 acc[2][2][2];
             set_nothing(acc[0]);
@@ -599,14 +629,16 @@ score_mfma_stats(ScoreArgs a)
             constexpr bool ONE = !Stream::AHEAD && NG % 2 == 0;
             for (; u + (ONE ? 0 : 1) < n_plain; u += ONE ? 1 : 2) {
                 ks.next(u, ka, kb);
-                stats_fast<0>(qa, ka, acc, z, a.c1);
-                if (ONE) continue;                             // nothing changes places
-                ks.next(u + 1, kb, ka);
-                stats_fast<NG & 1>(qa, kb, acc, z, a.c1);
+                stats_fast<0>(qa, ka, acc, cr, z, a.c1);
+                if (!ONE) {                                    // else nothing changes places
+                    ks.next(u + 1, kb, ka);
+                    stats_fast<NG & 1>(qa, kb, acc, cr, z, a.c1);
+                }
+                if ((u & 15) >= 14) level();
             }
             if (!ONE && u < n_plain) {
                 ks.next(u++, ka, kb);
-                stats_fast<0>(qa, ka, acc, z, a.c1);
+                stats_fast<0>(qa, ka, acc, cr, z, a.c1);
                 stats_add<0>(acc[(NG & 1) ^ 1], NG - 1, z, a.c1, 0, 0, 0);
                 copy_subtile(ka, kb);
             } else {
@@ -617,25 +649,26 @@ score_mfma_stats(ScoreArgs a)
                 ks.next(u, ka, kb);
 #pragma unroll
                 for (int j = 0; j < NG; ++j) {
-                    multiply(qa, ka, j, no_operand, acc[j & 1]);
+                    multiply(qa, ka, j, [&](int J) { return KS == 4 ? floatx4{} : cr[J]; }, acc[j & 1]);
                     stats_add<W>(acc[j & 1], j, z, a.c1, w.first + u * STRIDE + n, g, d.T);
                 }
                 copy_subtile(ka, kb);
             }
+            level();
             // per row: the lane group's 16 sums together
             float least = INFINITY, most = 0.f;
 #pragma unroll
             for (int J = 0; J < NT; ++J) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    z[J][i] = group_sum(z[J][i]);
-                    least = fminf(least, z[J][i]);
-                    most = fmaxf(most, z[J][i]);
+                    zo[J][i] = group_sum(zo[J][i]);
+                    least = fminf(least, zo[J][i]);
+                    most = fmaxf(most, zo[J][i]);
                 }
                 if (n == 0) {
                     floatx4 *st = state + (TILE * J + 4 * g) / 2;
-                    st[0] = floatx4{0.f, z[J][0], 0.f, z[J][1]};
-                    st[1] = floatx4{0.f, z[J][2], 0.f, z[J][3]};
+                    st[0] = floatx4{cr[J][0], zo[J][0], cr[J][1], zo[J][1]};
+                    st[1] = floatx4{cr[J][2], zo[J][2], cr[J][3], zo[J][3]};
                 }
             }
             again = most > SUM_MOST || (w.first <= d.T && least < SUM_LEAST);
