@@ -310,7 +310,7 @@ SABLOCK_API sablock_status sablock_segment_offsets(const int32_t *token_ids, int
 /*
  * The same two steps by slices of a sequence, for a caller that fetches the counts in between in any case: with the
  * slices' places known, no kernel walks more than its slice.  sablock_segment_slices gives the slices per sequence (0:
- * more than 256 in the call, use the calls above).
+ * more than 128 in the call, use the calls above).
  *   1. sablock_segment_slice_count writes the boundaries of every slice to slice_count_out (device or pinned host memory;
  *      n_seq * slices int32, a sequence's slices in order).
  *   2. the caller forms slice_place (HOST, n_seq * slices + 1 entries): the first is where the offsets begin, each next one

@@ -40,7 +40,7 @@ struct SeqPtr {                    // host CSR pointers of the segment offsets, 
     int32_t ptr[MAX_SEQ + 1];
 };
 
-constexpr int MAX_SLICES = 256;    // slices of all sequences of a sliced segmentation call
+constexpr int MAX_SLICES = 128;    // slices of all sequences of a sliced segmentation call
 struct SlicePlaces {               // place of each slice's offsets, by value in the kernel arguments; the end of the last one behind them
     int32_t at[MAX_SLICES + 1];
 };

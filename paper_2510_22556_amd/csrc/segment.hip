@@ -9,7 +9,8 @@
 //
 // A caller that fetches the counts between the two kernels anyway asks for them by slices of 16 384 tokens (one round of
 // loads for a workgroup) and hands the slices' places back: neither kernel then walks more than its slice.  Four sequences
-// of 65 472 tokens, both kernels and the wait between them: 37.9 -> 27.5 us.
+// of 65 472 tokens, both kernels and the wait between them: 38.4 -> 28.0 us, eight of 131 000
+// 57.2 -> 33.3.
 //
 // What bounds it: the latency of one workgroup's loads and compares, and in kernels this short the fetch of their own
 // instructions (eight steps in flight, i.e. twice the code, took 18.3 us where four take 14.5).  Four sequences of 65 472

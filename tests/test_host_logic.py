@@ -302,3 +302,12 @@ def test_bench_algorithmic_bytes_match_the_stated_formulas():
     assert abs(alg["score"] / w.n_layers - (k_bytes + w.n_q_heads * w.window * w.head_dim * 2
                                             + 2 * 4 * w.n_kv_heads * w.seq_len)) < 1
     assert 0.29e9 < per_layer < 0.32e9
+
+
+def test_slices_of_the_segmentation(lib):
+    # binding.segment computes them itself
+    for n_seq in (1, 3, 8, 64):
+        for T in (1, B.SLICE_TOKENS - 1, B.SLICE_TOKENS, B.SLICE_TOKENS + 1, 131072, 1 << 20, 1 << 22):
+            per = -(-T // B.SLICE_TOKENS)
+            assert lib.sablock_segment_slices(n_seq, T) == (per if n_seq * per <= B.MAX_SLICES else 0)
+    assert lib.sablock_segment_slices(0, 5) == lib.sablock_segment_slices(65, 5) == lib.sablock_segment_slices(1, 0) == 0
