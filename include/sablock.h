@@ -86,9 +86,7 @@ typedef struct {
                                  (1 = the per-row kernel alone); 0 = by row length and problems per compute unit */
     int32_t stats_per_key;    /* which kernel forms the row statistics where two exist (head_dim 128; 129 .. 256
                                  window-query rows per KV head, and G = 4 with W = 32): 1 = the kernel with a lane per
-                                 key on blocks of 128 rows (two blocks: K read twice by that pass), 2 = the kernel with a
-                                 lane per window query (one read of K for all rows); 0 = the faster one by measurement
-                                 (2 above 128 rows, 1 at 128) */
+                                 key, 2 = the kernel with a lane per window query; 0 = the faster one by measurement (1) */
     int32_t reserved[3];      /* must be 0 */
 } sablock_tuning;
 
