@@ -64,6 +64,7 @@ constexpr int RING_BYTES = NBUF * BUF_BYTES;
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr float RESCALE_AT = 64.f;         // pass 1, careful: a row's reference moves when an exponent exceeds this
+constexpr float COMMON_MOST = 100.f;       // pass 2, see common_power
 constexpr float SUM_MOST = 0x1p100f, SUM_LEAST = 0x1p-60f;     // pass 1, fast: a row's sum outside says that exponentials may have over- or underflowed
 
 struct ScoreArgs {
@@ -817,6 +818,21 @@ __device__ __forceinline__ float sum_groups(float x0, float x1)
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// smallest value of the four lane groups that hold a key's rows; numbers before what is none
+__device__ __forceinline__ float min_groups(float v)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fminf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fminf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// The power of two that the probabilities of all rows are taken by (see above), from the smallest of the rows' log-sum-exps:
+// no C operand is then larger than without it.  Never negative, as the exponentials flush to zero what lies below 2^-126 in
+// any case: at -100 that were all probabilities below 2^-26.  At most 2^100, so that the sums over the rows stay finite
+// (8 192 keys, 128 rows, all logits 60 above zero: scores 1.7e-6 off, 4.0e-6 with at most 2^32).
+__device__ __forceinline__ float common_power(float least) { return fminf(fmaxf(rintf(least), 0.f), COMMON_MOST); }
+
 // Column sums (Eq. st, lanes 0 .. 31: one of the subtile's 32 keys each) and entropy terms (inner sum of Eq. Dk, lanes 32
 // .. 63) from the lane's head means, which are to be taken `scale` times
 template <int NS>
@@ -889,11 +905,17 @@ score_mfma_columns(ScoreArgs a)
     ks.start(ka);
 
     floatx4 cinit[NT], acc[2][2][2];
-    const float common = fminf(fmaxf(rintf(lse2[0]), -100.f), 100.f);        // the rows' log-sum-exps are alike
-    const float scale = __builtin_amdgcn_exp2f(-common), inv_c1 = 1.0f / a.c1;
+    float least = INFINITY;
 #pragma unroll
     for (int J = 0; J < NT; ++J) {
         cinit[J] = *reinterpret_cast<const floatx4 *>(lse2 + TILE * J + 4 * g);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) least = fminf(least, cinit[J][i]);
+    }
+    const float common = common_power(min_groups(least));
+    const float scale = __builtin_amdgcn_exp2f(-common), inv_c1 = 1.0f / a.c1;
+#pragma unroll
+    for (int J = 0; J < NT; ++J) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) cinit[J][i] = (common - cinit[J][i]) * inv_c1;
     }
@@ -1166,10 +1188,11 @@ score_mfma_columns_layer(ScoreArgs a)
             }
             lse[k4] = m + __builtin_amdgcn_logf(zz) + log2_heads;
         }
-        if (threadIdx.x == 0) cmat[0] = lse[0];
+        const float least = min_groups(-group_max(-fminf(fminf(lse[0], lse[1]), fminf(lse[2], lse[3]))));
+        if (lane == 0) cmat[wave] = least;                     // the same power for all heads: their probabilities are added
     }
     __syncthreads();
-    const float common = fminf(fmaxf(rintf(cmat[0]), -100.f), 100.f);
+    const float common = common_power(fminf(fminf(cmat[0], cmat[1]), fminf(cmat[2], cmat[3])));
     __syncthreads();
 #pragma unroll
     for (int k4 = 0; k4 < 4; ++k4) cmat[threadIdx.x + 256 * k4] = (common - lse[k4]) * (1.0f / a.c1);

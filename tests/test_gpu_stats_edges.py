@@ -14,17 +14,21 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(4, 32, 128), (7, 16, 128), (3, 32, 128), (5, 8, 128), (1, 8, 128), (2, 64, 128), (4, 32, 64), (3, 32, 96), (2, 32, 256), (3, 32, 256)]
 
 
-def _check(oracle, torch, q, k, Hkv, G, W, D, L, **tuning):
+def _check(oracle, torch, q, k, Hkv, G, W, D, L, all_heads=False, row_lse=None, **tuning):
     from paper_2510_22556_amd import binding as B
 
     shape = B.make_shape(q, k, **tuning)
-    ws = torch.empty((B.sablock_workspace_bytes(shape, 0, 0),), dtype=torch.uint8, device="cuda")
-    s = torch.full((Hkv, L), float("nan"), dtype=torch.float32, device="cuda")
+    call, n_ws = ((B.sablock_score_all_heads, B.sablock_score_all_heads_workspace_bytes(shape)) if all_heads else
+                  (B.sablock_score, B.sablock_workspace_bytes(shape, 0, 0)))
+    ws = torch.empty((n_ws,), dtype=torch.uint8, device="cuda")
+    s = torch.full((1 if all_heads else Hkv, L), float("nan"), dtype=torch.float32, device="cuda")
     e = torch.full_like(s, float("nan"))
-    B.sablock_score(shape, q, k, s, e, ws)
+    call(shape, q, k, s, e, ws, row_lse=row_lse)
     torch.cuda.synchronize()
-    for p in range(Hkv):
-        sr, er = oracle.score(H.widen(H.to_np(q[0, 0, p * G:(p + 1) * G].contiguous())), H.widen(H.to_np(k[0, 0, p].contiguous())), 1e-6)
+    for p in range(len(s)):
+        of = oracle.score_layer if all_heads else oracle.score
+        qp, kp = (q[0, 0], k[0, 0]) if all_heads else (q[0, 0, p * G:(p + 1) * G], k[0, 0, p])
+        sr, er = of(H.widen(H.to_np(qp.contiguous())), H.widen(H.to_np(kp.contiguous())), 1e-6)
         # a logit of up to 300 in the log2 domain is rounded to 2^-16 in fp32, a probability by that relative
         np.testing.assert_allclose(H.to_np(s[p]), sr, rtol=5e-5, atol=1e-9)
         np.testing.assert_allclose(H.to_np(e[p]), er, rtol=5e-5, atol=5e-6)
@@ -66,3 +70,28 @@ def test_rows_whose_logits_lie_far_from_zero(oracle, torch_cuda, G, W, D, logit)
     k[..., 0] = 1.0
     q[:, :, :, W // 2, 0] = logit * D ** 0.5                   # every logit of the row moves by that much
     _check(oracle, torch, q, k, Hkv, G, W, D, L, score_chunk=512)
+
+
+FAR = SHAPES + [(7, 32, 128), (8, 32, 128), (4, 64, 128), (5, 16, 256), (6, 8, 256)]
+
+
+# the all-head call takes up to 128 rows of heads of 128 elements and windows of up to 32
+@pytest.mark.parametrize("entry,G,W,D", [(e, *f) for e in ("score", "row_lse") for f in FAR] +
+                         [("all_heads", *f) for f in FAR if f[2] == 128 and f[1] <= 32 and f[0] * f[1] <= 128])
+@pytest.mark.parametrize("rows,logit,sink", [("all", -100.0, 20.0), ("first", -100.0, 0.0), ("first", 60.0, 0.0), ("all", 60.0, 20.0)])
+def test_probabilities_of_rows_far_from_zero_are_not_flushed(oracle, torch_cuda, G, W, D, rows, logit, sink, entry):  # noqa: F811
+    # all rows, or the first row of every head alone, at a logit that the first element makes; one key `sink` above
+    # the others, whose probabilities of 2^-29 and less are in fp32's range whatever the rows' log-sum-exps
+    torch = torch_cuda
+    Hkv, L = 8 if entry == "all_heads" else 2, 1024 + 45 + W
+    q = synth.normal_torch(G * W + D, 5, (1, 1, G * Hkv, W, D), "cuda", torch.bfloat16)
+    k = synth.normal_torch(G * W + D, 6, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    k[..., 0] = 1.0
+    k[:, :, :, 300, 0] = 1.0 + sink / logit
+    q[:, :, :, slice(None) if rows == "all" else slice(0, 1), 0] = logit * D ** 0.5
+    lse = None
+    if entry == "row_lse":
+        x = torch.matmul(q[0, 0].double().reshape(Hkv, G * W, D), k[0, 0].double().transpose(1, 2).contiguous()) / D ** 0.5
+        seen = torch.arange(L, device="cuda")[None] <= L - W + torch.arange(W, device="cuda").repeat(G)[:, None]
+        lse = torch.logsumexp(x.masked_fill(~seen, float("-inf")), -1).float().contiguous()
+    _check(oracle, torch, q, k, Hkv, G, W, D, L, all_heads=entry == "all_heads", row_lse=lse, score_chunk=512)
