@@ -287,10 +287,11 @@ struct KeyStream {
     {
         for (int u = from; u < min(to, n_sub); ++u) issue(u);
     }
-    // AHEAD: subtile 0 into kb
+    // subtile 0 into kb, where the first next() expects it or (not AHEAD) LOOK asks for it
+    template <bool LOOK = false>
     __device__ __forceinline__ void start(bf16x8 (&kb)[2][4])
     {
-        if (!AHEAD || n_sub == 0) return;
+        if (!(AHEAD || LOOK) || n_sub == 0) return;
         wait_loads(min(NBUF, n_sub) - 1);
         read_subtile(lane_addr0, kb);
     }
@@ -336,6 +337,7 @@ struct KeyStreamDirect {
         }
     }
     __device__ __forceinline__ void issue_first(int = 0, int = 0) {}
+    template <bool = false>
     __device__ __forceinline__ void start(bf16x8 (&kb)[2][KS])
     {
         if (n_sub > 0) load(0, kb);
@@ -354,6 +356,14 @@ __device__ __forceinline__ void copy_subtile(bf16x8 (&to)[2][KS], const bf16x8 (
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int s = 0; s < KS; ++s) to[t][s] = from[t][s];
+}
+
+__device__ __forceinline__ void copy_group(floatx4 (&to)[2][2], const floatx4 (&from)[2][2])
+{
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) to[r][t] = from[r][t];
 }
 
 // the key stream by k-steps of 32 elements per key: 4 (D = 128) staged through LDS; 2 (D = 64), 3 (D = 96) and 8 (D =
@@ -439,14 +449,21 @@ __device__ __forceinline__ void pin_queries(bf16x8 (&qa)[NT][KS], const ScoreArg
 // Row statistics: per window-query row a reference and the sum z of exp2(c1 * <q,k> - ref) over the keys, kept per lane
 // (its keys) until the end.
 //
-// The loop has two bodies.  The fast one has no reference: a sum of positive terms is as
-// accurate as its terms whatever their size, as long as none overflows and those that underflow do not count.  Both can be
-// told from the row's sum: no logit that it holds exceeds SUM_MOST, and what was flushed to zero (below 2^-126 each) is
-// nothing beside SUM_LEAST.  Logits of attention lie within some tens of powers of two around 1; where a row's do not, the
-// wavefront runs its keys once more through the careful body alone.  That one keeps a reference per row and wavefront,
-// shared by the 16 lanes that hold the row (negated and divided by c1: the MFMA's C operand `cr`, so acc = <q,k> - ref / c1
-// and the exponent is c1 * acc), anchored at the row's maximum over the first subtile and moved before an exponent exceeds
-// RESCALE_AT: any finite logits are handled.
+// Keys of 128 elements are walked without references at first: a sum of positive terms is as accurate as its terms
+// whatever their size, as long as none overflows and those that underflow do not count.  Both can be told from the
+// row's sum: no logit that it holds exceeds SUM_MOST, and what was flushed to zero (below 2^-126 each) is nothing beside
+// SUM_LEAST.  Logits of unbiased keys lie within some tens of powers of two around 1; of a model whose keys carry a bias
+// they need not.  A wavefront that finds a row outside, as a rule after its first sixteen subtiles, begins again with
+// references: the row maxima over its first subtile, negated the MFMA's C operands, so acc = <q,k> - reference.  Those
+// cost an LDS read per tile and subtile (all registers are taken by 256 rows).  Where even then a sum is outside (a
+// logit 100 powers of two above the first subtile's, or a stream that begins inside the window) it walks once more, through
+// stats_careful, whose references move: any finite logits are handled.  Both passes, 128 rows, all logits at 0 and 50
+// below: 8 problems of 8 192 keys 21.9 and 29.7 us, 64 of 32 768 keys 237 and 272 (with stats_careful behind the whole first
+// walk 40.5 and 772).
+//
+// Keys of other lengths have references from the start, so that the exponent of a peak is small and rounds to less
+// (peaks of 2^26, heads of 64 elements: scores 5.9e-7 off with, 8.4e-7 without; of 128, where the products are off by as
+// much, 1.0e-6 with and without).
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v)
@@ -470,7 +487,8 @@ __device__ __forceinline__ float group_sum(float v)
 }
 
 // Careful body: the subtile in kb, whose first key is t0, against all row tiles.  A row's state sits in LDS: state[pos / 2] =
-// (cr, z) of two rows, z the sum over all lanes.  Rare: the tiles' loop is not unrolled and takes its queries from memory.
+// (cr, z) of two rows, z the sum over all lanes.  Three times as slow as the other walks: the tiles' loop is not unrolled and
+// takes its queries from memory, for less code.
 template <int NT, int W, int KS>
 __device__ __forceinline__ void stats_careful(const ScoreArgs &a, int p, const bf16x8 (&kb)[2][KS], floatx4 *state, bool first, int t0, int n, int g)
 {
@@ -530,14 +548,14 @@ __device__ __forceinline__ void stats_add(const floatx4 (&acc)[2][2], int j, flo
 
 // Fast body of one subtile: group j is multiplied into acc[(j + PAR) & 1] while the group before it is exponentiated from
 // the other set, at first the last group of the subtile before.  The last group is left waiting.
-template <int PAR, int NT, int KS>
+template <int PAR, int NT, int KS, typename C>
 __device__ __forceinline__ void stats_fast(const bf16x8 (&qa)[NT][KS], const bf16x8 (&kb)[2][KS], floatx4 (&acc)[2][2][2],
-                                           const floatx4 (&cr)[NT], floatx4 (&z)[NT], float c1)
+                                           C c, floatx4 (&z)[NT], float c1)
 {
     constexpr int NG = (NT + 1) / 2;
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
-        multiply(qa, kb, j, [&](int J) { return KS == 4 ? floatx4{} : cr[J]; }, acc[(j + PAR) & 1]);
+        multiply(qa, kb, j, c, acc[(j + PAR) & 1]);
         stats_add<0>(acc[(j + PAR + 1) & 1], j > 0 ? j - 1 : NG - 1, z, c1, 0, 0, 0);
     }
     // the sums as they are here: keeps the compiler from moving this subtile's exponentials behind the next one's loads
@@ -547,12 +565,144 @@ __device__ __forceinline__ void stats_fast(const bf16x8 (&qa)[NT][KS], const bf1
         if (NT <= 8) asm volatile("" : "+v"(z[J]));
 }
 
+// the lane, formed where it is used: what follows from it is not kept in registers through the loops in front
+__device__ __forceinline__ int lane_again()
+{
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
+// One walk over the stream, whose first subtiles are on their way, to the rows' states.  REF: with references, kept in refs[MP].
+// True (in some lane): a sum is outside what it can tell, the states are void; then the subtiles on their way may be any.
+template <bool REF, int NT, int W, int KS, typename Stream>
+__device__ __forceinline__ bool stats_walk(const ScoreArgs &a, const WaveWork &w, Stream &ks, const bf16x8 (&qa)[NT][KS],
+                                           floatx4 *state, float *refs, int n_plain, int lane)
+{
+    using R = Rows<NT, W>;
+    constexpr int NG = R::NG;
+    constexpr bool ONE = !Stream::AHEAD && NG % 2 == 0;        // a step is one subtile, and nothing changes places
+    constexpr bool SHORT = !ONE && REF && KS == 4;             // so is it here, for less code: what changes places is copied
+    const int T = a.d.T;
+    int n = lane & 15, g = lane >> 4;
+    bf16x8 ka[2][KS], ahead[2][KS];
+    auto &kb = Stream::AHEAD ? ahead : ka;
+    ks.template start<REF>(ka);
+    floatx4 cr[NT];                                            // in registers where there is room for them
+    if (REF) {
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            floatx4 first[2][2] = {};
+            if (n_plain > 0) multiply(qa, ka, j, no_operand, first);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                if (2 * j + r >= NT) continue;
+                floatx4 ref;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float rm = group_max(fmaxf(first[r][0][i], first[r][1][i]));
+                    ref[i] = fabsf(rm) < INFINITY ? -rm : 0.f;
+                }
+                if (n == 0) *reinterpret_cast<floatx4 *>(refs + TILE * (2 * j + r) + 4 * g) = ref;
+                if (KS != 4) cr[2 * j + r] = ref;
+            }
+        }
+        __builtin_amdgcn_wave_barrier();                       // written before the first subtile's reads
+    }
+    auto c = [&](int J) __attribute__((always_inline)) {
+        return !REF ? floatx4{} : KS != 4 ? cr[J] : *reinterpret_cast<const floatx4 *>(refs + TILE * J + 4 * g);
+    };
+    // in two levels: beside one large term, small ones that are added to it one by one are lost, sixteen subtiles of
+    // them together are not (rows with a peak of 2^26 times the rest, 131 072 keys: sums 5e-5 off without)
+    floatx4 z[NT], zo[NT];
+#pragma unroll
+    for (int J = 0; J < NT; ++J) z[J] = zo[J] = floatx4{};
+    auto level = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int J = 0; J < NT; ++J) {
+            zo[J] += z[J];
+            z[J] = floatx4{};
+        }
+    };
+    auto outside = [&](float &least) __attribute__((always_inline)) {
+        float most = 0.f;
+        least = INFINITY;
+#pragma unroll
+        for (int J = 0; J < NT; ++J)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                least = fminf(least, zo[J][i]);
+                most = fmaxf(most, zo[J][i]);
+            }
+        return most > SUM_MOST;
+    };
+    floatx4 acc[2][2][2];
+    set_nothing(acc[0]);
+    set_nothing(acc[1]);
+    int u = 0;
+    float least;
+    for (; u + (ONE || SHORT ? 0 : 1) < n_plain; u += ONE || SHORT ? 1 : 2) {
+        ks.next(u, ka, kb);
+        stats_fast<0>(qa, ka, acc, c, z, a.c1);
+        if (SHORT) {
+            copy_subtile(ka, kb);
+            if (NG & 1) copy_group(acc[1], acc[0]);
+        } else if (!ONE) {                                     // the operands, and with an odd number of groups the accumulators, change places
+            ks.next(u + 1, kb, ka);
+            stats_fast<NG & 1>(qa, kb, acc, c, z, a.c1);
+        }
+        if ((u & 15) >= 14) {
+            level();
+            if (!REF && u < 16 && __any(outside(least) || least < SUM_LEAST)) return true;
+        }
+    }
+    if (!ONE && !SHORT && u < n_plain) {
+        ks.next(u++, ka, kb);
+        stats_fast<0>(qa, ka, acc, c, z, a.c1);
+        stats_add<0>(acc[(NG & 1) ^ 1], NG - 1, z, a.c1, 0, 0, 0);
+        copy_subtile(ka, kb);
+    } else {
+        stats_add<0>(acc[1], NG - 1, z, a.c1, 0, 0, 0);
+    }
+    lane = lane_again();
+    n = lane & 15, g = lane >> 4;
+    // the subtiles with masked keys
+    for (; u < w.n_sub; ++u) {
+        ks.next(u, ka, kb);
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            multiply(qa, ka, j, c, acc[j & 1]);
+            stats_add<W>(acc[j & 1], j, z, a.c1, w.first + u * STRIDE + n, g, T);
+        }
+        copy_subtile(ka, kb);
+    }
+    level();
+    // per row: the lane group's 16 sums together
+#pragma unroll
+    for (int J = 0; J < NT; ++J) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) zo[J][i] = group_sum(zo[J][i]);
+        const floatx4 ref = c(J);
+        if (n == 0) {
+            floatx4 *st = state + (TILE * J + 4 * g) / 2;
+            st[0] = floatx4{ref[0], zo[J][0], ref[1], zo[J][1]};
+            st[1] = floatx4{ref[2], zo[J][2], ref[3], zo[J][3]};
+        }
+    }
+    bool again = outside(least);
+    if (w.first <= T) again |= least < SUM_LEAST;
+    else                                                       // inside the window: of the rows that see the stream's first key
+        for (int pos = lane; pos < R::MP; pos += 64)
+            again |= w.first <= T + R::row_of(pos) % W && reinterpret_cast<const float *>(state)[2 * pos + 1] < SUM_LEAST;
+    return again;
+}
+
 template <int NT, int W, int KS>
 __global__ void __launch_bounds__(WAVES * 64)
 score_mfma_stats(ScoreArgs a)
 {
     using R = Rows<NT, W>;
-    constexpr int MP = R::MP, NG = R::NG;
+    constexpr int MP = R::MP;
     extern __shared__ __attribute__((aligned(8192))) char lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -560,6 +710,7 @@ score_mfma_stats(ScoreArgs a)
     char *ring = lds + wave * RING_BYTES;
     floatx4 *wg_state = reinterpret_cast<floatx4 *>(lds + WAVES * RING_BYTES);     // [WAVES][MP / 2], see stats_careful
     floatx4 *state = wg_state + wave * (MP / 2);
+    float *refs = reinterpret_cast<float *>(wg_state + WAVES * (MP / 2)) + wave * MP;     // see stats_walk
     const WaveWork w = wave_work(a, wave);
 
     // queries before keys, as loads return in order; both are in flight together
@@ -584,108 +735,28 @@ score_mfma_stats(ScoreArgs a)
     }
 
     const int n_plain = plain_subtiles(w, d.T);
-    for (bool careful = false;; careful = true) {
-        bf16x8 ka[2][KS], kb[2][KS];
-        ks.start(ka);
-        int u = 0;
-        bool again = false;
-        if (!careful) {
-            // in two levels: beside one large term, small ones that are added to it one by one are lost, sixteen subtiles of
-            // them together are not (rows with a peak of 2^26 times the rest, 131 072 keys: sums 5e-5 off without)
-            floatx4 z[NT], zo[NT];
-#pragma unroll
-            for (int J = 0; J < NT; ++J) z[J] = zo[J] = floatx4{};
-            auto level = [&]() __attribute__((always_inline)) {
-#pragma unroll
-                for (int J = 0; J < NT; ++J) {
-                    zo[J] += z[J];
-                    z[J] = floatx4{};
-                }
-            };
-            // Keys of other lengths than 128 elements: the row maxima over the first subtile as references all the same, so that
-            // the exponent of a peak is small and rounds to less (peaks of 2^26, heads of 64 elements: scores 5.9e-7 off with,
-            // 8.4e-7 without; of 128, where the products are off by as much, 1.0e-6 with and without)
-            floatx4 cr[NT];
-#pragma unroll
-            for (int J = 0; J < NT; ++J) cr[J] = floatx4{};
-            if (KS != 4 && n_plain > 0) {
-#pragma unroll
-                for (int j = 0; j < NG; ++j) {
-                    floatx4 first[2][2];
-                    multiply(qa, ka, j, no_operand, first);
-#pragma unroll
-                    for (int r = 0; r < 2; ++r)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            if (2 * j + r >= NT) continue;
-                            const float rm = group_max(fmaxf(first[r][0][i], first[r][1][i]));
-                            cr[2 * j + r][i] = fabsf(rm) < INFINITY ? -rm : 0.f;
-                        }
-                }
+    if (__any(stats_walk<KS != 4, NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane))) {
+        auto restart = [&]() __attribute__((always_inline)) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");        // what is on its way to the ring or from it
+            ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane_again());
+            ks.issue_first();
+        };
+        restart();
+        bool careful = KS != 4 || n_plain == 0;
+        if constexpr (KS == 4)
+            if (!careful) {
+                careful = __any(stats_walk<true, NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane));
+                if (careful) restart();
             }
-            // two subtiles a step: the operands, and with an odd number of groups the accumulators, change places
-            floatx4 acc[2][2][2];
-            set_nothing(acc[0]);
-            set_nothing(acc[1]);
-            constexpr bool ONE = !Stream::AHEAD && NG % 2 == 0;
-            for (; u + (ONE ? 0 : 1) < n_plain; u += ONE ? 1 : 2) {
-                ks.next(u, ka, kb);
-                stats_fast<0>(qa, ka, acc, cr, z, a.c1);
-                if (!ONE) {                                    // else nothing changes places
-                    ks.next(u + 1, kb, ka);
-                    stats_fast<NG & 1>(qa, kb, acc, cr, z, a.c1);
-                }
-                if ((u & 15) >= 14) level();
-            }
-            if (!ONE && u < n_plain) {
-                ks.next(u++, ka, kb);
-                stats_fast<0>(qa, ka, acc, cr, z, a.c1);
-                stats_add<0>(acc[(NG & 1) ^ 1], NG - 1, z, a.c1, 0, 0, 0);
-                copy_subtile(ka, kb);
-            } else {
-                stats_add<0>(acc[1], NG - 1, z, a.c1, 0, 0, 0);
-            }
-            // the subtiles with masked keys
-            for (; u < w.n_sub; ++u) {
-                ks.next(u, ka, kb);
-#pragma unroll
-                for (int j = 0; j < NG; ++j) {
-                    multiply(qa, ka, j, [&](int J) { return KS == 4 ? floatx4{} : cr[J]; }, acc[j & 1]);
-                    stats_add<W>(acc[j & 1], j, z, a.c1, w.first + u * STRIDE + n, g, d.T);
-                }
-                copy_subtile(ka, kb);
-            }
-            level();
-            // per row: the lane group's 16 sums together
-            float least = INFINITY, most = 0.f;
-#pragma unroll
-            for (int J = 0; J < NT; ++J) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    zo[J][i] = group_sum(zo[J][i]);
-                    least = fminf(least, zo[J][i]);
-                    most = fmaxf(most, zo[J][i]);
-                }
-                if (n == 0) {
-                    floatx4 *st = state + (TILE * J + 4 * g) / 2;
-                    st[0] = floatx4{cr[J][0], zo[J][0], cr[J][1], zo[J][1]};
-                    st[1] = floatx4{cr[J][2], zo[J][2], cr[J][3], zo[J][3]};
-                }
-            }
-            again = most > SUM_MOST || (w.first <= d.T && least < SUM_LEAST);
-            if (w.first > d.T)                                 // inside the window: of the rows that see the stream's first key
-                for (int pos = lane; pos < MP; pos += 64)
-                    again |= w.first <= d.T + R::row_of(pos) % W && reinterpret_cast<const float *>(state)[2 * pos + 1] < SUM_LEAST;
-        } else {
-            for (; u < w.n_sub; ++u) {
+        if (careful) {
+            bf16x8 ka[2][KS], kb[2][KS];
+            ks.start(ka);
+            for (int u = 0; u < w.n_sub; ++u) {
                 ks.next(u, ka, kb);
                 stats_careful<NT, W>(a, w.p, ka, state, u == 0, w.first + u * STRIDE, n, g);
                 copy_subtile(ka, kb);
             }
         }
-        if (careful || !__any(again)) break;
-        ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane);
-        ks.issue_first();
     }
 
     // ---- the four wavefronts' (reference, sum) pairs together
@@ -708,7 +779,7 @@ score_mfma_stats(ScoreArgs a)
         o[1] = zz;
     }
 }
-template <int NT> constexpr int stats_lds() { return WAVES * RING_BYTES + WAVES * TILE * NT * 2 * 4; }   // rings + the rows' state
+template <int NT> constexpr int stats_lds() { return WAVES * RING_BYTES + WAVES * TILE * NT * 3 * 4; }   // rings + the rows' state and references
 
 // ------------------------------------------------------------------ pass 2
 // Folds the (reference, sum) pairs c0, c0 + step, ... < n of one row (`stride` floats apart) into (m, z).  The pairs
@@ -983,12 +1054,7 @@ score_mfma_columns(ScoreArgs a)
         if (u < end) {
             subtile(ka, kb, integral_constant<int, 0>{}, edge_t);
             copy_subtile(ka, kb);
-            if (NG & 1) {
-#pragma unroll
-                for (int r = 0; r < 2; ++r)
-#pragma unroll
-                    for (int kt = 0; kt < 2; ++kt) acc[1][r][kt] = acc[0][r][kt];
-            }
+            if (NG & 1) copy_group(acc[1], acc[0]);
         }
     };
     run(plain_subtiles(w, d.T), std::false_type{});

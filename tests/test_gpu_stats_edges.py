@@ -95,3 +95,51 @@ def test_probabilities_of_rows_far_from_zero_are_not_flushed(oracle, torch_cuda,
         seen = torch.arange(L, device="cuda")[None] <= L - W + torch.arange(W, device="cuda").repeat(G)[:, None]
         lse = torch.logsumexp(x.masked_fill(~seen, float("-inf")), -1).float().contiguous()
     _check(oracle, torch, q, k, Hkv, G, W, D, L, all_heads=entry == "all_heads", row_lse=lse, score_chunk=512)
+
+
+@pytest.mark.parametrize("G,W,D", FAR + [(6, 32, 128), (3, 64, 128), (3, 16, 128)])
+@pytest.mark.parametrize("logits", [(-60.0, -60.0), (80.0, 80.0), (0.0, 100.0), (-68.0, 0.0)])
+def test_rows_far_from_zero_in_long_streams(oracle, torch_cuda, G, W, D, logits):  # noqa: F811
+    # 33 subtiles to a stream.  All logits far from zero: a walk with references, begun after the first sixteen subtiles;
+    # only those of the last third far from the first subtile's: references that have to move
+    torch = torch_cuda
+    Hkv, L = 2, 4096 + 77 + W
+    q = synth.normal_torch(G * W + D, 7, (1, 1, G * Hkv, W, D), "cuda", torch.bfloat16)
+    k = synth.normal_torch(G * W + D, 8, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    q[..., 0] = D ** 0.5
+    k[..., 0] = logits[0]
+    k[:, :, :, 2800:, 0] = logits[1]
+    _check(oracle, torch, q, k, Hkv, G, W, D, L, score_chunk=8192)
+
+
+@pytest.mark.parametrize("G,W", [(4, 32), (4, 16), (7, 32), (4, 64)])
+@pytest.mark.parametrize("logit", [-50.0, 80.0])
+def test_rows_far_from_zero_cost_little_more(torch_cuda, G, W, logit):  # noqa: F811
+    # sixteen of 64 subtiles a second time and the references of a tile and subtile from LDS: less than half of one pass in two,
+    # where a walk of its own for every tile is three times the call and more
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    Hkv, L, D = 32, 65536, 128
+    q = synth.normal_torch(G * W, 9, (1, 1, G * Hkv, W, D), "cuda", torch.bfloat16)
+    k = synth.normal_torch(G * W, 10, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    q[..., 0] = D ** 0.5
+    shape = B.make_shape(q, k)
+    s = torch.empty((Hkv, L), dtype=torch.float32, device="cuda")
+    e, ws = torch.empty_like(s), torch.empty((B.sablock_workspace_bytes(shape, 0, 0),), dtype=torch.uint8, device="cuda")
+
+    def took():
+        times = []
+        for _ in range(15):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            B.sablock_score(shape, q, k, s, e, ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return sorted(times)[7]
+
+    k[..., 0] = 0.0
+    near = took()
+    k[..., 0] = logit
+    assert took() < 1.5 * near
