@@ -582,7 +582,8 @@ __device__ __forceinline__ bool stats_walk(const ScoreArgs &a, const WaveWork &w
     using R = Rows<NT, W>;
     constexpr int NG = R::NG;
     constexpr bool ONE = !Stream::AHEAD && NG % 2 == 0;        // a step is one subtile, and nothing changes places
-    constexpr bool SHORT = !ONE && REF && KS == 4;             // so is it here, for less code: what changes places is copied
+    // so is it here, and what changes places is copied: for less code, or because two subtiles of more than 192 rows spill
+    constexpr bool SHORT = !ONE && ((REF && KS == 4) || NT > 12);
     const int T = a.d.T;
     int n = lane & 15, g = lane >> 4;
     bf16x8 ka[2][KS], ahead[2][KS];

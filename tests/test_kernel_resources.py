@@ -57,3 +57,18 @@ def test_any_shape_scoring_plans_as_many_workgroups_as_the_registers_let_reside(
         assert k["private_segment_fixed_size"] == 0, name
         seen += 1
     assert seen == 48
+
+
+def test_scoring_kernels_do_not_spill(tmp_path):
+    # a reload waits, through the one counter of loads in order, for the keys that are on their way to LDS in front of it.
+    # Read from the object as it is built: these are 200 kernels, and take minutes to compile
+    os.makedirs(build.OBJ, exist_ok=True)
+    bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code.o")
+    llvm = os.path.join(os.path.dirname(os.path.realpath(build.HIPCC)), "..", "llvm", "bin")
+    subprocess.run([f"{llvm}/llvm-objcopy", f"--dump-section=.hip_fatbin={bundle}", build._compile("score_mfma.hip", False), os.devnull], check=True)
+    subprocess.run([f"{llvm}/clang-offload-bundler", "--unbundle", "--type=o", f"--input={bundle}", f"--output={code}",
+                    "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+    notes = subprocess.run([f"{llvm}/llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    scratch = dict(re.findall(r"\.name: +(_Z\S*score_mfma_\S+)\n +\.private_segment_fixed_size: (\d+)", notes))
+    assert len(scratch) == 88 + 108 + 1, len(scratch)          # statistics, columns and those of all heads of a layer
+    assert set(scratch.values()) == {"0"}, {n: x for n, x in scratch.items() if x != "0"}
