@@ -752,7 +752,7 @@ score_mfma_stats(ScoreArgs a)
     }
 
     const int n_plain = plain_subtiles(w, d.T);
-    if (__any(stats_walk<KS != 4, NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane))) {
+    if (__builtin_expect(__any(stats_walk<KS != 4, NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane)), 0)) {
         auto restart = [&]() __attribute__((always_inline)) {
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");        // what is on its way to the ring or from it
             ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane_again());
