@@ -389,18 +389,18 @@ def compress(shape: CShape, q, k, v, seg: Segments, cand: Sequence[int], budget:
     ``fused=False``: same results), compact."""
     # the calls above with their arguments marshalled once: small calls are bound by what the host does between launches
     lib, st, sp = load(), _stream(stream), ctypes.byref(shape)
-    s, ent, s_tilde, topb, idx, n_sel = (t.data_ptr() for t in (buf.s, buf.ent, buf.s_tilde, buf.topb, buf.idx, buf.n_sel))
-    kp, bk, g = k.data_ptr(), buf.seg_budget.data_ptr(), buf.block_size.data_ptr()
-    ws = (buf.ws.data_ptr(), buf.ws.numel() * buf.ws.element_size(), st)
-    segs = (seg.seg_off.data_ptr(), seg.c_ptr(), seg.max_segments)
+    s, ent, s_tilde, topb, idx, n_sel = (_ptr(t) for t in (buf.s, buf.ent, buf.s_tilde, buf.topb, buf.idx, buf.n_sel))
+    kp, bk, g = _ptr(k), _ptr(buf.seg_budget), _ptr(buf.block_size)
+    ws = (_ptr(buf.ws), buf.ws.numel() * buf.ws.element_size(), st)
+    segs = (_ptr(seg.seg_off), seg.c_ptr(), seg.max_segments)
     cl = ((ctypes.c_int32 * len(cand))(*[int(x) for x in cand]), len(cand))
-    _check(lib.sablock_score(sp, q.data_ptr(), kp, _ptr(row_lse), eps, s, ent, *ws))
-    _check(lib.sablock_refine(sp, s, ent, *segs, ctypes.byref(CHparams(0.0, alpha, eta, 0.0)), s_tilde, buf.omega.data_ptr(), *ws))
+    _check(lib.sablock_score(sp, _ptr(q), kp, _ptr(row_lse), eps, s, ent, *ws))
+    _check(lib.sablock_refine(sp, s, ent, *segs, ctypes.byref(CHparams(0.0, alpha, eta, 0.0)), s_tilde, _ptr(buf.omega), *ws))
     if fused:
         _check(lib.sablock_search_select(sp, s_tilde, *segs, *cl, budget, tau, bk, g, topb, idx, n_sel, *ws))
     else:
         _check(lib.sablock_search_blocks(sp, s_tilde, *segs, *cl, budget, tau, bk, g, topb, *ws))
         _check(lib.sablock_select(sp, s_tilde, *segs, bk, g, topb, budget, idx, n_sel, *ws))
-    _check(lib.sablock_compact(sp, kp, v.data_ptr(), idx, n_sel, budget, 1 if buf.append_window else 0, buf.k_out.data_ptr(),
-                               buf.v_out.data_ptr(), st))
+    _check(lib.sablock_compact(sp, kp, _ptr(v), idx, n_sel, budget, 1 if buf.append_window else 0, _ptr(buf.k_out),
+                               _ptr(buf.v_out), st))
     return buf

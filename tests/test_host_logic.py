@@ -8,6 +8,7 @@ import sys
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2510_22556_amd import binding as B
 from paper_2510_22556_amd import synth
@@ -311,3 +312,33 @@ def test_slices_of_the_segmentation(lib):
             per = -(-T // B.SLICE_TOKENS)
             assert lib.sablock_segment_slices(n_seq, T) == (per if n_seq * per <= B.MAX_SLICES else 0)
     assert lib.sablock_segment_slices(0, 5) == lib.sablock_segment_slices(65, 5) == lib.sablock_segment_slices(1, 0) == 0
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_compress_takes_buffers_without_the_optional_outputs(monkeypatch, fused):
+    # omega and the Top-B thresholds may be NULL in the calls, so None in the buffers
+    calls = []
+
+    class Recorder:
+        def __getattr__(self, name):
+            return lambda *a: calls.append((name, a)) or B.SABLOCK_OK
+
+    class Stream:
+        cuda_stream = 0
+
+    monkeypatch.setattr(B, "load", Recorder)
+    buf = B.Buffers.__new__(B.Buffers)
+    t = torch.zeros(4)
+    for name in "s ent s_tilde seg_budget block_size idx n_sel k_out v_out ws".split():
+        setattr(buf, name, t)
+    buf.omega = buf.topb = None
+    buf.append_window = True
+    B.compress(B.CShape(), t, t, t, B.Segments(t, [0, 2], 1), [1, 2], 1, buf, stream=Stream, fused=fused)
+    args = dict(calls)
+    at = t.data_ptr()
+    assert args["sablock_refine"][-5:-3] == (at, None)
+    if fused:
+        assert args["sablock_search_select"][-8:-3] == (at, at, None, at, at)
+    else:
+        assert args["sablock_search_blocks"][-6:-3] == (at, at, None)
+        assert args["sablock_select"][-9:-3] == (at, at, None, 1, at, at)
