@@ -90,7 +90,7 @@ __device__ inline void wave_steps(int first, int last, int &r0, int &r1)
     r0 = min(first + w * per, last);
     r1 = min(r0 + per, last);
 }
-__device__ __host__ inline int steps_of(int T) { return (T + SG_STEP - 1) / SG_STEP; }
+__device__ __host__ inline int steps_of(int T) { return T / SG_STEP + (T % SG_STEP != 0); }
 
 // sum of the wavefronts' values (wave-uniform) and of those before this one
 __device__ inline int over_waves(int v, int *sh_w, int &total)

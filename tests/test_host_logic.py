@@ -311,6 +311,8 @@ def test_slices_of_the_segmentation(lib):
         for T in (1, B.SLICE_TOKENS - 1, B.SLICE_TOKENS, B.SLICE_TOKENS + 1, 131072, 1 << 20, 1 << 22):
             per = -(-T // B.SLICE_TOKENS)
             assert lib.sablock_segment_slices(n_seq, T) == (per if n_seq * per <= B.MAX_SLICES else 0)
+    for T in (2**31 - 300, 2**31 - 255, 2**31 - 1):            # steps of tokens that an int cannot round up
+        assert lib.sablock_segment_slices(1, T) == lib.sablock_segment_slices(64, T) == 0
     assert lib.sablock_segment_slices(0, 5) == lib.sablock_segment_slices(65, 5) == lib.sablock_segment_slices(1, 0) == 0
 
 
