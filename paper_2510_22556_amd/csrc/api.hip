@@ -550,7 +550,7 @@ sablock_status sablock_segment_slice_offsets(const int32_t *token_ids, int64_t t
     if (slice_place[0] < 0) return fail(SABLOCK_ERR_INVALID_ARG, "slice_place[0] < 0");
     for (int i = 0; i <= MAX_SLICES; ++i) sp.at[i] = slice_place[std::min(i, n)];
     for (int i = 0; i < n; ++i)
-        if (sp.at[i + 1] - sp.at[i] < ((i + 1) % per == 0 ? 2 : 0))
+        if ((int64_t)sp.at[i + 1] - sp.at[i] < ((i + 1) % per == 0 ? 2 : 0))
             return fail(SABLOCK_ERR_INVALID_ARG, "slice_place descends, or leaves no room for the ends, at slice %d", i);
     DelimSet ds;
     sablock_status st = make_delims(delims, n_delim, &ds);

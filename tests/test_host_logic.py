@@ -316,6 +316,16 @@ def test_slices_of_the_segmentation(lib):
     assert lib.sablock_segment_slices(0, 5) == lib.sablock_segment_slices(65, 5) == lib.sablock_segment_slices(1, 0) == 0
 
 
+@pytest.mark.parametrize("T,place", [(100, [0, 1]), (100, [-1, 5]), (100, [5, 4]), (100, [5, -2**31]), (100, [2**31 - 1, -2**31 + 1]),
+                                     (40000, [0, 10, 20, 21]), (40000, [0, 10, 9, 30]), (40000, [7, 3, 20, 30])])
+def test_slice_places_without_room_are_refused(lib, T, place):
+    # before anything is enqueued: the kernel writes at these places
+    fake, delims = ctypes.c_void_p(0x1000), (ctypes.c_int32 * 1)(7)
+    at = (ctypes.c_int32 * len(place))(*place)
+    assert lib.sablock_segment_slice_offsets(fake, T, 1, T, delims, 1, at, fake, None) == 1
+    assert b"slice_place" in lib.sablock_last_error()
+
+
 @pytest.mark.parametrize("fused", [True, False])
 def test_compress_takes_buffers_without_the_optional_outputs(monkeypatch, fused):
     # omega and the Top-B thresholds may be NULL in the calls, so None in the buffers
