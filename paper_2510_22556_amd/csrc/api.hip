@@ -528,6 +528,7 @@ sablock_status sablock_segment_slice_count(const int32_t *token_ids, int64_t tok
     if (!token_ids || !slice_count_out) return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_count: NULL argument");
     if (n_seq < 1 || n_tokens < 1 || token_stride < n_tokens)
         return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_count: need n_seq >= 1, n_tokens >= 1, token_stride >= n_tokens");
+    if (n_seq > MAX_SEQ) return fail(SABLOCK_ERR_UNSUPPORTED, "n_seq %d: at most %d per call", n_seq, MAX_SEQ);
     if (sablock_segment_slices(n_seq, n_tokens) <= 0)
         return fail(SABLOCK_ERR_UNSUPPORTED, "sablock_segment_slice_count: more than %d slices in a call", MAX_SLICES);
     DelimSet ds;
@@ -544,6 +545,7 @@ sablock_status sablock_segment_slice_offsets(const int32_t *token_ids, int64_t t
     if (!token_ids || !slice_place || !seg_off_out) return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_offsets: NULL argument");
     if (n_seq < 1 || n_tokens < 1 || token_stride < n_tokens)
         return fail(SABLOCK_ERR_INVALID_ARG, "sablock_segment_slice_offsets: need n_seq >= 1, n_tokens >= 1, token_stride >= n_tokens");
+    if (n_seq > MAX_SEQ) return fail(SABLOCK_ERR_UNSUPPORTED, "n_seq %d: at most %d per call", n_seq, MAX_SEQ);
     const int per = sablock_segment_slices(n_seq, n_tokens), n = per * n_seq;
     if (n <= 0) return fail(SABLOCK_ERR_UNSUPPORTED, "sablock_segment_slice_offsets: more than %d slices in a call", MAX_SLICES);
     SlicePlaces sp;

@@ -326,6 +326,14 @@ def test_slice_places_without_room_are_refused(lib, T, place):
     assert b"slice_place" in lib.sablock_last_error()
 
 
+@pytest.mark.parametrize("n_seq,T,reason", [(65, 100, b"n_seq 65"), (64, 40000, b"slices"), (1, 2**31 - 1, b"slices")])
+def test_slice_calls_say_what_they_do_not_take(lib, n_seq, T, reason):
+    fake, delims, place = ctypes.c_void_p(0x1000), (ctypes.c_int32 * 1)(7), (ctypes.c_int32 * 256)(*range(256))
+    for call, where in ((lib.sablock_segment_slice_count, (fake,)), (lib.sablock_segment_slice_offsets, (place, fake))):
+        assert call(fake, T, n_seq, T, delims, 1, *where, None) == 2
+        assert reason in lib.sablock_last_error()
+
+
 @pytest.mark.parametrize("fused", [True, False])
 def test_compress_takes_buffers_without_the_optional_outputs(monkeypatch, fused):
     # omega and the Top-B thresholds may be NULL in the calls, so None in the buffers
