@@ -101,7 +101,7 @@ size_t score_generic_ws_bytes(const Dims &d);
 hipError_t launch_score_generic(const Dims &d, const void *q, const void *k, const float *row_lse, float eps,
                                 float *s_out, float *ent_out, void *ws, hipStream_t st);
 
-// MFMA scoring for bf16, D = 128, G*W = 128
+// MFMA scoring for bf16 (which shapes: score_mfma_supported)
 bool score_mfma_supported(const Dims &d);
 size_t score_mfma_ws_bytes(const Dims &d);
 hipError_t launch_score_mfma(const Dims &d, const void *q, const void *k, const float *row_lse, float eps,
@@ -174,8 +174,8 @@ struct PerDeviceOnce {
     void done() { done_dev = cur; }
 };
 
-// row statistics of the scoring step for 256 window-query rows per KV head with one read of K (the attention
-// kernel's first product alone): stats [P][row_stats_chunks][G * W][2] = (reference in the log2 domain, sum)
+// row statistics of the scoring step by the attention kernel's first product alone, a lane per window query, for 129 .. 256
+// window-query rows per KV head and for G = 4 with W = 32; on request (tuning.stats_per_key = 2): stats [P][row_stats_chunks][G * W][2] = (reference in the log2 domain, sum)
 bool row_stats_supported(const Dims &d);
 int row_stats_chunks(const Dims &d);
 hipError_t launch_row_stats(const Dims &d, const void *q, const void *k, float *stats, hipStream_t st);

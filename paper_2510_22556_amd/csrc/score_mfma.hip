@@ -1464,10 +1464,9 @@ Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)
     return pl;
 }
 
-// bytes of the chunk partials, and of their merged form behind them (more than 128 rows: room for 256)
-int stat_rows(const Dims &d) { return d.G * d.W > M_ROWS ? 2 * M_ROWS : d.G * d.W; }
-size_t partial_bytes(const Dims &d, const Plan &pl) { return align256((size_t)d.P * pl.n_chunks * stat_rows(d) * 2 * 4); }
-size_t merged_bytes(const Dims &d) { return align256((size_t)d.P * stat_rows(d) * 2 * 4); }
+// bytes of the chunk partials, and of their merged form behind them
+size_t partial_bytes(const Dims &d, const Plan &pl) { return align256((size_t)d.P * pl.n_chunks * d.G * d.W * 2 * 4); }
+size_t merged_bytes(const Dims &d) { return align256((size_t)d.P * d.G * d.W * 2 * 4); }
 
 // pass-1 bookkeeping of both entry points: where the partials go and what pass 2 reads
 void plan_partials(ScoreArgs &a, const Dims &d, const Plan &pl, void *ws)
@@ -1495,13 +1494,13 @@ bool score_mfma_supported(const Dims &d)
 
 // pass 1 by the window-attention kernel's first product (csrc/window_attn.hip), on request
 static bool stats_by_rows(const Dims &d) { return row_stats_supported(d) && d.tune.stats_per_key == 2; }
-static size_t row_stats_bytes(const Dims &d) { return align256((size_t)d.P * 2 * row_stats_chunks(d) * M_ROWS * 2 * 4); }
+static size_t row_stats_bytes(const Dims &d) { return align256((size_t)d.P * row_stats_chunks(d) * d.G * d.W * 2 * 4); }
 
 size_t score_mfma_ws_bytes(const Dims &d)
 {
     const Plan pl = make_plan(d);
     size_t part = partial_bytes(d, pl);
-    if (stats_by_rows(d) || wide_shape(d)) part = std::max(part, row_stats_bytes(d));
+    if (stats_by_rows(d)) part = std::max(part, row_stats_bytes(d));
     return part + merged_bytes(d);
 }
 

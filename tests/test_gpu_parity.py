@@ -498,12 +498,12 @@ def test_mfma_score_any_group_size(oracle, torch_cuda, G, W, D, chunk):
 
 
 @pytest.mark.parametrize("G,W", [(5, 32), (6, 32), (7, 32), (3, 64), (8, 32), (4, 64)])
-@pytest.mark.parametrize("chunk,per_key", [(0, 0), (1024, 0), (1024, 1)])
-def test_mfma_score_wide_groups(oracle, torch_cuda, G, W, chunk, per_key):
-    # 129 .. 256 rows on the eight-tile column kernel: G = 5, 6, 7 with W = 32 and G = 3 with W = 64 leave its last
-    # tiles as padding (zero queries, infinite log-sum-exp); both forms of the statistics pass (a lane per window
-    # query over all rows; a lane per key over blocks of 128 rows), one and several chunks, then the row_lse route
-    _mfma_row_shape_case(oracle, torch_cuda, G, W, 128, chunk, stats_per_key=per_key)
+@pytest.mark.parametrize("chunk,per_key,per_query_chunk", [(0, 0, 0), (1024, 0, 0), (1024, 1, 0), (0, 2, 0), (1024, 2, 1024), (0, 2, 96)])
+def test_mfma_score_wide_groups(oracle, torch_cuda, G, W, chunk, per_key, per_query_chunk):
+    # 129 .. 256 rows, 10 to 16 row tiles; both kernels of the statistics pass, a lane per key (by default) and a lane per
+    # window query on eight blocks of 32 rows, whose last ones G = 5, 6, 7 with W = 32 and G = 3 with W = 64 leave as padding:
+    # one and several chunks and (96: 48 of them) so many that they are merged first; then the row_lse route
+    _mfma_row_shape_case(oracle, torch_cuda, G, W, 128, chunk, stats_per_key=per_key, window_chunk=per_query_chunk)
 
 
 @pytest.mark.parametrize("chunk", [0, 1024])

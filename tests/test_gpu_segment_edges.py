@@ -1,6 +1,8 @@
 """Segmentation at the sizes where its kernels change course (steps of 256 tokens, four in flight, sixteen wavefronts, up to
 eight slices, masks too many for LDS), rows at every alignment, delimiters at every place: whole numbers, exact."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -47,17 +49,59 @@ def test_segment_whatever_torch_s_default_device_is(torch_cuda):  # noqa: F811
     assert seg.seg_off.cpu().tolist() == [0, 10, 100, 0, 20, 30, 100] and list(seg.seg_ptr) == [0, 3, 7]
 
 
-@pytest.mark.parametrize("T", [1, 257, 4099, 16384, 65472])
-def test_the_calls_by_whole_sequences_give_the_same(torch_cuda, T):  # noqa: F811
+def _tokens(torch, T, n_seq=2):
+    tok = np.random.default_rng(T).integers(0, 40, size=(n_seq, T)).astype(np.int32)
+    return tok, torch.as_tensor(tok).cuda()
+
+
+@pytest.mark.parametrize("T", [1, 257, 4099, 16384, 65472, 131075])
+def test_the_calls_by_whole_sequences_give_the_same(oracle, torch_cuda, T):  # noqa: F811
     torch = torch_cuda
     from paper_2510_22556_amd import binding as B
 
-    rng = np.random.default_rng(T)
-    tok = torch.as_tensor(rng.integers(0, 40, size=(2, T)).astype(np.int32)).cuda()
-    seg = B.segment(tok, [3, 5])
+    tok, dev = _tokens(torch, T)
+    ref = [oracle.segment(row, [3, 5]) for row in tok]
+    seg = B.segment(dev, [3, 5])
     count = torch.empty((2,), dtype=torch.int32, device="cuda")
-    B.sablock_segment_count(tok, [3, 5], count)
+    B.sablock_segment_count(dev, [3, 5], count)
     ptr = [0] + [int(x) for x in np.cumsum(count.cpu().numpy() + 1)]
     off = torch.full((ptr[-1],), -1, dtype=torch.int32, device="cuda")
-    B.sablock_segment_offsets(tok, [3, 5], ptr, off)
+    B.sablock_segment_offsets(dev, [3, 5], ptr, off)
     assert ptr == list(seg.seg_ptr) and torch.equal(off, seg.seg_off)
+    np.testing.assert_array_equal(off.cpu().numpy(), np.concatenate(ref))
+
+
+@pytest.mark.parametrize("T", [1, 257, 4099, 16383, 16384, 16385, 32768, 65472, 131075])
+@pytest.mark.parametrize("short", [0, 3])
+def test_the_calls_by_slices(oracle, torch_cuda, T, short):  # noqa: F811
+    # one slice and several, the last one of a token, a step or full; with `short` places too few for the last slice: its last
+    # boundaries are dropped, both ends are written, and nothing is outside the room that the places leave
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    lib, n_seq = B.load(), 2
+    tok, dev = _tokens(torch, T, n_seq)
+    delims, st = (ctypes.c_int32 * 2)(3, 5), torch.cuda.current_stream().cuda_stream or None
+    per = lib.sablock_segment_slices(n_seq, T)
+    assert per == -(-T // B.SLICE_TOKENS)
+    count = torch.full((n_seq * per,), -1, dtype=torch.int32, device="cuda")
+    args = (dev.data_ptr(), T, n_seq, T, delims, 2)
+    assert lib.sablock_segment_slice_count(*args, count.data_ptr(), st) == 0
+    ref = [oracle.segment(row, [3, 5]) for row in tok]
+    inner = [r[1:-1] for r in ref]
+    at = count.cpu().numpy().reshape(n_seq, per)
+    for s in range(n_seq):                                     # a boundary belongs to the slice of the delimiter in front of it
+        np.testing.assert_array_equal(at[s], np.bincount((inner[s] - 1) // B.SLICE_TOKENS, minlength=per))
+    short = min(short, int(at[-1, -1]))
+    place = [4]                                                # the offsets begin behind a few words of others
+    for s in range(n_seq):
+        for i in range(per):
+            place.append(place[-1] + int(at[s, i]) + (2 if i == per - 1 else 0))
+    place[-1] -= short
+    off = torch.full((place[-1] + 64,), -7, dtype=torch.int32, device="cuda")
+    assert lib.sablock_segment_slice_offsets(*args, (ctypes.c_int32 * len(place))(*place), off.data_ptr(), st) == 0
+    want = np.full(place[-1] + 64, -7, dtype=np.int32)
+    want[4:4 + len(ref[0])] = ref[0]
+    last = ref[1] if short == 0 else np.concatenate([ref[1][:-1 - short], [T]])
+    want[4 + len(ref[0]):place[-1]] = last
+    np.testing.assert_array_equal(off.cpu().numpy(), want)

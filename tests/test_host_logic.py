@@ -94,6 +94,11 @@ def test_launch_parameters_are_validated_and_change_only_the_plan(lib):
     assert B.sablock_workspace_bytes(shape(**llama, score_chunk=1024), 0, 0) > few
     assert B.sablock_workspace_bytes(shape(**llama, compute_units=4096), 0, 0) > few
     assert B.sablock_workspace_bytes(shape(**llama, topb_slices=1), 2100, 992) < base      # no sliced Top-B lists
+    # the row statistics take room for the rows that there are, and a kernel's own layout only where that kernel is asked for
+    rows = {(G, kernel): B.sablock_workspace_bytes(shape(**{**llama, "n_q_heads": 8 * G}, score_chunk=512, window_chunk=32, stats_per_key=kernel),
+                                                   0, 0) - 256 for G in (5, 8) for kernel in (0, 2)}
+    assert rows[5, 0] == 8 * (256 + 1) * 160 * 8 and rows[5, 2] == 8 * (4096 + 1) * 160 * 8
+    assert all(rows[5, kernel] * 8 == rows[8, kernel] * 5 for kernel in (0, 2))
     # the library reads no environment variable
     os.environ["SABLOCK_SCORE_CHUNK"] = "1024"
     try:
