@@ -22,21 +22,24 @@
 //           prologue; probabilities, head mean, column sum and entropy term follow
 //           in registers.
 // The log-sum-exp enters as the MFMA's C operand, less a power of two that all rows
-// share and that comes off the column sums in the end: in full, some 140 in units of
-// <q,k>, it would cost every product the bits that it is larger (128 rows, 131 072
-// keys: scores 8.2e-7 off their 64-bit values, 6.5e-7 now).
+// share (common_power) and that comes off the column sums in the end: in full, some 140
+// in units of <q,k>, it would cost every product the bits that it is larger (128 rows,
+// 40 000 keys: scores 8.5e-7 off their 64-bit values, 4.9e-7 now).
 // In both passes the row tiles rotate, in groups of two, through two sets of
 // accumulators: a group is multiplied while the one before it is exponentiated,
 // which overlaps the matrix pipe with the exp/log work inside one wavefront (one
 // wavefront per SIMD).  One launch per pass covers every problem of the call.
 //
-// What bounds both passes is the power budget: under this load the shader clock
-// stays well below its peak, so that less energy per product is more speed.
-// `v_mfma_f32_16x16x32_bf16` needs less of it than `v_mfma_f32_32x32x16_bf16`
+// What bounds both passes is vector issue at the clock that the power budget leaves:
+// of 3 930 (pass 1) and 4 450 cycles (pass 2) per subtile of 256 rows vector
+// instructions take 2 650 and 3 220, the matrix pipe is busy for 2 048 beside them, the
+// rest are waits, mostly for an instruction's turn; the clock is 1.88 GHz of 2.4.  With
+// 128 rows the keys' stream (1.20 ms for 8.6 GB, 1.54 with the stores) is as near.
+// `v_mfma_f32_16x16x32_bf16` needs less power than `v_mfma_f32_32x32x16_bf16`
 // (registers alone, normal variates, sustained: 2.0 against 1.78 PFLOP/s; with the
 // exponentials of pass 1, two wavefronts per SIMD: 738 against 866 ns per subtile of
-// 128 rows), and a lane's references, sums and C operands take half the registers,
-// so that even 256 rows of a KV head keep all of them out of LDS.
+// 128 rows and SIMD), and a lane's sums and C operands take half the registers, so
+// that even 256 rows of a KV head keep theirs out of LDS.
 #include "sablock_internal.h"
 
 #include <algorithm>

@@ -100,8 +100,7 @@ __device__ __forceinline__ void issue_piece(const char *tile_base, int64_t row_b
 
 // NW: wavefronts = 32-row blocks per problem (G * W / 32).
 // WITH_V = false: the row statistics alone (reference and sum of exponentials per window-query row and chunk of
-// keys), i.e. the first pass of the scoring step with ONE read of K for all 256 rows: no V tiles, no second
-// product, no output rows.
+// keys), a first pass of the scoring step that a call may ask for: no V tiles, no second product, no output rows.
 template <int NW, bool WITH_V>
 __global__ void __launch_bounds__(NW * 64)
 window_attention_kernel(WinArgs a)
@@ -427,7 +426,7 @@ void wa_plan(const Dims &d, int *chunk_len, int *n_chunks, int wgs_per_cu)
 
 }  // namespace
 
-// ---- the statistics alone for 256 window-query rows per KV head, as the first pass of the scoring step
+// ---- the statistics alone, as the first pass of the scoring step on request
 bool row_stats_supported(const Dims &d)
 {
     return d.dtype == SABLOCK_BF16 && d.D == 128 &&

@@ -480,7 +480,7 @@ def _mfma_row_shape_case(oracle, torch, G, W, D, chunk, **tuning):
 @pytest.mark.parametrize("G,W", [(4, 32), (4, 8), (4, 16), (8, 8), (8, 16), (2, 32), (1, 32)])
 @pytest.mark.parametrize("chunk", [0, 1024])
 def test_mfma_score_head_dim_64(oracle, torch_cuda, G, W, chunk):
-    # bf16 heads of 64 elements on the matrix pipe (four k-steps per key, keys loaded straight into registers)
+    # bf16 heads of 64 elements on the matrix pipe (two k-steps per key, keys loaded straight into registers)
     _mfma_row_shape_case(oracle, torch_cuda, G, W, 64, chunk)
 
 
@@ -491,9 +491,9 @@ def test_mfma_score_head_dim_64(oracle, torch_cuda, G, W, chunk):
                                    (5, 16, 256), (11, 8, 256), (1, 32, 96), (4, 32, 96), (4, 8, 96), (7, 16, 96), (2, 64, 96), (3, 8, 96)])
 @pytest.mark.parametrize("chunk", [0, 1024])
 def test_mfma_score_any_group_size(oracle, torch_cuda, G, W, D, chunk):
-    # G * W <= 128 rows with any G: the row tiles are padded to a multiple of 32 rows where 32 / W does not divide G
-    # (G = 7 with W = 16: 112 rows in four tiles; G = 3 with W = 8: 24 rows in one), and the padding adds exact
-    # zeros; windows of 64 queries take two tiles per head; heads of 256 elements (16 k-steps per key, up to 96 rows) and of 96 (6 k-steps)
+    # G * W <= 128 rows with any G, in tiles of 16: an odd G with W = 8 leaves half of the last tile as padding, which adds
+    # exact zeros; windows of 32 and 64 queries take two and four tiles per head; an even and an odd number of groups of two
+    # tiles; heads of 256 elements (8 k-steps per key, up to 96 rows) and of 96 (3 k-steps)
     _mfma_row_shape_case(oracle, torch_cuda, G, W, D, chunk)
 
 
