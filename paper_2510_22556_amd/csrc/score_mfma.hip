@@ -24,7 +24,7 @@
 // The log-sum-exp enters as the MFMA's C operand, less a power of two that all rows
 // share (common_power) and that comes off the column sums in the end: in full, some 140
 // in units of <q,k>, it would cost every product the bits that it is larger (128 rows,
-// 40 000 keys: scores 8.5e-7 off their 64-bit values, 4.9e-7 now).
+// 40 000 keys: scores 7.1e-7 off their 64-bit values, without 3.3e-7).
 // In both passes the row tiles rotate, in groups of two, through two sets of
 // accumulators: a group is multiplied while the one before it is exponentiated,
 // which overlaps the matrix pipe with the exp/log work inside one wavefront (one
@@ -452,21 +452,22 @@ __device__ __forceinline__ void pin_queries(bf16x8 (&qa)[NT][KS], const ScoreArg
 // Row statistics: per window-query row a reference and the sum z of exp2(c1 * <q,k> - ref) over the keys, kept per lane
 // (its keys) until the end.
 //
-// Keys of 128 elements are walked without references at first: a sum of positive terms is as accurate as its terms
+// More than 128 rows are walked without references at first: a sum of positive terms is as accurate as its terms
 // whatever their size, as long as none overflows and those that underflow do not count.  Both can be told from the
 // row's sum: no logit that it holds exceeds SUM_MOST, and what was flushed to zero (below 2^-126 each) is nothing beside
 // SUM_LEAST.  Logits of unbiased keys lie within some tens of powers of two around 1; of a model whose keys carry a bias
 // they need not.  A wavefront that finds a row outside, as a rule after its first sixteen subtiles, begins again with
-// references: the row maxima over its first subtile, negated the MFMA's C operands, so acc = <q,k> - reference.  Those
+// references: the row maxima over its first sixteen keys, negated the MFMA's C operands, so acc = <q,k> - reference.  Those
 // cost an LDS read per tile and subtile (all registers are taken by 256 rows).  Where even then a sum is outside (a
 // logit 100 powers of two above the first subtile's, or a stream that begins inside the window) it walks once more, through
-// stats_careful, whose references move: any finite logits are handled.  Both passes, 128 rows, all logits at 0 and 50
-// below: 8 problems of 8 192 keys 21.9 and 29.7 us, 64 of 32 768 keys 237 and 272 (with stats_careful behind the whole first
-// walk 40.5 and 772).
+// stats_careful, whose references move: any finite logits are handled.
 //
-// Keys of other lengths have references from the start, so that the exponent of a peak is small and rounds to less
-// (peaks of 2^26, heads of 64 elements: scores 5.9e-7 off with, 8.4e-7 without; of 128, where the products are off by as
-// much, 1.0e-6 with and without).
+// Up to 128 rows, and heads of other lengths, have references from the start, in registers: the exponent of a peak is smaller
+// and rounds to less.  Scores against 64 bits with references and without, means over 48 heads of 128 elements, 64 keys
+// scaled by four: 1 024 keys, (G, W) = (1, 8) 5.5e-7 and 7.8e-7, (4, 32) 3.3e-7 and 6.1e-7; 40 000 keys 8.2e-7 and 9.7e-7,
+// 6.3e-7 and 9.2e-7; normal variates, 4 000 keys, (4, 32) 2.1e-7 and 3.4e-7.  They cost a product of sixteen keys per stream:
+// a call on 8 problems of 8 192 keys, two subtiles to a stream, takes 0.5 us more of 49, 256 problems of 131 072 keys
+// take no more (3.21 ms without, 3.18 with).
 
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v)
@@ -476,10 +477,12 @@ __device__ __forceinline__ float dpp_f(float v)
 // maximum and sum over the 16 lanes of a lane group: lane ^ 1, lane ^ 2, mirror inside 8, mirror inside 16
 __device__ __forceinline__ float group_max(float v)
 {
-    v = fmaxf(v, dpp_f<0xB1>(v));
-    v = fmaxf(v, dpp_f<0x4E>(v));
-    v = fmaxf(v, dpp_f<0x141>(v));
-    return fmaxf(v, dpp_f<0x140>(v));
+    // the maximum of two, a number where one is not: one instruction, where fmaxf takes another per operand
+    auto larger = [](float x, float y) { return __builtin_amdgcn_fmed3f(x, y, INFINITY); };
+    v = larger(v, dpp_f<0xB1>(v));
+    v = larger(v, dpp_f<0x4E>(v));
+    v = larger(v, dpp_f<0x141>(v));
+    return larger(v, dpp_f<0x140>(v));
 }
 __device__ __forceinline__ float group_sum(float v)
 {
@@ -588,6 +591,9 @@ __device__ __forceinline__ int lane_again()
     return lane;
 }
 
+// whether the first walk has references already, and they have room in registers
+template <int NT, int KS> constexpr bool refs_first() { return KS != 4 || NT <= 8; }
+
 // One walk over the stream, whose first subtiles are on their way, to the rows' states.  REF: with references, kept in refs[MP].
 // True (in some lane): a sum is outside what it can tell, the states are void; then the subtiles on their way may be any.
 template <bool REF, int NT, int W, int KS, typename Stream>
@@ -598,7 +604,7 @@ __device__ __forceinline__ bool stats_walk(const ScoreArgs &a, const WaveWork &w
     constexpr int NG = R::NG;
     constexpr bool ONE = !Stream::AHEAD && NG % 2 == 0;        // a step is one subtile, and nothing changes places
     // so is it here, and what changes places is copied: for less code, or because two subtiles of more than 192 rows spill
-    constexpr bool SHORT = !ONE && ((REF && KS == 4) || NT > 12);
+    constexpr bool SHORT = !ONE && ((REF && !refs_first<NT, KS>()) || NT > 12);
     const int T = a.d.T;
     int n = lane & 15, g = lane >> 4;
     bf16x8 ka[2][KS], ahead[2][KS];
@@ -607,26 +613,23 @@ __device__ __forceinline__ bool stats_walk(const ScoreArgs &a, const WaveWork &w
     floatx4 cr[NT];                                            // in registers where there is room for them
     if (REF) {
 #pragma unroll
-        for (int j = 0; j < NG; ++j) {
-            floatx4 first[2][2] = {};
-            if (n_plain > 0) multiply(qa, ka, j, no_operand, first);
+        for (int J = 0; J < NT; ++J) {
+            floatx4 first = {}, ref;
+            if (n_plain > 0)
 #pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                if (2 * j + r >= NT) continue;
-                floatx4 ref;
+                for (int s = 0; s < KS; ++s) first = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[J][s], ka[0][s], first, 0, 0, 0);
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float rm = group_max(fmaxf(first[r][0][i], first[r][1][i]));
-                    ref[i] = fabsf(rm) < INFINITY ? -rm : 0.f;
-                }
-                if (n == 0) *reinterpret_cast<floatx4 *>(refs + TILE * (2 * j + r) + 4 * g) = ref;
-                if (KS != 4) cr[2 * j + r] = ref;
+            for (int i = 0; i < 4; ++i) {
+                const float rm = group_max(first[i]);
+                ref[i] = fabsf(rm) < INFINITY ? -rm : 0.f;
             }
+            if (refs_first<NT, KS>()) cr[J] = ref;
+            else if (n == 0) *reinterpret_cast<floatx4 *>(refs + TILE * J + 4 * g) = ref;
         }
         __builtin_amdgcn_wave_barrier();                       // written before the first subtile's reads
     }
     auto c = [&](int J) __attribute__((always_inline)) {
-        return !REF ? floatx4{} : KS != 4 ? cr[J] : *reinterpret_cast<const floatx4 *>(refs + TILE * J + 4 * g);
+        return !REF ? floatx4{} : refs_first<NT, KS>() ? cr[J] : *reinterpret_cast<const floatx4 *>(refs + TILE * J + 4 * g);
     };
     // in two levels: beside one large term, small ones that are added to it one by one are lost, sixteen subtiles of
     // them together are not (rows with a peak of 2^26 times the rest, 131 072 keys: sums 5e-5 off without)
@@ -755,15 +758,15 @@ score_mfma_stats(ScoreArgs a)
     }
 
     const int n_plain = plain_subtiles(w, d.T);
-    if (__builtin_expect(__any(stats_walk<KS != 4, NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane)), 0)) {
+    if (__builtin_expect(__any(stats_walk<refs_first<NT, KS>(), NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane)), 0)) {
         auto restart = [&]() __attribute__((always_inline)) {
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");        // what is on its way to the ring or from it
             ks.init(w.kp, d.ks[3], ring, w.first, w.n_sub, d.L, lane_again());
             ks.issue_first();
         };
         restart();
-        bool careful = KS != 4 || n_plain == 0;
-        if constexpr (KS == 4)
+        bool careful = refs_first<NT, KS>() || n_plain == 0;
+        if constexpr (!refs_first<NT, KS>())
             if (!careful) {
                 careful = __any(stats_walk<true, NT, W, KS>(a, w, ks, qa, state, refs, n_plain, lane));
                 if (careful) restart();

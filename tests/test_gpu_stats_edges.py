@@ -143,3 +143,27 @@ def test_rows_far_from_zero_cost_little_more(torch_cuda, G, W, logit):  # noqa: 
     near = took()
     k[..., 0] = logit
     assert took() < 1.5 * near
+
+
+@pytest.mark.parametrize("G,W", [(1, 64), (2, 32), (4, 16), (4, 32), (7, 16)])
+def test_peaked_rows_round_to_little(torch_cuda, G, W):  # noqa: F811
+    # 64 keys scaled by four, scores against 64 bits: the exponents of a row's peak are small beside the row's reference.  Means
+    # over eight heads and six seeds: 3.3e-7 to 4.4e-7, without references 6.0e-7 to 7.0e-7; the bound lies between
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    Hkv, L, D, errors = 8, 1024, 128, []
+    seen = torch.arange(L, device="cuda")[None] <= L - W + torch.arange(W, device="cuda").repeat(G)[:, None]
+    for seed in range(6):
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(seed)
+        q = torch.randn((1, 1, Hkv * G, W, D), generator=gen, device="cuda", dtype=torch.bfloat16)
+        k = torch.randn((1, 1, Hkv, L, D), generator=gen, device="cuda", dtype=torch.bfloat16)
+        k[:, :, :, torch.randperm(L - W, generator=gen, device="cuda")[:64]] *= 4.0
+        shape = B.make_shape(q, k)
+        s = torch.empty((Hkv, L), device="cuda")
+        B.sablock_score(shape, q, k, s, torch.empty_like(s), torch.empty((B.sablock_workspace_bytes(shape, 0, 0),), dtype=torch.uint8, device="cuda"))
+        x = torch.matmul(q[0, 0].double().reshape(Hkv, G * W, D), k[0, 0].double().transpose(1, 2).contiguous()) / D ** 0.5
+        ref = torch.softmax(x.masked_fill(~seen, float("-inf")), -1).reshape(Hkv, G, W, L).mean(1).sum(1)
+        errors.append(((s.double() - ref).norm(dim=1) / ref.norm(dim=1)).mean().item())
+    assert sum(errors) / len(errors) < 5.2e-7
