@@ -1,8 +1,9 @@
 // Budget-driven block-size search and selection (Alg. 2; Eqs. topk,
 // implicit_budget, rk, gk_star, final_selection).
 //
-// topb_kernel     one workgroup per problem: the min(B,T)-th best score of the row, ties
-//                 resolved by ascending index.
+// row_rank_kernel, topb_kernel  one workgroup per problem: the min(B,T)-th best score of
+//                 the row, ties resolved by ascending index (rows of up to 16 384 tokens,
+//                 and longer ones whose better tokens are listed; the others).
 //                 Result: (ordered key v, index cut c); token t is in T_topB iff
 //                 key(t) > v or (key(t) == v and t <= c).  Its last phase counts
 //                 the Top-B tokens of every segment: the implicit budgets b_k.
@@ -405,7 +406,7 @@ __device__ inline void append_tokens(const float4 (&v)[J], const int (&t0)[J], F
 __device__ inline float sample_bound(const RowView &r, int rank, uint32_t *hist, TopbShared &sh)
 {
     if (rank >= TB_ROUND) return -INFINITY;
-    const int tid = threadIdx.x, pieces = r.nvec >> 3;         // >= 512
+    const int tid = threadIdx.x, pieces = r.nvec >> 3;         // 511 or more (then one is read twice)
     float4 v[TB_REG / 4];
 #pragma unroll
     for (int j = 0; j < TB_REG / 4; ++j) {
@@ -1224,17 +1225,13 @@ struct PlanArgs {
     int32_t *counts;             // [P]
     int capacity;
     int32_t *idx_out, *n_sel_out;
-    // tokens at or above the row's bound, collected by several workgroups per row (null: the workgroup scans its row)
-    const int32_t *pre_list;     // [P][n_slices][pre_cap]
-    const int32_t *pre_cnt;      // [P][n_slices], more than pre_cap when some were dropped
-    int n_slices, pre_cap;
 };
 
 // ---- several workgroups per row (few problems in a call, long rows: one workgroup per row would be bound by the
 // latency of its own loads).  grid (slices, P): every workgroup forms the row's bound from the same sample and
 // collects its slice's tokens above it.
 __global__ void __launch_bounds__(TB_THREADS)
-topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, int32_t *pre_list, int32_t *pre_cnt)
+topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, uint2 *pre_list, int32_t *pre_cnt)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t sh_dyn[];   // histogram, then the list
     __shared__ TopbShared sh;
@@ -1251,8 +1248,420 @@ topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, 
     if (sl == 0) append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, pre_cap, sh);
     __syncthreads();
     const int64_t o = (int64_t)p * gridDim.x + sl;
-    for (int i = tid; i < min(sh.n, pre_cap); i += TB_THREADS) pre_list[o * pre_cap + i] = list[i];
+    for (int i = tid; i < min(sh.n, pre_cap); i += TB_THREADS) pre_list[o * pre_cap + i] = make_uint2(ordered_key(r.sp[list[i]]), (uint32_t)list[i]);
     if (tid == 0) pre_cnt[o] = sh.n;
+}
+
+// ------------------------------------------------------------------ Top-B of a row that a workgroup holds in registers
+constexpr int RR_KEYS = 16;                        // scores per thread of a row, and of a list
+constexpr int RUN = 4;                             // segments per thread where there are more of them than threads
+constexpr int RR_RANKED = 64;                      // entries of one bin that are ranked one against another
+
+template <int NTH> struct RowShared {
+    uint32_t most[NTH / 64], least[NTH / 64], w[NTH / 64];
+    uint32_t found[3];                             // bin, entries in front of it, entries in it
+    int n_bin, n_long, long_at;
+    uint32_t thr;
+    int cut;
+};
+
+// adds to a counter in LDS, a lane at a time; few lanes: the compiler's own form scans the wavefront first, and is forty instructions
+__device__ inline int lds_add(int *counter, int v)
+{
+    int r;
+    asm volatile("ds_add_rtn_u32 %0, %1, %2\n\ts_waitcnt lgkmcnt(0)" : "=&v"(r) : "v"((uint32_t)(uintptr_t)(__attribute__((address_space(3))) int *)counter), "v"(v) : "memory");
+    return r;
+}
+
+// sum of the wavefronts' totals in front of this one; `mine` is the lane's inclusive sum.  One barrier.
+template <int NTH>
+__device__ inline uint32_t waves_before(uint32_t mine, RowShared<NTH> &sh)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane == 63) sh.w[wave] = mine;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int w = 0; w < NTH / 64 - 1; ++w) before += w < wave ? sh.w[w] : 0u;
+    return before;
+}
+
+// The scores that a workgroup looks at: held in registers (thread i: entries i + e * NTH of n), ...
+template <int NTH, bool TOK> struct HeldScores {
+    uint32_t key[RR_KEYS];
+    int tok[TOK ? RR_KEYS : 1];
+    int n;
+    template <typename F>
+    __device__ __forceinline__ void each(F &&f) const       // f(key, token), for what this thread holds
+    {
+#pragma unroll
+        for (int e = 0; e < RR_KEYS; ++e) {
+            const int i = (int)threadIdx.x + e * NTH;
+            if (e * NTH < n && i < n) {            // the first is uniform
+                if constexpr (TOK) f(key[e], tok[e]);
+                else f(key[e], i);
+            }
+        }
+    }
+};
+// ... or read from the row each time
+template <int NTH> struct RowScores {
+    const float *sp;
+    int n;
+    template <typename F>
+    __device__ __forceinline__ void each(F &&f) const
+    {
+#pragma nounroll
+        for (int t = threadIdx.x; t < n; t += NTH) f(ordered_key(sp[t]), t);
+    }
+};
+
+// Key and index cut of the k-th best of the scores, 1 <= k <= their number: a histogram over the span of the keys gives the
+// k-th one's bin; a bin of few entries is ranked, one of many is the next span.  sp, T: the row, T - 1 the cut that cuts nothing.
+template <int NTH, typename S>
+__device__ __forceinline__ void row_kth_best(const S &sc, const float *sp, int T, int k, uint32_t *hist, RowShared<NTH> &sh, uint32_t &thr, int &cut)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t most = 0u, least = 0xFFFFFFFFu;
+    sc.each([&](uint32_t key, int) { most = max(most, key); least = min(least, key); });
+    most = wave_max_u(most);
+    least = ~wave_max_u(~least);
+    if (lane == 0) { sh.most[wave] = most; sh.least[wave] = least; }
+    if (tid == 0) sh.n_bin = 0;
+    reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);         // four bins per thread
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NTH / 64; ++w) { most = max(most, sh.most[w]); least = min(least, sh.least[w]); }
+    constexpr int BITS = NTH == 1024 ? 12 : NTH == 512 ? 11 : 10;
+    static_assert(4 * NTH == 1 << BITS, "bins");
+    uint32_t count;
+#pragma nounroll
+    for (bool again = false;; again = true) {
+        if (again) {                               // everyone has read its bins
+            reinterpret_cast<uint4 *>(hist)[tid] = make_uint4(0, 0, 0, 0);
+            __syncthreads();
+        }
+        const uint32_t range = most - least;
+        const int shift = max(0, 32 - BITS - __builtin_clz(range | 1u));
+        sc.each([&](uint32_t key, int) {
+            const uint32_t down = most - key;      // wraps above `most`
+            if (down <= range) atomicAdd(&hist[down >> shift], 1u);
+        });
+        __syncthreads();
+        const uint4 c = reinterpret_cast<const uint4 *>(hist)[tid];
+        const uint32_t mine = c.x + c.y + c.z + c.w, incl = wave_scan_u(mine);
+        uint32_t before = waves_before<NTH>(incl, sh) + incl - mine;
+        if (before < (uint32_t)k && (uint32_t)k <= before + mine) {
+            uint32_t b = 4 * tid, n = c.x;
+            if (before + n < (uint32_t)k) { before += n; ++b; n = c.y; }
+            if (before + n < (uint32_t)k) { before += n; ++b; n = c.z; }
+            if (before + n < (uint32_t)k) { before += n; ++b; n = c.w; }
+            sh.found[0] = b; sh.found[1] = before; sh.found[2] = n;
+        }
+        __syncthreads();
+        k -= (int)sh.found[1];
+        count = sh.found[2];
+        const uint32_t top = most - (sh.found[0] << shift), low = top - ((1u << shift) - 1u);       // of the bin; low wraps below key 0
+        least = low > top ? least : max(least, low);
+        most = top;
+        if (count <= (uint32_t)RR_RANKED || most == least) break;
+    }
+    if (count <= (uint32_t)RR_RANKED) {
+        uint2 *ent = reinterpret_cast<uint2 *>(hist);          // everyone has read its bins
+        sc.each([&](uint32_t key, int t) { if (key <= most && key >= least) ent[lds_add(&sh.n_bin, 1)] = make_uint2(key, (uint32_t)t); });
+        __syncthreads();
+        if (tid < (int)count) {
+            const uint2 me = ent[tid];
+            int rank = 0, gt = 0, eq = 0;
+#pragma nounroll
+            for (int j0 = 0; j0 < (int)count; j0 += 4) {
+                uint2 o[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = ent[min(j0 + j, (int)count - 1)];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int there = j0 + j < (int)count, above = there & (o[j].x > me.x), same = there & (o[j].x == me.x);
+                    gt += above;
+                    eq += same;
+                    rank += above | (same & (o[j].y < me.y));
+                }
+            }
+            if (rank == k - 1) {
+                sh.thr = me.x;
+                sh.cut = k - gt == eq ? T - 1 : (int)me.y;     // all ties inside: no cut
+            }
+        }
+        __syncthreads();
+        thr = sh.thr;
+        cut = sh.cut;
+        return;
+    }
+    // more ties than are ranked: k of `count`, lowest indices first
+    thr = most;
+    cut = T - 1;
+    if (k == (int)count) return;
+#pragma nounroll
+    for (int c0 = 0; c0 < T; c0 += NTH) {
+        const int t = c0 + tid;
+        const bool tie = t < T && ordered_key(sp[t]) == thr;
+        const unsigned long long bal = __ballot(tie);
+        if (lane == 0) sh.most[wave] = (uint32_t)__popcll(bal);
+        __syncthreads();
+        int before = 0, total = 0;
+        for (int w = 0; w < NTH / 64; ++w) { const int c = (int)sh.most[w]; if (w < wave) before += c; total += c; }
+        if (tie && before + lanes_below(bal) + 1 == k) sh.cut = t;
+        __syncthreads();
+        if (k <= total) { cut = sh.cut; return; }
+        k -= total;
+    }
+}
+
+// Tokens at or above a row's bound, collected by several workgroups per row
+struct Candidates {
+    const uint2 *entries;        // [P][n_slices][cap]: key, token
+    const int32_t *counts;       // [P][n_slices], more than cap when some were dropped
+    int n_slices, cap;
+};
+
+
+// LDS of row_rank_kernel: the histogram; per segment its first token, its Top-B tokens and one of them; and (not LISTED) a bit per token where a segment begins, with the
+// number of them in front of each word
+constexpr int RR_LDS_MOST = 150 * 1024;
+struct RowLds {
+    int cnt, one, off, bits, before, bytes;
+    __host__ __device__ RowLds(bool listed, int nth, int T, int K)
+    {
+        const int words = listed ? 0 : (T + 31) / 32, seg = 4 * ((K + 4) & ~3);
+        cnt = 16 * nth;
+        one = cnt + seg;
+        off = one + seg;
+        bits = off + seg;
+        before = bits + 4 * words;
+        bytes = (before + 4 * words + 15) & ~15;
+    }
+};
+
+// grid (P).  What topb_kernel does, 0 < k = B < T, for rows of up to 16 * NTH tokens (LISTED: for longer ones, of which
+// other workgroups have listed the tokens above a bound; a list that is none, of fewer than k or more than there is room for,
+// leaves the row to be read again and again).
+//
+// What bounds it: the latency of its steps and the instructions of its threads (one costs a compute unit 4 cycles per
+// wavefront and SIMD).  So a row gets as many threads as hold it with 16 scores each, and what a row has no tokens for is
+// jumped over; a token finds its segment by counting bits, and a segment with one token remembers it, so that the tokens
+// need no second look.  The kernel alone, 2 rows of 2 032 tokens 11.1 -> 7.2 us, 8 rows of 8 160 14.8 -> 10.4 against 1 024 threads
+// that list the tokens and look each segment up by halves; 8 rows of 131 040 from eight lists each 15.9 -> 12.6.
+template <bool PLAN, int NTH, bool LISTED>
+__global__ void __launch_bounds__(NTH, 4)
+row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView sv, int32_t *seg_budget, int32_t *block_size, PlanArgs pa,
+                Candidates cd, int most_segments)
+{
+    extern __shared__ __attribute__((aligned(16))) char sh_row[];
+    __shared__ __attribute__((aligned(16))) RowShared<NTH> sh;
+    const int p = blockIdx.x, T = d.T, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const RowLds lds(LISTED, NTH, T, most_segments);
+    uint32_t *hist = reinterpret_cast<uint32_t *>(sh_row);
+    int32_t *cnt = reinterpret_cast<int32_t *>(sh_row + lds.cnt), *one = reinterpret_cast<int32_t *>(sh_row + lds.one);
+    int32_t *off = reinterpret_cast<int32_t *>(sh_row + lds.off);
+    uint32_t *bits = reinterpret_cast<uint32_t *>(sh_row + lds.bits), *before = reinterpret_cast<uint32_t *>(sh_row + lds.before);
+    const float *sp = s_tilde + (int64_t)p * T;
+    const int seq = seq_of_problem(d, p);
+    const int32_t *seg_off = sv.seg_off + sv.seq_ptr[seq];
+    const int K = seg_budget ? sv.seq_ptr[seq + 1] - sv.seq_ptr[seq] - 1 : -1;
+    const int64_t row = (int64_t)p * sv.max_segments;
+
+    int32_t o[4];                                  // the first offsets, on their way with the scores
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = K >= 0 ? seg_off[min(tid + i * NTH, K)] : 0;        // K < 0: there may be no offsets
+    HeldScores<NTH, LISTED> held;
+    held.n = T;
+    const int words = LISTED ? 0 : (T + 31) / 32;
+    if constexpr (LISTED) {
+        // the lists one behind another
+        const int n = lane < cd.n_slices ? cd.counts[(int64_t)p * cd.n_slices + lane] : 0;
+        const int upto = (int)wave_scan_u((uint32_t)n);
+        held.n = __any(n > cd.cap) ? 0 : __builtin_amdgcn_readlane(upto, 63);
+        if (held.n < k || held.n > RR_KEYS * NTH) held.n = 0;
+#pragma unroll
+        for (int e = 0; e < RR_KEYS; ++e) {
+            if (e * NTH < held.n) {
+                const int i = tid + e * NTH;
+                int slice = 0, first = 0;          // of the entry
+#pragma nounroll
+                for (int sl = 0; sl < cd.n_slices - 1; ++sl) {
+                    const int end = __builtin_amdgcn_readlane(upto, sl);
+                    if (end <= i) { slice = sl + 1; first = end; }
+                }
+                if (i < held.n) {
+                    const uint2 c = cd.entries[((int64_t)p * cd.n_slices + slice) * cd.cap + (i - first)];
+                    held.key[e] = c.x;
+                    held.tok[e] = (int)c.y;
+                }
+            }
+        }
+    } else {
+        float v[RR_KEYS];
+#pragma unroll
+        for (int e = 0; e < RR_KEYS; ++e)
+            if (e * NTH < T) v[e] = sp[min(tid + e * NTH, T - 1)];
+#pragma nounroll
+        for (int w = tid; w < words; w += NTH) bits[w] = 0u;
+#pragma unroll
+        for (int e = 0; e < RR_KEYS; ++e)
+            if (e * NTH < T) held.key[e] = ordered_key(v[e]);
+    }
+    if (tid == 0) sh.n_long = sh.long_at = 0;
+    if (!LISTED) __syncthreads();                  // the bits are clear
+#pragma nounroll
+    for (int j0 = tid; j0 <= K; j0 += 4 * NTH) {
+        if (j0 >= 4 * NTH)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = seg_off[min(j0 + i * NTH, K)];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (j0 + i * NTH <= K) {
+                off[j0 + i * NTH] = o[i];
+                cnt[j0 + i * NTH] = 0;
+                if (!LISTED && o[i] < T) atomicOr(&bits[o[i] >> 5], 1u << (o[i] & 31));
+            }
+    }
+    uint32_t thr;
+    int cut;
+    const RowScores<NTH> all{sp, T};
+    const bool whole_row = LISTED && held.n == 0;
+    if (whole_row) row_kth_best<NTH>(all, sp, T, k, hist, sh, thr, cut);
+    else row_kth_best<NTH>(held, sp, T, k, hist, sh, thr, cut);
+    if (tid == 0) { thr_out[2 * p] = (int32_t)thr; thr_out[2 * p + 1] = cut; }
+    if (!seg_budget) return;
+
+    // ---- implicit budgets: every Top-B token adds one to its segment, the last one that begins at or in front of it
+    if (!LISTED) {
+        // words up to 512, so one of them per thread
+        const uint32_t mine = tid < words ? (uint32_t)__popc(bits[tid]) : 0u, incl = wave_scan_u(mine);
+        const uint32_t b = waves_before<NTH>(incl, sh) + incl - mine;
+        if (tid < words) before[tid] = b;
+        __syncthreads();
+    }
+    const int half = K > 1 ? 1 << (31 - __builtin_clz(K - 1)) : 0;
+    auto add = [&](const int (&t)[4], const bool (&in)[4]) __attribute__((always_inline)) {      // four at a time, for their latency
+        int sg[4];
+        if (LISTED) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sg[i] = 0;
+#pragma nounroll
+            for (int step = half; step > 0; step >>= 1) {
+                int at[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) at[i] = off[min(sg[i] + step, K)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sg[i] += (sg[i] + step < K) & (at[i] <= t[i]) ? step : 0;
+            }
+        } else {
+            uint32_t b[4], n[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { const int w = min(t[i], T - 1) >> 5; b[i] = bits[w]; n[i] = before[w]; }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sg[i] = max((int)(n[i] + (uint32_t)__popc(b[i] & (0xFFFFFFFFu >> (31 - (t[i] & 31))))) - 1, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (in[i]) {
+                atomicAdd(&cnt[sg[i]], 1);
+                one[sg[i]] = t[i];                 // the one there is, where there is one
+            }
+    };
+    if (whole_row) {
+        all.each([&](uint32_t key, int t) {
+            const int tt[4] = {t, t, t, t};
+            const bool in[4] = {key > thr || (key == thr && t <= cut), false, false, false};
+            add(tt, in);
+        });
+    } else {
+#pragma unroll
+        for (int e0 = 0; e0 < RR_KEYS; e0 += 4) {
+            if (e0 * NTH < held.n) {               // uniform
+                int t[4];
+                bool in[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int j = tid + (e0 + i) * NTH;
+                    t[i] = j;
+                    if constexpr (LISTED) t[i] = j < held.n ? held.tok[e0 + i] : 0;
+                    const uint32_t key = j < held.n ? held.key[e0 + i] : 0u;
+                    in[i] = (j < held.n) & ((key > thr) | ((key == thr) & (t[i] <= cut)));
+                }
+                add(t, in);
+            }
+        }
+    }
+    __syncthreads();
+    if (PLAN) {
+        // ---- the search begins with the longest segments, as their search takes longest: how many are there?  (As a rule none.)
+        bool longer = false;
+#pragma nounroll
+        for (int j = tid; j < K; j += NTH) longer |= off[j + 1] - off[j] > PRE_TOKENS && cnt[j] >= 2;
+        if (__any(longer)) {
+#pragma nounroll
+            for (int j = tid; j < K; j += NTH)
+                if (off[j + 1] - off[j] > PRE_TOKENS && cnt[j] >= 2) lds_add(&sh.n_long, 1);
+        }
+    }
+#pragma nounroll
+    for (int j = tid; j < sv.max_segments; j += NTH) {
+        const int c = j < K ? cnt[j] : 0;
+        seg_budget[row + j] = c;
+        block_size[row + j] = PLAN && c == 1 ? 1 : 0;          // the others: written by the search
+    }
+    if (!PLAN) return;
+    // ---- the exclusive prefix of the budgets is the place of a segment's tokens in the problem's idx row: a single token goes
+    // there straight away, segments of more to the search's list.  A run of segments per thread; in the upper half of the sums
+    // the segments of more that are not the longest
+    SegRec *recs = pa.list + (int64_t)p * pa.capacity;
+    int32_t *out = pa.idx_out + (int64_t)p * k;
+    const int per = K <= NTH ? 1 : RUN;
+    uint32_t run = 0;
+#pragma nounroll
+    for (int j0 = 0; j0 < K; j0 += per * NTH) {
+        int c[RUN], a[RUN + 1];
+        uint32_t mine = 0;
+        const int j = j0 + per * tid;
+#pragma unroll
+        for (int i = 0; i < RUN; ++i)
+            if (i < per) {
+                c[i] = j + i < K ? cnt[j + i] : 0;
+                a[i] = off[min(j + i, K)];
+                a[i + 1] = off[min(j + i + 1, K)];
+                mine += (uint32_t)c[i] + (c[i] >= 2 && a[i + 1] - a[i] <= PRE_TOKENS ? 0x10000u : 0u);
+            }
+        const uint32_t incl = wave_scan_u(mine);
+        __syncthreads();                                       // (the first time: n_long is complete; later: the totals have been read)
+        if (lane == 63) sh.w[wave] = incl;
+        __syncthreads();
+        uint32_t pos = run + incl - mine;
+#pragma unroll
+        for (int w = 0; w < NTH / 64; ++w) {
+            const uint32_t x = sh.w[w];
+            pos += w < wave ? x : 0u;
+            run += x;
+        }
+#pragma unroll
+        for (int i = 0; i < RUN; ++i)
+            if (i < per) {
+                if (c[i] == 1) out[pos & 0xFFFFu] = one[j + i];
+                if (c[i] >= 2) {
+                    const bool first = a[i + 1] - a[i] > PRE_TOKENS;
+                    const int at = first ? lds_add(&sh.long_at, 1) : sh.n_long + (int)(pos >> 16);
+                    SegRec r;
+                    r.p = p; r.k = j + i; r.a = a[i]; r.b = a[i + 1]; r.bk = c[i]; r.g = (int32_t)thr; r.pos = cut; r.out = (int)(pos & 0xFFFFu);
+                    recs[at] = r;
+                    if (!first) pos += 0x10000u;
+                }
+                pos += (uint32_t)c[i];
+            }
+    }
+    if (tid == 0) {
+        pa.n_sel_out[p] = k;                                   // k = B < T here, so there is nothing to pad
+        pa.counts[p] = K > 0 ? sh.n_long + (int)(run >> 16) : 0;
+    }
 }
 
 // grid (P).  Selection of the k-th best score, k = min(B, T), as (ordered key v, index cut c), and, with seg_budget
@@ -1275,8 +1684,7 @@ topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, 
 //
 // TWO: two workgroups share a CU, which calls with more rows than CUs gain from although 64 registers spill three (Top-B
 // and search, 1 024 rows of 65 472: 505 us, 529 with one per CU; 512 rows of 8 160: 112 and 116).  With fewer rows a
-// workgroup has its CU to itself and up to 128 registers (8 rows of 8 160: 34.0 us, 35.6 with 64; 256 rows of 131 040:
-// 110 and 112).
+// workgroup has its CU to itself and up to 128 registers (256 rows of 131 040: 110 and 112).
 template <bool PLAN, int E, bool TWO>
 __global__ void __launch_bounds__(TB_THREADS, TWO ? 8 : 4)
 topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView sv, int32_t *seg_budget,
@@ -1312,70 +1720,30 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
         thr = 0xFFFFFFFFu;                       // nothing is inside
         cut = -1;
     } else if (k < T) {
-        const bool sliced = PLAN && pa.pre_list;
         bool found = false;
-        if (!sliced && r.nvec <= TB_ROUND / 4) {
-            // ---- the whole row in registers
-            constexpr int J = TB_REG / 4;
-            float4 v[J];
-            int t0[J];
-            uint32_t valid = 0;
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                const int i = j * TB_THREADS + tid;
-                v[j] = r.nvec > 0 ? r.vp[min(i, r.nvec - 1)] : make_float4(0.f, 0.f, 0.f, 0.f);
-                t0[j] = i < r.nvec ? r.token(i) : -4;
-                if (i < r.nvec) valid |= 15u << (4 * j);
-            }
-            const float ve = r.extra >= 0 ? r.sp[r.extra] : 0.f;
-            if (r.extra >= 0) valid |= 1u << TB_REG;
-            uint32_t key[TB_REG + 1];
-#pragma unroll
-            for (int j = 0; j < J; ++j) {
-                key[4 * j] = ordered_key(v[j].x); key[4 * j + 1] = ordered_key(v[j].y);
-                key[4 * j + 2] = ordered_key(v[j].z); key[4 * j + 3] = ordered_key(v[j].w);
-            }
-            key[TB_REG] = ordered_key(ve);
-            found = kth_best<TB_REG + 1>(key, valid, [&](int e) { return e == TB_REG ? r.extra : t0[e >> 2] + (e & 3); }, k, T, hist,
-                                         sh, thr, cut);
-            if (found && k <= CAP && seg_budget) {
-                append_tokens<J>(v, t0, [&](int t, float x) { return t >= 0 && in_topb(x, t, thr, cut); }, list, CAP, sh);
-                append_extra(r, r.extra >= 0 && in_topb(ve, r.extra, thr, cut), list, CAP, sh);
-                hits_from_list();                // exactly k of them
-            }
-        } else if (k <= CAP) {
+        if (T > TB_ROUND && k <= CAP) {
             // ---- the tokens that reach a lower bound of the k-th best
-            if (sliced) {
-                int base = 0;
-                for (int sl = 0; sl < pa.n_slices; ++sl) {
-                    const int64_t o = (int64_t)p * pa.n_slices + sl;
-                    const int n = pa.pre_cnt[o];
-                    if (n > pa.pre_cap || base + n > CAP) { base = CAP + 1; break; }
-                    for (int i = tid; i < n; i += TB_THREADS) list[base + i] = pa.pre_list[o * pa.pre_cap + i];
-                    base += n;
-                }
-                if (tid == 0) sh.n = base;
-            } else {
-                const float bound = sample_bound(r, sample_rank, hist, sh);
-                __syncthreads();                 // the list's length is zero
-                collect_above(r, 0, r.nvec, bound, list, CAP, sh);
-                append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, CAP, sh);
-            }
+            const float bound = sample_bound(r, sample_rank, hist, sh);
+            __syncthreads();                     // the list's length is zero
+            collect_above(r, 0, r.nvec, bound, list, CAP, sh);
+            append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, CAP, sh);
             __syncthreads();
             const int n = sh.n;
             if (n >= k && n <= CAP) {
                 uint32_t key[E], valid = 0;
-                float x[E];
 #pragma unroll
-                for (int e = 0; e < E; ++e)
-                    if (tid + e * TB_THREADS < n) { hit[e] = list[tid + e * TB_THREADS]; x[e] = r.sp[hit[e]]; valid |= 1u << e; }
-#pragma unroll
-                for (int e = 0; e < E; ++e) key[e] = (valid >> e) & 1u ? ordered_key(x[e]) : 0u;
-                found = kth_best<E>(key, valid, [&](int e) { return hit[e]; }, k, T, hist, sh, thr, cut);
+                for (int e = 0; e < E; ++e) {
+                    const int i = tid + e * TB_THREADS;
+                    key[e] = 0u;
+                    if (i < n) { key[e] = ordered_key(r.sp[list[i]]); valid |= 1u << e; }
+                }
+                found = kth_best<E>(key, valid, [&](int e) { return list[tid + e * TB_THREADS]; }, k, T, hist, sh, thr, cut);
                 if (found) {
 #pragma unroll
-                    for (int e = 0; e < E; ++e)
-                        if (!(((valid >> e) & 1u) && (key[e] > thr || (key[e] == thr && hit[e] <= cut)))) hit[e] = -1;
+                    for (int e = 0; e < E; ++e) {
+                        const int t = (valid >> e) & 1u ? list[tid + e * TB_THREADS] : -1;
+                        if (((valid >> e) & 1u) && (key[e] > thr || (key[e] == thr && t <= cut))) hit[e] = t;
+                    }
                     have_hits = true;
                 }
             }
@@ -1853,10 +2221,44 @@ static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, 
     return hipGetLastError();
 }
 
+// ---- launches of row_rank_kernel: rows of up to 16 384 tokens and listed ones, but for all or nothing inside and more segments
+// than LDS has room for (11 000 to 12 000)
+static int most_segments(const Dims &d, const SegView &sv)
+{
+    int n = 0;
+    for (int s = 0; s < d.n_seq; ++s) n = std::max(n, sv.seq_ptr[s + 1] - sv.seq_ptr[s] - 1);
+    return n;
+}
+static bool row_rank_fits(bool listed, int nth, const Dims &d, int32_t budget, int segments)
+{
+    return budget > 0 && budget < d.T && segments < 65536 && RowLds(listed, nth, d.T, segments).bytes <= RR_LDS_MOST;
+}
+
+template <bool PLAN, int NTH, bool LISTED>
+static hipError_t run_row_rank(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
+                               int32_t *block_size, const PlanArgs &pa, const Candidates &cd, int segments, hipStream_t st)
+{
+    static thread_local PerDeviceOnce attr_once;
+    if (attr_once.needed()) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(row_rank_kernel<PLAN, NTH, LISTED>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, RR_LDS_MOST);
+        if (e != hipSuccess) return e;
+        attr_once.done();
+    }
+    hipLaunchKernelGGL((row_rank_kernel<PLAN, NTH, LISTED>), dim3(d.P), dim3(NTH), RowLds(LISTED, NTH, d.T, segments).bytes, st, d,
+                       s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments);
+    return hipGetLastError();
+}
+
 template <bool PLAN>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
                            int32_t *block_size, const PlanArgs &pa, hipStream_t st)
 {
+    const int nth = d.T <= 256 * RR_KEYS ? 256 : d.T <= 512 * RR_KEYS ? 512 : 1024, segments = most_segments(d, sv);
+    if (d.T <= 1024 * RR_KEYS && row_rank_fits(false, nth, d, budget, segments)) {
+        const auto run = nth == 256 ? run_row_rank<PLAN, 256, false> : nth == 512 ? run_row_rank<PLAN, 512, false> : run_row_rank<PLAN, 1024, false>;
+        return run(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, Candidates{}, segments, st);
+    }
     const bool two = d.P > d.cus;
     switch (topb_list_k(d, budget)) {
     case 4: return (two ? run_topb<PLAN, 4, true> : run_topb<PLAN, 4, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
@@ -1986,29 +2388,33 @@ bool search_select_fused(const Dims &d, const SegView &sv, int32_t budget)
 // layer at a time) one workgroup per long row would leave most of the chip idle.  1: the per-row kernel scans its row.
 static int topb_slices(const Dims &d, int32_t budget)
 {
-    if (topb_list_k(d, budget) > 8 || d.T <= TB_ROUND) return 1;
+    if (budget <= 0 || budget >= d.T || topb_list_k(d, budget) > 8 || d.T <= TB_ROUND) return 1;
     if (const int v = d.tune.topb_slices; v >= 1) return (int64_t)v * 4096 <= d.T ? v : 1;
     // a slice is one round of loads; a kernel of its own (5 us) for them pays when it saves the per-row kernel four rounds
-    // or more (both calls together, 8 rows: 32 768 tokens 32.7 us in one kernel, 34.3 in two; 65 536: 35.5, 33.0;
-    // 131 040: 41.2, 33.4; 1 000 000: 128, 77)
+    // or more (both calls together, 8 rows: 32 752 tokens 26.7 us in one kernel, 27.1 in two; 65 520: 32.5, 29.0; 32
+    // rows of 131 056: 43.0, 35.7)
     const int s = (d.T + TB_ROUND - 1) / TB_ROUND;
     return s >= 4 && (int64_t)s * d.P <= d.cus ? std::min(s, 64) : 1;
 }
 static size_t sliced_bytes(const Dims &d, int32_t budget)
 {
     const size_t n = (size_t)d.P * topb_slices(d, budget);
-    return align256(n * 4) + align256(n * topb_list_k(d, budget) * TB_THREADS * 4);
+    return align256(n * 4) + align256(n * topb_list_k(d, budget) * TB_THREADS * sizeof(uint2));
 }
 
+// without the room for the slices' lists, which a call does without if it has to
+size_t search_select_ws_least(const Dims &d, int32_t max_segments, int32_t budget)
+{
+    return std::max(search_ws_bytes(d, max_segments, budget), select_ws_bytes(d, max_segments, budget));
+}
 size_t search_select_ws_bytes(const Dims &d, int32_t max_segments, int32_t budget)
 {
-    const size_t a = search_ws_bytes(d, max_segments, budget), b = select_ws_bytes(d, max_segments, budget);
-    return (a > b ? a : b) + (topb_slices(d, budget) > 1 ? sliced_bytes(d, budget) : 0);
+    return search_select_ws_least(d, max_segments, budget) + (topb_slices(d, budget) > 1 ? sliced_bytes(d, budget) : 0);
 }
 
 hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand,
                                 int32_t budget, float tau, int32_t *seg_budget, int32_t *block_size, int32_t *topb_out,
-                                int32_t *idx_out, int32_t *n_sel_out, void *ws, hipStream_t st)
+                                int32_t *idx_out, int32_t *n_sel_out, void *ws, size_t ws_bytes, hipStream_t st)
 {
     if (d.P <= 0) return hipSuccess;
     if (!search_select_fused(d, sv, budget)) {
@@ -2022,21 +2428,22 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
     const int cap = max_heavy_segments(d, sv.max_segments, budget);
     const SearchWs w(d, ws);
     int32_t *thr = topb_out ? topb_out : w.thr;
-    PlanArgs pa{w.list, w.counts, cap, idx_out, n_sel_out, nullptr, nullptr, 0, 0};
-    if (const int n_slices = topb_slices(d, budget); n_slices > 1) {
+    const PlanArgs pa{w.list, w.counts, cap, idx_out, n_sel_out};
+    hipError_t e;
+    const int n_slices = topb_slices(d, budget), segments = most_segments(d, sv);
+    if (n_slices > 1 && row_rank_fits(true, 512, d, budget, segments) && ws_bytes >= search_select_ws_bytes(d, sv.max_segments, budget)) {
         // behind the larger of the search and select layouts
-        char *x = static_cast<char *>(ws) + (search_select_ws_bytes(d, sv.max_segments, budget) - sliced_bytes(d, budget));
-        int32_t *pre_cnt = reinterpret_cast<int32_t *>(x);
-        int32_t *pre_list = reinterpret_cast<int32_t *>(x + align256((size_t)d.P * n_slices * 4));
+        char *x = static_cast<char *>(ws) + search_select_ws_least(d, sv.max_segments, budget);
+        int32_t *counts = reinterpret_cast<int32_t *>(x);
+        uint2 *entries = reinterpret_cast<uint2 *>(x + align256((size_t)d.P * n_slices * 4));
         const int pre_cap = topb_list_k(d, budget) * TB_THREADS;
         hipLaunchKernelGGL(topb_collect_kernel, dim3(n_slices, d.P), dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, d, s_tilde,
-                           topb_rank(d, budget), pre_cap, pre_list, pre_cnt);
-        pa.pre_list = pre_list;
-        pa.pre_cnt = pre_cnt;
-        pa.n_slices = n_slices;
-        pa.pre_cap = pre_cap;
+                           topb_rank(d, budget), pre_cap, entries, counts);
+        const Candidates cd{entries, counts, n_slices, pre_cap};
+        e = run_row_rank<true, 512, true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments, st);
+    } else {
+        e = run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
     }
-    hipError_t e = run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
     if (e != hipSuccess) return e;
     if (cap > 0) run_search<true>(d, s_tilde, sv, cand, tau, w, cap, block_size, budget, idx_out, st);
     return hipGetLastError();

@@ -201,3 +201,18 @@ def test_scores_that_are_not_numbers_take_a_segment_s_share_and_no_more(torch_cu
     for budget in (7, T // 3, T - 2):
         b, g, idx, _ = _search_select_gpu(torch, st, off, [1, 2, 3, 8, 64], budget, 0.85)
         check(idx[:, :budget], b[:, :len(off) - 1])
+
+
+@pytest.mark.parametrize("T", [1, 255, 4096, 4097, 8192, 8193, 16384])
+@pytest.mark.parametrize("mean", [1, 2, 30])
+@pytest.mark.parametrize("levels", [0, 3])
+def test_rows_and_segments_around_the_threads_that_hold_them(oracle, torch_cuda, T, mean, levels):  # noqa: F811
+    # 256, 512 or 1 024 threads by the row's length; more segments than threads, than LDS has room for (mean 1, T = 16384);
+    # levels: more ties at the threshold than are ranked, cut by index
+    rng = np.random.default_rng(T + mean)
+    st = rng.random((3, T)) ** 3
+    if levels:
+        st = np.round(st * levels) / levels
+    off = _offsets(rng, T, rng.integers(1, 2 * mean, size=T) if mean > 1 else np.ones(T, np.int64))
+    for budget in sorted({1, T // 7, T // 2, T - 1} - {0}):
+        _assert_search_select(oracle, torch_cuda, st, off, CAND, budget, 0.85)
