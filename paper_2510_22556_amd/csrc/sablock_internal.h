@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <stdint.h>
 #include <stddef.h>
 
@@ -90,6 +91,41 @@ __host__ __device__ inline uint32_t ordered_key(float f)
 #endif
     if (u == 0x80000000u) u = 0u;
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// Keys per workgroup: a problem's L keys in chunks of `len`, the last one what is left.  A workgroup costs its keys and `fixed`
+// keys' time besides (prologue, epilogue); `slots` of them run at a time.  Equal chunks in whole rounds of workgroups, or, where
+// those leave places idle, larger ones whose remainders the idle places take (112 problems on 256: two and a shorter one); then
+// the workgroups start chunk by chunk (by_chunk), all problems' first ones first.  At most `most` keys each, and `wgs`
+// workgroups in all where one round needs no more.
+struct ChunkPlan { int len, n; bool by_chunk; };
+inline ChunkPlan plan_chunks(int64_t P, int64_t L, int64_t slots, int step, int fixed, int64_t most, int64_t wgs, bool remainders = true)
+{
+    auto up = [&](int64_t keys) { return (keys + step - 1) / step * step; };
+    int64_t best = 0, best_len = up(L);
+    bool by_chunk = false;
+    auto offer = [&](int64_t cost, int64_t len, bool rest) {
+        if (best == 0 || cost < best) { best = cost; best_len = len; by_chunk = rest; }
+    };
+    const int64_t least = (L + most - 1) / most, first = std::max<int64_t>(1, (least * P + slots - 1) / slots);
+    for (int64_t r = first; r < first + 8; ++r) {              // r rounds of equal chunks
+        const int64_t n = r * slots / P, len = std::min(up((L + n - 1) / n), most);
+        if (r > first && P * n > wgs) break;
+        offer((P * ((L + len - 1) / len) + slots - 1) / slots * (len + fixed), len, false);
+        if (len == step) break;
+    }
+    const int64_t ideal = P * L / slots + fixed;
+    if (remainders && best * 100 > ideal * 104)
+        for (int64_t n = std::max<int64_t>(2, least); n <= 6 && P * n <= wgs; ++n) {     // n - 1 chunks and the remainder of each
+            const int64_t from = up((L + n - 1) / n), to = std::min(up((L + n - 2) / (n - 1)) - step, most), by = std::max<int64_t>(step, up((to - from) / 16));
+            for (int64_t len = from + by; len <= to; len += by) {
+                const int64_t big = len + fixed, small = L - (n - 1) * len + fixed, q = P * (n - 1) / slots, late = P * (n - 1) % slots;
+                // `late` places have q + 1 chunks, the others q and a chunk's time for remainders; what is over comes on top
+                const int64_t early = slots - late, room = late ? early * (big / small) : 0, over = std::max<int64_t>(0, P - room);
+                offer((late ? q + 1 : q) * big + (over + slots - 1) / slots * small, len, true);
+            }
+        }
+    return {(int)best_len, (int)((L + best_len - 1) / best_len), by_chunk};
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }

@@ -76,6 +76,7 @@ struct ScoreArgs {
     const uint16_t *q, *k;
     int chunk_len;         // keys per workgroup, multiple of STRIDE
     int n_chunks;          // workgroups per problem
+    int by_chunk;          // grid (problems, n_chunks), else (n_chunks, problems)
     int pc;                // (reference, sum) pairs per row that pass 2 reads: n_chunks, or 1 once they are merged
     float c1;              // log2(e) / sqrt(D)
     float log2_G;          // log2 of the heads per KV head (the head mean is folded into the rows' log-sum-exp)
@@ -177,8 +178,8 @@ __device__ __forceinline__ WaveWork wave_work(const ScoreArgs &a, int stream)
 {
     stream = __builtin_amdgcn_readfirstlane(stream);         // wave-uniform: addresses below stay in scalar registers
     WaveWork w;
-    w.p = blockIdx.y;
-    w.chunk = blockIdx.x;
+    w.p = a.by_chunk ? blockIdx.x : blockIdx.y;
+    w.chunk = a.by_chunk ? blockIdx.y : blockIdx.x;
     w.kp = a.k + k_problem_offset(a.d, w.p);
     const int lo = w.chunk * a.chunk_len;
     const int hi = min(lo + a.chunk_len, a.d.L);
@@ -1440,6 +1441,7 @@ bool wide_shape(const Dims &d)
 struct Plan {
     int chunk_len;    // keys per workgroup
     int n_chunks;     // workgroups per problem
+    bool by_chunk;    // see plan_chunks
     bool merge;       // fold the chunk partials in a kernel of its own between the passes
 };
 
@@ -1451,22 +1453,20 @@ constexpr int MERGE_FROM = 33, MERGE_FROM_LAYER = 8;
 Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)
 {
     // One launch per pass covers every problem.  A workgroup owns chunk_len consecutive keys of one problem, and
-    // one workgroup fills a CU (registers and the load ring).  Each round of workgroups costs a prologue and an
-    // epilogue during which its CU loads nothing (measured: about 17 us per round and pass), so the plan aims at
-    // a whole number of rounds, as few as keep a chunk at or under MAX_CHUNK keys.
-    constexpr int MAX_CHUNK = 131072;
+    // one workgroup fills a CU (registers and the load ring).  Prologue and epilogue, during which its CU loads nothing, take
+    // some 6 us, as long as 640 keys.  The chunk partials stay within 4 MiB where one round of workgroups does.
+    constexpr int MAX_CHUNK = 131072, FIXED = 640;
     Plan pl;
-    int len;
-    if (d.tune.score_chunk >= STRIDE) len = (d.tune.score_chunk / STRIDE) * STRIDE;
-    else {
-        const int64_t cus = d.cus;
-        const int64_t rounds = ((int64_t)d.P * d.L + cus * MAX_CHUNK - 1) / (cus * MAX_CHUNK);
-        const int64_t per_problem = std::max<int64_t>(1, (cus * rounds + d.P / 2) / d.P);     // chunks per problem
-        len = (int)(((d.L + per_problem - 1) / per_problem + STRIDE - 1) / STRIDE) * STRIDE;
-        len = std::min(std::max(len, STRIDE), MAX_CHUNK);
+    if (d.tune.score_chunk >= STRIDE) {
+        pl.chunk_len = (d.tune.score_chunk / STRIDE) * STRIDE;
+        pl.n_chunks = (d.L + pl.chunk_len - 1) / pl.chunk_len;
+        pl.by_chunk = false;
+    } else {
+        const ChunkPlan c = plan_chunks(d.P, d.L, d.cus, STRIDE, FIXED, MAX_CHUNK, (4 << 20) / (d.G * d.W * 2 * 4));
+        pl.chunk_len = c.len;
+        pl.n_chunks = c.n;
+        pl.by_chunk = c.by_chunk;
     }
-    pl.chunk_len = len;
-    pl.n_chunks = (d.L + len - 1) / len;
     pl.merge = pl.n_chunks >= merge_from;
     return pl;
 }
@@ -1480,6 +1480,7 @@ void plan_partials(ScoreArgs &a, const Dims &d, const Plan &pl, void *ws)
 {
     a.chunk_len = pl.chunk_len;
     a.n_chunks = pl.n_chunks;
+    a.by_chunk = pl.by_chunk;
     a.partial = static_cast<float *>(ws);
     a.merged = a.partial;
     a.pc = pl.n_chunks;
@@ -1545,7 +1546,7 @@ hipError_t launch_score_mfma(const Dims &d, const void *q, const void *k, const 
         }
         with_stats = false;
     }
-    dim3 grid(pl.n_chunks, d.P);
+    const dim3 grid = a.by_chunk ? dim3(d.P, pl.n_chunks) : dim3(pl.n_chunks, d.P);
     const int nt = tiles_of(d);
 #define X(NTV, WV) if (nt == NTV && d.W == WV) return launch_shape<NTV, WV, false, 8>(a, grid, with_stats, st);
     if (d.D == 256) { SABLOCK_SHAPES_96(X) X(4, 64) }
@@ -1629,9 +1630,10 @@ hipError_t launch_stream_probe(const Dims &d, const void *k, int read_lds, float
     a.k = static_cast<const uint16_t *>(k);
     a.chunk_len = pl.chunk_len;
     a.n_chunks = pl.n_chunks;
+    a.by_chunk = pl.by_chunk;
     a.s_out = s_out;
     a.e_out = e_out;
-    dim3 grid(pl.n_chunks, d.P);
+    const dim3 grid = a.by_chunk ? dim3(d.P, pl.n_chunks) : dim3(pl.n_chunks, d.P);
     uint32_t *sk = static_cast<uint32_t *>(sink);
     const bool stores = s_out != nullptr;
 #define X(R, S) if ((read_lds != 0) == R && stores == S) hipLaunchKernelGGL((stream_probe_kernel<R, S>), grid, dim3(WAVES * 64), WAVES * RING_BYTES, st, a, sk);
@@ -1670,7 +1672,7 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
     a.eps = eps;
     a.lse = row_lse;
     a.abar = nullptr;
-    dim3 grid(pl.n_chunks, d.P);
+    const dim3 grid = a.by_chunk ? dim3(d.P, pl.n_chunks) : dim3(pl.n_chunks, d.P);
     if (layer_kernel_shape(d)) {
         static thread_local PerDeviceOnce attr_once;
         if (attr_once.needed()) {
@@ -1688,17 +1690,14 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
             hipLaunchKernelGGL((score_mfma_stats<8, 32, 4>), grid, dim3(WAVES * 64), stats_lds<8>(), st, a);
             launch_merge(a, d.P, M_ROWS, st);
         }
-        // pass 2 has its own decomposition: a workgroup walks a chunk of keys through all 8 KV heads of a layer,
-        // again in whole rounds of one workgroup per CU
-        constexpr int MAX_LAYER_CHUNK = 32768;
-        const int64_t n_sl = (int64_t)d.n_seq * d.n_layers, cus = d.cus;
-        const int64_t rounds = (n_sl * d.L + cus * MAX_LAYER_CHUNK - 1) / (cus * MAX_LAYER_CHUNK);
-        const int64_t per_layer = std::max<int64_t>(1, (cus * rounds + n_sl / 2) / n_sl);
-        int len = (int)(((d.L + per_layer - 1) / per_layer + SUB - 1) / SUB) * SUB;
-        len = std::min(std::max(len, SUB), MAX_LAYER_CHUNK);
+        // pass 2 has its own decomposition: a workgroup walks a chunk of keys through all 8 KV heads of a layer, one
+        // workgroup per CU; its prologue takes as long as some 96 keys
+        constexpr int MAX_LAYER_CHUNK = 32768, FIXED = 96;
+        const int64_t n_sl = (int64_t)d.n_seq * d.n_layers;
+        const ChunkPlan c = plan_chunks(n_sl, d.L, d.cus, SUB, FIXED, MAX_LAYER_CHUNK, INT32_MAX, false);
         ScoreArgs a2 = a;
-        a2.chunk_len = len;
-        a2.n_chunks = (d.L + len - 1) / len;
+        a2.chunk_len = c.len;
+        a2.n_chunks = c.n;
         hipLaunchKernelGGL(score_mfma_columns_layer, dim3(a2.n_chunks, (unsigned)n_sl), dim3(WAVES * 64), PL_LDS, st, a2);
         return hipGetLastError();
     }

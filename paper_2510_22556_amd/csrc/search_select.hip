@@ -248,16 +248,16 @@ struct RowView {
 };
 
 // f(t, s_tilde[t]) for every token of a row, in no particular order
-template <typename F>
+template <int NTH = TB_THREADS, typename F>
 __device__ inline void scan_row(const RowView &r, int tid, F &&f)
 {
-    for (int i0 = tid; i0 < r.nvec; i0 += 4 * TB_THREADS) {
+    for (int i0 = tid; i0 < r.nvec; i0 += 4 * NTH) {
         float4 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = r.vp[min(i0 + j * TB_THREADS, r.nvec - 1)];
+        for (int j = 0; j < 4; ++j) v[j] = r.vp[min(i0 + j * NTH, r.nvec - 1)];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int i = i0 + j * TB_THREADS;
+            const int i = i0 + j * NTH;
             if (i < r.nvec) {
                 const int t = r.token(i);
                 f(t, v[j].x); f(t + 1, v[j].y); f(t + 2, v[j].z); f(t + 3, v[j].w);
@@ -1306,13 +1306,11 @@ template <int NTH, bool TOK> struct HeldScores {
 };
 // ... or read from the row each time
 template <int NTH> struct RowScores {
-    const float *sp;
-    int n;
+    RowView r;
     template <typename F>
     __device__ __forceinline__ void each(F &&f) const
     {
-#pragma nounroll
-        for (int t = threadIdx.x; t < n; t += NTH) f(ordered_key(sp[t]), t);
+        scan_row<NTH>(r, threadIdx.x, [&](int t, float x) __attribute__((always_inline)) { f(ordered_key(x), t); });
     }
 };
 
@@ -1526,7 +1524,7 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
     }
     uint32_t thr;
     int cut;
-    const RowScores<NTH> all{sp, T};
+    const RowScores<NTH> all{RowView(sp, T, tid)};
     const bool whole_row = LISTED && held.n == 0;
     if (whole_row) row_kth_best<NTH>(all, sp, T, k, hist, sh, thr, cut);
     else row_kth_best<NTH>(held, sp, T, k, hist, sh, thr, cut);

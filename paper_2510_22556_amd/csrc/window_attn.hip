@@ -51,7 +51,7 @@ constexpr float RESCALE_AT = 64.f;
 struct WinArgs {
     Dims d;
     const uint16_t *q, *k, *v;
-    int chunk_len, n_chunks;
+    int chunk_len, n_chunks, by_chunk;       // by_chunk: grid (problems, chunks), else (chunks, problems)
     float c1;                  // log2(e) / sqrt(D)
     float *out;                // [P * G][W][D] fp32 (n_chunks == 1) ...
     float *lse;                // [P][G * W] natural log
@@ -112,7 +112,7 @@ window_attention_kernel(WinArgs a)
     const Dims &d = a.d;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hf = lane >> 5;                   // n: query (score tiles) or d column (output tiles)
-    const int p = blockIdx.x / a.n_chunks, chunk = blockIdx.x - p * a.n_chunks;
+    const int p = a.by_chunk ? blockIdx.x : blockIdx.y, chunk = a.by_chunk ? blockIdx.y : blockIdx.x;
     const int lo = chunk * a.chunk_len, hi = min(lo + a.chunk_len, d.L);
     const int n_sub = hi > lo ? (hi - lo + SUB - 1) / SUB : 0;                 // the same for all wavefronts
     // the problem's G * W rows in the order head * W + query; this lane's row of the wavefront's block of 32
@@ -409,20 +409,18 @@ window_attention_merge_kernel(const float *o_part, const float *ml_part, int n_c
     if (threadIdx.x == 0) lse[row] = (m + __builtin_amdgcn_logf(z)) * LN2;
 }
 
-// keys per workgroup: whole rounds of two workgroups per CU (two wavefronts per SIMD: while one waits for its
-// LDS reads or an MFMA result the other computes), as few as keep a chunk within 131 072 keys
-void wa_plan(const Dims &d, int *chunk_len, int *n_chunks, int wgs_per_cu)
+// keys per workgroup, two workgroups per CU (two wavefronts per SIMD: while one waits for its LDS reads or an MFMA result the
+// other computes).  Prologue, epilogue and a chunk's share of the merge take as long as some 256 keys; no more than two rounds,
+// as every chunk has partial results of 64 KiB per 128 rows.
+ChunkPlan wa_plan(const Dims &d, int wgs_per_cu)
 {
-    constexpr int MAX_CHUNK = 131072;
-    const int64_t cus = wgs_per_cu * (int64_t)d.cus;
-    const int64_t rounds = ((int64_t)d.P * d.L + cus * MAX_CHUNK - 1) / (cus * MAX_CHUNK);
-    const int64_t per_problem = std::max<int64_t>(1, (cus * rounds + d.P / 2) / d.P);
-    int len = (int)(((d.L + per_problem - 1) / per_problem + SUB - 1) / SUB) * SUB;
-    if (d.tune.window_chunk >= SUB) len = (d.tune.window_chunk / SUB) * SUB;
-    len = std::min(std::max(len, SUB), MAX_CHUNK);
-    *chunk_len = len;
-    *n_chunks = (d.L + len - 1) / len;
+    constexpr int MAX_CHUNK = 131072, FIXED = 256;
+    const int64_t slots = wgs_per_cu * (int64_t)d.cus;
+    if (d.tune.window_chunk < SUB) return plan_chunks(d.P, d.L, slots, SUB, FIXED, MAX_CHUNK, 2 * slots);
+    const int len = std::min((d.tune.window_chunk / SUB) * SUB, MAX_CHUNK);
+    return {len, (d.L + len - 1) / len, false};
 }
+dim3 wa_grid(const Dims &d, const ChunkPlan &c) { return c.by_chunk ? dim3(d.P, c.n) : dim3(c.n, d.P); }
 
 }  // namespace
 
@@ -438,9 +436,7 @@ static int row_stats_wgs_per_cu(const Dims &d) { return d.G * d.W > 128 ? 2 : 4;
 
 int row_stats_chunks(const Dims &d)
 {
-    int len, nc;
-    wa_plan(d, &len, &nc, row_stats_wgs_per_cu(d));
-    return nc;
+    return wa_plan(d, row_stats_wgs_per_cu(d)).n;
 }
 
 hipError_t launch_row_stats(const Dims &d, const void *q, const void *k, float *stats, hipStream_t st)
@@ -460,11 +456,14 @@ hipError_t launch_row_stats(const Dims &d, const void *q, const void *k, float *
     a.q = static_cast<const uint16_t *>(q);
     a.k = static_cast<const uint16_t *>(k);
     a.v = nullptr;
-    wa_plan(d, &a.chunk_len, &a.n_chunks, row_stats_wgs_per_cu(d));
+    const ChunkPlan plan = wa_plan(d, row_stats_wgs_per_cu(d));
+    a.chunk_len = plan.len;
+    a.n_chunks = plan.n;
+    a.by_chunk = plan.by_chunk;
     a.c1 = (float)(1.4426950408889634 / sqrt((double)d.D));
     a.out = a.lse = a.o_part = a.ml_part = nullptr;
     a.stats = stats;
-    const dim3 grid((unsigned)((int64_t)d.P * a.n_chunks));
+    const dim3 grid = wa_grid(d, plan);
     if (d.G * d.W > 128) hipLaunchKernelGGL((window_attention_kernel<8, false>), grid, dim3(8 * 64), wa_lds(8, false), st, a);
     else hipLaunchKernelGGL((window_attention_kernel<4, false>), grid, dim3(4 * 64), wa_lds(4, false), st, a);
     return hipGetLastError();
@@ -487,8 +486,7 @@ static int wa_blocks(const Dims &d)
 
 size_t window_attention_ws_bytes(const Dims &d)
 {
-    int len, nc;
-    wa_plan(d, &len, &nc, wa_blocks(d) <= 4 ? 2 : 1);
+    const int nc = wa_plan(d, wa_blocks(d) <= 4 ? 2 : 1).n;
     if (nc == 1) return 256;
     const size_t blocks = (size_t)d.P * wa_blocks(d);
     return align256(blocks * nc * ROWS * 128 * 4) + align256(blocks * nc * ROWS * 2 * 4);
@@ -520,13 +518,16 @@ hipError_t launch_window_attention(const Dims &d, const void *q, const void *k, 
     a.k = static_cast<const uint16_t *>(k);
     a.v = static_cast<const uint16_t *>(v);
     // workgroups of up to four wavefronts pair up on a CU; eight-wavefront ones already put two wavefronts on every SIMD
-    wa_plan(d, &a.chunk_len, &a.n_chunks, nw <= 4 ? 2 : 1);
+    const ChunkPlan plan = wa_plan(d, nw <= 4 ? 2 : 1);
+    a.chunk_len = plan.len;
+    a.n_chunks = plan.n;
+    a.by_chunk = plan.by_chunk;
     a.c1 = (float)(1.4426950408889634 / sqrt((double)d.D));
     a.out = out;
     a.lse = lse;
     a.o_part = static_cast<float *>(ws);
     a.ml_part = reinterpret_cast<float *>(static_cast<char *>(ws) + align256((size_t)d.P * nw * a.n_chunks * ROWS * 128 * 4));
-    const dim3 grid((unsigned)((int64_t)d.P * a.n_chunks));
+    const dim3 grid = wa_grid(d, plan);
     a.stats = nullptr;
     if (nw == 1) hipLaunchKernelGGL((window_attention_kernel<1, true>), grid, dim3(64), wa_lds(1), st, a);
     else if (nw == 2) hipLaunchKernelGGL((window_attention_kernel<2, true>), grid, dim3(2 * 64), wa_lds(2), st, a);

@@ -167,3 +167,29 @@ def test_peaked_rows_round_to_little(torch_cuda, G, W):  # noqa: F811
         ref = torch.softmax(x.masked_fill(~seen, float("-inf")), -1).reshape(Hkv, G, W, L).mean(1).sum(1)
         errors.append(((s.double() - ref).norm(dim=1) / ref.norm(dim=1)).mean().item())
     assert sum(errors) / len(errors) < 5.2e-7
+
+
+@pytest.mark.parametrize("cus", [1, 5, 9, 16, 20])
+@pytest.mark.parametrize("Hkv,G,W,D,all_heads", [(7, 4, 32, 128, False), (3, 8, 32, 128, False), (5, 2, 8, 64, False), (8, 4, 32, 128, True)])
+def test_chunks_of_a_plan_for_other_numbers_of_compute_units(oracle, torch_cuda, cus, Hkv, G, W, D, all_heads):  # noqa: F811
+    # whole rounds of equal chunks, and larger ones with a shorter remainder (7 problems on 16 units: three to a problem)
+    torch = torch_cuda
+    L = 2900 + W
+    q = synth.normal_torch(cus, 1, (1, 1, G * Hkv, W, D), "cuda", torch.bfloat16)
+    k = synth.normal_torch(cus, 2, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    _check(oracle, torch, q, k, Hkv, G, W, D, L, all_heads=all_heads, compute_units=cus)
+    if D == 128:
+        from paper_2510_22556_amd import binding as B
+
+        def attend(**tuning):
+            shape = B.make_shape(q, k, **tuning)
+            out = torch.full((1, 1, G * Hkv, W, D), float("nan"), dtype=torch.float32, device="cuda")
+            lse = torch.full((1, 1, G * Hkv, W), float("nan"), dtype=torch.float32, device="cuda")
+            ws = torch.empty((B.sablock_window_attention_workspace_bytes(shape),), dtype=torch.uint8, device="cuda")
+            B.sablock_window_attention(shape, q, k, k, out, lse, ws)
+            return H.to_np(out), H.to_np(lse)
+
+        (o, z), (o1, z1) = attend(compute_units=cus), attend(window_chunk=4096)
+        # probabilities of either cut are rounded to bf16 by themselves, 2^-9 each; log-sum-exps are fp32
+        np.testing.assert_allclose(z, z1, rtol=0, atol=2e-5)
+        np.testing.assert_allclose(o, o1, rtol=0, atol=2e-3 * float(k.abs().max()))
