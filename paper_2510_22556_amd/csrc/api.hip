@@ -129,6 +129,7 @@ sablock_status make_dims(const sablock_shape *s, Dims *d)
     d->n_seq = s->n_seq; d->n_layers = s->n_layers; d->Hq = s->n_q_heads; d->Hkv = s->n_kv_heads;
     d->G = s->n_q_heads / s->n_kv_heads; d->D = s->head_dim; d->L = s->seq_len; d->W = s->window;
     d->T = s->seq_len - s->window; d->M = d->G * d->W; d->P = (int32_t)P; d->dtype = s->dtype;
+    d->local = P * (int64_t)s->seq_len <= 2 << 20;             // 24 MiB of scores, entropy terms and refined scores
     d->inv_heads = inverse_of((uint32_t)d->Hkv);
     d->inv_seq = inverse_of((uint32_t)(d->n_layers * d->Hkv));
     for (int a = 0; a < 4; ++a) { d->qs[a] = s->q_stride[a]; d->ks[a] = s->k_stride[a]; d->vs[a] = s->v_stride[a]; }

@@ -10,7 +10,7 @@ namespace {
 constexpr int NT = 256;
 constexpr int RPT = 4;            // output rows per thread: that many independent 16-byte gathers in flight
 
-// grid (ceil(ceil(rows / RPT) * chunks / NT), P, 2): z = 0 copies K, z = 1 copies V.  A thread copies chunk `ch`
+// grid of ceil(ceil(rows / RPT) * chunks / NT) parts, twice: z = 0 copies K, z = 1 copies V.  A thread copies chunk `ch`
 // of output rows r, r + R4, r + 2 R4, r + 3 R4 (R4 = ceil(rows / RPT)), so consecutive lanes still cover a row.
 // idx_div = 1: every problem has its own index row; idx_div = Hkv: the KV heads of a (sequence, layer) share one
 // (retained set chosen per layer)
@@ -18,10 +18,10 @@ __global__ void __launch_bounds__(NT)
 compact_kernel(Dims d, const char *k, const char *v, const int32_t *idx, const int32_t *n_sel,
                int budget, int rows, int chunks, int elt, char *k_out, char *v_out, int idx_div)
 {
-    const int p = blockIdx.y;
+    const int p = grid_problem(d);
     const int ip = p / idx_div;                         // row of idx / n_sel: the problem, or its (sequence, layer)
     const int r4 = (rows + RPT - 1) / RPT;
-    const int e = blockIdx.x * NT + threadIdx.x;
+    const int e = grid_part(d) * NT + threadIdx.x;
     if (e >= r4 * chunks) return;
     const int row0 = e / chunks, ch = e - row0 * chunks;
     const bool is_v = blockIdx.z != 0;
@@ -64,7 +64,7 @@ hipError_t launch_compact(const Dims &d, const void *k, const void *v, const int
     const int chunks = d.D * elt / 16;
     if (rows <= 0 || d.P <= 0) return hipSuccess;
     const int r4 = (rows + RPT - 1) / RPT;
-    dim3 grid((unsigned)(((int64_t)r4 * chunks + NT - 1) / NT), d.P, 2);
+    const dim3 grid = parts_grid(d, (unsigned)(((int64_t)r4 * chunks + NT - 1) / NT), 2);
     hipLaunchKernelGGL(compact_kernel, grid, dim3(NT), 0, st, d, static_cast<const char *>(k),
                        static_cast<const char *>(v), idx, n_sel, budget, rows, chunks, elt,
                        static_cast<char *>(k_out), static_cast<char *>(v_out), shared_rows ? d.Hkv : 1);

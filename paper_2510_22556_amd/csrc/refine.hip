@@ -36,18 +36,18 @@ __device__ inline double group_sum(double v)
     return v;
 }
 
-// grid (ceil(max_segments / RSEG), P)
+// grid of ceil(max_segments / RSEG) parts
 __global__ void __launch_bounds__(NT)
 refine_kernel(Dims d, const float *s, const float *ent, SegView sv, sablock_hparams hp,
               float *s_tilde, float *omega)
 {
     __shared__ float sh_s[RCAP], sh_e[RCAP];
-    const int p = blockIdx.y;
+    const int p = grid_problem(d);
     const int sub = threadIdx.x & (GROUP - 1), grp = threadIdx.x / GROUP;
     const int seq = seq_of_problem(d, p);
     const int base = sv.seq_ptr[seq];
     const int K = sv.seq_ptr[seq + 1] - base - 1;
-    const int k0 = blockIdx.x * RSEG;
+    const int k0 = grid_part(d) * RSEG;
     const int k1 = min(k0 + RSEG, K);
     // rows of omega are max_segments wide: zero behind the sequence's last segment
     if (omega)
@@ -104,7 +104,7 @@ hipError_t launch_refine(const Dims &d, const float *s, const float *ent, const 
                          sablock_hparams hp, float *s_tilde, float *omega, hipStream_t st)
 {
     if (sv.max_segments <= 0 || d.P <= 0) return hipSuccess;
-    dim3 grid((sv.max_segments + RSEG - 1) / RSEG, d.P);
+    const dim3 grid = parts_grid(d, (sv.max_segments + RSEG - 1) / RSEG);
     hipLaunchKernelGGL(refine_kernel, grid, dim3(NT), 0, st, d, s, ent, sv, hp, s_tilde, omega);
     return hipGetLastError();
 }

@@ -16,6 +16,7 @@ struct Dims {
     int32_t P;                                            // problems = n_seq * n_layers * Hkv
     int32_t dtype;
     int32_t cus;                                          // compute units the launch plans assume (never 0)
+    int32_t local;                                        // a problem's workgroups share an XCD, see grid_problem
     uint32_t inv_heads, inv_seq;                          // ceil(2^32 / Hkv), ceil(2^32 / (n_layers * Hkv)); 0 for a divisor of 1
     sablock_tuning tune;                                  // the caller's launch parameters, validated (0 = plan)
     int64_t qs[4], ks[4], vs[4];
@@ -64,6 +65,15 @@ __host__ __device__ inline int32_t layer_of_problem(const Dims &d, int32_t p)
 {
     return quotient(p, d.inv_heads) - seq_of_problem(d, p) * d.n_layers;
 }
+
+// Grids over (parts, problems).  Workgroups go round the 8 XCDs, each of which has an L2
+// cache of 4 MiB; where what the steps hand on to each other (12 bytes per key) fits these caches, the problems come first, so that
+// with 8 problems, a layer of most models, every step finds what the one before it wrote in its own XCD's cache.  With more data
+// nothing is left of it, and neighbouring workgroups had better read neighbouring memory.
+__host__ inline dim3 parts_grid(const Dims &d, unsigned parts, unsigned z = 1) { return d.local ? dim3(d.P, parts, z) : dim3(parts, d.P, z); }
+__device__ __forceinline__ int grid_problem(const Dims &d) { return d.local ? blockIdx.x : blockIdx.y; }
+__device__ __forceinline__ int grid_part(const Dims &d) { return d.local ? blockIdx.y : blockIdx.x; }
+__device__ __forceinline__ int grid_parts(const Dims &d) { return d.local ? gridDim.y : gridDim.x; }
 
 __host__ __device__ inline int64_t k_problem_offset(const Dims &d, int32_t p)
 {

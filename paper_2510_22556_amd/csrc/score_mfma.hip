@@ -1480,7 +1480,7 @@ void plan_partials(ScoreArgs &a, const Dims &d, const Plan &pl, void *ws)
 {
     a.chunk_len = pl.chunk_len;
     a.n_chunks = pl.n_chunks;
-    a.by_chunk = pl.by_chunk;
+    a.by_chunk = pl.by_chunk || d.local;
     a.partial = static_cast<float *>(ws);
     a.merged = a.partial;
     a.pc = pl.n_chunks;
@@ -1630,7 +1630,7 @@ hipError_t launch_stream_probe(const Dims &d, const void *k, int read_lds, float
     a.k = static_cast<const uint16_t *>(k);
     a.chunk_len = pl.chunk_len;
     a.n_chunks = pl.n_chunks;
-    a.by_chunk = pl.by_chunk;
+    a.by_chunk = pl.by_chunk || d.local;
     a.s_out = s_out;
     a.e_out = e_out;
     const dim3 grid = a.by_chunk ? dim3(d.P, pl.n_chunks) : dim3(pl.n_chunks, d.P);

@@ -1228,7 +1228,7 @@ struct PlanArgs {
 };
 
 // ---- several workgroups per row (few problems in a call, long rows: one workgroup per row would be bound by the
-// latency of its own loads).  grid (slices, P): every workgroup forms the row's bound from the same sample and
+// latency of its own loads).  Grid of slices: every workgroup forms the row's bound from the same sample and
 // collects its slice's tokens above it.
 __global__ void __launch_bounds__(TB_THREADS)
 topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, uint2 *pre_list, int32_t *pre_cnt)
@@ -1237,17 +1237,17 @@ topb_collect_kernel(Dims d, const float *s_tilde, int sample_rank, int pre_cap, 
     __shared__ TopbShared sh;
     uint32_t *hist = sh_dyn;
     int32_t *list = reinterpret_cast<int32_t *>(sh_dyn + TB_BINS);
-    const int p = blockIdx.y, sl = blockIdx.x, tid = threadIdx.x;
+    const int p = grid_problem(d), sl = grid_part(d), n_slices = grid_parts(d), tid = threadIdx.x;
     const RowView r(s_tilde + (int64_t)p * d.T, d.T, tid);
     if (tid == 0) sh.n = 0;
     const float bound = r.nvec > TB_ROUND / 4 ? sample_bound(r, sample_rank, hist, sh) : -INFINITY;
     __syncthreads();
-    const int per = (r.nvec + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int per = (r.nvec + n_slices - 1) / n_slices;
     const int i0 = min(sl * per, r.nvec), i1 = min(i0 + per, r.nvec);
     if (i0 < i1) collect_above(r, i0, i1, bound, list, pre_cap, sh);
     if (sl == 0) append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, pre_cap, sh);
     __syncthreads();
-    const int64_t o = (int64_t)p * gridDim.x + sl;
+    const int64_t o = (int64_t)p * n_slices + sl;
     for (int i = tid; i < min(sh.n, pre_cap); i += TB_THREADS) pre_list[o * pre_cap + i] = make_uint2(ordered_key(r.sp[list[i]]), (uint32_t)list[i]);
     if (tid == 0) pre_cnt[o] = sh.n;
 }
@@ -1929,22 +1929,22 @@ search_kernel(Dims d, const float *s_tilde, int32_t max_segments, CandList cand,
               const int32_t *counts, int capacity, int32_t *block_size, int budget, int32_t *idx_out)
 {
     __shared__ __attribute__((aligned(16))) char slice[SLICE_BYTES];
-    const int p = blockIdx.y, lane = threadIdx.x;
+    const int p = grid_problem(d), stride = grid_parts(d), lane = threadIdx.x;
     const SegRec *recs = list + (int64_t)p * capacity;
     const SearchCtx x(s_tilde, d.T, p, block_size, max_segments, EMIT ? idx_out : nullptr, budget, tau, cand);
     const float *sp = x.sp;
 
-    int i = blockIdx.x;                                        // < capacity: the grid is no wider than the list can get
+    int i = grid_part(d);                                      // < capacity: the grid is no wider than the list can get
     SegRec nxt = recs[i];                                      // fetched together with the list's length
     const int n_rec = min(counts[p], capacity);
     if (i >= n_rec) return;
     float2 v_nxt = first_scores(sp, nxt);
-    for (bool more = true; more; i += gridDim.x) {
+    for (bool more = true; more; i += stride) {
         const SegRec r = nxt;
         const float2 v0 = v_nxt;
-        more = i + (int)gridDim.x < n_rec;
+        more = i + stride < n_rec;
         if (more) {                                            // the next record and its scores, under this one's work
-            nxt = recs[i + gridDim.x];
+            nxt = recs[i + stride];
             v_nxt = first_scores(sp, nxt);
         }
         const int a = r.a, b = r.b, n = b - a;
@@ -2303,7 +2303,7 @@ static void run_search(const Dims &d, const float *s_tilde, const SegView &sv, c
 {
     // wavefronts per problem: one per possible record up to 128 per CU (24 are resident at once), striding over the records
     const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)d.cus * 128 / d.P));
-    hipLaunchKernelGGL(search_kernel<EMIT>, dim3(gx, d.P), dim3(64), 0, st, d, s_tilde, sv.max_segments, cand, tau, w.list,
+    hipLaunchKernelGGL(search_kernel<EMIT>, parts_grid(d, gx), dim3(64), 0, st, d, s_tilde, sv.max_segments, cand, tau, w.list,
                        w.counts, cap, block_size, budget, idx_out);
 }
 
@@ -2435,7 +2435,7 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
         int32_t *counts = reinterpret_cast<int32_t *>(x);
         uint2 *entries = reinterpret_cast<uint2 *>(x + align256((size_t)d.P * n_slices * 4));
         const int pre_cap = topb_list_k(d, budget) * TB_THREADS;
-        hipLaunchKernelGGL(topb_collect_kernel, dim3(n_slices, d.P), dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, d, s_tilde,
+        hipLaunchKernelGGL(topb_collect_kernel, parts_grid(d, n_slices), dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, d, s_tilde,
                            topb_rank(d, budget), pre_cap, entries, counts);
         const Candidates cd{entries, counts, n_slices, pre_cap};
         e = run_row_rank<true, 512, true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments, st);
