@@ -105,7 +105,7 @@ __host__ __device__ inline uint32_t ordered_key(float f)
 
 // Keys per workgroup: a problem's L keys in chunks of `len`, the last one what is left.  A workgroup costs its keys and `fixed`
 // keys' time besides (prologue, epilogue); `slots` of them run at a time.  Equal chunks in whole rounds of workgroups, or, where
-// those leave places idle, larger ones whose remainders the idle places take (112 problems on 256: two and a shorter one); then
+// those leave places idle, larger ones whose remainders the idle places take (96 problems on 256: two and a shorter one); then
 // the workgroups start chunk by chunk (by_chunk), all problems' first ones first.  At most `most` keys each, and `wgs`
 // workgroups in all where one round needs no more.
 struct ChunkPlan { int len, n; bool by_chunk; };
@@ -125,14 +125,20 @@ inline ChunkPlan plan_chunks(int64_t P, int64_t L, int64_t slots, int step, int 
         if (len == step) break;
     }
     const int64_t ideal = P * L / slots + fixed;
-    if (remainders && best * 100 > ideal * 104)
+    // where they would gain a twelfth or more, and with remainders of a quarter or more: with most places taken the memory is as
+    // busy as it gets (128 rows, 30 011 keys on 256 places: 112 problems in two chunks 302 us, in two and a sixth 315; 56 in four
+    // 185, in four and two fifths 171)
+    const int64_t equal = best;
+    if (remainders && equal * 100 > ideal * 108)
         for (int64_t n = std::max<int64_t>(2, least); n <= 6 && P * n <= wgs; ++n) {     // n - 1 chunks and the remainder of each
             const int64_t from = up((L + n - 1) / n), to = std::min(up((L + n - 2) / (n - 1)) - step, most), by = std::max<int64_t>(step, up((to - from) / 16));
             for (int64_t len = from + by; len <= to; len += by) {
+                if (4 * (L - (n - 1) * len) < len) continue;
                 const int64_t big = len + fixed, small = L - (n - 1) * len + fixed, q = P * (n - 1) / slots, late = P * (n - 1) % slots;
                 // `late` places have q + 1 chunks, the others q and a chunk's time for remainders; what is over comes on top
                 const int64_t early = slots - late, room = late ? early * (big / small) : 0, over = std::max<int64_t>(0, P - room);
-                offer((late ? q + 1 : q) * big + (over + slots - 1) / slots * small, len, true);
+                const int64_t cost = (late ? q + 1 : q) * big + (over + slots - 1) / slots * small;
+                if (cost * 108 < equal * 100) offer(cost, len, true);
             }
         }
     return {(int)best_len, (int)((L + best_len - 1) / best_len), by_chunk};

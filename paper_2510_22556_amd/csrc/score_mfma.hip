@@ -1454,7 +1454,9 @@ Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)
 {
     // One launch per pass covers every problem.  A workgroup owns chunk_len consecutive keys of one problem, and
     // one workgroup fills a CU (registers and the load ring).  Prologue and epilogue, during which its CU loads nothing, take
-    // some 6 us, as long as 640 keys.  The chunk partials stay within 4 MiB where one round of workgroups does.
+    // some 6 us, as long as 640 keys.  The chunk partials stay within 4 MiB where one round of workgroups does.  Both passes,
+    // 128 rows, 30 011 keys, against the nearest whole number of chunks per unit: 24 problems 113 -> 74 us, 96 383 -> 287, 144
+    // 563 -> 432, 320 1 117 -> 883.
     constexpr int MAX_CHUNK = 131072, FIXED = 640;
     Plan pl;
     if (d.tune.score_chunk >= STRIDE) {
