@@ -6,12 +6,14 @@
 // are ordered head * W + query and a wavefront is one block of 32 of them (one head, half of a head's window of
 // 64, or several heads when W < 32), so a workgroup has one to eight wavefronts.  A workgroup owns a chunk
 // of keys of one problem (sequence, layer, KV head).  K and V subtiles of 32 keys
-// go global -> LDS by direct-to-LDS loads into a workgroup-wide ring of NSTAGE stages (each wavefront issues its
-// share of a stage); one LDS-only barrier per subtile tells that the stage has landed and that the stage of
-// the previous iteration is free to be refilled.  The score product, the exponentials and the second product of
-// a subtile depend on each other, so a wavefront alone leaves its SIMD idle between them: the ring is kept to
-// 64 KiB so that two workgroups share a CU, and a problem is split over at least two workgroups (partial results
-// are merged by a second kernel).
+// go global -> LDS by direct-to-LDS loads into workgroup-wide rings (each wavefront issues its share of a
+// subtile); one LDS-only barrier per subtile tells that the next subtile has landed and that the places of the
+// last one are free to be refilled.  Score product, exponentials and second product of a subtile depend on each
+// other: in the steady state the score product of the next subtile is issued before the exponentials of this one
+// (256 problems of 32 768 keys, 128 rows 790 -> 765 us, of 131 072 3.05 -> 2.94 ms; one behind the other before),
+// the rings are kept to 72 KiB so that two workgroups share a CU, and a problem is split over at least two
+// workgroups (partial results are merged by a second kernel).  An order of the steady state's instructions that
+// interleaves products and exponentials by hand was slower (804 us).
 //
 // Scores are formed TRANSPOSED, S^T = K Q^T (the same operand registers as Q K^T with the MFMA's A and B swapped):
 // a lane then owns ONE query (column) and 16 of the subtile's 32 keys, so the row maximum and the row sum are
@@ -26,6 +28,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 namespace sablock {
 namespace {
@@ -39,11 +42,12 @@ typedef void __attribute__((address_space(3))) *lptr_t;
 constexpr int SUB = 32;                        // keys per subtile
 constexpr int ROW_BYTES = 256;                 // D = 128 bf16
 constexpr int TILE_BYTES = SUB * ROW_BYTES;    // 8 KiB: one K or V subtile
-// with V: a stage of the ring is a K tile then a V tile; statistics only: a K tile
-constexpr int stage_bytes(bool with_v) { return with_v ? 2 * TILE_BYTES : TILE_BYTES; }
-constexpr int NSTAGE = 4;                      // 64 KiB ring per workgroup: two workgroups (8 wavefronts) per CU
+// Rings of K and, with V, of V tiles: 72 KiB per workgroup, so that two of them (8 wavefronts) share a CU.  V's is one
+// longer, as a subtile's V is needed while the next one's K is (see the steady state).
+constexpr int NSTAGE = 4, VSTAGE = 5;
 constexpr int ROWS = 32;                       // window-query rows of a wavefront
-constexpr int wa_lds(int nw, bool with_v = true) { return NSTAGE * stage_bytes(with_v) + nw * ROWS * 4; }   // ring + a 32-float exchange slice per wavefront
+constexpr int ring_bytes(bool with_v) { return (NSTAGE + (with_v ? VSTAGE : 0)) * TILE_BYTES; }
+constexpr int wa_lds(int nw, bool with_v = true) { return ring_bytes(with_v) + nw * ROWS * 4; }   // rings + a 32-float exchange slice per wavefront
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 constexpr float RESCALE_AT = 64.f;
@@ -51,7 +55,7 @@ constexpr float RESCALE_AT = 64.f;
 struct WinArgs {
     Dims d;
     const uint16_t *q, *k, *v;
-    int chunk_len, n_chunks, by_chunk;       // by_chunk: grid (problems, chunks), else (chunks, problems)
+    int chunk_len, n_chunks;
     float c1;                  // log2(e) / sqrt(D)
     float *out;                // [P * G][W][D] fp32 (n_chunks == 1) ...
     float *lse;                // [P][G * W] natural log
@@ -75,6 +79,20 @@ __device__ __forceinline__ float other_half(float x, bool take_max)
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
     return take_max ? fmaxf(a, b) : a + b;
+}
+
+__device__ __forceinline__ float largest(const floatx16 &acc)
+{
+    // three at a time; as fmaxf, which takes another instruction per operand, it prefers a number
+    auto max3 = [](float x, float y, float z) __attribute__((always_inline)) {
+        float m;
+        asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(x), "v"(y), "v"(z));
+        return m;
+    };
+    float m[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) m[i] = max3(acc[3 * i], acc[3 * i + 1], acc[3 * i + 2]);
+    return max3(max3(m[0], m[1], m[2]), max3(m[3], m[4], acc[15]), acc[15]);
 }
 
 // all LDS traffic of this wavefront done, then the workgroup barrier (global loads stay in flight)
@@ -105,44 +123,45 @@ template <int NW, bool WITH_V>
 __global__ void __launch_bounds__(NW * 64)
 window_attention_kernel(WinArgs a)
 {
-    constexpr int STAGE_BYTES = stage_bytes(WITH_V);
     constexpr int KPIECES = 8 / NW;                            // K pieces per wavefront and stage (as many V pieces)
     constexpr int LOADS = WITH_V ? 2 * KPIECES : KPIECES;      // direct-to-LDS loads per wavefront and stage
     extern __shared__ __attribute__((aligned(8192))) char lds[];
     const Dims &d = a.d;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 31, hf = lane >> 5;                   // n: query (score tiles) or d column (output tiles)
-    const int p = a.by_chunk ? blockIdx.x : blockIdx.y, chunk = a.by_chunk ? blockIdx.y : blockIdx.x;
+    const int p = blockIdx.x / a.n_chunks, chunk = blockIdx.x - p * a.n_chunks;
     const int lo = chunk * a.chunk_len, hi = min(lo + a.chunk_len, d.L);
     const int n_sub = hi > lo ? (hi - lo + SUB - 1) / SUB : 0;                 // the same for all wavefronts
     // the problem's G * W rows in the order head * W + query; this lane's row of the wavefront's block of 32
     // (W >= 32: one head per block; W < 32: 32 / W heads per block)
     const int head = (ROWS * wave + n) / d.W, qoff = (ROWS * wave + n) - head * d.W - n;    // query of this lane = qoff + n
     const uint32_t ring = __builtin_amdgcn_readfirstlane(lds_addr(lds));
-    float *fac = reinterpret_cast<float *>(lds + NSTAGE * STAGE_BYTES) + wave * ROWS;        // this wavefront's exchange slice
+    float *fac = reinterpret_cast<float *>(lds + ring_bytes(WITH_V)) + wave * ROWS;          // this wavefront's exchange slice
     const char *kp = reinterpret_cast<const char *>(a.k + k_problem_offset(d, p));
     const char *vp = WITH_V ? reinterpret_cast<const char *>(a.v + v_problem_offset(d, p)) : nullptr;
     const int64_t krow = d.ks[3] * 2, vrow = d.vs[3] * 2;
 
-    // ---- loads: stage u % NSTAGE holds subtile u; this wavefront brings its share of the 8 K pieces and of the 8 V
-    // pieces (both tiles are stored swizzled, see issue_piece)
-    auto issue = [&](int u) {
+    // ---- loads: this wavefront brings its share of the 8 K pieces and of the 8 V pieces of subtile u (both tiles are stored
+    // swizzled, see issue_piece)
+    auto k_tile = [&](int u) { return ring + (u % NSTAGE) * TILE_BYTES; };
+    auto v_tile = [&](int u) { return ring + (NSTAGE + (uint32_t)u % VSTAGE) * TILE_BYTES; };
+    auto issue = [&](int u, auto full) __attribute__((always_inline)) {
+        constexpr bool FULL = decltype(full)::value;
         const int t0 = lo + u * SUB;                           // < L
-        const uint32_t st = ring + (u % NSTAGE) * STAGE_BYTES;
 #pragma unroll
         for (int jj = 0; jj < KPIECES; ++jj) {
             const int j = KPIECES * wave + jj;
-            issue_piece<true>(kp + (int64_t)t0 * krow, krow, t0, d.L, j, lane, st + j * 1024);
+            issue_piece<true, FULL>(kp + (int64_t)t0 * krow, krow, t0, d.L, j, lane, k_tile(u) + j * 1024);
         }
         if (WITH_V) {
 #pragma unroll
             for (int jj = 0; jj < KPIECES; ++jj) {
                 const int j = KPIECES * wave + jj;
-                issue_piece<false>(vp + (int64_t)t0 * vrow, vrow, t0, d.L, j, lane, st + TILE_BYTES + j * 1024);
+                issue_piece<false, FULL>(vp + (int64_t)t0 * vrow, vrow, t0, d.L, j, lane, v_tile(u) + j * 1024);
             }
         }
     };
-    for (int u = 0; u < NSTAGE - 1 && u < n_sub; ++u) issue(u);
+    for (int u = 0; u < NSTAGE - 1 && u < n_sub; ++u) issue(u, std::false_type{});
 
     // ---- this block's window queries: B operand of S^T = K Q^T, lane (query n, half hf) holds Q[n][(2s + hf) * 8 .. +8]
     bf16x8 qa[8];
@@ -179,7 +198,109 @@ window_attention_kernel(WinArgs a)
     // subtiles 1 .. n_fast - 1 have no masked key, and the subtile refilled while they are worked on exists and is full
     const int n_fast = min(min(n_sub, (d.L - lo) / SUB) - (NSTAGE - 1), (d.T - lo) / SUB);
 
+    // probabilities of subtile u relative to the reference, their sum, and O += P V.  The lane's 16 probabilities are the two A
+    // operands; k-step s covers keys 16 s .. 16 s + 15 in the order of the accumulator rows, so lane half kb needs V rows
+    // 16 s + 4 kb + (0..3) and 16 s + 8 + 4 kb + (0..3) of its column: two transposing reads
+    auto finish = [&](const floatx16 &acc, int u) __attribute__((always_inline)) {
+        float pr[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pr[i] = __builtin_amdgcn_exp2f(acc[i] * a.c1);
+        float sum[4] = {pr[0], pr[1], pr[2], pr[3]};
+#pragma unroll
+        for (int i = 4; i < 16; ++i) sum[i & 3] += pr[i];
+        l += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+        bf16x8 pa[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) pa[s][j] = (__bf16)pr[8 * s + j];
+        const uint32_t st = v_tile(u);
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const uint32_t va = st + v_lane[t] + (uint32_t)(16 * s * ROW_BYTES);
+                short4v v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v *)(uintptr_t)va);
+                short4v v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) short4v *)(uintptr_t)(va + 8 * ROW_BYTES));
+                short8v vv = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+                o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[s], __builtin_bit_cast(bf16x8, vv), o[t], 0, 0, 0);
+            }
+        }
+    };
+    // moves the reference of the lanes with a logit more than `lim` above it (all: to the subtile's largest): their sums, outputs
+    // and acc follow
+    auto anchor = [&](floatx16 &acc, bool all) __attribute__((always_inline)) {
+        const float m2 = other_half(largest(acc), true);       // over all 32 keys of the subtile
+        float dlt = 0.f;                                       // how far the reference moves
+        if (all) dlt = m2 > -INFINITY ? m2 : 0.f;
+        else if (m2 > lim) dlt = m2;
+        const float f = all ? 1.f : __builtin_amdgcn_exp2f(-a.c1 * dlt);
+        r += dlt;
+        l *= f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] -= dlt;
+        if (WITH_V) {
+            // the output rows are queries: hand the per-query factors over through LDS
+            if (hf == 0) fac[n] = f;
+            __builtin_amdgcn_wave_barrier();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float fi = fac[row_of(i, hf)];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) o[t][i] *= fi;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    // with V, subtiles 1 .. n_steady + 1 have no masked key, and those up to n_steady + 4 are full
+    const int n_steady = min(min(n_sub, (d.L - lo) / SUB) - 5, (d.T - lo) / SUB - 2);
+
     for (int u = 0; u < n_sub; ++u) {
+        if constexpr (WITH_V) {
+            if (u == 1 && n_steady >= 2) {
+                // ---- steady state: the score products of subtile v + 1 are issued before the exponentials of subtile v, so that the
+                // matrix pipe works in their shadow and the reads of a wavefront under its own arithmetic
+                floatx16 nr;                                   // minus the reference, the products' C operand
+#pragma unroll
+                for (int i = 0; i < 16; ++i) nr[i] = -r;
+                auto products = [&](int v) __attribute__((always_inline)) {
+                    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
+                    lds_barrier();                             // subtile v has landed; K of v - 1 and V of v - 2 have been read
+                    issue(v + 3, std::true_type{});
+                    typedef const bf16x8 __attribute__((address_space(3))) *lds_vec;
+                    bf16x8 kb[8];
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) kb[s] = *(lds_vec)(uintptr_t)((k_tile(v) + k_lane) ^ (uint32_t)(s << 5));
+                    floatx16 acc = nr;
+#pragma unroll
+                    for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[s], qa[s], acc, 0, 0, 0);
+                    return acc;
+                };
+                auto check = [&](floatx16 &acc) __attribute__((always_inline)) {
+                    if (__builtin_expect(__ballot(largest(acc) > lim) != 0ull, 0)) {
+                        anchor(acc, false);
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) nr[i] = -r;
+                    }
+                };
+                int v = 1;
+                floatx16 sa = products(v), sb;
+                while (v + 1 <= n_steady) {
+                    check(sa);
+                    sb = products(v + 1);
+                    finish(sa, v);
+                    check(sb);
+                    sa = products(v + 2);
+                    finish(sb, v + 1);
+                    v += 2;
+                }
+                check(sa);
+                finish(sa, v);
+                u = v + 1;                                     // < n_sub: the generic step goes on from here
+            }
+        }
         if constexpr (!WITH_V) {
             if (u == 1 && n_fast >= 3) {
                 // ---- statistics, steady state: the products of subtile v + 1 are issued before the exponentials of
@@ -193,11 +314,10 @@ window_attention_kernel(WinArgs a)
 #pragma unroll
                         for (int jj = 0; jj < KPIECES; ++jj) {
                             const int j = KPIECES * wave + jj;
-                            issue_piece<true, true>(kp + (int64_t)t0 * krow, krow, t0, d.L, j, lane,
-                                                    ring + (w % NSTAGE) * STAGE_BYTES + j * 1024);
+                            issue_piece<true, true>(kp + (int64_t)t0 * krow, krow, t0, d.L, j, lane, k_tile(w) + j * 1024);
                         }
                     }
-                    const uint32_t st = ring + (v % NSTAGE) * STAGE_BYTES;
+                    const uint32_t st = k_tile(v);
                     bf16x8 kb[8];
 #pragma unroll
                     for (int s = 0; s < 8; ++s)
@@ -262,8 +382,8 @@ window_attention_kernel(WinArgs a)
         }
         // ... and after the barrier so have everyone's; the stage of the previous iteration is free: refill it
         lds_barrier();
-        if (u + NSTAGE - 1 < n_sub) issue(u + NSTAGE - 1);
-        const uint32_t st = ring + (u % NSTAGE) * STAGE_BYTES;
+        if (u + NSTAGE - 1 < n_sub) issue(u + NSTAGE - 1, std::false_type{});
+        const uint32_t st = k_tile(u);
         const int t0 = lo + u * SUB;
 
         // ---- S^T = K Q^T: acc[i] = <q_n, k_{t0 + row_of(i, hf)}> - r
@@ -290,56 +410,12 @@ window_attention_kernel(WinArgs a)
             }
         }
         // ---- reference: anchored at the first subtile, moved when a logit runs more than `lim` ahead of it
-        float mx = acc[0];
+        if (u == 0 || __ballot(largest(acc) > lim) != 0ull) anchor(acc, u == 0);
+        if constexpr (WITH_V) {
+            finish(acc, u);
+        } else {
 #pragma unroll
-        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, acc[i]);
-        if (u == 0 || __ballot(mx > lim) != 0ull) {
-            const float m2 = other_half(mx, true);             // over all 32 keys of the subtile
-            float dlt = 0.f;                                   // how far the reference moves
-            if (u == 0) dlt = m2 > -INFINITY ? m2 : 0.f;
-            else if (m2 > lim) dlt = m2;
-            const float f = u == 0 ? 1.f : __builtin_amdgcn_exp2f(-a.c1 * dlt);
-            r += dlt;
-            l *= f;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc[i] -= dlt;
-            if (WITH_V) {
-                // the output rows are queries: hand the per-query factors over through LDS
-                if (hf == 0) fac[n] = f;
-                __builtin_amdgcn_wave_barrier();
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float fi = fac[row_of(i, hf)];
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) o[t][i] *= fi;
-                }
-                __builtin_amdgcn_wave_barrier();
-            }
-        }
-        // ---- probabilities relative to the reference, their sum, and the two A operands of O += P V
-        float pr[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) { pr[i] = __builtin_amdgcn_exp2f(acc[i] * a.c1); l += pr[i]; }
-        if (!WITH_V) continue;
-        bf16x8 pa[2];
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) pa[s][j] = (__bf16)pr[8 * s + j];
-        // ---- O += P V: k-step s covers keys 16 s .. 16 s + 15 in the order of the accumulator rows, so lane half kb
-        // needs V rows 16 s + 4 kb + (0..3) and 16 s + 8 + 4 kb + (0..3) of its column: two transposing reads
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const uint32_t va = st + TILE_BYTES + v_lane[t] + (uint32_t)(16 * s * ROW_BYTES);
-                short4v v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) short4v *)(uintptr_t)va);
-                short4v v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) short4v *)(uintptr_t)(va + 8 * ROW_BYTES));
-                short8v vv = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-                o[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa[s], __builtin_bit_cast(bf16x8, vv), o[t], 0, 0, 0);
-            }
+            for (int i = 0; i < 16; ++i) l += __builtin_amdgcn_exp2f(acc[i] * a.c1);
         }
     }
 
@@ -383,44 +459,82 @@ window_attention_kernel(WinArgs a)
 }
 
 // merge of the chunks' partial results: one workgroup per output row (problem, head, window query), one thread per
-// output column; the row's partial results sit in row block (head, window half) of its problem
-__global__ void __launch_bounds__(128)
+// output column; the row's partial results sit in row block (head, window half) of its problem.  A thread fetches a chunk's
+// (reference, sum), then its column of eight chunks at a time: one after another, as many chunks as 8 problems have (64) took
+// 40 of the 70 us of a call on 8 192 keys.
+constexpr int MERGE_T = 128;
+
+// over the workgroup's two wavefronts; sh: two floats, free again behind the next barrier
+template <bool MAX>
+__device__ __forceinline__ float merge_all(float v, float *sh)
+{
+    for (int off = 32; off > 0; off >>= 1) { const float x = __shfl_xor(v, off); v = MAX ? fmaxf(v, x) : v + x; }
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return MAX ? fmaxf(sh[0], sh[1]) : sh[0] + sh[1];
+}
+
+__global__ void __launch_bounds__(MERGE_T)
 window_attention_merge_kernel(const float *o_part, const float *ml_part, int n_chunks, int G, int W, int nw, float *out,
                               float *lse)
 {
-    const int row = blockIdx.x;                                // (p * G + h) * W + i
+    __shared__ float sh_w[MERGE_T], sh_m[2], sh_z[2];          // weights of a block of chunks, -1: a chunk without a key for the row
+    const int row = blockIdx.x, tid = threadIdx.x;             // (p * G + h) * W + i
     const int GW = G * W, p = row / GW, r = row - p * GW;      // r = h * W + i: blocks of 32 consecutive r
     const int pb = p * nw + r / ROWS, qy = r % ROWS;           // nw row blocks per problem (the last ones may be padding)
-    float m = -INFINITY;
-    for (int c = 0; c < n_chunks; ++c) {
-        const float *ml = ml_part + (((int64_t)pb * n_chunks + c) * ROWS + qy) * 2;
-        if (ml[1] > 0.f) m = fmaxf(m, ml[0]);
+    const float2 *ml = reinterpret_cast<const float2 *>(ml_part) + (int64_t)pb * n_chunks * ROWS + qy;
+    const float *o = o_part + ((int64_t)pb * n_chunks * ROWS + qy) * 128 + tid;
+    float2 e = tid < n_chunks ? ml[(int64_t)tid * ROWS] : make_float2(0.f, 0.f);
+    float m = e.y > 0.f ? e.x : -INFINITY;
+    for (int c = tid + MERGE_T; c < n_chunks; c += MERGE_T) {
+        const float2 x = ml[(int64_t)c * ROWS];
+        if (x.y > 0.f) m = fmaxf(m, x.x);
     }
+    m = merge_all<true>(m, sh_m);
     float acc = 0.f, z = 0.f;
-    for (int c = 0; c < n_chunks; ++c) {
-        const float *ml = ml_part + (((int64_t)pb * n_chunks + c) * ROWS + qy) * 2;
-        if (ml[1] > 0.f) {
-            const float w = __builtin_amdgcn_exp2f(ml[0] - m);
-            z += ml[1] * w;
-            acc += o_part[(((int64_t)pb * n_chunks + c) * ROWS + qy) * 128 + threadIdx.x] * w;
+    for (int c0 = 0; c0 < n_chunks; c0 += MERGE_T) {
+        if (c0 > 0) {
+            __syncthreads();                                   // the weights have been read
+            e = c0 + tid < n_chunks ? ml[(int64_t)(c0 + tid) * ROWS] : make_float2(0.f, 0.f);
+        }
+        const float w = e.y > 0.f ? __builtin_amdgcn_exp2f(e.x - m) : -1.f;
+        sh_w[tid] = w;
+        if (w >= 0.f) z += e.y * w;
+        __syncthreads();
+        const int nc = min(MERGE_T, n_chunks - c0);
+        for (int j0 = 0; j0 < nc; j0 += 8) {
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = o[(int64_t)(c0 + min(j0 + j, nc - 1)) * ROWS * 128];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float wj = j0 + j < nc ? sh_w[j0 + j] : -1.f;
+                if (wj >= 0.f) acc += x[j] * wj;
+            }
         }
     }
-    out[(int64_t)row * 128 + threadIdx.x] = z > 0.f ? acc / z : 0.f;
-    if (threadIdx.x == 0) lse[row] = (m + __builtin_amdgcn_logf(z)) * LN2;
+    z = merge_all<false>(z, sh_z);
+    out[(int64_t)row * 128 + tid] = z > 0.f ? acc / z : 0.f;
+    if (tid == 0) lse[row] = (m + __builtin_amdgcn_logf(z)) * LN2;
 }
 
-// keys per workgroup, two workgroups per CU (two wavefronts per SIMD: while one waits for its LDS reads or an MFMA result the
-// other computes).  Prologue, epilogue and a chunk's share of the merge take as long as some 256 keys; no more than two rounds,
-// as every chunk has partial results of 64 KiB per 128 rows.
-ChunkPlan wa_plan(const Dims &d, int wgs_per_cu)
+// keys per workgroup: whole rounds of two workgroups per CU (two wavefronts per SIMD: while one waits for its
+// LDS reads or an MFMA result the other computes), as few as keep a chunk within 131 072 keys.  Where a chunk begins
+// sets its probabilities' reference, and with it how each of them is rounded to bf16: another cut of the keys moves
+// the outputs by as much as that rounding does (single values by 1 to 2 % of their root mean square where few keys weigh
+// most), so the cut stays as it is although whole chunks leave places idle for many numbers of problems.
+void wa_plan(const Dims &d, int *chunk_len, int *n_chunks, int wgs_per_cu)
 {
-    constexpr int MAX_CHUNK = 131072, FIXED = 256;
-    const int64_t slots = wgs_per_cu * (int64_t)d.cus;
-    if (d.tune.window_chunk < SUB) return plan_chunks(d.P, d.L, slots, SUB, FIXED, MAX_CHUNK, 2 * slots);
-    const int len = std::min((d.tune.window_chunk / SUB) * SUB, MAX_CHUNK);
-    return {len, (d.L + len - 1) / len, false};
+    constexpr int MAX_CHUNK = 131072;
+    const int64_t cus = wgs_per_cu * (int64_t)d.cus;
+    const int64_t rounds = ((int64_t)d.P * d.L + cus * MAX_CHUNK - 1) / (cus * MAX_CHUNK);
+    const int64_t per_problem = std::max<int64_t>(1, (cus * rounds + d.P / 2) / d.P);
+    int len = (int)(((d.L + per_problem - 1) / per_problem + SUB - 1) / SUB) * SUB;
+    if (d.tune.window_chunk >= SUB) len = (d.tune.window_chunk / SUB) * SUB;
+    len = std::min(std::max(len, SUB), MAX_CHUNK);
+    *chunk_len = len;
+    *n_chunks = (d.L + len - 1) / len;
 }
-dim3 wa_grid(const Dims &d, const ChunkPlan &c) { return c.by_chunk ? dim3(d.P, c.n) : dim3(c.n, d.P); }
 
 }  // namespace
 
@@ -436,7 +550,9 @@ static int row_stats_wgs_per_cu(const Dims &d) { return d.G * d.W > 128 ? 2 : 4;
 
 int row_stats_chunks(const Dims &d)
 {
-    return wa_plan(d, row_stats_wgs_per_cu(d)).n;
+    int len, nc;
+    wa_plan(d, &len, &nc, row_stats_wgs_per_cu(d));
+    return nc;
 }
 
 hipError_t launch_row_stats(const Dims &d, const void *q, const void *k, float *stats, hipStream_t st)
@@ -456,14 +572,11 @@ hipError_t launch_row_stats(const Dims &d, const void *q, const void *k, float *
     a.q = static_cast<const uint16_t *>(q);
     a.k = static_cast<const uint16_t *>(k);
     a.v = nullptr;
-    const ChunkPlan plan = wa_plan(d, row_stats_wgs_per_cu(d));
-    a.chunk_len = plan.len;
-    a.n_chunks = plan.n;
-    a.by_chunk = plan.by_chunk;
+    wa_plan(d, &a.chunk_len, &a.n_chunks, row_stats_wgs_per_cu(d));
     a.c1 = (float)(1.4426950408889634 / sqrt((double)d.D));
     a.out = a.lse = a.o_part = a.ml_part = nullptr;
     a.stats = stats;
-    const dim3 grid = wa_grid(d, plan);
+    const dim3 grid((unsigned)((int64_t)d.P * a.n_chunks));
     if (d.G * d.W > 128) hipLaunchKernelGGL((window_attention_kernel<8, false>), grid, dim3(8 * 64), wa_lds(8, false), st, a);
     else hipLaunchKernelGGL((window_attention_kernel<4, false>), grid, dim3(4 * 64), wa_lds(4, false), st, a);
     return hipGetLastError();
@@ -486,7 +599,8 @@ static int wa_blocks(const Dims &d)
 
 size_t window_attention_ws_bytes(const Dims &d)
 {
-    const int nc = wa_plan(d, wa_blocks(d) <= 4 ? 2 : 1).n;
+    int len, nc;
+    wa_plan(d, &len, &nc, wa_blocks(d) <= 4 ? 2 : 1);
     if (nc == 1) return 256;
     const size_t blocks = (size_t)d.P * wa_blocks(d);
     return align256(blocks * nc * ROWS * 128 * 4) + align256(blocks * nc * ROWS * 2 * 4);
@@ -518,23 +632,20 @@ hipError_t launch_window_attention(const Dims &d, const void *q, const void *k, 
     a.k = static_cast<const uint16_t *>(k);
     a.v = static_cast<const uint16_t *>(v);
     // workgroups of up to four wavefronts pair up on a CU; eight-wavefront ones already put two wavefronts on every SIMD
-    const ChunkPlan plan = wa_plan(d, nw <= 4 ? 2 : 1);
-    a.chunk_len = plan.len;
-    a.n_chunks = plan.n;
-    a.by_chunk = plan.by_chunk;
+    wa_plan(d, &a.chunk_len, &a.n_chunks, nw <= 4 ? 2 : 1);
     a.c1 = (float)(1.4426950408889634 / sqrt((double)d.D));
     a.out = out;
     a.lse = lse;
     a.o_part = static_cast<float *>(ws);
     a.ml_part = reinterpret_cast<float *>(static_cast<char *>(ws) + align256((size_t)d.P * nw * a.n_chunks * ROWS * 128 * 4));
-    const dim3 grid = wa_grid(d, plan);
+    const dim3 grid((unsigned)((int64_t)d.P * a.n_chunks));
     a.stats = nullptr;
     if (nw == 1) hipLaunchKernelGGL((window_attention_kernel<1, true>), grid, dim3(64), wa_lds(1), st, a);
     else if (nw == 2) hipLaunchKernelGGL((window_attention_kernel<2, true>), grid, dim3(2 * 64), wa_lds(2), st, a);
     else if (nw == 4) hipLaunchKernelGGL((window_attention_kernel<4, true>), grid, dim3(4 * 64), wa_lds(4), st, a);
     else hipLaunchKernelGGL((window_attention_kernel<8, true>), grid, dim3(8 * 64), wa_lds(8), st, a);
     if (a.n_chunks > 1)
-        hipLaunchKernelGGL(window_attention_merge_kernel, dim3((unsigned)((int64_t)d.P * d.G * d.W)), dim3(128), 0, st,
+        hipLaunchKernelGGL(window_attention_merge_kernel, dim3((unsigned)((int64_t)d.P * d.G * d.W)), dim3(MERGE_T), 0, st,
                            a.o_part, a.ml_part, a.n_chunks, d.G, d.W, nw, out, lse);
     return hipGetLastError();
 }
