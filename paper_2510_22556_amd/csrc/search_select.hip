@@ -1287,15 +1287,15 @@ __device__ inline uint32_t waves_before(uint32_t mine, RowShared<NTH> &sh)
 }
 
 // The scores that a workgroup looks at: held in registers (thread i: entries i + e * NTH of n), ...
-template <int NTH, bool TOK> struct HeldScores {
-    uint32_t key[RR_KEYS];
-    int tok[TOK ? RR_KEYS : 1];
+template <int NTH, int N, bool TOK> struct HeldScores {
+    uint32_t key[N];
+    int tok[TOK ? N : 1];
     int n;
     template <typename F>
     __device__ __forceinline__ void each(F &&f) const       // f(key, token), for what this thread holds
     {
 #pragma unroll
-        for (int e = 0; e < RR_KEYS; ++e) {
+        for (int e = 0; e < N; ++e) {
             const int i = (int)threadIdx.x + e * NTH;
             if (e * NTH < n && i < n) {            // the first is uniform
                 if constexpr (TOK) f(key[e], tok[e]);
@@ -1439,7 +1439,7 @@ struct RowLds {
     }
 };
 
-// grid (P).  What topb_kernel does, 0 < k = B < T, for rows of up to 16 * NTH tokens (LISTED: for longer ones, of which
+// grid (P).  What topb_kernel does, 0 < k = B < T, for rows of up to N * NTH tokens (LISTED: for longer ones, of which
 // other workgroups have listed the tokens above a bound; a list that is none, of fewer than k or more than there is room for,
 // leaves the row to be read again and again).
 //
@@ -1448,7 +1448,7 @@ struct RowLds {
 // jumped over; a token finds its segment by counting bits, and a segment with one token remembers it, so that the tokens
 // need no second look.  The kernel alone, 2 rows of 2 032 tokens 11.1 -> 7.2 us, 8 rows of 8 160 14.8 -> 10.4 against 1 024 threads
 // that list the tokens and look each segment up by halves; 8 rows of 131 040 from eight lists each 15.9 -> 12.6.
-template <bool PLAN, int NTH, bool LISTED>
+template <bool PLAN, int NTH, bool LISTED, int N = RR_KEYS>
 __global__ void __launch_bounds__(NTH, 4)
 row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView sv, int32_t *seg_budget, int32_t *block_size, PlanArgs pa,
                 Candidates cd, int most_segments)
@@ -1470,7 +1470,7 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
     int32_t o[4];                                  // the first offsets, on their way with the scores
 #pragma unroll
     for (int i = 0; i < 4; ++i) o[i] = K >= 0 ? seg_off[min(tid + i * NTH, K)] : 0;        // K < 0: there may be no offsets
-    HeldScores<NTH, LISTED> held;
+    HeldScores<NTH, N, LISTED> held;
     held.n = T;
     const int words = LISTED ? 0 : (T + 31) / 32;
     if constexpr (LISTED) {
@@ -1478,9 +1478,9 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
         const int n = lane < cd.n_slices ? cd.counts[(int64_t)p * cd.n_slices + lane] : 0;
         const int upto = (int)wave_scan_u((uint32_t)n);
         held.n = __any(n > cd.cap) ? 0 : __builtin_amdgcn_readlane(upto, 63);
-        if (held.n < k || held.n > RR_KEYS * NTH) held.n = 0;
+        if (held.n < k || held.n > N * NTH) held.n = 0;
 #pragma unroll
-        for (int e = 0; e < RR_KEYS; ++e) {
+        for (int e = 0; e < N; ++e) {
             if (e * NTH < held.n) {
                 const int i = tid + e * NTH;
                 int slice = 0, first = 0;          // of the entry
@@ -1497,14 +1497,14 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
             }
         }
     } else {
-        float v[RR_KEYS];
+        float v[N];
 #pragma unroll
-        for (int e = 0; e < RR_KEYS; ++e)
+        for (int e = 0; e < N; ++e)
             if (e * NTH < T) v[e] = sp[min(tid + e * NTH, T - 1)];
 #pragma nounroll
         for (int w = tid; w < words; w += NTH) bits[w] = 0u;
 #pragma unroll
-        for (int e = 0; e < RR_KEYS; ++e)
+        for (int e = 0; e < N; ++e)
             if (e * NTH < T) held.key[e] = ordered_key(v[e]);
     }
     if (tid == 0) sh.n_long = sh.long_at = 0;
@@ -1533,7 +1533,7 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
 
     // ---- implicit budgets: every Top-B token adds one to its segment, the last one that begins at or in front of it
     if (!LISTED) {
-        // words up to 512, so one of them per thread
+        static_assert(N <= 32, "a word per thread is enough");
         const uint32_t mine = tid < words ? (uint32_t)__popc(bits[tid]) : 0u, incl = wave_scan_u(mine);
         const uint32_t b = waves_before<NTH>(incl, sh) + incl - mine;
         if (tid < words) before[tid] = b;
@@ -1575,7 +1575,7 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
         });
     } else {
 #pragma unroll
-        for (int e0 = 0; e0 < RR_KEYS; e0 += 4) {
+        for (int e0 = 0; e0 < N; e0 += 4) {
             if (e0 * NTH < held.n) {               // uniform
                 int t[4];
                 bool in[4];
@@ -2232,18 +2232,18 @@ static bool row_rank_fits(bool listed, int nth, const Dims &d, int32_t budget, i
     return budget > 0 && budget < d.T && segments < 65536 && RowLds(listed, nth, d.T, segments).bytes <= RR_LDS_MOST;
 }
 
-template <bool PLAN, int NTH, bool LISTED>
+template <bool PLAN, int NTH, bool LISTED, int N = RR_KEYS>
 static hipError_t run_row_rank(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
                                int32_t *block_size, const PlanArgs &pa, const Candidates &cd, int segments, hipStream_t st)
 {
     static thread_local PerDeviceOnce attr_once;
     if (attr_once.needed()) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(row_rank_kernel<PLAN, NTH, LISTED>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(row_rank_kernel<PLAN, NTH, LISTED, N>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, RR_LDS_MOST);
         if (e != hipSuccess) return e;
         attr_once.done();
     }
-    hipLaunchKernelGGL((row_rank_kernel<PLAN, NTH, LISTED>), dim3(d.P), dim3(NTH), RowLds(LISTED, NTH, d.T, segments).bytes, st, d,
+    hipLaunchKernelGGL((row_rank_kernel<PLAN, NTH, LISTED, N>), dim3(d.P), dim3(NTH), RowLds(LISTED, NTH, d.T, segments).bytes, st, d,
                        s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments);
     return hipGetLastError();
 }
@@ -2252,9 +2252,12 @@ template <bool PLAN>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
                            int32_t *block_size, const PlanArgs &pa, hipStream_t st)
 {
+    // (more rows than CUs, of more than 8 192 tokens: half the threads with twice the scores, so that two workgroups share a CU;
+    // 1 024 rows of 16 000 tokens, 992 retained, Top-B and search 220 us, with 1 024 threads 244)
     const int nth = d.T <= 256 * RR_KEYS ? 256 : d.T <= 512 * RR_KEYS ? 512 : 1024, segments = most_segments(d, sv);
     if (d.T <= 1024 * RR_KEYS && row_rank_fits(false, nth, d, budget, segments)) {
-        const auto run = nth == 256 ? run_row_rank<PLAN, 256, false> : nth == 512 ? run_row_rank<PLAN, 512, false> : run_row_rank<PLAN, 1024, false>;
+        const auto run = nth == 256 ? run_row_rank<PLAN, 256, false> : nth == 512 ? run_row_rank<PLAN, 512, false> :
+                         d.P <= d.cus ? run_row_rank<PLAN, 1024, false> : run_row_rank<PLAN, 512, false, 2 * RR_KEYS>;
         return run(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, Candidates{}, segments, st);
     }
     const bool two = d.P > d.cus;
@@ -2302,7 +2305,11 @@ static void run_search(const Dims &d, const float *s_tilde, const SegView &sv, c
                        int32_t *block_size, int32_t budget, int32_t *idx_out, hipStream_t st)
 {
     // wavefronts per problem: one per possible record up to 128 per CU (24 are resident at once), striding over the records
-    const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)d.cus * 128 / d.P));
+    unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cap, (int64_t)d.cus * 128 / d.P));
+    // ... an odd number of them: segments are the same for all problems of a sequence and stand in the same order in their lists,
+    // and an XCD, which gets every eighth workgroup, would else get the same eighth of them of every problem (1 024 rows of 16 000
+    // tokens, 4 000 retained, Top-B and search: 894 us with 32 wavefronts per problem, 574 with 31)
+    if (gx > 1 && gx < (unsigned)cap) gx -= 1 - gx % 2;
     hipLaunchKernelGGL(search_kernel<EMIT>, parts_grid(d, gx), dim3(64), 0, st, d, s_tilde, sv.max_segments, cand, tau, w.list,
                        w.counts, cap, block_size, budget, idx_out);
 }
