@@ -79,11 +79,12 @@ typedef struct {
     int32_t compute_units;    /* compute units the launch plans assume; 0 = ask the current device (DEVICE error
                                  if there is none: set it to size a workspace on a host without a GPU) */
     int32_t score_chunk;      /* keys per workgroup of the MFMA scoring kernels, >= 128, rounded down to a multiple
-                                 of 128; 0 = whole rounds of one workgroup per compute unit */
+                                 of 128; 0 = whole rounds of workgroups, or equal chunks with the remainders of
+                                 the rows in chunks of their own, by the number of problems and the length */
     int32_t window_chunk;     /* keys per workgroup of sablock_window_attention and of the one-read row statistics,
                                  >= 32, rounded down to a multiple of 32; 0 = whole rounds of workgroups */
     int32_t topb_slices;      /* workgroups per row of the Top-B pass over the rows of sablock_search_select, 1 .. 64
-                                 (1 = the per-row kernel alone); 0 = by row length and problems per compute unit */
+                                 (1 = one workgroup per row); 0 = by row length and problems per compute unit */
     int32_t stats_per_key;    /* which kernel forms the row statistics where two exist (head_dim 128; 129 .. 256
                                  window-query rows per KV head, and G = 4 with W = 32): 1 = the kernel with a lane per
                                  key, 2 = the kernel with a lane per window query; 0 = the faster one by measurement (1) */
