@@ -81,13 +81,13 @@ __device__ __forceinline__ float other_half(float x, bool take_max)
     return take_max ? fmaxf(a, b) : a + b;
 }
 
+// Through operations that the compiler knows: it puts the wait states between a matrix product and the first read of its result,
+// and not in front of inline assembly.  Three at a time, v_maximum3_f32; a logit that is not a number is the largest (a comparison
+// with it is false: the reference of its query, whose sum is no number either, stays).
 __device__ __forceinline__ float largest(const floatx16 &acc)
 {
-    // three at a time; as fmaxf, which takes another instruction per operand, it prefers a number
     auto max3 = [](float x, float y, float z) __attribute__((always_inline)) {
-        float m;
-        asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(x), "v"(y), "v"(z));
-        return m;
+        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z);
     };
     float m[5];
 #pragma unroll

@@ -1379,6 +1379,60 @@ def test_window_attention_and_its_row_lse_feed_the_scoring(oracle, torch_cuda, G
     np.testing.assert_allclose(H.to_np(buf.ent), e0, rtol=1e-4, atol=1e-6)
 
 
+@pytest.mark.parametrize("G,W", [(4, 8), (2, 32), (4, 32), (8, 32)])
+@pytest.mark.parametrize("chunk", [992, 1024])
+def test_window_attention_s_reference_moves_for_logits_of_the_last_elements(oracle, torch_cuda, G, W, chunk):  # noqa: F811
+    # Keys that are far ahead by elements 112 .. 127 alone, the last step of the matrix product over a head's elements: by 150 and
+    # more in the log2 domain, so that exp2 overflows wherever the reference stays.  Sixteen queries have one of these elements each,
+    # all others none, so a key is ahead for one query only.  1, 2, 4 and 8 wavefronts; chunks of an odd and an even number of
+    # 32-key subtiles: the first subtile, the entry to the steady state, odd and even ones in it, two and three in a row, its last
+    # ones and the step behind it, in the first chunk and in a later one.
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    Hkv, D, L = 1, 128, 2 * chunk + 300 + W
+    q = synth.normal_torch(77, 1, (1, 1, G * Hkv, W, D), "cuda", torch.bfloat16)
+    k = synth.normal_torch(77, 2, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    v = synth.normal_torch(77, 3, (1, 1, Hkv, L, D), "cuda", torch.bfloat16)
+    n = chunk // 32
+    plans = [(0,), (1,), (2,), (3,), (8, 9), (9, 10), (1, 2, 3), (n - 6, n - 5), (n - 5, n - 4), (n - 4, n - 3, n - 2), (n - 1,),
+             (0, 1, n - 1), (4, 12, 20), (n + 1, n + 8), (n + 2, n + 3), (2 * n - 5, 2 * n + 2)]
+    rows = q.view(G * W, D)
+    rows[:, 112:] = 0
+    k[..., 112:] = 0
+    top = {}
+    for j, subtiles in enumerate(plans):
+        row = j * (G * W // 16) + j % (G * W // 16)
+        rows[row, 112 + j] = 4.0
+        for step, u in enumerate(subtiles):
+            t = 32 * u + (5 * j + 11 * step) % 32
+            assert t < L - W
+            k[0, 0, 0, t, 112 + j] = 320.0 * (step + 1)        # 4 * 320 * log2(e) / sqrt(128) = 163
+            top[row] = t
+    shape = B.make_shape(q, k, v, window_chunk=chunk)
+    out = torch.full((G * W, D), float("nan"), dtype=torch.float32, device="cuda")
+    lse = torch.full((1, G * W), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty((B.sablock_window_attention_workspace_bytes(shape),), dtype=torch.uint8, device="cuda")
+    B.sablock_window_attention(shape, q, k, v, out, lse, ws)
+    torch.cuda.synchronize()
+    q_np, k_np, v_np = H.widen(H.to_np(q[0, 0])), H.widen(H.to_np(k[0, 0, 0])), H.widen(H.to_np(v[0, 0, 0]))
+    o_ref, l_ref = oracle.window_attention(q_np, k_np, v_np)
+    out_g = H.to_np(out)
+    # logits to 340 in fp32: 2^-24 of them twice over; probabilities are rounded to bf16, 2^-9 each
+    np.testing.assert_allclose(H.to_np(lse).reshape(G, W), l_ref, rtol=2.0 ** -22, atol=2e-5)
+    np.testing.assert_allclose(out_g, o_ref.reshape(G * W, D), rtol=0, atol=4e-3 * np.abs(v_np).max())
+    for row, t in top.items():                                 # the last planted key is all there is: its value row
+        np.testing.assert_allclose(out_g[row], v_np[t], rtol=0, atol=1e-6)
+    if G * W == 256 or (G, W) == (4, 32):                      # the statistics by the same kernel without V
+        seg = B.make_segments(np.array([0, L - W], dtype=np.int32), [0, 2], "cuda")
+        s_ref, e_ref = oracle.score(q_np, k_np, 1e-6)
+        per_query = B.make_shape(q, k, v, window_chunk=chunk, stats_per_key=2)
+        buf = B.Buffers(per_query, seg, 16, "cuda")
+        B.sablock_score(per_query, q, k, buf.s, buf.ent, buf.ws, 1e-6)
+        H.close(H.to_np(buf.s)[0], s_ref, "s")
+        H.close(H.to_np(buf.ent)[0], e_ref, "ent")
+
+
 def test_signed_zero_scores_rank_as_equal(oracle, torch_cuda):
     # -0.0 and +0.0 compare equal, so among zero scores the index decides: a row of zeros of both signs must give
     # the same Top-B set, budgets and selection as the same row with every zero positive, and as the oracle

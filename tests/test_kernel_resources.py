@@ -9,12 +9,16 @@ import pytest
 from paper_2510_22556_amd import build
 
 
-def _kernels(source, folder):
+def _assembly(source, folder):
     asm = str(folder / "kernels.s")
     subprocess.run([build.HIPCC, *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, source), "-o", asm], check=True,
                    stderr=subprocess.DEVNULL)
     with open(asm) as f:
-        text = f.read()
+        return f.read()
+
+
+def _kernels(source, folder):
+    text = _assembly(source, folder)
     blocks = re.findall(r"\.amdhsa_kernel (\S+)\n(.*?)\.end_amdhsa_kernel", text, re.S)
     return {name: {k: int(v) for k, v in re.findall(r"\.amdhsa_(\w+) (\d+)\n", body)} for name, body in blocks}
 
@@ -38,6 +42,15 @@ def test_topb_and_search_kernels_do_not_spill(search_select_kernels):
     assert len(two) == 4
     assert all(scratch[n] <= 16 for n in two), scratch
     assert not any(scratch[n] for n in set(scratch) - two), scratch
+
+
+def test_inline_assembly_of_the_window_attention_reads_no_matrix_result(tmp_path):
+    # the compiler puts wait states between a matrix product and an instruction of its own that reads the result, but does not
+    # look into inline assembly: there, vector registers hold addresses only
+    text = _assembly("window_attn.hip", tmp_path)
+    assert "v_mfma_f32_32x32x16_bf16" in text
+    inline = set(re.findall(r"^\s+([a-z]\w+)", "\n".join(re.findall(r";;?#ASMSTART\n(.*?);;?#ASMEND", text, re.S)), re.M))
+    assert inline == {"s_mov_b32", "s_nop", "s_waitcnt", "s_barrier", "global_load_lds_dwordx4", "ds_read_b128"}
 
 
 def test_any_shape_scoring_plans_as_many_workgroups_as_the_registers_let_reside(tmp_path):
