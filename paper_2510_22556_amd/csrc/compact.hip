@@ -64,8 +64,9 @@ hipError_t launch_compact(const Dims &d, const void *k, const void *v, const int
     const int chunks = d.D * elt / 16;
     if (rows <= 0 || d.P <= 0) return hipSuccess;
     const int r4 = (rows + RPT - 1) / RPT;
-    const dim3 grid = parts_grid(d, (unsigned)(((int64_t)r4 * chunks + NT - 1) / NT), 2);
-    hipLaunchKernelGGL(compact_kernel, grid, dim3(NT), 0, st, d, static_cast<const char *>(k),
+    Dims o = d;
+    const dim3 grid = parts_grid(o, (unsigned)(((int64_t)r4 * chunks + NT - 1) / NT), 2);
+    hipLaunchKernelGGL(compact_kernel, grid, dim3(NT), 0, st, o, static_cast<const char *>(k),
                        static_cast<const char *>(v), idx, n_sel, budget, rows, chunks, elt,
                        static_cast<char *>(k_out), static_cast<char *>(v_out), shared_rows ? d.Hkv : 1);
     return hipGetLastError();

@@ -104,8 +104,9 @@ hipError_t launch_refine(const Dims &d, const float *s, const float *ent, const 
                          sablock_hparams hp, float *s_tilde, float *omega, hipStream_t st)
 {
     if (sv.max_segments <= 0 || d.P <= 0) return hipSuccess;
-    const dim3 grid = parts_grid(d, (sv.max_segments + RSEG - 1) / RSEG);
-    hipLaunchKernelGGL(refine_kernel, grid, dim3(NT), 0, st, d, s, ent, sv, hp, s_tilde, omega);
+    Dims o = d;
+    const dim3 grid = parts_grid(o, (unsigned)(((int64_t)sv.max_segments + RSEG - 1) / RSEG));
+    hipLaunchKernelGGL(refine_kernel, grid, dim3(NT), 0, st, o, s, ent, sv, hp, s_tilde, omega);
     return hipGetLastError();
 }
 

@@ -70,7 +70,14 @@ __host__ __device__ inline int32_t layer_of_problem(const Dims &d, int32_t p)
 // cache of 4 MiB; where what the steps hand on to each other (12 bytes per key) fits these caches, the problems come first, so that
 // with 8 problems, a layer of most models, every step finds what the one before it wrote in its own XCD's cache.  With more data
 // nothing is left of it, and neighbouring workgroups had better read neighbouring memory.
-__host__ inline dim3 parts_grid(const Dims &d, unsigned parts, unsigned z = 1) { return d.local ? dim3(d.P, parts, z) : dim3(parts, d.P, z); }
+// A grid's second axis has 65 535 places: problems always fit it (make_dims), parts that do not come first.  Clears d.local for them:
+// the kernel gets the same d.
+constexpr unsigned GRID_Y_MOST = 65535;
+__host__ inline dim3 parts_grid(Dims &d, unsigned parts, unsigned z = 1)
+{
+    if (parts > GRID_Y_MOST) d.local = 0;
+    return d.local ? dim3(d.P, parts, z) : dim3(parts, d.P, z);
+}
 __device__ __forceinline__ int grid_problem(const Dims &d) { return d.local ? blockIdx.x : blockIdx.y; }
 __device__ __forceinline__ int grid_part(const Dims &d) { return d.local ? blockIdx.y : blockIdx.x; }
 __device__ __forceinline__ int grid_parts(const Dims &d) { return d.local ? gridDim.y : gridDim.x; }

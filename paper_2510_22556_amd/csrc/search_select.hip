@@ -2310,7 +2310,9 @@ static void run_search(const Dims &d, const float *s_tilde, const SegView &sv, c
     // and an XCD, which gets every eighth workgroup, would else get the same eighth of them of every problem (1 024 rows of 16 000
     // tokens, 4 000 retained, Top-B and search: 894 us with 32 wavefronts per problem, 574 with 31)
     if (gx > 1 && gx < (unsigned)cap) gx -= 1 - gx % 2;
-    hipLaunchKernelGGL(search_kernel<EMIT>, parts_grid(d, gx), dim3(64), 0, st, d, s_tilde, sv.max_segments, cand, tau, w.list,
+    Dims o = d;
+    const dim3 grid = parts_grid(o, gx);
+    hipLaunchKernelGGL(search_kernel<EMIT>, grid, dim3(64), 0, st, o, s_tilde, sv.max_segments, cand, tau, w.list,
                        w.counts, cap, block_size, budget, idx_out);
 }
 
@@ -2442,7 +2444,9 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
         int32_t *counts = reinterpret_cast<int32_t *>(x);
         uint2 *entries = reinterpret_cast<uint2 *>(x + align256((size_t)d.P * n_slices * 4));
         const int pre_cap = topb_list_k(d, budget) * TB_THREADS;
-        hipLaunchKernelGGL(topb_collect_kernel, parts_grid(d, n_slices), dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, d, s_tilde,
+        Dims o = d;
+        const dim3 grid = parts_grid(o, n_slices);
+        hipLaunchKernelGGL(topb_collect_kernel, grid, dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, o, s_tilde,
                            topb_rank(d, budget), pre_cap, entries, counts);
         const Candidates cd{entries, counts, n_slices, pre_cap};
         e = run_row_rank<true, 512, true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments, st);

@@ -1379,6 +1379,38 @@ def test_window_attention_and_its_row_lse_feed_the_scoring(oracle, torch_cuda, G
     np.testing.assert_allclose(H.to_np(buf.ent), e0, rtol=1e-4, atol=1e-6)
 
 
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_more_parts_than_a_grid_s_second_axis_has_places(oracle, torch_cuda, beyond):  # noqa: F811
+    # refinement and compaction of a few thousand tokens with rows of segments, and of retained tokens, so wide that their workgroups
+    # fill the axis, and one more: 16 segments and, of fp32 rows of 256, 16 retained rows each
+    torch = torch_cuda
+    from paper_2510_22556_amd import binding as B
+
+    W, D, L, budget = 8, 256, 3000, 200
+    wide = 16 * 65535 + beyond
+    q = synth.normal_torch(5, 1, (1, 1, 2, W, D), "cuda", torch.float32)
+    k, v = (synth.normal_torch(5, i, (1, 1, 1, L, D), "cuda", torch.float32) for i in (2, 3))
+    off = synth.segment_offsets(5, L - W, mean=20.0, min_len=1, max_len=120)
+    shape = B.make_shape(q, k, v)
+    seg = B.make_segments(off, [0, len(off)], "cuda")
+    seg.max_segments = wide
+    s, ent = (synth.normal_torch(5, i, (1, L), "cuda", torch.float32).abs() for i in (4, 5))
+    st = torch.full((1, L - W), float("nan"), device="cuda")
+    omega = torch.full((1, wide), float("nan"), device="cuda")
+    ws = torch.empty((B.sablock_workspace_bytes(shape, wide, budget),), dtype=torch.uint8, device="cuda")
+    B.sablock_refine(shape, s, ent, seg, st, ws, omega_out=omega)
+    st_ref, om_ref = oracle.refine(H.to_np(s)[0], H.to_np(ent)[0], off, H.f32(0.9), 1.0)
+    np.testing.assert_allclose(H.to_np(st)[0], st_ref, rtol=3e-7, atol=0)
+    np.testing.assert_allclose(H.to_np(omega[0, :len(off) - 1]), om_ref, rtol=3e-7)
+    assert not bool(omega[0, len(off) - 1:].any())
+    idx = torch.arange(0, 2 * budget, 2, dtype=torch.int32, device="cuda")
+    rows = torch.cat([idx, torch.full((wide - budget,), -1, dtype=torch.int32, device="cuda")])
+    k_out, v_out = (torch.full((1, wide, D), float("nan"), device="cuda") for _ in range(2))
+    B.sablock_compact(shape, k, v, rows, torch.tensor([budget], dtype=torch.int32, device="cuda"), wide, False, k_out, v_out)
+    for o, x in ((k_out, k), (v_out, v)):
+        assert torch.equal(o[0, :budget], x[0, 0, 0, :2 * budget:2]) and not bool(o[0, budget:].any())
+
+
 @pytest.mark.parametrize("G,W", [(4, 8), (2, 32), (4, 32), (8, 32)])
 @pytest.mark.parametrize("chunk", [992, 1024])
 def test_window_attention_s_reference_moves_for_logits_of_the_last_elements(oracle, torch_cuda, G, W, chunk):  # noqa: F811

@@ -4,6 +4,7 @@ and rejects bad host arguments before anything is enqueued (no GPU needed)."""
 import ctypes
 import os
 import re
+import subprocess
 import sys
 
 import numpy as np
@@ -55,6 +56,34 @@ def test_struct_layout_matches_header():
     body = re.search(r"typedef struct \{([^}]*)\} sablock_tuning;", hdr).group(1)
     fields = re.findall(r"int32_t\s+(\w+)", body)
     assert fields == [f[0] for f in B.CTuning._fields_]
+
+
+def test_grids_of_parts_stay_within_the_places_of_their_axes(tmp_path):
+    # few keys, so the problems would come first: not where the parts are more than a grid's second axis takes
+    from paper_2510_22556_amd import build
+
+    src, exe = tmp_path / "grids.hip", tmp_path / "grids"
+    src.write_text("""
+#include "sablock_internal.h"
+#include <cstdio>
+int main()
+{
+    for (unsigned parts : {1u, 65535u, 65536u, 4000000u})
+        for (int local : {0, 1}) {
+            sablock::Dims d{};
+            d.P = 3;
+            d.local = local;
+            const dim3 g = sablock::parts_grid(d, parts, 2);
+            std::printf("%u %d %u %u %u %d\\n", parts, local, g.x, g.y, g.z, d.local);
+        }
+}
+""")
+    subprocess.run([build.HIPCC, "-std=c++17", "--offload-host-only", "-I", build.CSRC, "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)],
+                   check=True)
+    for line in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines():
+        parts, local, x, y, z, first = map(int, line.split())
+        problems_first = bool(local) and parts <= 65535
+        assert (x, y, z, bool(first)) == ((3, parts) if problems_first else (parts, 3)) + (2, problems_first)
 
 
 def test_workspace_bytes_and_shape_validation(lib):
