@@ -365,11 +365,11 @@ sablock_status sablock_search_select(const sablock_shape *shape, const float *s_
     SegView sv;
     st = make_segview(d, seg_off, seg_ptr, max_segments, &sv);
     if (st != SABLOCK_OK) return st;
-    const size_t need = search_select_ws_least(d, max_segments, budget);
+    const size_t need = search_select_ws_bytes(d, max_segments, budget);
     if (!ws || ws_bytes < need)
         return fail(SABLOCK_ERR_WORKSPACE_TOO_SMALL, "sablock_search_select: workspace %zu < %zu bytes", ws_bytes, need);
     return dev(launch_search_select(d, s_tilde, sv, cl, budget, tau, seg_budget_out, block_size_out, topb_out, idx_out,
-                                    n_sel_out, ws, ws_bytes, static_cast<hipStream_t>(stream)), "sablock_search_select");
+                                    n_sel_out, ws, static_cast<hipStream_t>(stream)), "sablock_search_select");
 }
 
 sablock_status sablock_compact(const sablock_shape *shape, const void *k, const void *v,

@@ -198,10 +198,9 @@ hipError_t launch_select(const Dims &d, const float *s_tilde, const SegView &sv,
 // output rows and the search kernel writes the selected tokens, so no select kernel runs
 bool search_select_fused(const Dims &d, const SegView &sv, int32_t budget);
 size_t search_select_ws_bytes(const Dims &d, int32_t max_segments, int32_t budget);
-size_t search_select_ws_least(const Dims &d, int32_t max_segments, int32_t budget);      // what a call needs at least
 hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand,
                                 int32_t budget, float tau, int32_t *seg_budget, int32_t *block_size, int32_t *topb_out,
-                                int32_t *idx_out, int32_t *n_sel_out, void *ws, size_t ws_bytes, hipStream_t st);
+                                int32_t *idx_out, int32_t *n_sel_out, void *ws, hipStream_t st);
 
 hipError_t launch_compact(const Dims &d, const void *k, const void *v, const int32_t *idx,
                           const int32_t *n_sel, int32_t budget, int32_t append_window,

@@ -2409,19 +2409,19 @@ static size_t sliced_bytes(const Dims &d, int32_t budget)
     return align256(n * 4) + align256(n * topb_list_k(d, budget) * TB_THREADS * sizeof(uint2));
 }
 
-// without the room for the slices' lists, which a call does without if it has to
-size_t search_select_ws_least(const Dims &d, int32_t max_segments, int32_t budget)
+// The slices' lists lie behind the larger of the search and select layouts.
+static size_t sliced_offset(const Dims &d, int32_t max_segments, int32_t budget)
 {
     return std::max(search_ws_bytes(d, max_segments, budget), select_ws_bytes(d, max_segments, budget));
 }
 size_t search_select_ws_bytes(const Dims &d, int32_t max_segments, int32_t budget)
 {
-    return search_select_ws_least(d, max_segments, budget) + (topb_slices(d, budget) > 1 ? sliced_bytes(d, budget) : 0);
+    return sliced_offset(d, max_segments, budget) + (topb_slices(d, budget) > 1 ? sliced_bytes(d, budget) : 0);
 }
 
 hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegView &sv, const CandList &cand,
                                 int32_t budget, float tau, int32_t *seg_budget, int32_t *block_size, int32_t *topb_out,
-                                int32_t *idx_out, int32_t *n_sel_out, void *ws, size_t ws_bytes, hipStream_t st)
+                                int32_t *idx_out, int32_t *n_sel_out, void *ws, hipStream_t st)
 {
     if (d.P <= 0) return hipSuccess;
     if (!search_select_fused(d, sv, budget)) {
@@ -2438,9 +2438,8 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
     const PlanArgs pa{w.list, w.counts, cap, idx_out, n_sel_out};
     hipError_t e;
     const int n_slices = topb_slices(d, budget), segments = most_segments(d, sv);
-    if (n_slices > 1 && row_rank_fits(true, 512, d, budget, segments) && ws_bytes >= search_select_ws_bytes(d, sv.max_segments, budget)) {
-        // behind the larger of the search and select layouts
-        char *x = static_cast<char *>(ws) + search_select_ws_least(d, sv.max_segments, budget);
+    if (n_slices > 1 && row_rank_fits(true, 512, d, budget, segments)) {
+        char *x = static_cast<char *>(ws) + sliced_offset(d, sv.max_segments, budget);
         int32_t *counts = reinterpret_cast<int32_t *>(x);
         uint2 *entries = reinterpret_cast<uint2 *>(x + align256((size_t)d.P * n_slices * 4));
         const int pre_cap = topb_list_k(d, budget) * TB_THREADS;

@@ -122,7 +122,12 @@ def test_launch_parameters_are_validated_and_change_only_the_plan(lib):
     few = B.sablock_workspace_bytes(shape(**llama), 0, 0)
     assert B.sablock_workspace_bytes(shape(**llama, score_chunk=1024), 0, 0) > few
     assert B.sablock_workspace_bytes(shape(**llama, compute_units=4096), 0, 0) > few
-    assert B.sablock_workspace_bytes(shape(**llama, topb_slices=1), 2100, 992) < base      # no sliced Top-B lists
+    plain = B.sablock_workspace_bytes(shape(**llama, topb_slices=1), 2100, 992)
+    assert plain < base                                                                    # no sliced Top-B lists
+    fake, ptr, cand = ctypes.c_void_p(0x1000), (ctypes.c_int32 * 2)(0, 2101), (ctypes.c_int32 * 2)(1, 2)
+    for nbytes in (plain, base - 257):      # (256 bytes are to spare) room for everything but those: too small (refused before anything is launched)
+        assert lib.sablock_search_select(ctypes.byref(shape(**llama)), fake, fake, ptr, 2100, cand, 2, 992, 0.85, fake, fake, None, fake, fake,
+                                         fake, nbytes, None) == 3
     # the row statistics take room for the rows that there are, and a kernel's own layout only where that kernel is asked for
     rows = {(G, kernel): B.sablock_workspace_bytes(shape(**{**llama, "n_q_heads": 8 * G}, score_chunk=512, window_chunk=32, stats_per_key=kernel),
                                                    0, 0) - 256 for G in (5, 8) for kernel in (0, 2)}
