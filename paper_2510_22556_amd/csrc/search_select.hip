@@ -3,7 +3,8 @@
 //
 // row_rank_kernel, topb_kernel  one workgroup per problem: the min(B,T)-th best score of
 //                 the row, ties resolved by ascending index (rows of up to 16 384 tokens,
-//                 and longer ones whose better tokens are listed; the others).
+//                 and longer ones whose better tokens are listed, of not too many segments;
+//                 the others).
 //                 Result: (ordered key v, index cut c); token t is in T_topB iff
 //                 key(t) > v or (key(t) == v and t <= c).  Its last phase counts
 //                 the Top-B tokens of every segment: the implicit budgets b_k.
@@ -1670,8 +1671,8 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
 // 131 040: 77 -> 46 us (134 MB, 2.9 TB/s with the sample); 1 024 rows of 65 472: 402 -> 111 us; 8 rows of 8 160, where
 // the chain of barriers is all there is: 18.6 -> 15.4 us.
 //
-// A row of up to TB_ROUND tokens is held in registers and its k-th best found there (kth_best).  Of a longer row a
-// sample gives a lower bound first, ONE pass over the row lists the tokens that reach it (somewhat more than k), and the
+// A row of up to TB_ROUND tokens (those of many segments, see row_rank_for) is held in registers and its k-th best found there
+// (kth_best).  Of a longer row a sample gives a lower bound first, ONE pass over the row lists the tokens that reach it (somewhat more than k), and the
 // k-th best is found among those.  E * 1024 tokens fit the list; when they do not (many equal scores, a sample that
 // misled), three histogram passes over the row (11 + 11 + 10 bits) and one to cut the ties by ascending index decide.
 //
@@ -1686,7 +1687,7 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
 template <bool PLAN, int E, bool TWO>
 __global__ void __launch_bounds__(TB_THREADS, TWO ? 8 : 4)
 topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView sv, int32_t *seg_budget,
-            int32_t *block_size, PlanArgs pa, int offs_cap, int sample_rank)
+            int32_t *block_size, PlanArgs pa, Candidates cd, int offs_cap, int sample_rank)
 {
     constexpr int CAP = E * TB_THREADS;          // tokens the list holds
     extern __shared__ __attribute__((aligned(16))) uint32_t sh_dyn[];   // histogram [TB_BINS] and list [CAP]; later offsets and counters [2][offs_cap]
@@ -1718,13 +1719,55 @@ topb_kernel(Dims d, const float *s_tilde, int budget, int32_t *thr_out, SegView 
         thr = 0xFFFFFFFFu;                       // nothing is inside
         cut = -1;
     } else if (k < T) {
+        const bool sliced = PLAN && cd.n_slices > 0;
         bool found = false;
-        if (T > TB_ROUND && k <= CAP) {
+        if (!sliced && r.nvec <= TB_ROUND / 4) {
+            // ---- the whole row in registers
+            constexpr int J = TB_REG / 4;
+            float4 v[J];
+            int t0[J];
+            uint32_t valid = 0;
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                const int i = j * TB_THREADS + tid;
+                v[j] = r.nvec > 0 ? r.vp[min(i, r.nvec - 1)] : make_float4(0.f, 0.f, 0.f, 0.f);
+                t0[j] = i < r.nvec ? r.token(i) : -4;
+                if (i < r.nvec) valid |= 15u << (4 * j);
+            }
+            const float ve = r.extra >= 0 ? r.sp[r.extra] : 0.f;
+            if (r.extra >= 0) valid |= 1u << TB_REG;
+            uint32_t key[TB_REG + 1];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                key[4 * j] = ordered_key(v[j].x); key[4 * j + 1] = ordered_key(v[j].y);
+                key[4 * j + 2] = ordered_key(v[j].z); key[4 * j + 3] = ordered_key(v[j].w);
+            }
+            key[TB_REG] = ordered_key(ve);
+            found = kth_best<TB_REG + 1>(key, valid, [&](int e) { return e == TB_REG ? r.extra : t0[e >> 2] + (e & 3); }, k, T, hist,
+                                         sh, thr, cut);
+            if (found && k <= CAP && seg_budget) {
+                append_tokens<J>(v, t0, [&](int t, float x) { return t >= 0 && in_topb(x, t, thr, cut); }, list, CAP, sh);
+                append_extra(r, r.extra >= 0 && in_topb(ve, r.extra, thr, cut), list, CAP, sh);
+                hits_from_list();                // exactly k of them
+            }
+        } else if (k <= CAP) {
             // ---- the tokens that reach a lower bound of the k-th best
-            const float bound = sample_bound(r, sample_rank, hist, sh);
-            __syncthreads();                     // the list's length is zero
-            collect_above(r, 0, r.nvec, bound, list, CAP, sh);
-            append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, CAP, sh);
+            if (sliced) {
+                int base = 0;
+                for (int sl = 0; sl < cd.n_slices; ++sl) {
+                    const int64_t o = (int64_t)p * cd.n_slices + sl;
+                    const int n = cd.counts[o];
+                    if (n > cd.cap || base + n > CAP) { base = CAP + 1; break; }
+                    for (int i = tid; i < n; i += TB_THREADS) list[base + i] = (int)cd.entries[o * cd.cap + i].y;
+                    base += n;
+                }
+                if (tid == 0) sh.n = base;
+            } else {
+                const float bound = sample_bound(r, sample_rank, hist, sh);
+                __syncthreads();                 // the list's length is zero
+                collect_above(r, 0, r.nvec, bound, list, CAP, sh);
+                append_extra(r, r.extra >= 0 && !(r.sp[max(r.extra, 0)] < bound), list, CAP, sh);
+            }
             __syncthreads();
             const int n = sh.n;
             if (n >= k && n <= CAP) {
@@ -2200,7 +2243,8 @@ static int topb_offs_cap(int32_t max_segments)
 
 template <bool PLAN, int E, bool TWO>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
-                           int32_t *block_size, const PlanArgs &pa, hipStream_t st)
+                           int32_t *block_size, const PlanArgs &pa, const Candidates &cd,
+                           hipStream_t st)
 {
     const int offs_cap = PLAN || seg_budget ? topb_offs_cap(sv.max_segments) : 0;
     const size_t lds = std::max((size_t)(TB_BINS + E * TB_THREADS) * 4, (size_t)offs_cap * 8);
@@ -2215,21 +2259,29 @@ static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, 
         }
     }
     hipLaunchKernelGGL((topb_kernel<PLAN, E, TWO>), dim3(d.P), dim3(TB_THREADS), lds, st, d, s_tilde, budget, thr, sv, seg_budget,
-                       block_size, pa, offs_cap, topb_rank(d, std::min(budget, d.T)));
+                       block_size, pa, cd, offs_cap, topb_rank(d, std::min(budget, d.T)));
     return hipGetLastError();
 }
 
-// ---- launches of row_rank_kernel: rows of up to 16 384 tokens and listed ones, but for all or nothing inside and more segments
-// than LDS has room for (11 000 to 12 000)
+// ---- launches of row_rank_kernel: rows of up to 16 384 tokens and listed ones, but for all or nothing inside and too many segments
 static int most_segments(const Dims &d, const SegView &sv)
 {
     int n = 0;
     for (int s = 0; s < d.n_seq; ++s) n = std::max(n, sv.seq_ptr[s + 1] - sv.seq_ptr[s] - 1);
     return n;
 }
-static bool row_rank_fits(bool listed, int nth, const Dims &d, int32_t budget, int segments)
+// Where segments have hardly two tokens, the bits of neighbours meet in the same words and three words of LDS per segment cost more than
+// topb_kernel's two or none; and rows that are more than the compute units have to leave room for two workgroups on each.  Search and
+// selection of 8, 256 and 1 024 rows: 8 160 tokens of mean length 1.3, 22.6, 31.2 and 97.7 us, topb_kernel 20.3, 30.7 and 77.7; of 2, 19.4, 34.2
+// and 95.9, topb_kernel 20.1, 36.0 and 105.7; 1 024 of 16 000 of mean length 2, 137 and 98, of 3, 116 and 119; 2 000 tokens, whatever their
+// segments, a tenth to a third less.  Listed rows of as many segments as fit: 8 of 131 040 tokens and 9 360 segments, 30.3 and 32.6.
+static bool row_rank_for(bool listed, int nth, const Dims &d, int32_t budget, int segments)
 {
-    return budget > 0 && budget < d.T && segments < 65536 && RowLds(listed, nth, d.T, segments).bytes <= RR_LDS_MOST;
+    if (budget <= 0 || budget >= d.T) return false;
+    const int bytes = RowLds(listed, nth, d.T, std::min(segments, 65535)).bytes;
+    if (listed) return bytes <= RR_LDS_MOST;
+    const bool two = d.P > d.cus;
+    return bytes <= (two ? RR_LDS_MOST / 2 : RR_LDS_MOST) && segments <= std::max(2048, two ? d.T / 4 * 3 : d.T / 2);
 }
 
 template <bool PLAN, int NTH, bool LISTED, int N = RR_KEYS>
@@ -2250,29 +2302,29 @@ static hipError_t run_row_rank(const Dims &d, const float *s_tilde, int32_t budg
 
 template <bool PLAN>
 static hipError_t run_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, const SegView &sv, int32_t *seg_budget,
-                           int32_t *block_size, const PlanArgs &pa, hipStream_t st)
+                           int32_t *block_size, const PlanArgs &pa, const Candidates &cd, hipStream_t st)
 {
     // (more rows than CUs, of more than 8 192 tokens: half the threads with twice the scores, so that two workgroups share a CU;
     // 1 024 rows of 16 000 tokens, 992 retained, Top-B and search 220 us, with 1 024 threads 244)
-    const int nth = d.T <= 256 * RR_KEYS ? 256 : d.T <= 512 * RR_KEYS ? 512 : 1024, segments = most_segments(d, sv);
-    if (d.T <= 1024 * RR_KEYS && row_rank_fits(false, nth, d, budget, segments)) {
-        const auto run = nth == 256 ? run_row_rank<PLAN, 256, false> : nth == 512 ? run_row_rank<PLAN, 512, false> :
-                         d.P <= d.cus ? run_row_rank<PLAN, 1024, false> : run_row_rank<PLAN, 512, false, 2 * RR_KEYS>;
+    const bool two = d.P > d.cus;
+    const int nth = d.T <= 256 * RR_KEYS ? 256 : d.T <= 512 * RR_KEYS || two ? 512 : 1024, segments = most_segments(d, sv);
+    if (d.T <= 1024 * RR_KEYS && row_rank_for(false, nth, d, budget, segments)) {
+        const auto run = nth == 256 ? run_row_rank<PLAN, 256, false> : nth == 1024 ? run_row_rank<PLAN, 1024, false> :
+                         d.T <= 512 * RR_KEYS ? run_row_rank<PLAN, 512, false> : run_row_rank<PLAN, 512, false, 2 * RR_KEYS>;
         return run(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, Candidates{}, segments, st);
     }
-    const bool two = d.P > d.cus;
     switch (topb_list_k(d, budget)) {
-    case 4: return (two ? run_topb<PLAN, 4, true> : run_topb<PLAN, 4, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
-    case 8: return (two ? run_topb<PLAN, 8, true> : run_topb<PLAN, 8, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
-    case 16: return run_topb<PLAN, 16, false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
-    default: return run_topb<PLAN, 32, false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+    case 4: return (two ? run_topb<PLAN, 4, true> : run_topb<PLAN, 4, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, st);
+    case 8: return (two ? run_topb<PLAN, 8, true> : run_topb<PLAN, 8, false>)(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, st);
+    case 16: return run_topb<PLAN, 16, false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, st);
+    default: return run_topb<PLAN, 32, false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, st);
     }
 }
 
 hipError_t launch_topb(const Dims &d, const float *s_tilde, int32_t budget, int32_t *thr, hipStream_t st)
 {
     if (d.P <= 0) return hipSuccess;
-    return run_topb<false>(d, s_tilde, budget, thr, SegView{}, nullptr, nullptr, PlanArgs{}, st);
+    return run_topb<false>(d, s_tilde, budget, thr, SegView{}, nullptr, nullptr, PlanArgs{}, Candidates{}, st);
 }
 
 // upper bound of a problem's records: a recorded segment holds at least two of the |T_topB| tokens
@@ -2324,7 +2376,7 @@ hipError_t launch_search(const Dims &d, const float *s_tilde, const SegView &sv,
     const int cap = max_heavy_segments(d, sv.max_segments, budget);
     const SearchWs w(d, ws);
     int32_t *thr = topb_out ? topb_out : w.thr;
-    hipError_t e = run_topb<false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, PlanArgs{}, st);
+    hipError_t e = run_topb<false>(d, s_tilde, budget, thr, sv, seg_budget, block_size, PlanArgs{}, Candidates{}, st);
     if (e != hipSuccess) return e;
     if (budget > 0 && d.T > 0) {
         hipLaunchKernelGGL(heavy_list_kernel, dim3(d.P), dim3(LIST_THREADS), 0, st, d, sv, thr, seg_budget, block_size, w.list,
@@ -2436,9 +2488,8 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
     const SearchWs w(d, ws);
     int32_t *thr = topb_out ? topb_out : w.thr;
     const PlanArgs pa{w.list, w.counts, cap, idx_out, n_sel_out};
-    hipError_t e;
-    const int n_slices = topb_slices(d, budget), segments = most_segments(d, sv);
-    if (n_slices > 1 && row_rank_fits(true, 512, d, budget, segments)) {
+    Candidates cd{};
+    if (const int n_slices = topb_slices(d, budget); n_slices > 1) {
         char *x = static_cast<char *>(ws) + sliced_offset(d, sv.max_segments, budget);
         int32_t *counts = reinterpret_cast<int32_t *>(x);
         uint2 *entries = reinterpret_cast<uint2 *>(x + align256((size_t)d.P * n_slices * 4));
@@ -2447,11 +2498,15 @@ hipError_t launch_search_select(const Dims &d, const float *s_tilde, const SegVi
         const dim3 grid = parts_grid(o, n_slices);
         hipLaunchKernelGGL(topb_collect_kernel, grid, dim3(TB_THREADS), (size_t)(TB_BINS + pre_cap) * 4, st, o, s_tilde,
                            topb_rank(d, budget), pre_cap, entries, counts);
-        const Candidates cd{entries, counts, n_slices, pre_cap};
-        e = run_row_rank<true, 512, true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments, st);
-    } else {
-        e = run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, st);
+        cd = Candidates{entries, counts, n_slices, pre_cap};
     }
+    // threads of the listed rows' kernel: for a thread's share of the lists, or of the segments where they are more (8 rows of 131 040
+    // tokens: 512 and 1 024 threads 50.9 and 51.2 us with 1 092 segments, 31.7 and 31.2 with 2 184, 30.8 and 28.7 with 6 552)
+    const int segments = most_segments(d, sv), nth = segments <= 2048 ? 512 : 1024;
+    const auto ranked = nth == 512 ? run_row_rank<true, 512, true> : run_row_rank<true, 1024, true, RR_KEYS / 2>;
+    hipError_t e = cd.n_slices > 0 && row_rank_for(true, nth, d, budget, segments)
+                       ? ranked(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, segments, st)
+                       : run_topb<true>(d, s_tilde, budget, thr, sv, seg_budget, block_size, pa, cd, st);
     if (e != hipSuccess) return e;
     if (cap > 0) run_search<true>(d, s_tilde, sv, cand, tau, w, cap, block_size, budget, idx_out, st);
     return hipGetLastError();

@@ -207,7 +207,7 @@ def test_scores_that_are_not_numbers_take_a_segment_s_share_and_no_more(torch_cu
 @pytest.mark.parametrize("mean", [1, 2, 30])
 @pytest.mark.parametrize("levels", [0, 3])
 def test_rows_and_segments_around_the_threads_that_hold_them(oracle, torch_cuda, T, mean, levels):  # noqa: F811
-    # 256, 512 or 1 024 threads by the row's length; more segments than threads, than LDS has room for (mean 1, T = 16384);
+    # 256, 512 or 1 024 threads by the row's length; more segments than threads, as many as tokens (mean 1);
     # levels: more ties at the threshold than are ranked, cut by index
     rng = np.random.default_rng(T + mean)
     st = rng.random((3, T)) ** 3
@@ -216,3 +216,33 @@ def test_rows_and_segments_around_the_threads_that_hold_them(oracle, torch_cuda,
     off = _offsets(rng, T, rng.integers(1, 2 * mean, size=T) if mean > 1 else np.ones(T, np.int64))
     for budget in sorted({1, T // 7, T // 2, T - 1} - {0}):
         _assert_search_select(oracle, torch_cuda, st, off, CAND, budget, 0.85)
+
+
+@pytest.mark.parametrize("T", [2049, 4096, 8161, 16000])
+@pytest.mark.parametrize("cus", [2, 256])
+@pytest.mark.parametrize("levels", [0, 3])
+def test_rows_around_the_number_of_segments_that_changes_their_kernel(oracle, torch_cuda, T, cus, levels):  # noqa: F811
+    # half as many segments as tokens, three quarters, what two workgroups have room for; rows beyond the compute units and not
+    rng = np.random.default_rng(T + cus)
+    st = rng.random((3, T)) ** 3
+    if levels:
+        st = np.round(st * levels) / levels
+    for n in {min(n, T) for n in (2048, 2049, T // 2, T // 2 + 1, T // 4 * 3, T // 4 * 3 + 1, 5300, 5400)}:
+        off = np.concatenate([[0], np.sort(rng.choice(T - 1, n - 1, replace=False)) + 1, [T]]).astype(np.int32)
+        for budget in (T // 9, T // 2):
+            _assert_search_select(oracle, torch_cuda, st, off, CAND, budget, 0.85, compute_units=cus)
+
+
+@pytest.mark.parametrize("levels", [0, 3])
+def test_listed_rows_of_as_many_segments_as_one_call_takes(oracle, torch_cuda, levels):  # noqa: F811
+    # long rows whose better tokens are listed by several workgroups (levels: more ties than the lists hold), ranked by 512 threads, by
+    # 1 024, and by the kernel for any number of segments
+    rng = np.random.default_rng(levels)
+    T = 131072
+    st = rng.random((3, T)) ** 5
+    if levels:
+        st = np.round(st * levels) / levels
+    for n in (2048, 2049, 11431, 11432, 16383):
+        off = np.concatenate([[0], np.sort(rng.choice(T - 1, n - 1, replace=False)) + 1, [T]]).astype(np.int32)
+        for budget in (700, 2000):
+            _assert_search_select(oracle, torch_cuda, st, off, CAND, budget, 0.85)

@@ -58,12 +58,21 @@ def test_struct_layout_matches_header():
     assert fields == [f[0] for f in B.CTuning._fields_]
 
 
-def test_grids_of_parts_stay_within_the_places_of_their_axes(tmp_path):
-    # few keys, so the problems would come first: not where the parts are more than a grid's second axis takes
+def _run_host_code(folder, code, header="cstdio"):
+    """stdout of a program of the library's host code (no kernel is compiled), as rows of whole numbers."""
     from paper_2510_22556_amd import build
 
-    src, exe = tmp_path / "grids.hip", tmp_path / "grids"
-    src.write_text("""
+    src, exe = folder / "host.hip", folder / "host"
+    src.write_text(f"#include <{header}>\n{code}")
+    subprocess.run([build.HIPCC, "-std=c++17", "-w", "--offload-host-only", "-I", build.CSRC, "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe),
+                    "-Wl,--unresolved-symbols=ignore-all"], check=True)
+    out = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout
+    return [[int(x) for x in line.split()] for line in out.splitlines()]
+
+
+def test_grids_of_parts_stay_within_the_places_of_their_axes(tmp_path):
+    # few keys, so the problems would come first: not where the parts are more than a grid's second axis takes
+    rows = _run_host_code(tmp_path, """
 #include "sablock_internal.h"
 #include <cstdio>
 int main()
@@ -78,12 +87,35 @@ int main()
         }
 }
 """)
-    subprocess.run([build.HIPCC, "-std=c++17", "--offload-host-only", "-I", build.CSRC, "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)],
-                   check=True)
-    for line in subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.splitlines():
-        parts, local, x, y, z, first = map(int, line.split())
+    assert len(rows) == 8
+    for parts, local, x, y, z, first in rows:
         problems_first = bool(local) and parts <= 65535
         assert (x, y, z, bool(first)) == ((3, parts) if problems_first else (parts, 3)) + (2, problems_first)
+
+
+def test_rows_of_many_segments_are_not_the_row_kernel_s(tmp_path):
+    # (listed, problems, threads, tokens, segments): it is slower than the other kernel where segments are short, or leave two
+    # workgroups no room on a compute unit; listed rows: all that LDS has room for, beside a histogram of the threads
+    yes = [(0, 8, 256, 2000, 2000), (0, 8, 256, 4096, 2048), (0, 8, 512, 8160, 4080), (0, 256, 1024, 16000, 8000), (0, 257, 512, 8160, 5500),
+           (0, 1024, 512, 16000, 5333), (1, 8, 512, 131040, 2048), (1, 8, 1024, 131040, 11431)]
+    no = [(0, 8, 256, 4096, 2049), (0, 8, 512, 8160, 4081), (0, 256, 1024, 16384, 8193), (0, 257, 512, 8160, 6121), (0, 1024, 512, 16000, 5500),
+          (0, 8, 1024, 16384, 16384), (1, 8, 1024, 131040, 11432), (1, 1, 1024, 1000000, 200000)]
+    cases = ",".join("{%d,%d,%d,%d,%d}" % c for c in yes + no)
+    rows = _run_host_code(tmp_path, """
+#include "search_select.hip"
+#include <cstdio>
+int main()
+{
+    for (const auto &c : std::initializer_list<std::array<int, 5>>{%s}) {
+        sablock::Dims d{};
+        d.P = c[1];
+        d.cus = 256;
+        d.T = c[3];
+        std::printf("%%d\\n", (int)sablock::row_rank_for(c[0], c[2], d, 100, c[4]));
+    }
+}
+""" % cases, "array")
+    assert rows == [[1]] * len(yes) + [[0]] * len(no)
 
 
 def test_workspace_bytes_and_shape_validation(lib):
