@@ -114,9 +114,11 @@ __host__ __device__ inline uint32_t ordered_key(float f)
 // keys' time besides (prologue, epilogue); `slots` of them run at a time.  Equal chunks in whole rounds of workgroups, or, where
 // those leave places idle, larger ones whose remainders the idle places take (96 problems on 256: two and a shorter one); then
 // the workgroups start chunk by chunk (by_chunk), all problems' first ones first.  At most `most` keys each, and `wgs`
-// workgroups in all where one round needs no more.
+// workgroups in all where one round needs no more.  Where one round does, more of them have to gain a ninth or to have chunks of
+// `from_one` keys; where several do, chunks are not cut below `shortest`.
 struct ChunkPlan { int len, n; bool by_chunk; };
-inline ChunkPlan plan_chunks(int64_t P, int64_t L, int64_t slots, int step, int fixed, int64_t most, int64_t wgs, bool remainders = true)
+inline ChunkPlan plan_chunks(int64_t P, int64_t L, int64_t slots, int step, int fixed, int64_t most, int64_t wgs, int shortest, int from_one,
+                             bool remainders)
 {
     auto up = [&](int64_t keys) { return (keys + step - 1) / step * step; };
     int64_t best = 0, best_len = up(L);
@@ -125,29 +127,35 @@ inline ChunkPlan plan_chunks(int64_t P, int64_t L, int64_t slots, int step, int 
         if (best == 0 || cost < best) { best = cost; best_len = len; by_chunk = rest; }
     };
     const int64_t least = (L + most - 1) / most, first = std::max<int64_t>(1, (least * P + slots - 1) / slots);
+    int64_t one = 0, one_len = 0;
     for (int64_t r = first; r < first + 8; ++r) {              // r rounds of equal chunks
         const int64_t n = r * slots / P, len = std::min(up((L + n - 1) / n), most);
-        if (r > first && P * n > wgs) break;
+        if (r > first && (P * n > wgs || (first > 1 && len < shortest))) break;
         offer((P * ((L + len - 1) / len) + slots - 1) / slots * (len + fixed), len, false);
+        if (r == 1) { one = best; one_len = len; }
         if (len == step) break;
     }
     const int64_t ideal = P * L / slots + fixed;
-    // where they would gain a twelfth or more, and with remainders of a quarter or more: with most places taken the memory is as
-    // busy as it gets (128 rows, 30 011 keys on 256 places: 112 problems in two chunks 302 us, in two and a sixth 315; 56 in four
-    // 185, in four and two fifths 171)
+    // where they would gain a twelfth or more (a tenth where whole rows fit one round), and with remainders of a quarter or more: with most
+    // places taken the memory is as busy as it gets (128 rows, 30 011 keys on 256 places: 112 problems in two chunks 302 us, in two and a sixth
+    // 315; 56 in four 185, in four and two fifths 171)
     const int64_t equal = best;
     if (remainders && equal * 100 > ideal * 108)
         for (int64_t n = std::max<int64_t>(2, least); n <= 6 && P * n <= wgs; ++n) {     // n - 1 chunks and the remainder of each
             const int64_t from = up((L + n - 1) / n), to = std::min(up((L + n - 2) / (n - 1)) - step, most), by = std::max<int64_t>(step, up((to - from) / 16));
             for (int64_t len = from + by; len <= to; len += by) {
-                if (4 * (L - (n - 1) * len) < len) continue;
+                if (4 * (L - (n - 1) * len) < len || len < shortest) continue;
                 const int64_t big = len + fixed, small = L - (n - 1) * len + fixed, q = P * (n - 1) / slots, late = P * (n - 1) % slots;
                 // `late` places have q + 1 chunks, the others q and a chunk's time for remainders; what is over comes on top
-                const int64_t early = slots - late, room = late ? early * (big / small) : 0, over = std::max<int64_t>(0, P - room);
+                const int64_t per = big / small, early = slots - late, room = late ? early * per : 0, over = std::max<int64_t>(0, P - room);
+                // a few places that take remainders one behind the other need some to spare (128 rows, 109 problems of 22 569 keys in two chunks
+                // 235 us, in two and a quarter, room for 114 remainders, 266; 64 rows of heads of 64, 106 of 21 609, room for 132, 147 and 134)
+                if (n > 2 && over == 0 && room * 100 <= P * (100 + 6 * (per - 1) * (per - 1))) continue;
                 const int64_t cost = (late ? q + 1 : q) * big + (over + slots - 1) / slots * small;
-                if (cost * 108 < equal * 100) offer(cost, len, true);
+                if (cost * 108 < equal * 100 && (one_len < L || cost * 100 < one * 90)) offer(cost, len, true);
             }
         }
+    if (one > 0 && !by_chunk && best * 100 >= one * 89 && best_len < from_one) best_len = one_len;
     return {(int)best_len, (int)((L + best_len - 1) / best_len), by_chunk};
 }
 

@@ -1464,7 +1464,11 @@ Plan make_plan(const Dims &d, int merge_from = MERGE_FROM)
         pl.n_chunks = (d.L + pl.chunk_len - 1) / pl.chunk_len;
         pl.by_chunk = false;
     } else {
-        const ChunkPlan c = plan_chunks(d.P, d.L, d.cus, STRIDE, FIXED, MAX_CHUNK, (4 << 20) / (d.G * d.W * 2 * 4));
+        // More rounds than one, 128 rows of heads of 128: 175 problems of 5 943 keys in four chunks each 129 us, in one 112; 196 of 15 374
+        // in five 302, in one 290; 200 of 49 215 907 and 947; 8 rows, 212 of 24 863 433 and 455.  More than two: 368 of 2 105 in two 113, in one 106.
+        const int from_one = d.D < 128 || d.G * d.W <= 32 ? 5 * FIXED : d.G * d.W <= 64 ? 7 * FIXED : 10 * FIXED;
+        const ChunkPlan c = plan_chunks(d.P, d.L, d.cus, STRIDE, FIXED, MAX_CHUNK, (4 << 20) / (d.G * d.W * 2 * 4),
+                                        d.D == 128 && tiles_of(d) > 4 && tiles_of(d) <= 8 ? 1600 : 0, from_one, true);
         pl.chunk_len = c.len;
         pl.n_chunks = c.n;
         pl.by_chunk = c.by_chunk;
@@ -1696,7 +1700,7 @@ hipError_t launch_score_all_heads(const Dims &d, const void *q, const void *k, c
         // workgroup per CU; its prologue takes as long as some 96 keys
         constexpr int MAX_LAYER_CHUNK = 32768, FIXED = 96;
         const int64_t n_sl = (int64_t)d.n_seq * d.n_layers;
-        const ChunkPlan c = plan_chunks(n_sl, d.L, d.cus, SUB, FIXED, MAX_LAYER_CHUNK, INT32_MAX, false);
+        const ChunkPlan c = plan_chunks(n_sl, d.L, d.cus, SUB, FIXED, MAX_LAYER_CHUNK, INT32_MAX, 0, INT32_MAX, false);
         ScoreArgs a2 = a;
         a2.chunk_len = c.len;
         a2.n_chunks = c.n;

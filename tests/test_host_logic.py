@@ -118,6 +118,33 @@ int main()
     assert rows == [[1]] * len(yes) + [[0]] * len(no)
 
 
+def test_plans_fill_idle_places_only_where_that_gains(tmp_path):
+    # 256 places, 128 rows of heads of 128: (problems, keys) -> chunks per problem, problems first.  One round of whole rows or of equal
+    # chunks where the memory is busy anyway, no chunks of hardly more than a prologue, no remainders that just fit
+    fixed = {(175, 5943): (1, 0), (196, 15374): (1, 0), (186, 6572): (1, 0), (203, 11753): (1, 0), (200, 49215): (5, 0), (109, 22569): (2, 0),
+             (112, 30011): (2, 0), (76, 28476): (3, 0), (368, 2105): (1, 0), (374, 2244): (1, 0), (24, 30011): (10, 0), (56, 30011): (5, 1),
+             (96, 13454): (3, 1), (187, 15242): (2, 1), (320, 30799): (4, 0), (8, 131072): (32, 0)}
+    rng = np.random.default_rng(3)
+    drawn = [(int(p), int(n)) for p, n in zip(rng.integers(1, 3000, 3000), np.exp(rng.uniform(4.9, 12.5, 3000)))]
+    cases = ",".join("{%d,%d}" % c for c in list(fixed) + drawn)
+    rows = _run_host_code(tmp_path, """
+#include "sablock_internal.h"
+#include <initializer_list>
+int main()
+{
+    for (const auto &c : std::initializer_list<std::array<long, 2>>{%s}) {
+        const auto p = sablock::plan_chunks(c[0], c[1], 256, 128, 640, 131072, (4 << 20) / 1024, 1600, 6400, true);
+        std::printf("%%d %%d %%d\\n", p.len, p.n, (int)p.by_chunk);
+    }
+}
+""" % cases, "cstdio>\n#include <array")
+    for (problems, keys), (length, n, by_chunk), want in zip(list(fixed) + drawn, rows, list(fixed.values()) + [None] * len(drawn)):
+        assert length % 128 == 0 and 128 <= length <= 131072 and (n - 1) * length < keys <= n * length
+        rounds = -(-problems * -(-keys // 131072) // 256)          # the fewest there can be
+        assert problems * n <= max(4096, 256 * rounds)              # the partials' room, or one such round of workgroups
+        assert want is None or (n, by_chunk) == want, (problems, keys, n, by_chunk)
+
+
 def test_workspace_bytes_and_shape_validation(lib):
     n = B.sablock_workspace_bytes(_shape(), 100, 112)
     assert n > 0 and n % 256 == 0
