@@ -1168,17 +1168,12 @@ __device__ __forceinline__ void xch_write(uint32_t addr, const float (&ab)[2][8]
 }
 __device__ __forceinline__ void xch_add(uint32_t addr, float (&ab)[2][8])
 {
+    typedef const floatx4 __attribute__((address_space(3))) *lds_vec;
     floatx4 v[3][4];
 #pragma unroll
     for (int sl = 0; sl < 3; ++sl)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            asm volatile("ds_read_b128 %0, %1" : "=v"(v[sl][j]) : "v"(addr + sl * XCH_BYTES + j * 1024) : "memory");
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(v[0][0]), "+v"(v[0][1]), "+v"(v[0][2]), "+v"(v[0][3]), "+v"(v[1][0]), "+v"(v[1][1]), "+v"(v[1][2]),
-                   "+v"(v[1][3]), "+v"(v[2][0]), "+v"(v[2][1]), "+v"(v[2][2]), "+v"(v[2][3])
-                 :
-                 : "memory");
+        for (int j = 0; j < 4; ++j) v[sl][j] = *(lds_vec)(uintptr_t)(addr + sl * XCH_BYTES + j * 1024);
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll

@@ -254,6 +254,12 @@ window_attention_kernel(WinArgs a)
             __builtin_amdgcn_wave_barrier();
         }
     };
+    // this lane's share of K's subtile u, which has landed
+    auto read_k = [&](int u, bf16x8 (&kb)[8]) __attribute__((always_inline)) {
+        typedef const bf16x8 __attribute__((address_space(3))) *lds_vec;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) kb[s] = *(lds_vec)(uintptr_t)((k_tile(u) + k_lane) ^ (uint32_t)(s << 5));
+    };
     // with V, subtiles 1 .. n_steady + 1 have no masked key, and those up to n_steady + 4 are full
     const int n_steady = min(min(n_sub, (d.L - lo) / SUB) - 5, (d.T - lo) / SUB - 2);
 
@@ -269,10 +275,8 @@ window_attention_kernel(WinArgs a)
                     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LOADS) : "memory");
                     lds_barrier();                             // subtile v has landed; K of v - 1 and V of v - 2 have been read
                     issue(v + 3, std::true_type{});
-                    typedef const bf16x8 __attribute__((address_space(3))) *lds_vec;
                     bf16x8 kb[8];
-#pragma unroll
-                    for (int s = 0; s < 8; ++s) kb[s] = *(lds_vec)(uintptr_t)((k_tile(v) + k_lane) ^ (uint32_t)(s << 5));
+                    read_k(v, kb);
                     floatx16 acc = nr;
 #pragma unroll
                     for (int s = 0; s < 8; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[s], qa[s], acc, 0, 0, 0);
@@ -317,15 +321,8 @@ window_attention_kernel(WinArgs a)
                             issue_piece<true, true>(kp + (int64_t)t0 * krow, krow, t0, d.L, j, lane, k_tile(w) + j * 1024);
                         }
                     }
-                    const uint32_t st = k_tile(v);
                     bf16x8 kb[8];
-#pragma unroll
-                    for (int s = 0; s < 8; ++s)
-                        asm volatile("ds_read_b128 %0, %1" : "=v"(kb[s]) : "v"((st + k_lane) ^ (uint32_t)(s << 5)) : "memory");
-                    asm volatile("s_waitcnt lgkmcnt(0)"
-                                 : "+v"(kb[0]), "+v"(kb[1]), "+v"(kb[2]), "+v"(kb[3]), "+v"(kb[4]), "+v"(kb[5]), "+v"(kb[6]), "+v"(kb[7])
-                                 :
-                                 : "memory");
+                    read_k(v, kb);
                     floatx16 acc;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[i] = 0.f;
@@ -383,18 +380,11 @@ window_attention_kernel(WinArgs a)
         // ... and after the barrier so have everyone's; the stage of the previous iteration is free: refill it
         lds_barrier();
         if (u + NSTAGE - 1 < n_sub) issue(u + NSTAGE - 1, std::false_type{});
-        const uint32_t st = k_tile(u);
         const int t0 = lo + u * SUB;
 
         // ---- S^T = K Q^T: acc[i] = <q_n, k_{t0 + row_of(i, hf)}> - r
         bf16x8 kb[8];
-#pragma unroll
-        for (int s = 0; s < 8; ++s)
-            asm volatile("ds_read_b128 %0, %1" : "=v"(kb[s]) : "v"((st + k_lane) ^ (uint32_t)(s << 5)) : "memory");
-        asm volatile("s_waitcnt lgkmcnt(0)"
-                     : "+v"(kb[0]), "+v"(kb[1]), "+v"(kb[2]), "+v"(kb[3]), "+v"(kb[4]), "+v"(kb[5]), "+v"(kb[6]), "+v"(kb[7])
-                     :
-                     : "memory");
+        read_k(u, kb);
         floatx16 acc;
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[i] = -r;

@@ -50,7 +50,21 @@ def test_inline_assembly_of_the_window_attention_reads_no_matrix_result(tmp_path
     text = _assembly("window_attn.hip", tmp_path)
     assert "v_mfma_f32_32x32x16_bf16" in text
     inline = set(re.findall(r"^\s+([a-z]\w+)", "\n".join(re.findall(r";;?#ASMSTART\n(.*?);;?#ASMEND", text, re.S)), re.M))
-    assert inline == {"s_mov_b32", "s_nop", "s_waitcnt", "s_barrier", "global_load_lds_dwordx4", "ds_read_b128"}
+    assert inline == {"s_mov_b32", "s_nop", "s_waitcnt", "s_barrier", "global_load_lds_dwordx4"}
+
+
+def test_inline_assembly_waits_for_what_it_loads():
+    # the compiler takes the registers of a load in inline assembly as written at once: it is waited for in the same statement, or the
+    # load is the compiler's own
+    loads = 0
+    for name in build.SOURCES:
+        with open(os.path.join(build.CSRC, name)) as f:
+            for statement in re.findall(r"\basm\b[^;]*;", re.sub(r"//.*", "", f.read())):
+                for load in re.findall(r"\b(?:ds_read|ds_load|ds_\w*_rtn|(?:global|buffer|flat|scratch|s)_load(?!_lds))\w*", statement):
+                    if "_load_lds" not in load:
+                        assert "s_waitcnt" in statement.split(load, 1)[1], (name, statement)
+                        loads += 1
+    assert loads == 1                                          # the addition to a counter in LDS that returns it
 
 
 def test_any_shape_scoring_plans_as_many_workgroups_as_the_registers_let_reside(tmp_path):
