@@ -1331,7 +1331,7 @@ def test_window_attention_short_contexts(oracle, torch_cuda, G, W, extra):
     np.testing.assert_allclose(H.to_np(buf.ent), e0, rtol=1e-4, atol=1e-6)
 
 
-@pytest.mark.parametrize("G,W,chunk", [(4, 32, 0), (4, 32, 512), (4, 64, 0), (4, 64, 512), (8, 32, 0), (8, 32, 1024)])
+@pytest.mark.parametrize("G,W,chunk", [(4, 32, 0), (4, 32, 512), (4, 32, 640), (4, 32, 800), (4, 32, 1600), (4, 64, 0), (4, 64, 512), (8, 32, 0), (8, 32, 1024)])
 def test_window_attention_and_its_row_lse_feed_the_scoring(oracle, torch_cuda, G, W, chunk):
     # Attention of the window queries (the producer of row_lse) against the oracle: outputs and log-sum-exp; keys
     # planted along query rows so that the running reference moves late in the stream, inside the window and in a
