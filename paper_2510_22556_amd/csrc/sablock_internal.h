@@ -69,7 +69,9 @@ __host__ __device__ inline int32_t layer_of_problem(const Dims &d, int32_t p)
 // Grids over (parts, problems).  Workgroups go round the 8 XCDs, each of which has an L2
 // cache of 4 MiB; where what the steps hand on to each other (12 bytes per key) fits these caches, the problems come first, so that
 // with 8 problems, a layer of most models, every step finds what the one before it wrote in its own XCD's cache.  With more data
-// nothing is left of it, and neighbouring workgroups had better read neighbouring memory.
+// nothing is left of it, and neighbouring workgroups had better read neighbouring memory.  The whole path against parts first, G = 4, W =
+// 32: 8 problems of 8 192 keys 46.6 -> 43.0 us, of 131 072 137.9 -> 134.0; 9, 12, 20 and 28 of 20 011 1.00, 0.97, 0.97 and 0.96 of the time;
+// at the line, 16 of 131 072 229 -> 232, 64 of 20 011 184 -> 178 (147 shapes of 1 to 120 problems: 0.91 to 1.02).
 // A grid's second axis has 65 535 places: problems always fit it (make_dims), parts that do not come first.  Clears d.local for them:
 // the kernel gets the same d.
 constexpr unsigned GRID_Y_MOST = 65535;

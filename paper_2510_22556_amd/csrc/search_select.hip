@@ -1668,8 +1668,7 @@ row_rank_kernel(Dims d, const float *s_tilde, int k, int32_t *thr_out, SegView s
 //
 // What bounds it: LDS atomics, if every score is counted (a histogram of 12 key bits puts a fifth of a row into one bin),
 // and two reads of the row; so only a sample is counted, in bins fitted to it, and the row is read once.  256 rows of
-// 131 040: 77 -> 46 us (134 MB, 2.9 TB/s with the sample); 1 024 rows of 65 472: 402 -> 111 us; 8 rows of 8 160, where
-// the chain of barriers is all there is: 18.6 -> 15.4 us.
+// 131 040: 77 -> 46 us (134 MB, 2.9 TB/s with the sample); 1 024 rows of 65 472: 402 -> 111 us.
 //
 // A row of up to TB_ROUND tokens (those of many segments, see row_rank_for) is held in registers and its k-th best found there
 // (kth_best).  Of a longer row a sample gives a lower bound first, ONE pass over the row lists the tokens that reach it (somewhat more than k), and the

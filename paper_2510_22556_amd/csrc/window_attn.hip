@@ -2,7 +2,8 @@
 // softmax denominators of its rows as a second output: the part of a prefill attention whose row statistics the
 // scoring step (Sec. 3.2) needs.  With them sablock_score reads K once (its column pass alone).
 //
-// bf16, D = 128; W in {8, 16, 32, 64} with G * W in {32, 64, 128, 256} window-query rows per KV head.  The rows
+// bf16, D = 128; W in {8, 16, 32, 64} with up to 256 window-query rows G * W per KV head, in one, two, four or
+// eight blocks of 32 (what is over is padding).  The rows
 // are ordered head * W + query and a wavefront is one block of 32 of them (one head, half of a head's window of
 // 64, or several heads when W < 32), so a workgroup has one to eight wavefronts.  A workgroup owns a chunk
 // of keys of one problem (sequence, layer, KV head).  K and V subtiles of 32 keys

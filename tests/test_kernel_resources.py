@@ -30,8 +30,8 @@ def search_select_kernels(tmp_path_factory):
 
 def test_dynamic_lds_of_the_topb_kernels_begins_on_16_bytes(search_select_kernels):
     # it lies behind the static part and is read and written 16 bytes at a time
-    topb = {n: k for n, k in search_select_kernels.items() if "topb_" in n}
-    assert len(topb) == 13
+    topb = {n: k for n, k in search_select_kernels.items() if "topb_" in n or "row_rank_" in n}
+    assert len(topb) == 13 + 10
     assert all(k["group_segment_fixed_size"] % 16 == 0 for k in topb.values()), topb
 
 
